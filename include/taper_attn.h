@@ -159,13 +159,14 @@ typedef struct {
                                       query heads per KV head; head_dim 64: 8 row tiles); wider
                                       requests are cut into equal sub-groups of at most this
                                       size; at most 12 row tiles                               */
-    int32_t shared_cost_pct;   /* 0 = default (160 when no shared item is wider than 4 row tiles,
-                                  200 up to 8, 140 above at head_dim 128): cost of a
-                                  shared-prefix token relative to a private one when cutting
-                                  the work into equal shares                                    */
-    int32_t shared_item_cost;  /* 0 = default (800): fixed cost of a shared-prefix item, in private
-                                  tokens' streaming time                                       */
-    int32_t private_item_cost; /* 0 = default (128): fixed cost of a private item, same unit      */
+    int32_t shared_cost_pct;   /* 0 = default (80; 180 when the step has fewer than 600 tokens per
+                                  share): cost of a shared-prefix token relative to a private
+                                  one when cutting the work into equal shares                   */
+    int32_t shared_item_cost;  /* 0 = default (450; below 600 tokens per share 60 and 32 per branch): fixed
+                                  cost of a shared-prefix item, in private tokens' streaming
+                                  time                                                          */
+    int32_t private_item_cost; /* 0 = default (192; 128 below 600 tokens per share and in steps without
+                                  shared-prefix work): fixed cost of a private item, same unit  */
     int32_t private_merge_cost; /* 0 = default (192 when the step has shared-prefix work, else none),
                                   -1 = none: extra cost of the private item that ends a sequence
                                   (as a rule it delivers the last partial and merges)           */
@@ -176,12 +177,13 @@ typedef struct {
                                   rather than into shares below this size.  0 = default: 256, or 1/16
                                   of the longest private segment if that is more (keeps the partials
                                   of one sequence to about 16)                                   */
-    int32_t pool_pct;          /* 0 = default (25 when the step has shared-prefix work, else none):
-                                  percentage of the private tokens that no share owns; workgroups
+    int32_t pool_pct;          /* 0 = default (25 when the step has shared-prefix work, rising to 60 for
+                                  shares of 5120 tokens; none below 600 tokens per share or
+                                  without shared-prefix work): percentage of the private tokens that no share owns; workgroups
                                   that finish their share take them, an item at a time, so the
                                   launch ends evenly.  -1 = none; values above 90 count as 90    */
     int32_t pool_item_tokens;  /* size of the pool's items, rounded down to a multiple of 32 tokens (at
-                                  least 32); 0 = default: a quarter of a share, between 512 and 1536 */
+                                  least 32); 0 = default: a quarter of a share, between 512 and 2048 */
     int32_t small_step_grid;   /* 0 = default: when target_workgroups is 0, a step without shared-prefix work
                                   is cut for one workgroup per compute unit instead of two if that cuts
                                   sequences into so many fewer pieces that it pays (each piece costs

@@ -69,6 +69,7 @@ struct DeviceImage {
     const int32_t* bt = nullptr;
     const taper_work_item* items = nullptr;
     const int32_t* part_start = nullptr;
+    const int32_t* part_turn = nullptr;
     const int32_t* merge_start = nullptr;
     const taper_merge_entry* merge = nullptr;
     const int32_t* prefix_len = nullptr;
@@ -144,13 +145,14 @@ int acquire_buffers(taper_ctx* ctx, size_t bytes, PlanBuffers* out) {
 }
 
 // The arrays of a host plan as one image: bt | items | part_start | merge_start | merge | prefix_len |
-// seg_start | ctx_len | seg_len | seg_page0, each piece 256-byte aligned.
+// seg_start | ctx_len | seg_len | seg_page0 | part_turn, each piece 256-byte aligned.
 struct ImagePiece {
     const void* src;
     size_t bytes, off;
 };
-size_t layout_image(const taper::HostPlan& h, ImagePiece (&pieces)[10]) {
-    const ImagePiece init[10] = {
+constexpr int kImagePieces = 11;
+size_t layout_image(const taper::HostPlan& h, ImagePiece (&pieces)[kImagePieces]) {
+    const ImagePiece init[kImagePieces] = {
         {h.block_table.data(), h.block_table.size() * sizeof(int32_t), 0},
         {h.items.data(), h.items.size() * sizeof(taper_work_item), 0},
         {h.part_start.data(), h.part_start.size() * sizeof(int32_t), 0},
@@ -161,20 +163,21 @@ size_t layout_image(const taper::HostPlan& h, ImagePiece (&pieces)[10]) {
         {h.ctx_len.data(), h.ctx_len.size() * sizeof(int32_t), 0},
         {h.seg_len.data(), h.seg_len.size() * sizeof(int32_t), 0},
         {h.seg_page0.data(), h.seg_page0.size() * sizeof(int32_t), 0},
+        {h.part_turn.data(), h.part_turn.size() * sizeof(int32_t), 0},
     };
     size_t total = 0;
-    for (int i = 0; i < 10; ++i) {
+    for (int i = 0; i < kImagePieces; ++i) {
         pieces[i] = init[i];
         pieces[i].off = total;
         total += align_up(std::max<size_t>(pieces[i].bytes, 16), 256);
     }
     return total;
 }
-void write_image(const ImagePiece (&pieces)[10], void* host_dst) {
+void write_image(const ImagePiece (&pieces)[kImagePieces], void* host_dst) {
     for (const ImagePiece& p : pieces)
         if (p.bytes) std::memcpy((char*)host_dst + p.off, p.src, p.bytes);
 }
-DeviceImage bind_image(const ImagePiece (&pieces)[10], void* dev_base) {
+DeviceImage bind_image(const ImagePiece (&pieces)[kImagePieces], void* dev_base) {
     char* d = (char*)dev_base;
     DeviceImage m;
     m.bt = (const int32_t*)(d + pieces[0].off);
@@ -187,6 +190,7 @@ DeviceImage bind_image(const ImagePiece (&pieces)[10], void* dev_base) {
     m.ctx_len = (const int32_t*)(d + pieces[7].off);
     m.seg_len = (const int32_t*)(d + pieces[8].off);
     m.seg_page0 = (const int32_t*)(d + pieces[9].off);
+    m.part_turn = (const int32_t*)(d + pieces[10].off);
     return m;
 }
 
@@ -276,6 +280,7 @@ taper::StepArgs make_args(const taper_ctx* ctx, const taper::HostPlan& h, const 
     a.bt = img.bt;
     a.items = img.items;
     a.part_start = img.part_start;
+    a.part_turn = img.part_turn;
     a.merge_start = img.merge_start;
     a.merge = img.merge;
     a.prefix_len = img.prefix_len;
@@ -502,7 +507,7 @@ int taper_plan_build_segments(taper_ctx* ctx, int n_seqs, const int32_t* block_t
         *out_plan = plan;
         return TAPER_OK;
     }
-    ImagePiece pieces[10];
+    ImagePiece pieces[kImagePieces];
     const size_t total = layout_image(h, pieces);
     hipError_t e = hipSetDevice(ctx->cfg.device);
     if (e != hipSuccess) {
@@ -639,7 +644,7 @@ int taper_decode_step_attention_static(taper_ctx* ctx, int n_seqs, const void* q
                                     n_pool_pages, &o, &h, &err);
     if (st != TAPER_OK) return fail(st, err);
     // layout inside the array: plan image | counters | statistics | partial rows
-    ImagePiece pieces[10];
+    ImagePiece pieces[kImagePieces];
     const size_t image = layout_image(h, pieces);
     size_t ml_off = 0, o_off = 0;
     const int64_t counters = counters_needed(ctx->cfg, h.n_seqs);

@@ -17,6 +17,7 @@ struct StepArgs {
     const int32_t* bt;         // [S][bt_stride]
     const taper_work_item* items;
     const int32_t* part_start;
+    const int32_t* part_turn;  // [n_parts] kv head of a share's first workgroup
     const int32_t* merge_start;
     const taper_merge_entry* merge;
     const int32_t* prefix_len;

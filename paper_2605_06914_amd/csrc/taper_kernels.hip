@@ -52,15 +52,34 @@ DEV void mask_tail(f32x4& sx, f32x4& sy, int qd, int n_valid) {
     }
 }
 
+// A row lives in lanes n, n + 16, n + 32, n + 48.  The swap instructions exchange 32- or 16-lane halves of two
+// registers without a trip through LDS (a ds_bpermute costs some 100 cycles, and each block has a chain of them).
+DEV float max_lane_groups(float v) {
+    unsigned u = __float_as_uint(v);
+    auto p = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    u = __float_as_uint(fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1])));
+    p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+DEV float sum_lane_groups(float v) {
+    unsigned u = __float_as_uint(v);
+    auto p = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    u = __float_as_uint(__uint_as_float(p[0]) + __uint_as_float(p[1]));
+    p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+
 // Online softmax over one 32-token block for one 16-row tile.  Every block passed
-// in holds at least one valid token, so the new max is finite.
+// in holds at least one valid token, so a first block's max is finite.  m is a reference value rather than
+// the exact maximum: it follows the maximum when that is more than kMaxSlack (in log2 units) above it.  The
+// weights then reach 2^kMaxSlack instead of 1, which no format here notices (bf16 and fp32 round relative to
+// the value, and everything is divided by l, which carries the same factor), and accumulators are rarely rescaled.
+constexpr float kMaxSlack = 8.f;
 template <int DT>
 DEV bf16x8 softmax_block(f32x4 sx, f32x4 sy, float c, float& m, float& l, f32x4 (&O)[DT]) {
     float mx = fmaxf(max4(sx), max4(sy));
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float mn = fmaxf(m, mx * c);
-    if (__any(mn > m)) {  // wave-uniform: rescale only when some row's max moved
+    if (__any(mx * c > m + kMaxSlack)) {  // wave-uniform; the lane groups' maxima are only brought together here
+        const float mn = fmaxf(m, max_lane_groups(mx) * c);
         const float alpha = fast_exp2(m - mn);
         l *= alpha;
 #pragma unroll
@@ -89,13 +108,6 @@ DEV void settle() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-DEV float sum_lane_groups(float v) {
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
-}
-
-
 // Partials travel between workgroups inside one launch.  Workgroups may sit on
 // different XCDs, whose L2s are not kept coherent for ordinary cached accesses,
 // and a device-scope fence per workgroup (L2 write-back + invalidate) is far too
@@ -106,9 +118,17 @@ DEV void coherent_store2(float* p, float x, float y) {
     unsigned long long v = ((unsigned long long)__float_as_uint(y) << 32) | __float_as_uint(x);
     __hip_atomic_store((unsigned long long*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-DEV float2 coherent_load2(const float* p) {
-    const unsigned long long v = __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
+// The reader's side: 16 bytes past the caches (the sc1 bit, what a device-scope atomic load carries too),
+// through a buffer descriptor with a 32-bit byte offset.  An offset at or above the descriptor's 2^31 - 1
+// bytes makes the hardware return zeros without a memory access, which is how a round of merge loads
+// leaves out what does not exist without a branch (the plan keeps a step's partial rows below 2^31 bytes).
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+constexpr unsigned kNoLoad = 0x80000000u;
+DEV __amdgpu_buffer_rsrc_t partial_buffer(const void* base) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00027000);
+}
+DEV u32x4 coherent_load16(__amdgpu_buffer_rsrc_t buf, unsigned byte_off) {
+    return __builtin_amdgcn_raw_buffer_load_b128(buf, byte_off, 0, 16 /* sc1 */);
 }
 // The accumulator part of a partial row travels normalised (divided by the row's own sum, so that
 // it is a weighted mean of V rows), in one of two formats (taper_partial_format):
@@ -120,10 +140,7 @@ DEV float2 coherent_load2(const float* p) {
 //            statistics record and is multiplied back in by the merge.
 constexpr int PF_F16S = TAPER_PARTIAL_F16_SCALED, PF_F32 = TAPER_PARTIAL_F32;
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-template <int PF>
-struct PartialRaw {
-    unsigned long long w[PF == PF_F32 ? 2 : 1];
-};
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 template <int PF>
 DEV void partial_store4(void* rows, int64_t elem, f32x4 v) {
     if constexpr (PF == PF_F32) {
@@ -136,35 +153,17 @@ DEV void partial_store4(void* rows, int64_t elem, f32x4 v) {
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
-// (the reader addresses a row by a 32-bit element offset from the workspace's base, which is the same for every
-// lane and stays in scalar registers: one address register per row instead of two per load.  The plan
-// keeps the partial rows of a step below 2^31 bytes.)
+// The elements of a partial row that one 16-byte load delivers.
 template <int PF>
-DEV PartialRaw<PF> partial_load4_raw(const void* rows, int elem) {
-    PartialRaw<PF> r;
-    if constexpr (PF == PF_F32) {
-        const unsigned long long* p = (const unsigned long long*)((const char*)rows + elem * 4);
-        r.w[0] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        r.w[1] = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        r.w[0] = __hip_atomic_load((const unsigned long long*)((const char*)rows + elem * 2), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+struct PartialVec {
+    static constexpr int N = PF == PF_F32 ? 4 : 8;
+    typedef float type __attribute__((ext_vector_type(N)));
+    typedef __bf16 out_type __attribute__((ext_vector_type(N)));
+    DEV static type unpack(u32x4 r) {
+        if constexpr (PF == PF_F32) return __builtin_bit_cast(type, r);
+        else return __builtin_convertvector(__builtin_bit_cast(f16x8, r), type);
     }
-    return r;
-}
-template <int PF>
-DEV f32x4 partial_unpack4(const PartialRaw<PF>& r) {
-    if constexpr (PF == PF_F32) {
-        f32x4 v;
-        v[0] = __uint_as_float((unsigned)r.w[0]);
-        v[1] = __uint_as_float((unsigned)(r.w[0] >> 32));
-        v[2] = __uint_as_float((unsigned)r.w[1]);
-        v[3] = __uint_as_float((unsigned)(r.w[1] >> 32));
-        return v;
-    } else {
-        return __builtin_convertvector(__builtin_bit_cast(f16x4, r.w[0]), f32x4);
-    }
-}
+};
 // The power of two 2^e that brings a row whose largest magnitude is `maxabs` into [0.5, 1), as
 // (2^e, 2^-e); e is kept inside [-126, 126] so that both are normal numbers (an all-zero row, or one
 // that holds Inf, is multiplied by some power of two all the same: it stays what it is).
@@ -231,14 +230,22 @@ DEV void zero_tail(bf16x4 (&va)[DT], bf16x4 (&vb)[DT], int qd, int n_valid) {
     }
 }
 
+// A work item by one scalar load (the compiler is not told that nothing here writes to the plan, and would use vector loads).
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+DEV taper_work_item load_item(const StepArgs& a, const int it) {
+    return __builtin_bit_cast(taper_work_item, ((const __attribute__((address_space(4))) i32x8*)a.items)[it]);
+}
+
+// (No branches: a lane without a value asks for one past the descriptor's end and gets zeros, so nothing is waited
+// for before meta_store.)
 DEV MetaRegs meta_load(const StepArgs& a, const taper_work_item& item, const int tid_) {
     const int tid = opaque(tid_);
+    const auto starts = partial_buffer(a.merge_start), entries = partial_buffer(a.merge);
     MetaRegs r;
-    r.ms = 0;
-    r.me.first_row = 0;
-    r.me.rows_per_head = 0;
-    if (tid <= item.n_branch) r.ms = a.merge_start[item.seq0 + tid];
-    if (tid < kMetaWindow && item.merge0 + tid < a.n_merge) r.me = a.merge[item.merge0 + tid];
+    r.ms = __builtin_amdgcn_raw_buffer_load_b32(starts, tid <= item.n_branch ? (item.seq0 + tid) * 4 : kNoLoad, 0, 0);
+    r.me = __builtin_bit_cast(taper_merge_entry,
+                              __builtin_amdgcn_raw_buffer_load_b64(
+                                  entries, tid < kMetaWindow && item.merge0 + tid < a.n_merge ? (item.merge0 + tid) * 8 : kNoLoad, 0, 0));
     return r;
 }
 DEV void meta_store(MergeMeta& mm, const MetaRegs& r, const int n_branch, const int tid_) {
@@ -246,89 +253,98 @@ DEV void meta_store(MergeMeta& mm, const MetaRegs& r, const int n_branch, const 
     if (tid <= n_branch) mm.ms[tid] = r.ms;
     if (tid < kMetaWindow) mm.me[tid] = r.me;
 }
-DEV taper_merge_entry merge_entry(const StepArgs& a, const MergeMeta& mm, const int e) {
-    const int t = e - mm.ms[0];
-    if (t < kMetaWindow) return mm.me[t];
-    return a.merge[e];
-}
-
 // Log-sum-exp merge of all partials of (sequence s, kv head hk) -- its request's
 // prefix chunks and its own private chunks, entries [e0, e1) of the merge map -- then
-// normalisation and rounding to bf16.  Entries are taken in plan order, so the result
-// does not depend on which workgroup happens to run this.  The loads bypass the caches
-// and cost a full memory latency per round, so a round keeps R entries in flight.
+// normalisation and rounding to bf16.  Entries are taken in plan order, in rounds whose sizes follow from
+// their number alone, whoever runs it, so the result does not depend on which workgroup that is.
+//
+// Bound by latency: the loads bypass the caches, and a trip takes 0.6 us on an idle machine and several
+// times that on a saturated one.  So a round has no branch and nothing waits inside it: the entries come
+// from the window in LDS, and the loads of all of them (statistics and row) are in flight together; past the
+// sequence's last entry they are turned off by their offset.  (With a branch per entry the compiler waits
+// for each entry's loads before it issues the next one's: 4.8 us for 8 entries on an idle machine, 2.0 this way.)
+// Rounds of 8, the rest in one of 8, 4 or 2 (fp32 rows: 4 or 2): a load that is turned off still takes its turn in the
+// compute unit's memory pipeline, and most sequences have two or three entries.
 //
 // A group of n_thr consecutive lanes (a workgroup, a wave or half a wave) merges one sequence;
 // groups of one wave may work on different sequences side by side.  Lane idx of the group owns
-// float4 columns c, c + LPR, ... (U of them) of one row, where LPR = D/4/U lanes cover a row;
-// n_thr / LPR rows are merged per pass.
-//
-// ALL: every round issues R loads per column whatever is left of the list -- past the sequence's last
-// entry that entry once more, with weight zero -- so that a round has no branches (what the compiler
-// makes of R conditional loads needs many more registers; the callers that run half-waves side by
-// side have none to spare).  Otherwise only the entries that exist are loaded: every load here is a
-// full trip to memory through a saturated memory system, and the slowest one ends the round.
-template <int D, int U, int R, int PF, bool ALL>
+// 16-byte columns c, c + LPR, ... (U of them) of one row; n_thr / LPR rows are merged per pass.
+template <int D, int U, int PF>
 DEV void merge_rows(const StepArgs& a, const MergeMeta& mm, const int s, const int hk, const int e0, const int e1,
                     const int idx_, const int n_thr) {
-    constexpr int LPR = D / 4 / U;
-    const int g = a.gqa;
+    typedef PartialVec<PF> Vec;
+    typedef typename Vec::type vec;
+    constexpr int LPR = D / Vec::N / U;
+    constexpr int ROW_BYTES = D * 16 / Vec::N;
+    const auto rows = partial_buffer(a.ws_o), stats = partial_buffer(a.ws_ml);
+    const int g = a.gqa, w0 = mm.ms[0];
     const int idx = opaque(idx_);
     const int jr = idx / LPR, c0 = idx % LPR;
     for (int j0 = 0; j0 < g; j0 += n_thr / LPR) {
         const int j = j0 + jr;
         const bool okr = j < g;
         float M = -INFINITY, L = 0.f;
-        f32x4 acc[U];
+        vec acc[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) acc[u] = (f32x4)(0.f);
-        for (int e = e0; e < e1; e += R) {
-            float2 ml[R];
-            float sc[R];
-            PartialRaw<PF> o[R][U];  // unpacked when they are used
+        for (int u = 0; u < U; ++u) acc[u] = (vec)(0.f);
+        auto round = [&](const int e, auto size) {
+            constexpr int R = decltype(size)::value;
+            taper_merge_entry me[R];
+            if ((e + R < e1 ? e + R : e1) - w0 <= kMetaWindow) {
+#pragma unroll
+                for (int k = 0; k < R; ++k) me[k] = mm.me[(e + k < e1 ? e + k : e1 - 1) - w0];
+            } else {
+#pragma unroll
+                for (int k = 0; k < R; ++k) me[k] = a.merge[e + k < e1 ? e + k : e1 - 1];
+            }
+            u32x4 st[R], o[R][U];
 #pragma unroll
             for (int k = 0; k < R; ++k) {
-                const bool real = e + k < e1;
-                ml[k] = make_float2(-INFINITY, 0.f);
-                sc[k] = 1.f;
+                const bool real = okr && e + k < e1;
+                const unsigned row = me[k].first_row + hk * me[k].rows_per_head + j;
+                st[k] = coherent_load16(stats, real ? row * 16 : kNoLoad);
 #pragma unroll
-                for (int u = 0; u < U; ++u) o[k][u] = PartialRaw<PF>{};
-                if (ALL || real) {
-                    const taper_merge_entry me = merge_entry(a, mm, real ? e + k : e1 - 1);
-                    const int row = me.first_row + hk * me.rows_per_head + (okr ? j : 0);
-                    const float* rec = (const float*)((const char*)a.ws_ml + row * 16);
-                    const float2 v = coherent_load2(rec);
-                    if (real && okr) ml[k] = v;
-                    if constexpr (PF == PF_F16S) sc[k] = coherent_load2(rec + 2).x;
-#pragma unroll
-                    for (int u = 0; u < U; ++u) o[k][u] = partial_load4_raw<PF>(a.ws_o, row * D + 4 * (c0 + LPR * u));
-                }
+                for (int u = 0; u < U; ++u) o[k][u] = coherent_load16(rows, real ? row * ROW_BYTES + 16 * (c0 + LPR * u) : kNoLoad);
             }
-            float mn = M;
+            float mk[R], mn = M;
 #pragma unroll
-            for (int k = 0; k < R; ++k) mn = fmaxf(mn, ml[k].x);
+            for (int k = 0; k < R; ++k) {
+                mk[k] = okr && e + k < e1 ? __uint_as_float(st[k][0]) : -INFINITY;
+                mn = fmaxf(mn, mk[k]);
+            }
             const float keep = fast_exp2(M - mn);  // first round: exp2(-inf) = 0
             L *= keep;
 #pragma unroll
             for (int u = 0; u < U; ++u) acc[u] *= keep;
 #pragma unroll
             for (int k = 0; k < R; ++k) {
-                const float w = fast_exp2(ml[k].x - mn) * ml[k].y;  // (the row was stored divided by its sum)
+                const float w = fast_exp2(mk[k] - mn) * __uint_as_float(st[k][1]);  // (the row was stored divided by its sum)
                 L += w;
-                const float ws = PF == PF_F16S ? w * sc[k] : w;
+                const float ws = PF == PF_F16S ? w * __uint_as_float(st[k][2]) : w;
 #pragma unroll
-                for (int u = 0; u < U; ++u) acc[u] += ws * partial_unpack4<PF>(o[k][u]);
+                for (int u = 0; u < U; ++u) acc[u] += ws * Vec::unpack(o[k][u]);
             }
             M = mn;
+        };
+        for (int e = e0; e < e1;) {
+            if (PF == PF_F16S && e1 - e > 4) {
+                round(e, std::integral_constant<int, PF == PF_F16S ? 8 : 2>{});
+                e += 8;
+            } else if (e1 - e > 2) {
+                round(e, std::integral_constant<int, 4>{});
+                e += 4;
+            } else {
+                round(e, std::integral_constant<int, 2>{});
+                e += 2;
+            }
         }
         if (okr) {
             const int h = hk * g + j;
             const float inv = 1.0f / L;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const f32x4 r = acc[u] * inv;
-                *(bf16x4*)((__bf16*)a.out + ((int64_t)s * a.n_q_heads + h) * D + 4 * (c0 + LPR * u)) = __builtin_convertvector(r, bf16x4);
-            }
+            for (int u = 0; u < U; ++u)
+                *(typename Vec::out_type*)((__bf16*)a.out + ((int64_t)s * a.n_q_heads + h) * D + Vec::N * (c0 + LPR * u)) =
+                    __builtin_convertvector(acc[u] * inv, typename Vec::out_type);
             if (a.lse && c0 == 0) a.lse[(int64_t)s * a.n_q_heads + h] = (M + __log2f(L)) * 0.6931471805599453f;
         }
     }
@@ -363,18 +379,16 @@ DEV void arrive_and_merge(const StepArgs& a, const MergeMeta& mm, int* todo, int
     }
     __syncthreads();
     const int n = *n_todo;
-    // entries in flight per round: as many as leave the launch free of register spills (the streaming loops
-    // of the callers are at the limit of the register file, and any scratch use costs microseconds per launch)
-    constexpr int R64 = 6, R32 = PF == PF_F32 ? 2 : 4;
+    constexpr int N = PartialVec<PF>::N;
     if (n <= 4) {
         if (wave < n) {
             const int b = todo[wave];
-            merge_rows<D, D / 32, R64, PF, false>(a, mm, item.seq0 + b, hk, mm.ms[b], mm.ms[b + 1], lane, 64);
+            merge_rows<D, D / N / 8, PF>(a, mm, item.seq0 + b, hk, mm.ms[b], mm.ms[b + 1], lane, 64);
         }
     } else {
         for (int i = tid >> 5; i < n; i += 8) {
             const int b = todo[i];
-            merge_rows<D, D / 16, R32, PF, true>(a, mm, item.seq0 + b, hk, mm.ms[b], mm.ms[b + 1], tid & 31, 32);
+            merge_rows<D, D / N / 4, PF>(a, mm, item.seq0 + b, hk, mm.ms[b], mm.ms[b + 1], tid & 31, 32);
         }
     }
 }
@@ -404,12 +418,9 @@ struct PrivateSmem {
 // SOLO: the item is run by the calling wave alone (short sequences that are a single item:
 // four of them proceed side by side in a workgroup, with no barrier and no LDS); otherwise the
 // four waves of the workgroup share the item's blocks.
-// SB: the block-table row is read through the constant address space from a pointer the compiler knows to
-// be the same in all lanes.  Its entries then come by scalar loads, which do not wait for the KV loads in
-// flight (a vector load of a page id completes in order, behind everything issued before it: one block in
-// flight per wave).  That deeper pipeline pays on steps without shared-prefix work; next to shared-prefix
-// workgroups it takes bandwidth from them, and those launches keep the vector loads.
-template <int D, bool SOLO, int PF, bool SB>
+// The block-table row is read by scalar loads (constant address space, wave-uniform pointer), which do not wait for
+// the KV loads in flight; a vector load of a page id completes in order, behind everything issued before it.
+template <int D, bool SOLO, int PF>
 DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem<D>& sm) {
     constexpr int KS = D / 32, DT = D / 16, TILE = 16 * D;
     auto& sm_o = sm.o;
@@ -418,20 +429,11 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, qd = lane >> 4;
     const int Hkv = a.n_kv_heads, g = a.gqa;
-    const __bf16* __restrict__ kvb = (const __bf16*)a.kv;
-    const int64_t page_elems = 2LL * Hkv * TILE;
     const float c = a.scale_log2e;
-    const int koff = lane * 8, voff = qd * (4 * D) + n * 4;
     {
-        const taper_work_item item = a.items[it];
+        const taper_work_item item = load_item(a, it);
         typedef const __attribute__((address_space(4))) int32_t* scalar_row;
-        typedef const int32_t* __restrict__ vector_row;
-        typename std::conditional<SB, scalar_row, vector_row>::type row;
-        if constexpr (SB)
-            row = (scalar_row)(a.bt + (int64_t)__builtin_amdgcn_readfirstlane(item.seq0) * a.bt_stride +
-                               __builtin_amdgcn_readfirstlane(item.page0));
-        else
-            row = a.bt + (int64_t)item.seq0 * a.bt_stride + item.page0;
+        const scalar_row row = (scalar_row)(a.bt + (int64_t)item.seq0 * a.bt_stride + item.page0);
         const int n_tok = item.n_tokens;
         const int n_pages = (n_tok + 15) >> 4;
         const int n_blocks = (n_tok + 31) >> 5;
@@ -439,40 +441,43 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
         MetaRegs mr = {};
         if (!sole) mr = meta_load(a, item, threadIdx.x);
 
-        bf16x8 qf[KS];
+        bf16x8 qf[KS];  // (lane columns past the last query head repeat the first; not stored)
         {
             const __bf16* qrow = (const __bf16*)a.q + ((int64_t)item.seq0 * a.n_q_heads + hk * g + (n < g ? n : 0)) * D;
 #pragma unroll
-            for (int j = 0; j < KS; ++j) {
-                bf16x8 v = *(const bf16x8*)(qrow + 8 * (4 * j + qd));
-                if (n >= g) v = (bf16x8)(0);
-                qf[j] = v;
-            }
+            for (int j = 0; j < KS; ++j) qf[j] = *(const bf16x8*)(qrow + 8 * (4 * j + qd));
         }
         float m = -INFINITY, l = 0.f;
         f32x4 O[DT];
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) O[dt] = (f32x4)(0.f);
 
-        auto load_block = [&](int b, KVRegs<D>& r) {
-            const int ia = 2 * b, ib = (2 * b + 1 < n_pages) ? 2 * b + 1 : ia;
-            const int64_t pa = row[ia], pb = row[ib];
-            const __bf16* ka = kvb + pa * page_elems + (int64_t)hk * TILE;
-            const __bf16* kb = kvb + pb * page_elems + (int64_t)hk * TILE;
-            const __bf16* va = ka + (int64_t)Hkv * TILE;
-            const __bf16* vb = kb + (int64_t)Hkv * TILE;
+        const int64_t page_bytes = (int64_t)Hkv * TILE * 4;
+        const char* kvb = (const char*)a.kv + (int64_t)hk * TILE * 2;
+        const unsigned koff = lane * 16, voff = (qd * (4 * D) + n * 4) * 2;
+        int pid_a = 0, pid_b = 0;  // the pages of the block loaded next
+        auto fetch_ids = [&](int b) {
+            const int ia = 2 * b < n_pages ? 2 * b : n_pages - 1, ib = 2 * b + 1 < n_pages ? 2 * b + 1 : n_pages - 1;
+            pid_a = row[ia];
+            pid_b = row[ib];
+        };
+        auto load_block = [&](KVRegs<D>& r) {
+            const char* ka = kvb + pid_a * page_bytes;
+            const char* kb = kvb + pid_b * page_bytes;
+            const char* va = ka + (int64_t)Hkv * TILE * 2;
+            const char* vb = kb + (int64_t)Hkv * TILE * 2;
 #pragma unroll
             for (int j = 0; j < KS; ++j) {
-                r.kx[j] = stream_load((const bf16x8*)(ka + koff + j * 512));
-                r.ky[j] = stream_load((const bf16x8*)(kb + koff + j * 512));
+                r.kx[j] = stream_load((const bf16x8*)(ka + koff + j * 1024));
+                r.ky[j] = stream_load((const bf16x8*)(kb + koff + j * 1024));
             }
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
-                r.va[dt] = stream_load((const bf16x4*)(va + voff + dt * 64));
-                r.vb[dt] = stream_load((const bf16x4*)(vb + voff + dt * 64));
+                r.va[dt] = stream_load((const bf16x4*)(va + voff + dt * 128));
+                r.vb[dt] = stream_load((const bf16x4*)(vb + voff + dt * 128));
             }
         };
-        auto compute_block = [&](int b, KVRegs<D>& r) {
+        auto compute_block = [&](int b, KVRegs<D>& r, auto last) {
             f32x4 sx = (f32x4)(0.f), sy = (f32x4)(0.f);
 #pragma unroll
             for (int j = 0; j < KS; ++j) {
@@ -480,29 +485,42 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
                 sy = mfma16(r.ky[j], qf[j], sy);
             }
             const int nv = n_tok - 32 * b;
-            if (nv < 32) mask_tail(sx, sy, qd, nv);
+            if (last && nv < 32) mask_tail(sx, sy, qd, nv);
             const bf16x8 pf = softmax_block<DT>(sx, sy, c, m, l, O);
-            if (nv < 32) zero_tail(r.va, r.vb, qd, nv);
+            if (last && nv < 32) zero_tail(r.va, r.vb, qd, nv);
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) O[dt] = mfma16(cat(r.va[dt], r.vb[dt]), pf, O[dt]);
-            // (at head_dim 128 the same statement here costs this loop a few spilled registers, and the code
-            // the compiler makes for it keeps the distance by itself; a build check scans every kernel for it)
-            if constexpr (D == 64) settle();
+            settle();
         };
 
-        KVRegs<D> r0, r1;
-        constexpr int STEP = SOLO ? 1 : 4;  // blocks wave, wave + 4, ... of a shared item; all blocks of a solo one
+        // Blocks wave, wave + 4, ... of a shared item; all blocks of a solo one.  Two register sets: inside the loop the
+        // next block's loads are issued unconditionally before the current block is computed, so that the waits the
+        // compiler makes leave exactly those in flight (a load behind a branch would have to be waited for with the rest).
+        constexpr int STEP = SOLO ? 1 : 4;
         int b = SOLO ? 0 : wave;
-        if (b < n_blocks) load_block(b, r0);
-        while (b < n_blocks) {
-            const int b1 = b + STEP;
-            if (b1 < n_blocks) load_block(b1, r1);
-            compute_block(b, r0);
-            if (b1 >= n_blocks) break;
-            const int b2 = b1 + STEP;
-            if (b2 < n_blocks) load_block(b2, r0);
-            compute_block(b1, r1);
-            b = b2;
+        if (b < n_blocks) {
+            KVRegs<D> r0;
+            fetch_ids(b);
+            load_block(r0);
+            fetch_ids(b + STEP);
+            while (b + 2 * STEP < n_blocks) {
+                KVRegs<D> r1;
+                load_block(r1);
+                fetch_ids(b + 2 * STEP);
+                compute_block(b, r0, std::false_type{});
+                load_block(r0);
+                fetch_ids(b + 3 * STEP);
+                compute_block(b + STEP, r1, std::false_type{});
+                b += 2 * STEP;
+            }
+            if (b + STEP < n_blocks) {
+                KVRegs<D> r1;
+                load_block(r1);
+                compute_block(b, r0, std::false_type{});
+                r0 = r1;
+                b += STEP;
+            }
+            compute_block(b, r0, std::true_type{});
         }
 
         if constexpr (SOLO) {  // this wave holds the whole result: normalise and write it
@@ -575,7 +593,7 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
 #ifdef TAPER_WG_TRACE
         const long long t_m0 = wall_clock64();
 #endif
-        if (sm.last) merge_rows<D, 1, 8, PF, false>(a, sm.meta, item.seq0, hk, sm.meta.ms[0], sm.meta.ms[1], threadIdx.x, 256);
+        if (sm.last) merge_rows<D, 1, PF>(a, sm.meta, item.seq0, hk, sm.meta.ms[0], sm.meta.ms[1], threadIdx.x, 256);
 #ifdef TAPER_WG_TRACE
         if (threadIdx.x == 0 && a.trace) a.trace[4 * blockIdx.x + 3] += wall_clock64() - t_m0;
 #endif
@@ -586,7 +604,7 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
 // can take from its kv head's pool.  Every workgroup makes exactly one claim past the end of
 // the pool; the one that makes the last of those puts the counter back to zero for the next
 // launch.
-template <int D, int PF, bool SB>
+template <int D, int PF>
 DEV void private_items(const StepArgs& a, int it0, const int it1, const int hk, PrivateSmem<D>& sm) {
     const int wgs_per_head = a.n_parts_shared + a.n_parts_private;  // = gridDim.x / n_kv_heads
 #ifdef TAPER_WG_TRACE
@@ -604,7 +622,7 @@ DEV void private_items(const StepArgs& a, int it0, const int it1, const int hk, 
 #endif
             if (threadIdx.x == 0) sm.pick = atomicAdd(a.pool_ctr + hk, 1);
             __syncthreads();
-            const int i = sm.pick;
+            const int i = __builtin_amdgcn_readfirstlane(sm.pick);
             __syncthreads();
             if (i >= a.n_pool_items) {
                 if (threadIdx.x == 0 && i == a.n_pool_items + wgs_per_head - 1)
@@ -613,58 +631,83 @@ DEV void private_items(const StepArgs& a, int it0, const int it1, const int hk, 
             }
             it = a.pool_first + i;
         }
-        if (a.items[it].kind == 3) {  // a run of solo items of this share: dealt to the waves, no barrier inside
+        if (load_item(a, it).kind == 3) {  // a run of solo items of this share: dealt to the waves, no barrier inside
             int end = it + 1;
-            while (end < it1 && a.items[end].kind == 3) ++end;
+            while (end < it1 && load_item(a, end).kind == 3) ++end;
             const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-            for (int k = it + wave; k < end; k += 4) private_item<D, true, PF, SB>(a, k, hk, sm);
+            for (int k = it + wave; k < end; k += 4) private_item<D, true, PF>(a, k, hk, sm);
             it0 = end;
             __syncthreads();
             continue;
         }
-        private_item<D, false, PF, SB>(a, it, hk, sm);
+        private_item<D, false, PF>(a, it, hk, sm);
     }
 }
 
 // ---------------------------------------------------------------------------
 // Shared-prefix kernel: a chunk of one request's prefix pages is staged in LDS
-// once (64 tokens per iteration, double buffered) and multiplied against the
-// query rows of all n_branch admitted branches x g heads.  16-row tiles are
-// dealt round-robin to the four waves, up to NTW tiles per wave.
+// once and multiplied against the query rows of all n_branch admitted branches x g
+// heads.  16-row tiles are dealt round-robin to the four waves, up to 3 tiles per wave.
+//
+// KV goes from global memory straight into LDS, 16 KiB blocks (32 tokens at head_dim 128, 64 at 64) in a ring
+// of four: one is computed from while three are in flight, whatever the number of tiles.  Every wave-level
+// 16-byte load lands as 1 KiB at a wave-uniform LDS address, lane after lane.  Which 16 bytes of memory
+// a lane fetches is free, and that is where V's bank swizzle is made: inside an odd 4-token quarter the two
+// 128-byte halves of each 256 bytes change places, so that the 8-byte fragment reads of lane groups 0/1
+// (2/3) hit different bank halves.
+//
+// The loads are written in assembly because the compiler does not see which buffer an LDS read touches and
+// would wait for every outstanding load before each one; it is kept from moving anything across the waits by
+// their memory clobbers.  (The loads have no register results, and the waits the compiler makes for its own
+// loads only get longer by loads it does not know of.)
 // ---------------------------------------------------------------------------
 template <int D>
 struct SharedSmem {
-    static constexpr int TILE = 16 * D;
-    static constexpr int QE = 4 * D;        // elements of one 4-token quarter of a V tile
-    static constexpr int VQ = QE + 64;      // padded quarter: odd multiple of 128 B -> quarters alternate bank halves
-    static constexpr int PAGE_LDS = TILE + 4 * VQ;
-    static constexpr int BUF = 4 * PAGE_LDS;  // 4 pages = 64 tokens
-    __bf16 kv[2 * BUF];
+    static constexpr int TILE_BYTES = 32 * D;                  // one (page, K or V, kv head) tile
+    static constexpr int PAGE_BYTES = 2 * TILE_BYTES;
+    static constexpr int BLOCK_BYTES = 16384;
+    static constexpr int PAGES = BLOCK_BYTES / PAGE_BYTES;     // pages per block: 2 at head_dim 128, 4 at 64
+    static constexpr int TOKENS = 16 * PAGES;
+    static constexpr int RING = 4;
+    // A block: the K tiles of its pages one after the other, then V in 1 KiB chunks (token quarters at head_dim 128, pairs
+    // of quarters at 64): pair of pages, chunk, page of the pair.  The two pages' fragments that make up one operand
+    // are then 1 KiB apart, which one two-address read fetches into neighbouring registers.
+    static constexpr int V_OFF = PAGES * TILE_BYTES;
+    static constexpr int v_chunk(int page, int chunk) { return V_OFF + (page >> 1) * 2 * TILE_BYTES + chunk * 2048 + (page & 1) * 1024; }
+    char kv[RING * BLOCK_BYTES];
     int todo[64];  // branches of the current item whose partials are complete
     int n_todo;
     MergeMeta meta;
 };
 
+DEV unsigned lds_address(const void* p) { return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)p; }
+// 64 lanes x 16 bytes: lane l's from base + off (per lane) to LDS address `lds` + 16 l; streamed past the caches
+DEV void load_to_lds(const char* base, unsigned off, unsigned lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds) : "m0", "memory");
+}
+// All but this wave's N youngest loads have landed, its LDS reads are done, and every wave of the workgroup is here.
+template <int N>
+DEV void wait_loads_and_meet() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
 // The partial rows of a shared-prefix item: tile k of this wave holds row 16 * (wave + 4k) + n of the
 // item's R rows in lane column n, 4 values per 16-dim group and lane group.
 template <int D, int NTW, int PF>
-DEV void store_shared_partials(const StepArgs& a, const taper_work_item& item, const int hk, const int R, const int n_act,
-                               const int wave, const int n, const int qd, const float (&m)[NTW], const float (&l)[NTW],
+DEV void store_shared_partials(const StepArgs& a, const taper_work_item& item, const int hk, const int R, const int wave, const int n, const int qd, const float (&m)[NTW], const float (&l)[NTW],
                                const f32x4 (&O)[NTW][D / 16]) {
     constexpr int DT = D / 16;
 #pragma unroll
     for (int k = 0; k < NTW; ++k) {
-        if (k < n_act) {
+        {
             const float lt = sum_lane_groups(l[k]);
             const float inv = 1.0f / lt;
             float2 sc = make_float2(1.f, 1.f);
-            if constexpr (PF == PF_F16S) {  // (all 64 lanes are here: k < n_act is wave-uniform)
+            if constexpr (PF == PF_F16S) {
                 float mx = 0.f;
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) mx = fmaxf(mx, maxabs4(O[k][dt]));
-                mx = fmaxf(mx, __shfl_xor(mx, 16));
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
-                sc = row_scale(mx * inv);
+                sc = row_scale(max_lane_groups(mx) * inv);
             }
             const int r = 16 * (wave + 4 * k) + n;
             if (r < R) {
@@ -681,401 +724,181 @@ DEV void store_shared_partials(const StepArgs& a, const taper_work_item& item, c
     }
 }
 
-template <int D, int NTW, int PF>
-DEV void shared_path(const StepArgs& a, const int part, const int hk, SharedSmem<D>& sm) {
-    constexpr int KS = D / 32, DT = D / 16, TILE = 16 * D;
-    constexpr int QE = SharedSmem<D>::QE, VQ = SharedSmem<D>::VQ, PAGE_LDS = SharedSmem<D>::PAGE_LDS,
-                  BUF = SharedSmem<D>::BUF;
-    __bf16* lds = sm.kv;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+// Streams the item's tokens against the NA tiles wave, wave + 4, ... of its rows and stores their partial rows.
+// Every wave of the workgroup takes its part in staging and meets the others once per block, whatever its NA.
+template <int D, int NA, int PF>
+DEV void shared_stream(const StepArgs& a, const taper_work_item& item, const int hk, SharedSmem<D>& sm, const int tid,
+                       const int wave) {
+    typedef SharedSmem<D> Sm;
+    constexpr int KS = D / 32, DT = D / 16, NT = NA ? NA : 1, QB = 8 * D;  // QB: bytes of a 4-token quarter of a V tile
+    constexpr int LOADS = 4;  // wave-level loads per wave and block
+    const int lane = tid & 63, n = lane & 15, qd = lane >> 4;
     const int Hkv = a.n_kv_heads, g = a.gqa;
-    const __bf16* __restrict__ kvb = (const __bf16*)a.kv;
-    const int64_t page_elems = 2LL * Hkv * TILE;
+    const int64_t page_bytes = (int64_t)Hkv * Sm::PAGE_BYTES;
+    const char* kvb = (const char*)a.kv + (int64_t)hk * Sm::TILE_BYTES;
     const float c = a.scale_log2e;
+    typedef const __attribute__((address_space(4))) int32_t* scalar_row;  // (wave-uniform: page ids come by scalar loads)
+    const scalar_row row = (scalar_row)(a.bt + (int64_t)item.seq0 * a.bt_stride + item.page0);
+    const int n_tok = item.n_tokens, n_pages = (n_tok + 15) >> 4, n_blocks = (n_tok + Sm::TOKENS - 1) / Sm::TOKENS;
+    const int R = item.n_branch * g;
 
-    const int it0 = a.part_start[part], it1 = a.part_start[part + 1];
-    for (int it = it0; it < it1; ++it) {
-        // per-lane constants are derived inside the loop from an opaque thread id, so that they are
-        // not kept alive across the item's end (the merge wants the registers)
-        const int tid = opaque(threadIdx.x);
-        const int lane = tid & 63;
-        const int n = lane & 15, qd = lane >> 4;
-        const int se = tid * 8;                       // staging: this thread's element offset inside a tile
-        const bool stager = se < TILE;
-        const int sv = (se / QE) * VQ + se % QE;      // ... and inside the padded V tile in LDS
-        const int koff = lane * 8;
-        const int voff = TILE + qd * VQ + n * 4;
-        const taper_work_item item = a.items[it];
-        const int32_t* __restrict__ row = a.bt + (int64_t)item.seq0 * a.bt_stride + item.page0;
-        const int n_tok = item.n_tokens;
-        const int n_pages = (n_tok + 15) >> 4;
-        const int n_blocks = (n_tok + 63) >> 6;
-        const int R = item.n_branch * g;           // query rows
-        const int tiles = (R + 15) >> 4;
-        int n_act = (tiles - wave + 3) >> 2;       // tiles wave, wave+4, ...
-        n_act = n_act < 0 ? 0 : (n_act > NTW ? NTW : n_act);
-        meta_store(sm.meta, meta_load(a, item, tid), item.n_branch, tid);
-
-        bf16x8 qf[NTW][KS];
-        float m[NTW], l[NTW];
-        f32x4 O[NTW][DT];
+    const MetaRegs mr = meta_load(a, item, tid);
+    bf16x8 qf[NT][KS];
+    float m[NT], l[NT];
+    f32x4 O[NT][DT];
+    if constexpr (NA > 0) {
 #pragma unroll
-        for (int k = 0; k < NTW; ++k) {
-            const int r = 16 * (wave + 4 * k) + n;
-            const bool ok = k < n_act && r < R;
-            const int rr = ok ? r : 0;
+        for (int k = 0; k < NA; ++k) {
+            const int r = 16 * (wave + 4 * k) + n, rr = r < R ? r : 0;  // (lane columns past the last row repeat the first; not stored)
             const __bf16* qrow = (const __bf16*)a.q + ((int64_t)(item.seq0 + rr / g) * a.n_q_heads + hk * g + rr % g) * D;
 #pragma unroll
-            for (int j = 0; j < KS; ++j) {
-                bf16x8 v = *(const bf16x8*)(qrow + 8 * (4 * j + qd));
-                if (!ok) v = (bf16x8)(0);
-                qf[k][j] = v;
-            }
+            for (int j = 0; j < KS; ++j) qf[k][j] = *(const bf16x8*)(qrow + 8 * (4 * j + qd));
             m[k] = -INFINITY;
             l[k] = 0.f;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) O[k][dt] = (f32x4)(0.f);
         }
-
-        // Register sets for staging: while block b is computed from LDS, the next blocks are in flight.
-        bf16x8 stgA[8], stgB[8];
-        auto stage_load = [&](int b, bf16x8 (&stg)[8]) {
-            if (stager && b < n_blocks) {
-#pragma unroll
-                for (int pg = 0; pg < 4; ++pg) {
-                    const int ip = 4 * b + pg < n_pages ? 4 * b + pg : n_pages - 1;
-                    const int64_t pid = row[ip];
-                    const __bf16* kp = kvb + pid * page_elems + (int64_t)hk * TILE + se;
-                    stg[2 * pg] = stream_load((const bf16x8*)kp);
-                    stg[2 * pg + 1] = stream_load((const bf16x8*)(kp + (int64_t)Hkv * TILE));
-                }
-            }
-        };
-        auto stage_store = [&](int b, const bf16x8 (&stg)[8]) {
-            if (stager && b < n_blocks) {
-                __bf16* base = lds + (b & 1) * BUF;
-#pragma unroll
-                for (int pg = 0; pg < 4; ++pg) {
-                    *(bf16x8*)(base + pg * PAGE_LDS + se) = stg[2 * pg];
-                    *(bf16x8*)(base + pg * PAGE_LDS + TILE + sv) = stg[2 * pg + 1];
-                }
-            }
-        };
-        auto compute = [&](int b, int buf) {
-            if (n_act == 0) return;
-#pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-                const int nv = n_tok - (64 * b + 32 * hf);
-                if (nv <= 0) break;
-                const __bf16* pa = lds + buf * BUF + (2 * hf) * PAGE_LDS;
-                const __bf16* pb = pa + PAGE_LDS;
-                bf16x8 pf[NTW];
-                if constexpr (NTW == 1) {
-                    // one tile per wave: every K fragment is used once, so the two pages' fragments take turns
-                    // in one set of registers (this variant has none to spare beside its three staging sets)
-                    f32x4 sx = (f32x4)(0.f), sy = (f32x4)(0.f);
-                    bf16x8 kf[KS];
-#pragma unroll
-                    for (int j = 0; j < KS; ++j) kf[j] = *(const bf16x8*)(pa + koff + j * 512);
-#pragma unroll
-                    for (int j = 0; j < KS; ++j) sx = mfma16(kf[j], qf[0][j], sx);
-#pragma unroll
-                    for (int j = 0; j < KS; ++j) kf[j] = *(const bf16x8*)(pb + koff + j * 512);
-#pragma unroll
-                    for (int j = 0; j < KS; ++j) sy = mfma16(kf[j], qf[0][j], sy);
-                    if (nv < 32) mask_tail(sx, sy, qd, nv);
-                    pf[0] = softmax_block<DT>(sx, sy, c, m[0], l[0], O[0]);
-                } else {
-                    bf16x8 kx[KS], ky[KS];
-#pragma unroll
-                    for (int j = 0; j < KS; ++j) {
-                        kx[j] = *(const bf16x8*)(pa + koff + j * 512);
-                        ky[j] = *(const bf16x8*)(pb + koff + j * 512);
-                    }
-#pragma unroll
-                    for (int k = 0; k < NTW; ++k) {
-                        if (k < n_act) {
-                            f32x4 sx = (f32x4)(0.f), sy = (f32x4)(0.f);
-#pragma unroll
-                            for (int j = 0; j < KS; ++j) {
-                                sx = mfma16(kx[j], qf[k][j], sx);
-                                sy = mfma16(ky[j], qf[k][j], sy);
-                            }
-                            if (nv < 32) mask_tail(sx, sy, qd, nv);
-                            pf[k] = softmax_block<DT>(sx, sy, c, m[k], l[k], O[k]);
-                        }
-                    }
-                }
-                // (four V fragment pairs at a time, then one branch for the ragged tail: a branch per
-                // fragment would keep the compiler from issuing the LDS reads ahead of the matrix
-                // instructions; all eight pairs at once do not fit the registers of two tiles per wave)
-#pragma unroll
-                for (int h = 0; h < DT / 4; ++h) {
-                    bf16x4 va[4], vb[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        va[i] = *(const bf16x4*)(pa + voff + (4 * h + i) * 64);
-                        vb[i] = *(const bf16x4*)(pb + voff + (4 * h + i) * 64);
-                    }
-                    if (nv < 32) zero_tail(va, vb, qd, nv);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const bf16x8 vf = cat(va[i], vb[i]);
-#pragma unroll
-                        for (int k = 0; k < NTW; ++k)
-                            if (k < n_act) O[k][4 * h + i] = mfma16(vf, pf[k], O[k][4 * h + i]);
-                    }
-                }
-                settle();
-            }
-        };
-
-        if constexpr (NTW == 1) {
-            // registers to spare: a third set, so that three blocks are in flight while one is computed
-            // (a workgroup's share of a saturated memory system grows with what it keeps in flight)
-            bf16x8 stgC[8];
-            stage_load(0, stgA);
-            stage_load(1, stgB);
-            stage_load(2, stgC);
-            stage_store(0, stgA);
-            __syncthreads();
-            for (int b = 0; b < n_blocks; b += 3) {
-                stage_load(b + 3, stgA);
-                compute(b, b & 1);
-                stage_store(b + 1, stgB);
-                __syncthreads();
-                if (b + 1 >= n_blocks) break;
-                stage_load(b + 4, stgB);
-                compute(b + 1, (b + 1) & 1);
-                stage_store(b + 2, stgC);
-                __syncthreads();
-                if (b + 2 >= n_blocks) break;
-                stage_load(b + 5, stgC);
-                compute(b + 2, b & 1);
-                stage_store(b + 3, stgA);
-                __syncthreads();
-            }
-        } else {
-            stage_load(0, stgA);
-            stage_load(1, stgB);
-            stage_store(0, stgA);
-            __syncthreads();
-            for (int b = 0; b < n_blocks; b += 2) {
-                stage_load(b + 2, stgA);
-                compute(b, b & 1);
-                stage_store(b + 1, stgB);
-                __syncthreads();
-                if (b + 1 >= n_blocks) break;
-                stage_load(b + 3, stgB);
-                compute(b + 1, (b + 1) & 1);
-                stage_store(b + 2, stgA);
-                __syncthreads();
-            }
-        }
-
-        // (lane coordinates are derived afresh: shared with the ones above, they would stay live through the streaming loop)
-        const int tid_e = opaque(threadIdx.x);
-        store_shared_partials<D, NTW, PF>(a, item, hk, R, n_act, wave, tid_e & 15, (tid_e & 63) >> 4, m, l, O);
-        // publish the partials; merge every branch whose set is now complete
-        stores_done();
-        __syncthreads();
-#ifdef TAPER_WG_TRACE
-        const long long t_m0 = wall_clock64();
-#endif
-        arrive_and_merge<D, PF>(a, sm.meta, sm.todo, &sm.n_todo, item, hk, tid_e);
-#ifdef TAPER_WG_TRACE
-        __syncthreads();
-        if (tid == 0 && a.trace) a.trace[4 * blockIdx.x + 3] += wall_clock64() - t_m0;
-#endif
-        __syncthreads();
     }
-}
 
-// ---------------------------------------------------------------------------
-// Shared-prefix kernel for requests wider than 8 row tiles (9 to 12: up to 24 branches at
-// 8 query heads per KV head), head_dim 128.  Three tiles per wave leave no registers for
-// staging sets, so KV goes from global memory straight into LDS: every wave-level 16-byte
-// load lands as 1 KiB at a wave-uniform LDS address, lane after lane, which is exactly one
-// quarter of a K tile or one (padded) quarter of a V tile.  Four 32-token buffers: one is
-// computed from while three are in flight.
-//
-// The compiler does not see which buffer an LDS read touches and would wait for every
-// outstanding load before each one, so the fragment reads are written out (with their own
-// wait), and the barrier is the bare instruction behind an explicit wait: "all but the
-// loads of the blocks after this one have landed, and my LDS reads are done".
-// ---------------------------------------------------------------------------
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
-typedef const __attribute__((address_space(1))) void* global_void_ptr;
-DEV unsigned lds_address(const void* p) { return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)p; }
-// Two block-table entries through the scalar cache.  (The compiler reads the table with vector
-// loads once direct-to-LDS loads are in the loop, and a vector load's completion waits for
-// every load issued before it: the pipeline would drain at each one.)  The wait is part of
-// the statement: the compiler may copy the results right after it.
-DEV void page_ids_fetch(const int32_t* px, const int32_t* py, int& x, int& y) {
-    asm volatile("s_load_dword %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=&s"(x), "=&s"(y) : "s"(px), "s"(py));
-}
-template <int N>
-DEV void wait_loads_but() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N)); }
-
-// K fragments of a 32-token block: four 16-byte reads per page, 1 KiB apart; PB = bytes from one page to the next
-template <int PB>
-DEV void lds_read_k(unsigned addr, bf16x8 (&kx)[4], bf16x8 (&ky)[4]) {
-    asm volatile(
-        "ds_read_b128 %0, %8\n\t"
-        "ds_read_b128 %1, %8 offset:1024\n\t"
-        "ds_read_b128 %2, %8 offset:2048\n\t"
-        "ds_read_b128 %3, %8 offset:3072\n\t"
-        "ds_read_b128 %4, %8 offset:%9\n\t"
-        "ds_read_b128 %5, %8 offset:%10\n\t"
-        "ds_read_b128 %6, %8 offset:%11\n\t"
-        "ds_read_b128 %7, %8 offset:%12\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(kx[0]), "=&v"(kx[1]), "=&v"(kx[2]), "=&v"(kx[3]), "=&v"(ky[0]), "=&v"(ky[1]), "=&v"(ky[2]), "=&v"(ky[3])
-        : "v"(addr), "n"(PB), "n"(PB + 1024), "n"(PB + 2048), "n"(PB + 3072));
-}
-// V fragments of four consecutive 16-dim groups (128 bytes apart), both pages
-template <int PB>
-DEV void lds_read_v(unsigned addr, bf16x4 (&va)[4], bf16x4 (&vb)[4]) {
-    asm volatile(
-        "ds_read_b64 %0, %8\n\t"
-        "ds_read_b64 %1, %8 offset:128\n\t"
-        "ds_read_b64 %2, %8 offset:256\n\t"
-        "ds_read_b64 %3, %8 offset:384\n\t"
-        "ds_read_b64 %4, %8 offset:%9\n\t"
-        "ds_read_b64 %5, %8 offset:%10\n\t"
-        "ds_read_b64 %6, %8 offset:%11\n\t"
-        "ds_read_b64 %7, %8 offset:%12\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(va[0]), "=&v"(va[1]), "=&v"(va[2]), "=&v"(va[3]), "=&v"(vb[0]), "=&v"(vb[1]), "=&v"(vb[2]), "=&v"(vb[3])
-        : "v"(addr), "n"(PB), "n"(PB + 128), "n"(PB + 256), "n"(PB + 384));
-}
-
-template <int D, int PF>
-DEV void shared_path_wide(const StepArgs& a, const int part, const int hk, SharedSmem<D>& sm) {
-    static_assert(D == 128, "a wave's 64 x 16 bytes must be one quarter of a tile");
-    constexpr int NTW = 3, KS = D / 32, DT = D / 16, TILE = 16 * D;
-    constexpr int QE = SharedSmem<D>::QE, VQ = SharedSmem<D>::VQ, PAGE_LDS = SharedSmem<D>::PAGE_LDS;
-    constexpr int BLK = 2 * PAGE_LDS;  // one 32-token buffer; sm.kv holds four
-    constexpr int PB = 2 * PAGE_LDS;   // bytes per page in LDS
-    __bf16* lds = sm.kv;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int Hkv = a.n_kv_heads, g = a.gqa;
-    const __bf16* __restrict__ kvb = (const __bf16*)a.kv;
-    const int64_t page_elems = 2LL * Hkv * TILE;
-    const float c = a.scale_log2e;
-
-    const int it0 = a.part_start[part], it1 = a.part_start[part + 1];
-    for (int it = it0; it < it1; ++it) {
-        const int tid = opaque(threadIdx.x);
-        const int lane = tid & 63;
-        const int n = lane & 15, qd = lane >> 4;
-        const int se = tid * 8;  // this thread's 8 elements of every tile it stages
-        const taper_work_item item = a.items[it];
-        const int32_t* __restrict__ row = a.bt + (int64_t)item.seq0 * a.bt_stride + item.page0;
-        const int n_tok = item.n_tokens;
-        const int n_pages = (n_tok + 15) >> 4;
-        const int n_blocks = (n_tok + 31) >> 5;
-        const int R = item.n_branch * g;
-        const int tiles = (R + 15) >> 4;
-        int n_act = (tiles - wave + 3) >> 2;
-        n_act = n_act < 0 ? 0 : (n_act > NTW ? NTW : n_act);
-        meta_store(sm.meta, meta_load(a, item, tid), item.n_branch, tid);
-
-        bf16x8 qf[NTW][KS];
-        float m[NTW], l[NTW];
-        f32x4 O[NTW][DT];
-#pragma unroll
-        for (int k = 0; k < NTW; ++k) {
-            const int r = 16 * (wave + 4 * k) + n;
-            const bool ok = k < n_act && r < R;
-            const int rr = ok ? r : 0;
-            const __bf16* qrow = (const __bf16*)a.q + ((int64_t)(item.seq0 + rr / g) * a.n_q_heads + hk * g + rr % g) * D;
-#pragma unroll
-            for (int j = 0; j < KS; ++j) {
-                bf16x8 v = *(const bf16x8*)(qrow + 8 * (4 * j + qd));
-                if (!ok) v = (bf16x8)(0);
-                qf[k][j] = v;
-            }
-            m[k] = -INFINITY;
-            l[k] = 0.f;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) O[k][dt] = (f32x4)(0.f);
+    // staging: at head_dim 128 a wave loads quarter `wave` of K and V of both pages, at 64 all of page `wave`
+    const unsigned ring = lds_address(sm.kv);
+    const unsigned off_k = lane * 16;
+    const unsigned off_v = (lane ^ ((D == 128 ? wave & 1 : lane >> 5) << 3)) * 16;
+    int pid[D == 128 ? 2 : 1];  // the pool pages this wave stages next
+    auto fetch_ids = [&](int b) {  // past the last page (a block that ends early or does not exist): the last page
+        if constexpr (D == 128) {
+            const int i0 = 2 * b, i1 = 2 * b + 1;
+            pid[0] = row[i0 < n_pages ? i0 : n_pages - 1];
+            pid[1] = row[i1 < n_pages ? i1 : n_pages - 1];
+        } else {
+            const int i = 4 * b + wave;
+            pid[0] = row[i < n_pages ? i : n_pages - 1];
         }
-
-        // 4 loads of 16 bytes per thread and block: K and V quarter `wave` of both pages
-        int pid0, pid1;  // the pool pages of the block staged next (wave-uniform)
-        auto fetch_ids = [&](int b) {  // past the last page (an odd count's second page, a block that does not exist): the last page
-            const int i0 = 2 * b < n_pages ? 2 * b : n_pages - 1, i1 = 2 * b + 1 < n_pages ? 2 * b + 1 : n_pages - 1;
-            page_ids_fetch(row + i0, row + i1, pid0, pid1);
-        };
-        auto stage = [&](int b) {
-            __bf16* buf = lds + (b & 3) * BLK;
+    };
+    auto stage = [&](int b) {
+        const unsigned buf = ring + (b & (Sm::RING - 1)) * Sm::BLOCK_BYTES;
+        if constexpr (D == 128) {
 #pragma unroll
             for (int pg = 0; pg < 2; ++pg) {
-                const int64_t pid = pg ? pid1 : pid0;
-                const __bf16* kp = kvb + pid * page_elems + (int64_t)hk * TILE + se;
-                __builtin_amdgcn_global_load_lds((global_void_ptr)kp, (lds_void_ptr)(buf + pg * PAGE_LDS + wave * QE), 16, 0, 2);
-                __builtin_amdgcn_global_load_lds((global_void_ptr)(kp + (int64_t)Hkv * TILE),
-                                                 (lds_void_ptr)(buf + pg * PAGE_LDS + TILE + wave * VQ), 16, 0, 2);
+                const char* k = kvb + pid[pg] * page_bytes + wave * 1024;
+                load_to_lds(k, off_k, buf + pg * Sm::TILE_BYTES + wave * 1024);
+                load_to_lds(k + (int64_t)Hkv * Sm::TILE_BYTES, off_v, buf + Sm::v_chunk(pg, wave));
             }
-        };
-        auto compute = [&](int b) {
-            const int nv = n_tok - 32 * b;
-            const unsigned base = lds_address(lds + (b & 3) * BLK);
-            bf16x8 kx[KS], ky[KS];
-            lds_read_k<PB>(base + lane * 16, kx, ky);
-            bf16x8 pf[NTW];
+        } else {
+            const char* k = kvb + pid[0] * page_bytes;
 #pragma unroll
-            for (int k = 0; k < NTW; ++k) {
-                if (k < n_act) {
+            for (int h = 0; h < 2; ++h) {
+                load_to_lds(k + h * 1024, off_k, buf + wave * Sm::TILE_BYTES + h * 1024);
+                load_to_lds(k + (int64_t)Hkv * Sm::TILE_BYTES + h * 1024, off_v, buf + Sm::v_chunk(wave, h));
+            }
+        }
+    };
+    // this lane's V fragment of 16-dim group dt (the swizzle: odd quarters have their 128-byte halves exchanged)
+    const int v_lane = Sm::V_OFF + (D == 128 ? qd * 2048 : (qd >> 1) * 2048 + (qd & 1) * QB) + n * 8;
+    const int v_even = v_lane + (qd & 1) * 128, v_odd = v_lane - (qd & 1) * 128;
+    auto compute = [&](int b, auto tail) {
+        if constexpr (NA > 0) {
+            const char* blk = sm.kv + (b & (Sm::RING - 1)) * Sm::BLOCK_BYTES;
+#pragma unroll
+            for (int hf = 0; hf < Sm::PAGES / 2; ++hf) {
+                const int nv = n_tok - Sm::TOKENS * b - 32 * hf;
+                if (tail && nv <= 0) break;
+                const char *kp = blk + hf * 2 * Sm::TILE_BYTES + lane * 16, *vp = blk + hf * 2 * Sm::TILE_BYTES;
+                bf16x8 kx[KS], ky[KS], pf[NA];
+#pragma unroll
+                for (int j = 0; j < KS; ++j) {
+                    kx[j] = *(const bf16x8*)(kp + j * 1024);
+                    ky[j] = *(const bf16x8*)(kp + Sm::TILE_BYTES + j * 1024);
+                }
+#pragma unroll
+                for (int k = 0; k < NA; ++k) {
                     f32x4 sx = (f32x4)(0.f), sy = (f32x4)(0.f);
 #pragma unroll
                     for (int j = 0; j < KS; ++j) {
                         sx = mfma16(kx[j], qf[k][j], sx);
                         sy = mfma16(ky[j], qf[k][j], sy);
                     }
-                    if (nv < 32) mask_tail(sx, sy, qd, nv);
+                    if (tail && nv < 32) mask_tail(sx, sy, qd, nv);
                     pf[k] = softmax_block<DT>(sx, sy, c, m[k], l[k], O[k]);
                 }
-            }
+                // (four V fragment pairs at a time: all eight do not fit the registers of three tiles per wave)
 #pragma unroll
-            for (int h = 0; h < DT / 4; ++h) {
-                bf16x4 va[4], vb[4];
-                lds_read_v<PB>(base + 2 * (TILE + qd * VQ + n * 4) + h * 512, va, vb);
-                if (nv < 32) zero_tail(va, vb, qd, nv);
+                for (int h = 0; h < DT / 4; ++h) {
+                    bf16x4 va[4], vb[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const bf16x8 vf = cat(va[i], vb[i]);
+                    for (int i = 0; i < 4; ++i) {
+                        const char* v = vp + (i & 1 ? v_odd : v_even) + (4 * h + i) * 128;
+                        va[i] = *(const bf16x4*)v;
+                        vb[i] = *(const bf16x4*)(v + 1024);
+                    }
+                    if (tail && nv < 32) zero_tail(va, vb, qd, nv);
 #pragma unroll
-                    for (int k = 0; k < NTW; ++k)
-                        if (k < n_act) O[k][4 * h + i] = mfma16(vf, pf[k], O[k][4 * h + i]);
+                    for (int i = 0; i < 4; ++i) {
+                        const bf16x8 vf = cat(va[i], vb[i]);
+#pragma unroll
+                        for (int k = 0; k < NA; ++k) O[k][4 * h + i] = mfma16(vf, pf[k], O[k][4 * h + i]);
+                    }
                 }
+                settle();
             }
-            settle();
-        };
-
-        // (the previous item's LDS reads of these buffers ended before its closing barriers)
-        for (int b = 0; b < 3; ++b) {
-            fetch_ids(b);
-            if (b < n_blocks) stage(b);
         }
-        fetch_ids(3);
-        for (int b = 0; b < n_blocks; ++b) {
-            const int after = n_blocks - 1 - b;  // blocks staged behind this one: 12, 8 or 4 loads may stay in flight
-            if (after >= 2) wait_loads_but<8>();
-            else if (after == 1) wait_loads_but<4>();
-            else wait_loads_but<0>();
-            __builtin_amdgcn_s_barrier();  // block b is in LDS for every wave; everyone is done with block b - 1
-            if (b + 3 < n_blocks) stage(b + 3);  // into the buffer block b - 1 was computed from
-            if (n_act > 0) compute(b);
-            fetch_ids(b + 4);  // for the next iteration's stage: its latency overlaps the wait for block b + 1
-        }
+    };
 
+    // (the previous item's LDS reads of these buffers ended before its closing barriers)
+#pragma unroll
+    for (int b = 0; b < Sm::RING - 1; ++b) {
+        fetch_ids(b);
+        if (b < n_blocks) stage(b);
+    }
+    fetch_ids(Sm::RING - 1);
+    meta_store(sm.meta, mr, item.n_branch, tid);
+    // (the queries' loads are waited for here: inside the loop that wait would also drain the blocks in flight, every time)
+    if constexpr (NA > 0) {
+#pragma unroll
+        for (int k = 0; k < NA; ++k)
+#pragma unroll
+            for (int j = 0; j < KS; ++j) asm volatile("" : "+v"(qf[k][j]));
+    }
+    for (int b = 0; b < n_blocks - 1; ++b) {
+        if (b + 2 < n_blocks) wait_loads_and_meet<2 * LOADS>();  // block b is in LDS for every wave; everyone is done with block b - 1
+        else wait_loads_and_meet<LOADS>();
+        if (b + Sm::RING - 1 < n_blocks) stage(b + Sm::RING - 1);  // into the buffer block b - 1 was computed from
+        compute(b, std::false_type{});
+        fetch_ids(b + Sm::RING);  // for the next iteration's stage: waited for together with block b + 1
+    }
+    wait_loads_and_meet<0>();
+    compute(n_blocks - 1, std::true_type{});
+    if constexpr (NA > 0) {
+        // (lane coordinates are derived afresh: shared with the ones above, they would stay live through the streaming loop)
         const int tid_e = opaque(threadIdx.x);
-        store_shared_partials<D, NTW, PF>(a, item, hk, R, n_act, wave, tid_e & 15, (tid_e & 63) >> 4, m, l, O);
+        store_shared_partials<D, NA, PF>(a, item, hk, R, wave, tid_e & 15, (tid_e & 63) >> 4, m, l, O);
+    }
+}
+
+template <int D, int NTW, int PF>
+DEV void shared_path(const StepArgs& a, const int part, const int hk, SharedSmem<D>& sm) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int it0 = a.part_start[part], it1 = a.part_start[part + 1];
+    for (int it = it0; it < it1; ++it) {
+        const taper_work_item item = load_item(a, it);
+        const int tid = opaque(threadIdx.x);
+        const int tiles = (item.n_branch * a.gqa + 15) >> 4;
+        const int n_act = (tiles - wave + 3) >> 2;  // tiles wave, wave + 4, ...; 0 for a wave past the last tile (tiles >= 1)
+        if (NTW >= 3 && n_act >= 3) shared_stream<D, NTW >= 3 ? 3 : 1, PF>(a, item, hk, sm, tid, wave);
+        else if (NTW >= 2 && n_act == 2) shared_stream<D, NTW >= 2 ? 2 : 1, PF>(a, item, hk, sm, tid, wave);
+        else if (n_act == 1) shared_stream<D, 1, PF>(a, item, hk, sm, tid, wave);
+        else shared_stream<D, 0, PF>(a, item, hk, sm, tid, wave);
+        // publish the partials; merge every branch whose set is now complete
         stores_done();
         __syncthreads();
-        arrive_and_merge<D, PF>(a, sm.meta, sm.todo, &sm.n_todo, item, hk, tid_e);
+#ifdef TAPER_WG_TRACE
+        const long long t_m0 = wall_clock64();
+#endif
+        arrive_and_merge<D, PF>(a, sm.meta, sm.todo, &sm.n_todo, item, hk, opaque(threadIdx.x));
+#ifdef TAPER_WG_TRACE
+        __syncthreads();
+        if (tid == 0 && a.trace) a.trace[4 * blockIdx.x + 3] += wall_clock64() - t_m0;
+#endif
         __syncthreads();
     }
 }
@@ -1086,14 +909,14 @@ DEV void shared_path_wide(const StepArgs& a, const int part, const int hk, Share
 // ---------------------------------------------------------------------------
 // ALLP: a launch without shared-prefix work (no shared path in the kernel, block-table rows by scalar loads).
 template <int D, int NTW, int PF, bool ALLP>
-__global__ __launch_bounds__(256, (NTW <= 2 || D == 128 ? 2 : 1)) void decode_kernel(StepArgs a) {
+__global__ __launch_bounds__(256, 2) void decode_kernel(StepArgs a) {
     union Smem {
         SharedSmem<D> sh;
         PrivateSmem<D> pr;
     };
     __shared__ __attribute__((aligned(16))) char smem_raw[sizeof(Smem)];
     const int part = blockIdx.x / a.n_kv_heads;
-    const int hk = blockIdx.x % a.n_kv_heads;
+    const int hk = (blockIdx.x + a.part_turn[part]) % a.n_kv_heads;
 #ifdef TAPER_WG_TRACE  // trace builds only (wg_trace.py): per-workgroup clocks -- start, own share done, left, time in merges
     long long* trace = a.trace;
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x] = wall_clock64();
@@ -1103,10 +926,7 @@ __global__ __launch_bounds__(256, (NTW <= 2 || D == 128 ? 2 : 1)) void decode_ke
         it0 = a.part_start[part];
         it1 = a.part_start[part + 1];
     } else if (part < a.n_parts_shared) {
-        if constexpr (NTW == 3 && D == 128)
-            shared_path_wide<D, PF>(a, part, hk, *reinterpret_cast<SharedSmem<D>*>(smem_raw));
-        else
-            shared_path<D, NTW, PF>(a, part, hk, *reinterpret_cast<SharedSmem<D>*>(smem_raw));
+        shared_path<D, NTW, PF>(a, part, hk, *reinterpret_cast<SharedSmem<D>*>(smem_raw));
         __syncthreads();
     } else {
         it0 = a.part_start[part];
@@ -1115,7 +935,7 @@ __global__ __launch_bounds__(256, (NTW <= 2 || D == 128 ? 2 : 1)) void decode_ke
 #ifdef TAPER_WG_TRACE
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x + 1] = wall_clock64();  // shared share done (a private share: overwritten when it is done)
 #endif
-    private_items<D, PF, ALLP>(a, it0, it1, hk, *reinterpret_cast<PrivateSmem<D>*>(smem_raw));
+    private_items<D, PF>(a, it0, it1, hk, *reinterpret_cast<PrivateSmem<D>*>(smem_raw));
 #ifdef TAPER_WG_TRACE
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x + 2] = wall_clock64();
 #endif
@@ -1183,7 +1003,6 @@ hipError_t launch_kv_append(const void* k_new, const void* v_new, const int64_t*
 // flight; nothing is computed but an XOR that keeps the loads alive.  What this reaches on the
 // same bytes and launch shape is the rate the machine leaves for any read-bound kernel.
 // ---------------------------------------------------------------------------
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void stream_read_kernel(const u32x4* __restrict__ base, int64_t pieces_per_wg, unsigned* sink) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const u32x4* mine = base + (int64_t)blockIdx.x * pieces_per_wg * 256;  // 256 x 16 B = one 4 KiB piece

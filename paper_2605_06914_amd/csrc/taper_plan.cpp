@@ -8,6 +8,7 @@
 #include "taper_plan.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 
@@ -52,6 +53,8 @@ namespace {
 
 constexpr int64_t kPieceCostTokens = 200;   // what one more piece of a cut sequence costs, in tokens' streaming time
 constexpr int64_t kOnePerUnitLossPct = 3;   // what one workgroup per compute unit instead of two costs, percent
+constexpr double kTokensPerMergedRow = 4.0;      // see least_tokens
+constexpr int64_t kSaturatingShareTokens = 600;  // shares of fewer tokens are over before the memory system is saturated
 
 struct Segment {
     int32_t seq0, n_branch, page0, n_tokens, kind;
@@ -66,6 +69,8 @@ struct Segment {
 struct Cost {
     int64_t per_token_pct, fixed;
     int64_t merge = 0;  // extra cost of the item that ends a sequence: it arrives last as a rule and merges the partials
+    int64_t per_branch = 0;  // further fixed cost for each of a shared item's branches
+    int64_t item(const Segment& s) const { return fixed + per_branch * s.n_branch; }
 };
 
 // Cuts `segs` into workgroup shares of about `quota` cost units, at multiples of `blk` tokens
@@ -128,6 +133,14 @@ int partition_fill(const std::vector<Segment>& segs, int64_t quota, int blk, con
     return fill > 0 ? part + 1 : part;
 }
 
+// A prefix of n tokens cut into k items takes n / k tokens' time to stream and k times its R query rows to merge, and one
+// workgroup merges them all: the last to arrive, as a rule, for every branch of the request.  A token costs a
+// shared workgroup 20 ns, a row and item 7 ns (5 branches x 16 heads: 109 us for 195 items), so that k items are best at
+// k * k = kTokensPerMergedRow * n / R.
+int64_t least_tokens(const Segment& s, int gqa) {
+    return (int64_t)std::sqrt((double)s.n_tokens * s.n_branch * gqa / kTokensPerMergedRow);
+}
+
 // The same for items with a large fixed cost (shared-prefix items).  A segment that does not
 // fit what is left of the current share tops it up (if that is worth an item); what then
 // remains, if it is more than one share, is cut into equal items with a share each rather than
@@ -135,12 +148,10 @@ int partition_fill(const std::vector<Segment>& segs, int64_t quota, int blk, con
 // cost or make the last item much longer than the others).  The last of those items is
 // `tail_discount` blocks shorter: the workgroup that finishes a shared prefix usually finds the
 // request's branches complete and has to merge them all.
-int partition_even(const std::vector<Segment>& segs, int64_t quota, int blk, const Cost cost, int64_t tail_discount,
+int partition_even(const std::vector<Segment>& segs, int gqa, int64_t quota, int blk, const Cost cost, int64_t tail_discount,
                    int part_id0, std::vector<taper_work_item>* items) {
     quota = std::max<int64_t>(1, quota);
     const int64_t blk_cost = std::max<int64_t>(1, blk * cost.per_token_pct / 100);
-    const int64_t min_blocks = std::max<int64_t>(1, (cost.fixed + blk_cost - 1) / blk_cost);
-    const int64_t cap = std::max<int64_t>(min_blocks, (quota - cost.fixed) / blk_cost);  // blocks of an item with a share to itself
     int part = 0;
     int64_t fill = 0;
     auto emit = [&](const Segment& s, int64_t off, int64_t take) {
@@ -153,7 +164,7 @@ int partition_even(const std::vector<Segment>& segs, int64_t quota, int blk, con
         it.kind = s.kind;
         it.part = part_id0 + part;
         items->push_back(it);
-        fill += cost.fixed + take * blk_cost;
+        fill += cost.item(s) + take * blk_cost;
     };
     auto close = [&]() {
         if (fill > 0) ++part;
@@ -161,6 +172,9 @@ int partition_even(const std::vector<Segment>& segs, int64_t quota, int blk, con
     };
     for (size_t si = 0; si < segs.size(); ++si) {
         const Segment& s = segs[si];
+        const int64_t min_blocks = std::max<int64_t>(1, (cost.item(s) + blk_cost - 1) / blk_cost);
+        // blocks of an item with a share to itself
+        const int64_t cap = std::max({min_blocks, (quota - cost.item(s)) / blk_cost, least_tokens(s, gqa) / blk});
         if (s.siblings >= 2) {
             // Sub-groups of one request read the same pages.  They get the same cuts, every item a share of its
             // own and therefore the launch's start as its start, in workgroups next to each other: the sub-groups
@@ -185,7 +199,7 @@ int partition_even(const std::vector<Segment>& segs, int64_t quota, int blk, con
             continue;
         }
         int64_t remaining = (s.n_tokens + blk - 1) / blk, off = 0;  // blocks
-        int64_t room = (quota - fill - cost.fixed) / blk_cost;      // blocks that still fit the current share
+        int64_t room = (quota - fill - cost.item(s)) / blk_cost;    // blocks that still fit the current share
         if (fill > 0 && room < remaining && room < min_blocks) {    // not worth an item: start the next share
             close();
             room = cap;
@@ -214,6 +228,23 @@ int partition_even(const std::vector<Segment>& segs, int64_t quota, int blk, con
     }
     close();
     return part;
+}
+
+// Workgroup w of share q works on kv head (w + turn[q]) mod n_kv_heads.  Workgroups are dealt to the XCDs in turn, and the
+// XCDs do not read equally fast (the odd ones were 12 to 15 % behind in launches of shared work alone), so the
+// shares take turns: every XCD then has workgroups of every head, and each head's pool evens the XCDs out.  The
+// sub-groups of one request keep the turn of the first: the same head of the same chunk stays on one XCD, whose
+// L2 they share it in.
+void plan_part_turns(const taper_attn_config& cfg, const int32_t* branch_group, HostPlan* p) {
+    const int n_parts = p->n_parts_shared + p->n_parts_private;
+    p->part_turn.resize(n_parts);
+    for (int q = 0; q < n_parts; ++q) {
+        p->part_turn[q] = q % cfg.n_kv_heads;
+        if (q == 0 || q >= p->n_parts_shared || p->part_start[q - 1] == p->part_start[q] || p->part_start[q] == p->part_start[q + 1]) continue;
+        const taper_work_item &a = p->items[p->part_start[q - 1]], &b = p->items[p->part_start[q]];
+        if (a.seq0 != b.seq0 && branch_group[a.seq0] == branch_group[b.seq0] && a.page0 == b.page0 && a.n_tokens == b.n_tokens)
+            p->part_turn[q] = p->part_turn[q - 1];
+    }
 }
 
 }  // namespace
@@ -404,40 +435,54 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
         for (Segment& s : priv) s.whole_seq = pieces[s.seq0] == 1;
     }
 
-    // ---- workgroup shares: both kinds run in one launch and should finish together.  A workgroup of
-    // the shared kind keeps fewer bytes in flight than one of the private kind and so gets a smaller
-    // slice of a saturated memory system: its tokens are weighted by shared_cost_pct / 100.  Every
-    // item also has a fixed cost (a shared item's is large: rows of several branches to store, and
-    // the merges of all branches it completes).
-    int widest = 0;  // row tiles of the widest shared item: up to 4, the kernel stages with three register sets,
-                     // up to 8 with two, above that straight into LDS (measured weights for each)
-    for (const Segment& s : shared) widest = std::max(widest, (s.n_branch * g + 15) / 16);
-    const Cost cost_shared = {opts && opts->shared_cost_pct > 0 ? opts->shared_cost_pct : (widest <= 4 ? 160 : (widest <= 8 || cfg.head_dim != 128) ? 200 : 140),
-                              opts && opts->shared_item_cost > 0 ? opts->shared_item_cost : 800};
-    const Cost cost_priv = {100, opts && opts->private_item_cost > 0 ? opts->private_item_cost : 128,
+    // ---- workgroup shares: both kinds run in one launch and should finish together.  A share's time is, to a few
+    // percent, a sum over its items of a fixed part (first loads, rows of several branches to store, arrival,
+    // merges) and a part per token.  Which kind's tokens cost more depends on what bounds the launch:
+    //  * shares of some hundred tokens and more keep the memory system saturated, and a workgroup gets a slice of it.  A
+    //    shared workgroup then takes 0.6 to 0.65 of the time of a private one per token (20.6 against 31.8 us per 1024
+    //    tokens in the mixed batch, least squares over its shares) and 13.8 us per item, a private one 6.1 us.  Measured
+    //    optimum of the launch, with the pool evening out the rest: 70 to 90 % per token.
+    //  * shorter ones are over before that, and what counts is a workgroup's own chain of blocks: 20 us per 1024 tokens for
+    //    a shared one, 9 for a private one, whose four waves each have a block in flight.  (The mixed batch on one
+    //    kv head, 232 tokens per share: 27.4 us at 120 %, 25.0 at 200 %, and 25.7 without a pool against 31.9 with 30 % in it.)
+    const int parts_total = std::max(1, target_wgs / cfg.n_kv_heads);
+    int64_t tok_listed = 0, tok_priv = 0;
+    for (const Segment& s : shared) tok_listed += s.n_tokens;
+    for (const Segment& s : priv) tok_priv += s.n_tokens;
+    tok_listed += tok_priv;
+    const int64_t share_tokens = tok_listed / parts_total;
+    const bool latency_bound = share_tokens < kSaturatingShareTokens;
+    const Cost cost_shared = {opts && opts->shared_cost_pct > 0 ? opts->shared_cost_pct : (latency_bound ? 180 : 80),
+                              opts && opts->shared_item_cost > 0 ? opts->shared_item_cost : (latency_bound ? 60 : 450), 0,
+                              opts && opts->shared_item_cost > 0 ? 0 : (latency_bound ? 32 : 0)};
+    const Cost cost_priv = {100, opts && opts->private_item_cost > 0 ? opts->private_item_cost : (shared.empty() || latency_bound ? 128 : 192),
                             opts && opts->private_merge_cost != 0 ? std::max(0, opts->private_merge_cost)
                                                                   : (shared.empty() ? 0 : 192)};
     const int64_t shared_tail_discount = 3;  // blocks: about what merging a request's branches costs
     int64_t cost_total = 0;
     for (const Segment& s : shared) {
-        cost_total += cost_shared.fixed + (int64_t)s.n_tokens * cost_shared.per_token_pct / 100;
+        cost_total += cost_shared.item(s) + (int64_t)s.n_tokens * cost_shared.per_token_pct / 100;
     }
     for (const Segment& s : priv) {
         cost_total += cost_priv.fixed + s.n_tokens + (s.ends_seq ? cost_priv.merge : 0);
     }
-    const int parts_total = std::max(1, target_wgs / cfg.n_kv_heads);
     // ---- the pool: private tokens no share owns.  No cost model predicts the shares' running times
-    // to better than some ten percent (the kinds' speeds depend on the mix, page placement matters),
-    // so the shares are cut a little short and every workgroup that finishes its share takes items
-    // from the pool until it is empty.  Pool items are small: the last one bounds the tail.
-    // Without shared-prefix work the shares are alike and end within a few percent of each other:
-    // a pool would only add items.
-    const int pool_pct = opts && opts->pool_pct != 0 ? std::max(0, std::min(90, opts->pool_pct)) : (shared.empty() ? 0 : 25);
+    // to better than some ten percent (the XCDs are not equally fast, page placement matters, and of two workgroups
+    // on a compute unit the one dispatched first is served first: with equal long shares it leaves at half the
+    // launch), so the shares are cut short and every workgroup that finishes its share takes items
+    // from the pool until it is empty.  The longer the shares, the larger the differences and the less a pool
+    // item's fixed cost weighs: a quarter of the private tokens for shares of up to 2048 tokens, rising to 60 % at
+    // 5120.  (25 / 40 / 60 %: mixed batch, 1900 tokens per share, 84.2 / 84.4 / 86.1 us; 8 requests of 64 branches, 5400 per
+    // share, 312 / 300 / 277; 640 sequences, 19000 per share, 841 / 827 / 803.)
+    // Without shared-prefix work the shares are alike and cutting a sequence costs more than the balance gains; and
+    // where latency bounds the launch a claim's round trip is too much.
+    const int pool_default = shared.empty() || latency_bound
+                                 ? 0
+                                 : (int)(25 + 35 * std::min<int64_t>(3072, std::max<int64_t>(0, share_tokens - 2048)) / 3072);
+    const int pool_pct = opts && opts->pool_pct != 0 ? std::max(0, std::min(90, opts->pool_pct)) : pool_default;
     const int pool_item_opt = opts && opts->pool_item_tokens > 0 ? opts->pool_item_tokens : 0;
     std::vector<Segment> pool;
     {
-        int64_t tok_priv = 0;
-        for (const Segment& s : priv) tok_priv += s.n_tokens;
         int64_t want = tok_priv * pool_pct / 100;
         while (want >= kPrivateBlockTokens && !priv.empty()) {
             Segment& s = priv.back();
@@ -469,7 +514,7 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     int64_t quota = std::max<int64_t>(std::max<int64_t>(kSharedBlockTokens, min_share), (cost_total + parts_total - 1) / parts_total);
     for (;;) {  // never more shares than asked for: an extra one would run after all the others
         p.items.clear();
-        p.n_parts_shared = partition_even(shared, quota, kSharedBlockTokens, cost_shared, shared_tail_discount, 0, &p.items);
+        p.n_parts_shared = partition_even(shared, g, quota, kSharedBlockTokens, cost_shared, shared_tail_discount, 0, &p.items);
         p.n_parts_private = partition_fill(priv, quota, kPrivateBlockTokens, cost_priv, p.n_parts_shared, &p.items);
         if (p.n_parts_shared + p.n_parts_private <= parts_total || quota >= cost_total * 2 + 4096) break;
         quota += std::max<int64_t>(16, quota / 256);
@@ -478,10 +523,11 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     p.part_start.assign(n_parts + 1, 0);
     for (const taper_work_item& it : p.items) p.part_start[it.part + 1]++;
     for (int i = 0; i < n_parts; ++i) p.part_start[i + 1] += p.part_start[i];
-    // size of the pool's items: a quarter of a share, between 512 and 1536 tokens, unless the caller says otherwise
+    plan_part_turns(cfg, branch_group, &p);
+    // size of the pool's items: a quarter of a share, between 512 and 2048 tokens, unless the caller says otherwise
     const int pool_item_tokens = std::max<int>(
         kPrivateBlockTokens,
-        (pool_item_opt ? pool_item_opt : (int)std::min<int64_t>(1536, std::max<int64_t>(512, quota / 4))) / kPrivateBlockTokens * kPrivateBlockTokens);
+        (pool_item_opt ? pool_item_opt : (int)std::min<int64_t>(2048, std::max<int64_t>(512, quota / 4))) / kPrivateBlockTokens * kPrivateBlockTokens);
     for (const Segment& s : pool) {  // pool items follow the shares' items; their `part` is n_parts
         const int k = (s.n_tokens + pool_item_tokens - 1) / pool_item_tokens;
         const int piece = ((s.n_tokens + k - 1) / k + kPrivateBlockTokens - 1) / kPrivateBlockTokens * kPrivateBlockTokens;

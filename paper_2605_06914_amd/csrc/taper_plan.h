@@ -25,6 +25,7 @@ struct HostPlan {
     int n_parts_shared = 0, n_parts_private = 0;
     int n_pool_items = 0;  // items after the shares' items, owned by no share
     std::vector<int32_t> part_start;  // [n_parts + 1]
+    std::vector<int32_t> part_turn;   // [n_parts] which kv head a share's first workgroup takes (see plan_part_turns)
     std::vector<int32_t> merge_start; // [n_seqs + 1]
     std::vector<taper_merge_entry> merge;
     int64_t n_partial_rows = 0;
