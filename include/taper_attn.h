@@ -159,13 +159,13 @@ typedef struct {
                                       query heads per KV head; head_dim 64: 8 row tiles); wider
                                       requests are cut into equal sub-groups of at most this
                                       size; at most 12 row tiles                               */
-    int32_t shared_cost_pct;   /* 0 = default (80; 180 when the step has fewer than 600 tokens per
+    int32_t shared_cost_pct;   /* 0 = default (80; 180 when the step has fewer than 350 tokens per
                                   share): cost of a shared-prefix token relative to a private
                                   one when cutting the work into equal shares                   */
-    int32_t shared_item_cost;  /* 0 = default (450; below 600 tokens per share 60 and 32 per branch): fixed
+    int32_t shared_item_cost;  /* 0 = default (450; below 350 tokens per share 60 and 32 per branch): fixed
                                   cost of a shared-prefix item, in private tokens' streaming
                                   time                                                          */
-    int32_t private_item_cost; /* 0 = default (192; 128 below 600 tokens per share and in steps without
+    int32_t private_item_cost; /* 0 = default (192; 128 below 350 tokens per share and in steps without
                                   shared-prefix work): fixed cost of a private item, same unit  */
     int32_t private_merge_cost; /* 0 = default (192 when the step has shared-prefix work, else none),
                                   -1 = none: extra cost of the private item that ends a sequence
@@ -178,7 +178,7 @@ typedef struct {
                                   of the longest private segment if that is more (keeps the partials
                                   of one sequence to about 16)                                   */
     int32_t pool_pct;          /* 0 = default (25 when the step has shared-prefix work, rising to 60 for
-                                  shares of 5120 tokens; none below 600 tokens per share or
+                                  shares of 5120 tokens; none below 350 tokens per share or
                                   without shared-prefix work): percentage of the private tokens that no share owns; workgroups
                                   that finish their share take them, an item at a time, so the
                                   launch ends evenly.  -1 = none; values above 90 count as 90    */
@@ -310,7 +310,7 @@ TAPER_API int taper_decode_step_attention_simple(taper_ctx *ctx, int n_seqs, con
  * of the library's device image, one copy per GPU, held until the process ends.  The call
  * allocates and frees nothing, on the device or in pinned memory (its pinned staging buffer
  * and the array's address are set up by taper_create), and unlike _simple it only enqueues
- * (an upload of the plan, a clear of the counters, the decode kernel) and returns; the host
+ * (an upload of the plan that also clears the counters, the decode kernel) and returns; the host
  * arrays are read during the call only.  No lse output.
  * TAPER_EINVAL with a message naming the sizes when the step needs more than the array holds
  * (plan image above 8 MiB, or image + workspace above 64 MiB: the 64-layer admission-sweep batch at

@@ -48,6 +48,7 @@ int set_error(int code, const std::string& msg) { return fail(code, msg); }
 struct PlanBuffers {
     void* dev = nullptr;      // one device allocation holding every integer array
     void* staging = nullptr;  // pinned host image of `dev`
+    void* staging_dev = nullptr;  // the same memory as the device addresses it
     size_t bytes = 0;
     hipEvent_t uploaded = nullptr;  // recorded after the host-to-device copy
 };
@@ -92,6 +93,7 @@ struct taper_ctx {
     void* static_scratch = nullptr;
     std::string static_error;  // why static_scratch is null
     void* static_staging = nullptr;
+    void* static_staging_dev = nullptr;  // the same memory as the device addresses it
     hipEvent_t static_uploaded = nullptr;
 #ifdef TAPER_WG_TRACE
     long long* trace = nullptr;
@@ -133,6 +135,7 @@ int acquire_buffers(taper_ctx* ctx, size_t bytes, PlanBuffers* out) {
     PlanBuffers b;
     b.bytes = align_up(bytes + bytes / 2, 4096);
     hipError_t e = hipHostMalloc(&b.staging, b.bytes, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostGetDevicePointer(&b.staging_dev, b.staging, 0);
     if (e == hipSuccess) e = hipMalloc(&b.dev, b.bytes);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b.uploaded, hipEventDisableTiming);
     if (e != hipSuccess) {
@@ -437,6 +440,7 @@ int taper_create(const taper_attn_config* cfg, taper_ctx** out_ctx) {
         // set-up of the entry point that allocates nothing (cfg->device is current)
         e = taper::static_scratch(cfg->device, &ctx->static_scratch);
         if (e == hipSuccess) e = hipHostMalloc(&ctx->static_staging, kStaticImageBytes, hipHostMallocDefault);
+        if (e == hipSuccess) e = hipHostGetDevicePointer(&ctx->static_staging_dev, ctx->static_staging, 0);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->static_uploaded, hipEventDisableTiming);
         if (e != hipSuccess) {  // the other entry points do not need it: the static one reports this
             ctx->static_error = std::string("static scratch set-up: ") + hipGetErrorString(e);
@@ -521,7 +525,7 @@ int taper_plan_build_segments(taper_ctx* ctx, int n_seqs, const int32_t* block_t
     }
     write_image(pieces, plan->buf.staging);
     hipStream_t s = (hipStream_t)hip_stream;
-    e = hipMemcpyAsync(plan->buf.dev, plan->buf.staging, total, hipMemcpyHostToDevice, s);
+    e = taper::launch_upload(plan->buf.dev, plan->buf.staging_dev, total, nullptr, 0, s);
     if (e == hipSuccess) e = hipEventRecord(plan->buf.uploaded, s);
     if (e != hipSuccess) {
         std::string msg = std::string("plan upload: ") + hipGetErrorString(e);
@@ -659,11 +663,10 @@ int taper_decode_step_attention_static(taper_ctx* ctx, int n_seqs, const void* q
     HIP_TRY(hipEventSynchronize(ctx->static_uploaded));  // the previous call's upload has read the pinned image
     write_image(pieces, ctx->static_staging);
     char* base = (char*)ctx->static_scratch;
-    HIP_TRY(hipMemcpyAsync(base, ctx->static_staging, image, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipEventRecord(ctx->static_uploaded, s));
-    // the array keeps the last call's contents: what must start at zero is cleared (the counters)
     char* ws = base + image;
-    HIP_TRY(taper::launch_zero_words((int32_t*)ws, counters, s));
+    // (the array keeps the last call's contents: what must start at zero, the counters, is cleared by the same launch)
+    HIP_TRY(taper::launch_upload(base, ctx->static_staging_dev, image, (int32_t*)ws, counters, s));
+    HIP_TRY(hipEventRecord(ctx->static_uploaded, s));
     const taper::StepArgs a = make_args(ctx, h, bind_image(pieces, base), ws, ml_off, o_off, q, kv_pages, out, nullptr);
     HIP_TRY(taper::launch_decode(a, s));
     return TAPER_OK;

@@ -965,26 +965,27 @@ __global__ __launch_bounds__(256) void resolve_slots_kernel(StepArgs a, int64_t*
 // KV append: the new key and value rows of every sequence (bf16 [S][Hkv][D]) go to
 // slot[s] = page * 16 + token of the pool, in the tile layouts the attention kernels read:
 // K element d at (d/8)*128 + tok*8 + d%8 (16-byte groups of 8 dims), V element d at
-// (tok/4)*4D + d*4 + tok%4.  One workgroup per sequence, thread = (kv head, group of 8 dims).
+// (tok/4)*4D + d*4 + tok%4.  One workgroup per sequence, thread = (K or V, kv head, group of 8 dims).  Bound by
+// the launch and two trips to memory side by side (the slot, the row); K and V of a group are different threads'
+// work so that each has one load and one address to make.
 __global__ __launch_bounds__(256) void kv_append_kernel(const __bf16* __restrict__ k_new, const __bf16* __restrict__ v_new,
                                                         const int64_t* __restrict__ slot, __bf16* __restrict__ kv,
                                                         const int n_kv_heads, const int D) {
-    const int s = blockIdx.x;
-    const int64_t sl = slot[s];
-    const int64_t page = sl >> 4;
-    const int tok = (int)(sl & 15);
-    const int groups = D / 8;
-    const int64_t tile = 16LL * D;
-    for (int i = threadIdx.x; i < n_kv_heads * groups; i += blockDim.x) {
-        const int hk = i / groups, d8 = i % groups;
-        const int64_t src = ((int64_t)s * n_kv_heads + hk) * D + 8 * d8;
-        const bf16x8 kx = *(const bf16x8*)(k_new + src);
-        const bf16x8 vx = *(const bf16x8*)(v_new + src);
-        __bf16* kt = kv + ((page * 2 + 0) * n_kv_heads + hk) * tile;
-        __bf16* vt = kv + ((page * 2 + 1) * n_kv_heads + hk) * tile;
-        *(bf16x8*)(kt + d8 * 128 + tok * 8) = kx;
+    const int s = blockIdx.x, rows = n_kv_heads * (D / 8);
+    const int shift = D == 128 ? 4 : 3;  // (D is 64 or 128)
+    for (int i = threadIdx.x; i < 2 * rows; i += blockDim.x) {
+        const bool is_v = i >= rows;
+        const int r = is_v ? i - rows : i, hk = r >> shift, d8 = r & (D / 8 - 1);
+        const bf16x8 x = *(const bf16x8*)((is_v ? v_new : k_new) + ((int64_t)s * rows + r) * 8);
+        const int64_t sl = slot[s];
+        const int tok = (int)(sl & 15);
+        __bf16* t = kv + (((sl >> 4) * 2 + is_v) * n_kv_heads + hk) * (16LL * D);
+        if (is_v) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) vt[(tok >> 2) * (4 * D) + (8 * d8 + j) * 4 + (tok & 3)] = vx[j];
+            for (int j = 0; j < 8; ++j) t[(tok >> 2) * (4 * D) + (8 * d8 + j) * 4 + (tok & 3)] = x[j];
+        } else {
+            *(bf16x8*)(t + d8 * 128 + tok * 8) = x;
+        }
     }
 }
 

@@ -54,7 +54,7 @@ namespace {
 constexpr int64_t kPieceCostTokens = 200;   // what one more piece of a cut sequence costs, in tokens' streaming time
 constexpr int64_t kOnePerUnitLossPct = 3;   // what one workgroup per compute unit instead of two costs, percent
 constexpr double kTokensPerMergedRow = 4.0;      // see least_tokens
-constexpr int64_t kSaturatingShareTokens = 600;  // shares of fewer tokens are over before the memory system is saturated
+constexpr int64_t kSaturatingShareTokens = 350;  // shares of fewer tokens are over before the memory system is saturated
 
 struct Segment {
     int32_t seq0, n_branch, page0, n_tokens, kind;

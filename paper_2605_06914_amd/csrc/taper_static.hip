@@ -25,15 +25,23 @@ hipError_t static_scratch(int device, void** ptr) {
     return hipSuccess;
 }
 
-// Clears n 32-bit words (a kernel rather than a memset node: the call may be recorded into a graph).
-__global__ __launch_bounds__(256) void zero_words_kernel(int32_t* p, int64_t n) {
+// Brings a plan's image from pinned host memory to the device and clears the counters behind it: the lanes read host
+// memory themselves.  A copy command would do the first part, but it runs on a copy engine, and the hand-overs from the
+// kernels before it and to the kernels after it took longer than the 0.1-1 MB themselves (a decode step of four layers:
+// 383 us with copy commands, 367 this way).  (Nor is a fill command used: the call may be recorded into a graph.)
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(256) void upload_kernel(u32x4* __restrict__ dst, const u32x4* __restrict__ src, int64_t n,
+                                                     int32_t* __restrict__ zero, int64_t n_zero) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0;
+    if (i < n) dst[i] = src[i];
+    if (i < n_zero) zero[i] = 0;
 }
 
-hipError_t launch_zero_words(int32_t* p, int64_t n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
+hipError_t launch_upload(void* dst, const void* src, size_t bytes, int32_t* zero, int64_t n_zero, hipStream_t s) {
+    const int64_t n = (int64_t)(bytes / 16), most = n > n_zero ? n : n_zero;
+    if (most <= 0) return hipSuccess;
+    hipLaunchKernelGGL(upload_kernel, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, s, (u32x4*)dst, (const u32x4*)src, n, zero,
+                       n_zero);
     return hipGetLastError();
 }
 
