@@ -114,7 +114,8 @@ def load_library() -> ctypes.CDLL:
         raise ImportError(f"{LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
                           "(or paper_2605_06914_amd/build.py); there is no fallback path")
     try:  # share torch's HIP runtime (same soname) when torch is importable
-        import torch  # noqa: F401
+        import torch
+        _torch_names(torch)
     except Exception:  # pragma: no cover - torch is only needed for device work
         pass
     lib = ctypes.CDLL(LIB_PATH)
@@ -187,10 +188,29 @@ def _ptr(t) -> int:
     return int(t) if isinstance(t, int) else int(t.data_ptr())
 
 
+# What the checks of every call need of torch, looked up once when the library is loaded.
+_Tensor = None
+_DTYPES: dict = {}
+_raw_stream = _current_device = None
+
+
+def _torch_names(torch):
+    global _Tensor, _raw_stream, _current_device
+    _DTYPES.update(bfloat16=torch.bfloat16, float32=torch.float32, int64=torch.int64)
+    _current_device = torch.cuda.current_device
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _Tensor = torch.Tensor
+
+
 def _dev(t, what: str, numel: int, dtype: str, device: int) -> int:
     """Device pointer of tensor `t` after checking what the C ABI cannot see from a bare pointer: element
     type, contiguity, device and size (an undersized, strided or wrong-device tensor would become an
     out-of-bounds access inside the kernel).  A raw int is passed through: the caller vouches for it."""
+    # The calls of small steps are bound by this file (four tensors are checked per call: 9.5 us a call with the
+    # checks below alone), so a plain tensor that is all right is recognised first; whatever it is not, the checks say.
+    if (type(t) is _Tensor and t.dtype is _DTYPES[dtype] and t.is_cuda and t.get_device() == device and t.numel() >= numel
+            and t.is_contiguous()):
+        return t.data_ptr()
     if isinstance(t, int):
         return t
     if str(t.dtype).rsplit(".", 1)[-1] != dtype:
@@ -206,6 +226,8 @@ def _dev(t, what: str, numel: int, dtype: str, device: int) -> int:
 
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(_current_device())
         import torch
         return int(torch.cuda.current_stream().cuda_stream)
     return int(stream) if isinstance(stream, int) else int(stream.cuda_stream)
@@ -276,6 +298,9 @@ class Context:
         _check(lib.taper_create(ctypes.byref(cfg), ctypes.byref(h)))
         self._h = h.value
         self.cfg = cfg
+        # elements of q and out per sequence, of the new K or V rows per sequence, of a pool page
+        self._qo_row = int(n_q_heads) * int(head_dim)
+        self._kv_row, self._page = int(n_kv_heads) * int(head_dim), 2 * int(n_kv_heads) * int(page_size) * int(head_dim)
 
     def close(self):
         if self._h:
@@ -335,36 +360,28 @@ class Context:
                                                         int(n_pool_pages), ctypes.byref(opts), st, ctypes.byref(h)))
         return Plan(self, h.value, bt.shape[0], n_pool_pages)
 
-    # elements of the tensors of a step of n_seqs sequences over a pool of n_pool_pages pages
-    def _qo_elems(self, n_seqs: int) -> int:
-        return int(n_seqs) * self.cfg.n_q_heads * self.cfg.head_dim
-
-    def _kv_row_elems(self, n_seqs: int) -> int:
-        return int(n_seqs) * self.cfg.n_kv_heads * self.cfg.head_dim
-
-    def _pool_elems(self, n_pool_pages: int) -> int:
-        return int(n_pool_pages) * 2 * self.cfg.n_kv_heads * self.cfg.page_size * self.cfg.head_dim
-
     def _step_ptrs(self, n_seqs, n_pool_pages, q, kv_pages, out, lse=None):
-        d = self.cfg.device
-        return (_dev(q, "q", self._qo_elems(n_seqs), "bfloat16", d),
-                _dev(kv_pages, "kv_pages", self._pool_elems(n_pool_pages), "bfloat16", d),
-                _dev(out, "out", self._qo_elems(n_seqs), "bfloat16", d),
+        d, qo = self.cfg.device, int(n_seqs) * self._qo_row
+        return (_dev(q, "q", qo, "bfloat16", d),
+                _dev(kv_pages, "kv_pages", int(n_pool_pages) * self._page, "bfloat16", d),
+                _dev(out, "out", qo, "bfloat16", d),
                 _dev(lse, "lse", int(n_seqs) * self.cfg.n_q_heads, "float32", d) if lse is not None else None)
 
     def kv_append(self, k_new, v_new, slots_dev, kv_pages, n_seqs: int, stream=None, n_pool_pages: int = 0):
         """n_pool_pages (optional): the pool's size, so that the pool tensor's size can be checked too."""
-        d = self.cfg.device
-        _check(load_library().taper_kv_append(self._h, int(n_seqs),
-                                              _dev(k_new, "k_new", self._kv_row_elems(n_seqs), "bfloat16", d),
-                                              _dev(v_new, "v_new", self._kv_row_elems(n_seqs), "bfloat16", d),
-                                              _dev(slots_dev, "slots", int(n_seqs), "int64", d),
-                                              _dev(kv_pages, "kv_pages", self._pool_elems(n_pool_pages), "bfloat16", d),
-                                              _stream(stream)))
+        d, rows = self.cfg.device, int(n_seqs) * self._kv_row
+        status = _lib.taper_kv_append(self._h, int(n_seqs),
+                                      _dev(k_new, "k_new", rows, "bfloat16", d), _dev(v_new, "v_new", rows, "bfloat16", d),
+                                      _dev(slots_dev, "slots", int(n_seqs), "int64", d),
+                                      _dev(kv_pages, "kv_pages", int(n_pool_pages) * self._page, "bfloat16", d), _stream(stream))
+        if status != TAPER_OK:
+            _check(status)
 
     def decode_step_attention(self, plan: Plan, q, kv_pages, out, lse=None, stream=None):
         pq, pkv, pout, plse = self._step_ptrs(plan.n_seqs, plan.n_pool_pages, q, kv_pages, out, lse)
-        _check(load_library().taper_decode_step_attention(self._h, plan._h, pq, pkv, pout, plse, _stream(stream)))
+        status = _lib.taper_decode_step_attention(self._h, plan._h, pq, pkv, pout, plse, _stream(stream))
+        if status != TAPER_OK:
+            _check(status)
 
     def decode_step_attention_simple(self, q, kv_pages, n_pool_pages, block_table, branch_group, prefix_len,
                                      suffix_len, out, stream=None):
