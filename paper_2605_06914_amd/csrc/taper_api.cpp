@@ -644,15 +644,22 @@ int taper_decode_step_attention_static(taper_ctx* ctx, int n_seqs, const void* q
     o.share_prefix = 1;
     o.target_workgroups = ctx->default_workgroups;
     o.small_step_grid = 1;
-    int st = taper::build_host_plan(ctx->cfg, n_seqs, block_table, bt_row_stride, branch_group, prefix_len, suffix_len,
-                                    n_pool_pages, &o, &h, &err);
-    if (st != TAPER_OK) return fail(st, err);
     // layout inside the array: plan image | counters | statistics | partial rows
     ImagePiece pieces[kImagePieces];
-    const size_t image = layout_image(h, pieces);
-    size_t ml_off = 0, o_off = 0;
-    const int64_t counters = counters_needed(ctx->cfg, h.n_seqs);
-    const size_t ws_bytes = layout_workspace(ctx->cfg, h.n_partial_rows, counters, &ml_off, &o_off);
+    size_t image = 0, ws_bytes = 0, ml_off = 0, o_off = 0;
+    const int64_t counters = counters_needed(ctx->cfg, n_seqs);
+    for (int coarser = 0; coarser < 2; ++coarser) {
+        if (coarser) {  // a step that does not fit as it would best be cut: fewer pieces, fewer partial rows
+            o.pool_pct = -1;
+            o.target_workgroups = std::max(1, o.target_workgroups / 2);
+        }
+        const int st = taper::build_host_plan(ctx->cfg, n_seqs, block_table, bt_row_stride, branch_group, prefix_len, suffix_len,
+                                              n_pool_pages, &o, &h, &err);
+        if (st != TAPER_OK) return fail(st, err);
+        image = layout_image(h, pieces);
+        ws_bytes = layout_workspace(ctx->cfg, h.n_partial_rows, counters, &ml_off, &o_off);
+        if (image <= kStaticImageBytes && image + ws_bytes <= taper::kStaticScratchBytes) break;
+    }
     if (image > kStaticImageBytes || image + ws_bytes > taper::kStaticScratchBytes)
         return fail(TAPER_EINVAL, "step too large for the static scratch array: plan image " + std::to_string(image) +
                                       " bytes (limit " + std::to_string(kStaticImageBytes) + "), image + workspace " +
