@@ -183,7 +183,7 @@ int partition_even(const std::vector<Segment>& segs, int gqa, int64_t quota, int
             close();
             const int64_t blocks = (s.n_tokens + blk - 1) / blk;
             const int64_t spread = blocks + tail_discount;
-            const int64_t k = blocks <= cap + min_blocks / 2 ? 1 : std::max<int64_t>(1, (spread + cap - 1) / cap);
+            const int64_t k = blocks <= cap + min_blocks / 2 ? 1 : std::min(blocks, std::max<int64_t>(1, (spread + cap - 1) / cap));
             int64_t remaining = blocks, off = 0;
             for (int64_t i = 0; i < k; ++i) {
                 int64_t take = spread / k + (i < spread % k ? 1 : 0);
@@ -216,7 +216,7 @@ int partition_even(const std::vector<Segment>& segs, int gqa, int64_t quota, int
             continue;
         }
         const int64_t spread = remaining + tail_discount;
-        const int64_t k = std::max<int64_t>(1, (spread + cap - 1) / cap);
+        const int64_t k = std::min(remaining, std::max<int64_t>(1, (spread + cap - 1) / cap));  // (the discount is no block to cut)
         for (int64_t i = 0; i < k; ++i) {
             int64_t take = spread / k + (i < spread % k ? 1 : 0);
             take = i + 1 < k ? std::max<int64_t>(1, std::min(take, remaining - (k - 1 - i))) : remaining;
@@ -552,6 +552,10 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     std::vector<std::vector<taper_merge_entry>> per_seq(n_seqs);
     int64_t rows = 0;
     for (taper_work_item& it : p.items) {
+        if (it.n_tokens < 1) {  // the kernels index pages by an item's last token: never launched
+            *err = "internal error: a work item without tokens";
+            return TAPER_EINVAL;
+        }
         // (the merge addresses partial rows by 32-bit byte offsets: fp32 rows of a step stay below 2^31 bytes)
         if ((rows + (int64_t)it.n_branch * cfg.n_q_heads) * cfg.head_dim * 4 > INT32_MAX) {
             *err = "too many partial rows";

@@ -61,7 +61,56 @@ def random_case(seed, shape):
 @pytest.mark.parametrize("seed", range(48))
 def test_random_plans_are_exact_covers_with_in_bounds_indices(seed):
     shape = TINY if seed % 6 == 5 else QWEN
-    seg, opts = random_case(seed, shape)
+    check_plan(shape, *random_case(seed, shape))
+
+
+def cost_case(seed, shape):
+    """Short prefixes, few tokens per share, and every cost option drawn by itself over what a caller may pass."""
+    rng = np.random.default_rng(9000 + seed)
+    reqs = []
+    for _ in range(int(rng.integers(1, 4))):
+        width = int(rng.choice([2, 3, 5, 8, 17, 30, 64]))
+        reqs.append((int(rng.integers(64, 900)), [int(x) for x in rng.integers(0, 60, size=width)]))
+    if rng.random() < 0.5:
+        reqs.append((int(rng.integers(1, 3000)), [0]))
+    st = structure_custom(shape, reqs, seed=9500 + seed)
+    opts = {}
+    if rng.random() < 0.7:
+        opts["shared_cost_pct"] = int(rng.choice([1, 30, 150, 205, 210, 300, 400, 1000, 100000]))
+    if rng.random() < 0.4:
+        opts["shared_item_cost"] = int(rng.choice([1, 20, 120, 450, 800, 100000]))
+    if rng.random() < 0.4:
+        opts["private_item_cost"] = int(rng.choice([1, 60, 192, 10000]))
+    if rng.random() < 0.3:
+        opts["private_merge_cost"] = int(rng.choice([-1, 1, 5000]))
+    if rng.random() < 0.4:
+        opts["target_workgroups"] = int(rng.choice([8, 64, 512, 4096]))
+    if rng.random() < 0.3:
+        opts["min_share_tokens"] = int(rng.choice([1, 64]))
+    if rng.random() < 0.3:
+        opts["scatter_sub_groups"] = 1
+    keep = range(int(st.branch_group[-1]) + 1)
+    return reduce_structure(st, z_len=[0] * len(keep), seed=seed, keep_parallel=list(keep)), opts
+
+
+@pytest.mark.parametrize("seed", range(120))
+def test_plans_are_exact_covers_whatever_the_costs(seed):
+    shape = [QWEN, AttnShape(16, 1, 128, 16), AttnShape(32, 8, 64, 16)][seed % 3]
+    check_plan(shape, *cost_case(seed, shape))
+
+
+def test_a_short_prefix_is_not_cut_into_more_items_than_it_has_blocks():
+    """A shared token made expensive leaves a share room for one block: 130 tokens are three blocks and three items."""
+    st = structure_custom(QWEN, [(130, [0, 0])], seed=3)
+    ctx = Context(64, 8, 128, device=-1)
+    for pct in (205, 210, 400, 100000):
+        e = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, shared_cost_pct=pct).export()
+        F = {n: i for i, n in enumerate(e["item_fields"])}
+        assert e["items"][:, F["n_tokens"]].tolist() in ([64, 64, 2], [128, 2], [64, 66], [130]), pct
+    ctx.close()
+
+
+def check_plan(shape, seg, opts):
     g = shape.gqa
     ctx = Context(shape.n_q_heads, shape.n_kv_heads, shape.head_dim, device=-1)
     plan = ctx.plan_build_segments(seg.block_table, seg.branch_group, seg.prefix_len, seg.seg_start, seg.seg_len,
