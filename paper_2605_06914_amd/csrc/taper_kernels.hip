@@ -690,10 +690,16 @@ struct SharedSmem {
 };
 
 DEV unsigned lds_address(const void* p) { return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)p; }
-// 64 lanes x 16 bytes: lane l's from base + off (per lane) to LDS address `lds` + 16 l; streamed past the caches
+// 64 lanes x 16 bytes: lane l's from base + off (per lane) to LDS address `lds` + 16 l; streamed past the caches.
+// The compiler's hazard pass does not look inside: the statement itself keeps the one wait state from m0's write and the five that
+// lie between a vector instruction's write of the base (a v_readlane of a spilled register) and the load that reads it.
+// (That m0 is reserved is what the compiler would warn of at each use; nothing else in these kernels reads m0.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 DEV void load_to_lds(const char* base, unsigned off, unsigned lds) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds) : "m0", "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 // All but this wave's N youngest loads have landed, its LDS reads are done, and every wave of the workgroup is here.
 template <int N>
 DEV void wait_loads_and_meet() {

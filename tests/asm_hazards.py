@@ -106,3 +106,70 @@ def scan(asm_text, name_filter="decode_kernel", need=NEED):
                         stack.append((fallthrough[bb], 0, ws, live))
         i = j
     return findings, kernels
+
+
+NEED_SCALAR = 5  # wait states between a vector-ALU write of a scalar register and a memory instruction that reads it
+_SREG = re.compile(r"\bs\[(\d+):(\d+)\]|\bs(\d+)\b")
+
+
+def _scalar_regs(text):
+    out = set()
+    for m in _SREG.finditer(text):
+        if m.group(1):
+            out.update(range(int(m.group(1)), int(m.group(2)) + 1))
+        else:
+            out.add(int(m.group(3)))
+    return out
+
+
+def scan_scalar_addresses(asm_text, name_filter="decode_kernel", need=NEED_SCALAR):
+    """Memory instructions that read a scalar register too soon after a vector-ALU instruction wrote it (v_readlane of a
+    spilled register, v_readfirstlane, a compare), along every path.  The compiler keeps the distance between its own instructions
+    but does not look inside inline assembly.  Returns [(kernel, block, writer, reader, wait states)], number of kernels."""
+    text = asm_text.split("\n")
+    findings, kernels, i = [], 0, 0
+    while i < len(text):
+        m = re.match(r"^(_Z\S+):", text[i])
+        if not (m and name_filter in m.group(1)):
+            i += 1
+            continue
+        j = i + 1
+        while j < len(text) and "s_endpgm" not in text[j]:
+            j += 1
+        kernels += 1
+        blocks, order = _blocks(text[i + 1 : j + 1])
+        follows = {b: order[k + 1] if k + 1 < len(order) else None for k, b in enumerate(order)}
+        for b in order:
+            for k, x in enumerate(blocks[b]):
+                op, _, operands = x.partition(" ")
+                if not op.startswith("v_") or op.startswith("v_mfma"):
+                    continue
+                # (a carry or compare result is the second operand of some instructions)
+                written = frozenset(r for p in operands.split(",")[: 2 if "_co_" in op or "div_scale" in op else 1] for r in _scalar_regs(p))
+                seen, stack = set(), [(b, k + 1, 0, written)]
+                while stack:
+                    bb, pos, ws, live = stack.pop()
+                    if ws >= need or not live or (bb, pos, ws, live) in seen:
+                        continue
+                    seen.add((bb, pos, ws, live))
+                    if pos >= len(blocks[bb]):
+                        if follows[bb]:
+                            stack.append((follows[bb], 0, ws, live))
+                        continue
+                    y = blocks[bb][pos]
+                    yop, _, yargs = y.partition(" ")
+                    if yop == "s_nop":
+                        stack.append((bb, pos + 1, ws + int(yargs) + 1, live))
+                        continue
+                    if re.match(r"(global|flat|buffer|scratch|tbuffer)_", yop) and _scalar_regs(yargs) & live:
+                        findings.append((m.group(1), bb, x, y, ws))
+                        continue
+                    if yop.startswith("s_") and not re.match(r"s_(cmp|bitcmp|cbranch|branch|waitcnt|barrier|setprio|store|dcache)", yop):
+                        live = live - _scalar_regs(yargs.split(",")[0])
+                    t = re.match(r"s_c?branch(?:_\w+)?\s+(\S+)", y)
+                    if t and t.group(1) in blocks:
+                        stack.append((t.group(1), 0, ws + 1, live))
+                    if not yop.startswith("s_branch"):
+                        stack.append((bb, pos + 1, ws + 1, live))
+        i = j
+    return findings, kernels

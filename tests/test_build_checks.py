@@ -8,7 +8,7 @@ import subprocess
 import pytest
 
 from paper_2605_06914_amd.build import CSRC, HIP_FLAGS, ROOT
-from tests.asm_hazards import NEED, scan
+from tests.asm_hazards import NEED, NEED_SCALAR, scan, scan_scalar_addresses
 
 
 @pytest.fixture(scope="module")
@@ -67,3 +67,42 @@ def test_the_scanner_sees_a_planted_hazard():
     assert good == []
     overwritten, _ = scan(kernel(["\tv_mov_b64_e32 v[108:109], v[4:5]", "\tv_mov_b64_e32 v[110:111], v[6:7]"]))
     assert [f for f in overwritten if f[1] == ".LBB0_2" and "v[2:3]" in f[3]] == []
+
+
+def test_no_memory_instruction_reads_a_scalar_register_inside_a_vector_writers_latency(compiled):
+    asm, _ = compiled
+    findings, kernels = scan_scalar_addresses(asm)
+    assert kernels == 16
+    assert not findings, "\n".join(f"{k}: {blk}: `{w}` then `{r}` after {ws} wait states (need {NEED_SCALAR})"
+                                   for k, blk, w, r, ws in findings[:10])
+
+
+def test_loads_in_inline_assembly_keep_that_distance_by_themselves(compiled):
+    """The compiler does not look for hazards inside inline assembly, and what it puts in front of a statement changes from
+    build to build: the wait states stand inside the statement."""
+    asm, _ = compiled
+    statements = [s for s in re.findall(r";;#ASMSTART\n(.*?);;#ASMEND", asm, re.S) if "global_load_lds" in s]
+    assert statements
+    for s in statements:
+        before = s.split("global_load_lds")[0]
+        waits = sum(int(n) + 1 for n in re.findall(r"s_nop (\d+)", before))
+        assert waits >= NEED_SCALAR, s
+
+
+def test_the_compiler_has_nothing_to_warn_about(compiled):
+    """A warning per use of some statement would hide all others."""
+    _, remarks = compiled
+    warnings = [l for l in remarks.splitlines() if "warning:" in l]
+    assert warnings == [], warnings[:5]
+
+
+def test_the_scanner_sees_a_planted_scalar_hazard():
+    def kernel(*body):
+        return "\n".join(["_ZN5taper13decode_kernelILi64ELi2ELi0EEEvNS_8StepArgsE:", *body, ".LBB0_9:", "\ts_endpgm"])
+    lane, load = "\tv_readlane_b32 s4, v9, 3", "\tglobal_load_lds_dwordx4 v62, s[4:5] nt"
+    bad, n = scan_scalar_addresses(kernel(lane, "\ts_mov_b32 m0, s91", "\ts_nop 0", load))
+    assert n == 1 and len(bad) == 1 and bad[0][4] == 2
+    assert len(scan_scalar_addresses(kernel(lane, "\ts_cbranch_scc0 .LBB0_1", "\ts_nop 9", ".LBB0_1:", "\ts_nop 2", load))[0]) == 1  # over the branch
+    assert scan_scalar_addresses(kernel(lane, "\ts_mov_b32 m0, s91", "\ts_nop 3", load))[0] == []
+    assert scan_scalar_addresses(kernel(lane, "\ts_add_u32 s4, s6, s7", load))[0] == []  # the add reads nothing of it and overwrites it
+    assert len(scan_scalar_addresses(kernel("\tv_cmp_lt_i32_e64 s[4:5], v1, v2", load))[0]) == 1
