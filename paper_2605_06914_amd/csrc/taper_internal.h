@@ -50,8 +50,7 @@ constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 // Address of the calling device's copy of the array (looked up once per device; `device` must be current).
 hipError_t static_scratch(int device, void** ptr);
 // `bytes` (a multiple of 16, both ends 16-byte aligned) from pinned host memory as the device addresses it, and n_zero words cleared.
-// (weak: a build of the host code alone, whose contexts launch nothing, links without it)
-__attribute__((weak)) hipError_t launch_upload(void* dst, const void* src, size_t bytes, int32_t* zero, int64_t n_zero, hipStream_t s);
+hipError_t launch_upload(void* dst, const void* src, size_t bytes, int32_t* zero, int64_t n_zero, hipStream_t s);
 
 hipError_t launch_decode(const StepArgs& a, hipStream_t s);
 hipError_t launch_kv_append(const void* k_new, const void* v_new, const int64_t* slot, void* kv, int n_seqs, int n_kv_heads,

@@ -106,3 +106,19 @@ def test_the_scanner_sees_a_planted_scalar_hazard():
     assert scan_scalar_addresses(kernel(lane, "\ts_mov_b32 m0, s91", "\ts_nop 3", load))[0] == []
     assert scan_scalar_addresses(kernel(lane, "\ts_add_u32 s4, s6, s7", load))[0] == []  # the add reads nothing of it and overwrites it
     assert len(scan_scalar_addresses(kernel("\tv_cmp_lt_i32_e64 s[4:5], v1, v2", load))[0]) == 1
+
+
+def test_every_launch_the_host_code_makes_is_a_strong_symbol(tmp_path):
+    """A weak declaration would turn a missing or changed launch function into a call through a null pointer; and the stand-ins of
+    the sanitized build are exactly the functions that the host code calls."""
+    def symbols(source):
+        obj = tmp_path / (os.path.basename(source) + ".o")
+        subprocess.check_call(["g++", "-std=c++17", "-fPIC", "-c", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                               "-I", "/opt/rocm/include", "-o", str(obj), source])
+        out = subprocess.run(["nm", "-C", str(obj)], capture_output=True, text=True, check=True).stdout
+        rows = [re.match(r"\s*[0-9a-f]*\s+(\S)\s+(taper::(?:launch_\w+|static_scratch))\(", l) for l in out.splitlines()]
+        return {m.group(2): m.group(1) for m in rows if m}
+    calls = symbols(os.path.join(CSRC, "taper_api.cpp"))
+    assert len(calls) >= 5 and set(calls.values()) == {"U"}, calls
+    stubs = symbols(os.path.join(ROOT, "tests", "sanitize", "kernel_stubs.cpp"))
+    assert set(stubs) == set(calls) and set(stubs.values()) == {"T"}, (stubs, calls)
