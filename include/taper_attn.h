@@ -312,9 +312,11 @@ TAPER_API int taper_decode_step_attention_simple(taper_ctx *ctx, int n_seqs, con
  * and the array's address are set up by taper_create), and unlike _simple it only enqueues
  * (an upload of the plan that also clears the counters, the decode kernel) and returns; the host
  * arrays are read during the call only.  No lse output.
- * TAPER_EINVAL with a message naming the sizes when the step needs more than the array holds
- * (plan image above 8 MiB, or image + workspace above 64 MiB: the 64-layer admission-sweep batch at
- * 640 sequences takes 30 MiB), TAPER_EHIP on a host-only context or when the array's address
+ * A step whose plan, cut as taper_plan_build would cut it, does not fit the array is cut coarser:
+ * without a pool, then for half the workgroups, a quarter and so on.
+ * TAPER_EINVAL with a message naming the sizes when the step needs more than the array holds all the
+ * same (plan image above 8 MiB, or image + workspace above 64 MiB: the 64-layer admission-sweep batch at
+ * 640 sequences takes 33 MiB), TAPER_EHIP on a host-only context or when the array's address
  * could not be looked up.
  * All calls on one GPU, from any context, share that GPU's array, which keeps the previous
  * call's contents: a call must not be enqueued before every earlier one on that GPU has been

@@ -147,18 +147,19 @@ int acquire_buffers(taper_ctx* ctx, size_t bytes, PlanBuffers* out) {
     return TAPER_OK;
 }
 
-// The arrays of a host plan as one image: bt | items | part_start | merge_start | merge | prefix_len |
-// seg_start | ctx_len | seg_len | seg_page0 | part_turn, each piece 256-byte aligned.
+// The arrays of a host plan as one image: bt | items | part_start, part_turn | merge_start | merge | prefix_len |
+// seg_start | ctx_len | seg_len | seg_page0, each piece 256-byte aligned but for part_turn, which follows part_start directly.
 struct ImagePiece {
     const void* src;
     size_t bytes, off;
 };
-constexpr int kImagePieces = 11;
+constexpr int kImagePieces = 11, kPartStartPiece = 2;
 size_t layout_image(const taper::HostPlan& h, ImagePiece (&pieces)[kImagePieces]) {
     const ImagePiece init[kImagePieces] = {
         {h.block_table.data(), h.block_table.size() * sizeof(int32_t), 0},
         {h.items.data(), h.items.size() * sizeof(taper_work_item), 0},
         {h.part_start.data(), h.part_start.size() * sizeof(int32_t), 0},
+        {h.part_turn.data(), h.part_turn.size() * sizeof(int32_t), 0},
         {h.merge_start.data(), h.merge_start.size() * sizeof(int32_t), 0},
         {h.merge.data(), h.merge.size() * sizeof(taper_merge_entry), 0},
         {h.prefix_len.data(), h.prefix_len.size() * sizeof(int32_t), 0},
@@ -166,13 +167,12 @@ size_t layout_image(const taper::HostPlan& h, ImagePiece (&pieces)[kImagePieces]
         {h.ctx_len.data(), h.ctx_len.size() * sizeof(int32_t), 0},
         {h.seg_len.data(), h.seg_len.size() * sizeof(int32_t), 0},
         {h.seg_page0.data(), h.seg_page0.size() * sizeof(int32_t), 0},
-        {h.part_turn.data(), h.part_turn.size() * sizeof(int32_t), 0},
     };
     size_t total = 0;
     for (int i = 0; i < kImagePieces; ++i) {
         pieces[i] = init[i];
         pieces[i].off = total;
-        total += align_up(std::max<size_t>(pieces[i].bytes, 16), 256);
+        total = i == kPartStartPiece ? total + pieces[i].bytes : align_up(total + std::max<size_t>(pieces[i].bytes, 16), 256);
     }
     return total;
 }
@@ -186,14 +186,14 @@ DeviceImage bind_image(const ImagePiece (&pieces)[kImagePieces], void* dev_base)
     m.bt = (const int32_t*)(d + pieces[0].off);
     m.items = (const taper_work_item*)(d + pieces[1].off);
     m.part_start = (const int32_t*)(d + pieces[2].off);
-    m.merge_start = (const int32_t*)(d + pieces[3].off);
-    m.merge = (const taper_merge_entry*)(d + pieces[4].off);
-    m.prefix_len = (const int32_t*)(d + pieces[5].off);
-    m.seg_start = (const int32_t*)(d + pieces[6].off);
-    m.ctx_len = (const int32_t*)(d + pieces[7].off);
-    m.seg_len = (const int32_t*)(d + pieces[8].off);
-    m.seg_page0 = (const int32_t*)(d + pieces[9].off);
-    m.part_turn = (const int32_t*)(d + pieces[10].off);
+    m.part_turn = (const int32_t*)(d + pieces[3].off);
+    m.merge_start = (const int32_t*)(d + pieces[4].off);
+    m.merge = (const taper_merge_entry*)(d + pieces[5].off);
+    m.prefix_len = (const int32_t*)(d + pieces[6].off);
+    m.seg_start = (const int32_t*)(d + pieces[7].off);
+    m.ctx_len = (const int32_t*)(d + pieces[8].off);
+    m.seg_len = (const int32_t*)(d + pieces[9].off);
+    m.seg_page0 = (const int32_t*)(d + pieces[10].off);
     return m;
 }
 
@@ -317,6 +317,44 @@ taper::StepArgs make_args(const taper_ctx* ctx, const taper::HostPlan& h, const 
 taper::StepArgs make_args(const taper_ctx* ctx, const taper_plan* plan, const void* q, const void* kv, void* out,
                           float* lse) {
     return make_args(ctx, plan->host, plan->img, plan->ws->base, plan->ws->ml_off, plan->ws->o_off, q, kv, out, lse);
+}
+
+// Where the parts of a step lie in the static scratch array: plan image | counters | statistics | partial rows.
+struct StaticLayout {
+    size_t image = 0, workspace = 0, ml_off = 0, o_off = 0;
+    int64_t counters = 0;
+};
+
+// The plan of the entry point that allocates nothing, cut as taper_plan_build would cut it where that fits the array.  Where
+// it does not, coarser: without a pool (fewer pieces, so fewer partial rows, at the same grid), then for half the grid, a
+// quarter ... one share per kv head.  What no cut makes smaller (block table, lengths) is not tried again.
+int static_plan(const taper_ctx* ctx, int n_seqs, int64_t n_pool_pages, const int32_t* block_table, int bt_row_stride,
+                const int32_t* branch_group, const int32_t* prefix_len, const int32_t* suffix_len, taper::HostPlan* h,
+                ImagePiece (&pieces)[kImagePieces], StaticLayout* lay) {
+    taper_plan_options o;
+    std::memset(&o, 0, sizeof o);
+    o.share_prefix = 1;
+    o.target_workgroups = ctx->default_workgroups;
+    o.small_step_grid = 1;
+    lay->counters = counters_needed(ctx->cfg, n_seqs);
+    for (;;) {
+        std::string err;
+        const int st = taper::build_host_plan(ctx->cfg, n_seqs, block_table, bt_row_stride, branch_group, prefix_len, suffix_len,
+                                              n_pool_pages, &o, h, &err);
+        if (st != TAPER_OK) return fail(st, err);
+        lay->image = layout_image(*h, pieces);
+        lay->workspace = layout_workspace(ctx->cfg, h->n_partial_rows, lay->counters, &lay->ml_off, &lay->o_off);
+        if (lay->image <= kStaticImageBytes && lay->image + lay->workspace <= taper::kStaticScratchBytes) return TAPER_OK;
+        const size_t cut_bytes = h->items.size() * sizeof(taper_work_item) + h->merge.size() * sizeof(taper_merge_entry) +
+                                 (h->part_start.size() + h->part_turn.size()) * sizeof(int32_t);
+        if (lay->image > kStaticImageBytes + cut_bytes || o.target_workgroups <= ctx->cfg.n_kv_heads)
+            return fail(TAPER_EINVAL, "step too large for the static scratch array: plan image " + std::to_string(lay->image) +
+                                          " bytes (limit " + std::to_string(kStaticImageBytes) + "), image + workspace " +
+                                          std::to_string(lay->image + lay->workspace) + " bytes (limit " +
+                                          std::to_string(taper::kStaticScratchBytes) + ")");
+        if (o.pool_pct == 0 && h->n_pool_items > 0) o.pool_pct = -1;
+        else o.target_workgroups /= 2;
+    }
 }
 
 int check_step(const taper_ctx* ctx, const taper_plan* plan) {
@@ -638,43 +676,20 @@ int taper_decode_step_attention_static(taper_ctx* ctx, int n_seqs, const void* q
     if (!ctx->static_scratch) return fail(TAPER_EHIP, ctx->static_error.empty() ? "static scratch unavailable" : ctx->static_error);
     // the plan, on the host (host memory only)
     taper::HostPlan h;
-    std::string err;
-    taper_plan_options o;
-    std::memset(&o, 0, sizeof o);
-    o.share_prefix = 1;
-    o.target_workgroups = ctx->default_workgroups;
-    o.small_step_grid = 1;
-    // layout inside the array: plan image | counters | statistics | partial rows
     ImagePiece pieces[kImagePieces];
-    size_t image = 0, ws_bytes = 0, ml_off = 0, o_off = 0;
-    const int64_t counters = counters_needed(ctx->cfg, n_seqs);
-    for (int coarser = 0; coarser < 2; ++coarser) {
-        if (coarser) {  // a step that does not fit as it would best be cut: fewer pieces, fewer partial rows
-            o.pool_pct = -1;
-            o.target_workgroups = std::max(1, o.target_workgroups / 2);
-        }
-        const int st = taper::build_host_plan(ctx->cfg, n_seqs, block_table, bt_row_stride, branch_group, prefix_len, suffix_len,
-                                              n_pool_pages, &o, &h, &err);
-        if (st != TAPER_OK) return fail(st, err);
-        image = layout_image(h, pieces);
-        ws_bytes = layout_workspace(ctx->cfg, h.n_partial_rows, counters, &ml_off, &o_off);
-        if (image <= kStaticImageBytes && image + ws_bytes <= taper::kStaticScratchBytes) break;
-    }
-    if (image > kStaticImageBytes || image + ws_bytes > taper::kStaticScratchBytes)
-        return fail(TAPER_EINVAL, "step too large for the static scratch array: plan image " + std::to_string(image) +
-                                      " bytes (limit " + std::to_string(kStaticImageBytes) + "), image + workspace " +
-                                      std::to_string(image + ws_bytes) + " bytes (limit " +
-                                      std::to_string(taper::kStaticScratchBytes) + ")");
+    StaticLayout lay;
+    const int st = static_plan(ctx, n_seqs, n_pool_pages, block_table, bt_row_stride, branch_group, prefix_len, suffix_len, &h, pieces, &lay);
+    if (st != TAPER_OK) return st;
     hipStream_t s = (hipStream_t)hip_stream;
     HIP_TRY(hipSetDevice(ctx->cfg.device));
     HIP_TRY(hipEventSynchronize(ctx->static_uploaded));  // the previous call's upload has read the pinned image
     write_image(pieces, ctx->static_staging);
     char* base = (char*)ctx->static_scratch;
-    char* ws = base + image;
+    char* ws = base + lay.image;
     // (the array keeps the last call's contents: what must start at zero, the counters, is cleared by the same launch)
-    HIP_TRY(taper::launch_upload(base, ctx->static_staging_dev, image, (int32_t*)ws, counters, s));
+    HIP_TRY(taper::launch_upload(base, ctx->static_staging_dev, lay.image, (int32_t*)ws, lay.counters, s));
     HIP_TRY(hipEventRecord(ctx->static_uploaded, s));
-    const taper::StepArgs a = make_args(ctx, h, bind_image(pieces, base), ws, ml_off, o_off, q, kv_pages, out, nullptr);
+    const taper::StepArgs a = make_args(ctx, h, bind_image(pieces, base), ws, lay.ml_off, lay.o_off, q, kv_pages, out, nullptr);
     HIP_TRY(taper::launch_decode(a, s));
     return TAPER_OK;
 }

@@ -86,3 +86,42 @@ def test_static_entry_rejects_a_step_beyond_the_array():
                                          np.zeros(S, np.int32), out)
     assert e.value.status == TAPER_EINVAL and "static scratch" in str(e.value)
     ctx.close()
+
+
+@pytest.mark.parametrize("n_req,width,prefix,suffix,halvings", [(30, 24, 6000, 100, 0), (36, 22, 4500, 100, 1)])
+def test_static_entry_cuts_a_step_coarser_that_does_not_fit_as_it_would_best_be_cut(n_req, width, prefix, suffix, halvings):
+    """Many wide requests with fp32 partial rows: the default cut needs more than the array's 64 MiB, without a pool (and, for the
+    second, at half the grid) it fits.  Same bits as the allocating entry with that cut, and the oracle's values."""
+    import torch
+
+    from paper_2605_06914_amd import Context
+    from taper_inputs import f32_from_bf16_bits
+    from tests.gpu_util import device_random_batch, host_subbatch, run_gpu_device
+
+    reqs = [(prefix + 97 * i, [suffix - (7 * i + 13 * j) % (suffix // 2) for j in range(width)]) for i in range(n_req)]
+    st = structure_custom(QWEN, reqs, seed=3)
+    ctx = Context(64, 8, 128, device=0, partial_format="f32")
+    grid = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    row_bytes = 128 * 4 + 16
+
+    def rows(**kw):
+        p = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, **kw)
+        n = p.export()["n_partial_rows"]
+        p.free()
+        return n
+
+    coarse = dict(pool_pct=-1, target_workgroups=grid >> halvings)
+    assert rows() * row_bytes > 64 << 20 and rows(**coarse) * row_bytes < 63 << 20
+    assert halvings == 0 or rows(pool_pct=-1, target_workgroups=grid) * row_bytes > 64 << 20
+    q, kv = device_random_batch(st)
+    print(f"[no-alloc] {n_req} requests x {width} branches: S={st.n_seqs}", flush=True)
+    got = torch.full_like(q, float("nan"))
+    ctx.decode_step_attention_static(q, kv, st.n_pool_pages, st.block_table, st.branch_group, st.prefix_len, st.suffix_len, got)
+    torch.cuda.synchronize()
+    want = run_gpu_device(ctx, st, q, kv, **coarse)
+    same = np.array_equal(bits_from_torch(got), bits_from_torch(want))
+    assert same
+    picked, sub = host_subbatch(st, q, kv, [0, width - 1, 7 * width + 3, st.n_seqs - 1])
+    ref, _ = run_oracle(sub)
+    assert_parity(f32_from_bf16_bits(bits_from_torch(got)[picked]).astype(np.float64), ref, "static entry, coarser cut")
+    ctx.close()
