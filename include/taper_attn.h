@@ -159,9 +159,10 @@ typedef struct {
                                       query heads per KV head; head_dim 64: 8 row tiles); wider
                                       requests are cut into equal sub-groups of at most this
                                       size; at most 12 row tiles                               */
-    int32_t shared_cost_pct;   /* 0 = default (80; 180 when the step has fewer than 350 tokens per
-                                  share): cost of a shared-prefix token relative to a private
-                                  one when cutting the work into equal shares                   */
+    int32_t shared_cost_pct;   /* 0 = default (80 for items of up to 4 row tiles, 120 for wider ones, 110 for
+                                  wider sub-groups of one request; 180 when the step has fewer than
+                                  350 tokens per share): cost of a shared-prefix token relative to a
+                                  private one when cutting the work into equal shares           */
     int32_t shared_item_cost;  /* 0 = default (450; below 350 tokens per share 60 and 32 per branch): fixed
                                   cost of a shared-prefix item, in private tokens' streaming
                                   time                                                          */
@@ -183,7 +184,7 @@ typedef struct {
                                   that finish their share take them, an item at a time, so the
                                   launch ends evenly.  -1 = none; values above 90 count as 90    */
     int32_t pool_item_tokens;  /* size of the pool's items, rounded down to a multiple of 32 tokens (at
-                                  least 32); 0 = default: a quarter of a share, between 512 and 2048 */
+                                  least 32); 0 = default: a quarter of a share, between 512 and 1536 */
     int32_t small_step_grid;   /* 0 = default: when target_workgroups is 0, a step without shared-prefix work
                                   is cut for one workgroup per compute unit instead of two if that cuts
                                   sequences into so many fewer pieces that it pays (each piece costs

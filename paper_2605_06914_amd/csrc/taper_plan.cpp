@@ -61,13 +61,14 @@ struct Segment {
     int32_t ends_seq = 0;  // private: the last tokens of its sequence in plan order (whoever streams them usually merges)
     int32_t whole_seq = 0;  // private: the sequence's whole context
     int32_t siblings = 0;   // shared: this and the next siblings - 1 segments stream the same prefix (one request, cut into sub-groups)
+    int32_t pct = 100;      // cost of a token, percent of a private one's
 };
 
 // Cost model of a workgroup share, in units of one private token's streaming time: an item of
-// n tokens costs fixed + n * per_token_pct / 100, `fixed` covering what an item costs beyond
+// n tokens costs fixed + n * pct / 100 (pct: its segment's), `fixed` covering what an item costs beyond
 // streaming its tokens (query load, pipeline fill, partial rows, arrival, merges).
 struct Cost {
-    int64_t per_token_pct, fixed;
+    int64_t fixed;
     int64_t merge = 0;  // extra cost of the item that ends a sequence: it arrives last as a rule and merges the partials
     int64_t per_branch = 0;  // further fixed cost for each of a shared item's branches
     int64_t item(const Segment& s) const { return fixed + per_branch * s.n_branch; }
@@ -83,7 +84,7 @@ int partition_fill(const std::vector<Segment>& segs, int64_t quota, int blk, con
     for (const Segment& s : segs) total_tokens += s.n_tokens;
     if (total_tokens == 0) return 0;
     quota = std::max<int64_t>(1, quota);
-    const int64_t blk_cost = std::max<int64_t>(1, blk * cost.per_token_pct / 100);
+    const int64_t blk_cost = blk;
     // a piece is only worth an item of its own if its streaming outweighs the item's fixed cost
     const int64_t min_blocks = std::max<int64_t>(1, (cost.fixed + blk_cost - 1) / blk_cost);
     const int64_t cap = std::max<int64_t>(1, (quota - cost.fixed) / blk_cost);  // blocks of an item with a share to itself
@@ -151,9 +152,8 @@ int64_t least_tokens(const Segment& s, int gqa) {
 int partition_even(const std::vector<Segment>& segs, int gqa, int64_t quota, int blk, const Cost cost, int64_t tail_discount,
                    int part_id0, std::vector<taper_work_item>* items) {
     quota = std::max<int64_t>(1, quota);
-    const int64_t blk_cost = std::max<int64_t>(1, blk * cost.per_token_pct / 100);
     int part = 0;
-    int64_t fill = 0;
+    int64_t fill = 0, blk_cost = 1;
     auto emit = [&](const Segment& s, int64_t off, int64_t take) {
         taper_work_item it;
         std::memset(&it, 0, sizeof it);
@@ -172,6 +172,7 @@ int partition_even(const std::vector<Segment>& segs, int gqa, int64_t quota, int
     };
     for (size_t si = 0; si < segs.size(); ++si) {
         const Segment& s = segs[si];
+        blk_cost = std::max<int64_t>(1, (int64_t)blk * s.pct / 100);
         const int64_t min_blocks = std::max<int64_t>(1, (cost.item(s) + blk_cost - 1) / blk_cost);
         // blocks of an item with a share to itself
         const int64_t cap = std::max({min_blocks, (quota - cost.item(s)) / blk_cost, least_tokens(s, gqa) / blk});
@@ -441,7 +442,7 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     //  * shares of some hundred tokens and more keep the memory system saturated, and a workgroup gets a slice of it.  A
     //    shared workgroup then takes 0.6 to 0.65 of the time of a private one per token (20.6 against 31.8 us per 1024
     //    tokens in the mixed batch, least squares over its shares) and 13.8 us per item, a private one 6.1 us.  Measured
-    //    optimum of the launch, with the pool evening out the rest: 70 to 90 % per token.
+    //    optimum of the launch, with the pool evening out the rest: 70 to 90 % per token for items of up to 4 row tiles.
     //  * shorter ones are over before that, and what counts is a workgroup's own chain of blocks: 20 us per 1024 tokens for
     //    a shared one, 9 for a private one, whose four waves each have a block in flight.  (The mixed batch on one
     //    kv head, 232 tokens per share: 27.4 us at 120 %, 25.0 at 200 %, and 25.7 without a pool against 31.9 with 30 % in it.)
@@ -452,16 +453,30 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     tok_listed += tok_priv;
     const int64_t share_tokens = tok_listed / parts_total;
     const bool latency_bound = share_tokens < kSaturatingShareTokens;
-    const Cost cost_shared = {opts && opts->shared_cost_pct > 0 ? opts->shared_cost_pct : (latency_bound ? 180 : 80),
-                              opts && opts->shared_item_cost > 0 ? opts->shared_item_cost : (latency_bound ? 60 : 450), 0,
+    // An item of more than 4 row tiles gives waves two or three tiles, and a block's chain 0.85 or 1.05 us instead of 0.65: it no
+    // longer keeps up with its slice of a saturated memory system.  (80 / 100 / 120 / 140 %, 8 requests of 2048 to 8192 tokens
+    // beside 16 serial ones, us: 4 branches, 2 tiles, 76.0 / 76.5 / 76.3 / 77.1; 10, 5 tiles, 101.7 / 95.0 / 94.0 / 94.6; 18, 9 tiles,
+    // 130.5 / 116.9 / 114.9 / 114.8; 24, 12 tiles, 159 / 138 / 134 / 135.)  Sub-groups of one request find part of their tokens in the L2
+    // (64 branches, 11 tiles: 270 at 80 to 110 %, 275 at 120; 48, 12 tiles: 221 / 216 / 217 / 218).
+    auto shared_pct = [&](const Segment& s, bool sub_group) -> int32_t {
+        if (opts && opts->shared_cost_pct > 0) return opts->shared_cost_pct;
+        if (latency_bound) return 180;
+        return s.n_branch * g <= 4 * 16 ? 80 : sub_group ? 110 : 120;
+    };
+    for (size_t i = 0; i < shared.size(); ++i) {
+        Segment& s = shared[i];  // (the sub-groups of a request follow each other: same pages, another first sequence)
+        auto same_request = [&](size_t j) { return j < shared.size() && branch_group[shared[j].seq0] == branch_group[s.seq0]; };
+        s.pct = shared_pct(s, same_request(i + 1) || (i > 0 && same_request(i - 1)));
+    }
+    const Cost cost_shared = {opts && opts->shared_item_cost > 0 ? opts->shared_item_cost : (latency_bound ? 60 : 450), 0,
                               opts && opts->shared_item_cost > 0 ? 0 : (latency_bound ? 32 : 0)};
-    const Cost cost_priv = {100, opts && opts->private_item_cost > 0 ? opts->private_item_cost : (shared.empty() || latency_bound ? 128 : 192),
+    const Cost cost_priv = {opts && opts->private_item_cost > 0 ? opts->private_item_cost : (shared.empty() || latency_bound ? 128 : 192),
                             opts && opts->private_merge_cost != 0 ? std::max(0, opts->private_merge_cost)
                                                                   : (shared.empty() ? 0 : 192)};
     const int64_t shared_tail_discount = 3;  // blocks: about what merging a request's branches costs
     int64_t cost_total = 0;
     for (const Segment& s : shared) {
-        cost_total += cost_shared.item(s) + (int64_t)s.n_tokens * cost_shared.per_token_pct / 100;
+        cost_total += cost_shared.item(s) + (int64_t)s.n_tokens * s.pct / 100;
     }
     for (const Segment& s : priv) {
         cost_total += cost_priv.fixed + s.n_tokens + (s.ends_seq ? cost_priv.merge : 0);
@@ -524,10 +539,10 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     for (const taper_work_item& it : p.items) p.part_start[it.part + 1]++;
     for (int i = 0; i < n_parts; ++i) p.part_start[i + 1] += p.part_start[i];
     plan_part_turns(cfg, branch_group, &p);
-    // size of the pool's items: a quarter of a share, between 512 and 2048 tokens, unless the caller says otherwise
+    // size of the pool's items: a quarter of a share, between 512 and 1536 tokens, unless the caller says otherwise
     const int pool_item_tokens = std::max<int>(
         kPrivateBlockTokens,
-        (pool_item_opt ? pool_item_opt : (int)std::min<int64_t>(2048, std::max<int64_t>(512, quota / 4))) / kPrivateBlockTokens * kPrivateBlockTokens);
+        (pool_item_opt ? pool_item_opt : (int)std::min<int64_t>(1536, std::max<int64_t>(512, quota / 4))) / kPrivateBlockTokens * kPrivateBlockTokens);
     for (const Segment& s : pool) {  // pool items follow the shares' items; their `part` is n_parts
         const int k = (s.n_tokens + pool_item_tokens - 1) / pool_item_tokens;
         const int piece = ((s.n_tokens + k - 1) / k + kPrivateBlockTokens - 1) / kPrivateBlockTokens * kPrivateBlockTokens;

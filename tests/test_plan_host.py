@@ -251,3 +251,29 @@ def test_small_steps_without_shared_work_take_half_the_grid_when_that_saves_piec
     assert check_plan_against_oracle(big)["n_parts_private"] == 64
     mixed = check_plan_against_oracle(structure_config3())
     assert mixed["n_parts_shared"] + mixed["n_parts_private"] == 64
+
+
+@pytest.mark.parametrize("head_shape,width,pct", [((64, 8, 128), 2, 80), ((64, 8, 128), 8, 80), ((64, 8, 128), 9, 120), ((64, 8, 128), 24, 120),
+                                                  ((64, 8, 128), 25, 110), ((64, 8, 128), 64, 110), ((32, 8, 64), 16, 80), ((32, 8, 64), 17, 120),
+                                                  ((64, 4, 128), 5, 120), ((64, 4, 128), 24, 110)])
+def test_a_shared_token_weighs_more_in_items_of_more_row_tiles(head_shape, width, pct):
+    """Items of up to 4 row tiles 80 %, wider ones 120, wider sub-groups of one request 110 (steps of long shares)."""
+    st = structure_custom(AttnShape(*head_shape, 16), [(3000, [0])] * 30 + [(8000 + 500 * i, [700] * width) for i in range(8)], seed=5)
+    ctx = Context(*head_shape, device=-1)
+    a, b = (ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, **kw).export()
+            for kw in ({}, dict(shared_cost_pct=pct)))
+    assert np.array_equal(a["items"], b["items"]) and np.array_equal(a["part_start"], b["part_start"])
+    ctx.close()
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_pool_items_stay_within_their_default_size(seed):
+    """A quarter of a share, between 512 and 1536 tokens, also where a quarter of a share is more."""
+    rng = np.random.default_rng(seed)
+    st = structure_custom(QWEN, [(int(x), [0]) for x in rng.integers(20000, 40000, 64)] + [(20000, [3000] * 6)] * 4, seed=seed)
+    ctx = Context(64, 8, 128, device=-1)
+    e = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages).export()
+    F = {n: i for i, n in enumerate(e["item_fields"])}
+    pool = e["items"][e["part_start"][-1]:, F["n_tokens"]]
+    assert e["n_pool_items"] > 0 and 1024 < pool.max() <= 1536, pool.max()
+    ctx.close()

@@ -88,10 +88,11 @@ def test_static_entry_rejects_a_step_beyond_the_array():
     ctx.close()
 
 
-@pytest.mark.parametrize("n_req,width,prefix,suffix,halvings", [(30, 24, 6000, 100, 0), (36, 22, 4500, 100, 1)])
-def test_static_entry_cuts_a_step_coarser_that_does_not_fit_as_it_would_best_be_cut(n_req, width, prefix, suffix, halvings):
-    """Many wide requests with fp32 partial rows: the default cut needs more than the array's 64 MiB, without a pool (and, for the
-    second, at half the grid) it fits.  Same bits as the allocating entry with that cut, and the oracle's values."""
+@pytest.mark.parametrize("n_req,width,prefix,suffix", [(30, 24, 3000, 300), (30, 24, 6000, 100), (36, 22, 6500, 100)])
+def test_static_entry_cuts_a_step_coarser_that_does_not_fit_as_it_would_best_be_cut(n_req, width, prefix, suffix):
+    """Many wide requests with fp32 partial rows: the default cut needs more than the array's 64 MiB; without a pool or, where that
+    is not enough, at a half (a quarter ...) of the grid it fits.  Same bits as the allocating entry with that cut, and the
+    oracle's values."""
     import torch
 
     from paper_2605_06914_amd import Context
@@ -102,23 +103,26 @@ def test_static_entry_cuts_a_step_coarser_that_does_not_fit_as_it_would_best_be_
     st = structure_custom(QWEN, reqs, seed=3)
     ctx = Context(64, 8, 128, device=0, partial_format="f32")
     grid = 2 * torch.cuda.get_device_properties(0).multi_processor_count
-    row_bytes = 128 * 4 + 16
 
-    def rows(**kw):
+    def needs(**kw):  # image (every piece aligned to 256 bytes) and workspace of the plan
         p = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, **kw)
-        n = p.export()["n_partial_rows"]
+        e = p.export()
         p.free()
-        return n
+        S, rows, shares = st.n_seqs, e["n_partial_rows"], len(e["part_start"]) - 1
+        pieces = [st.block_table.size * 4, len(e["items"]) * 32, (2 * shares + 1) * 4, len(e["merge"]) * 8, (S + 1) * 8 * 4, rows * 16,
+                  rows * 128 * 4] + [(S + 1) * 4] * 2 + [S * 4] * 4
+        return sum(-(-n // 256) * 256 for n in pieces)
 
-    coarse = dict(pool_pct=-1, target_workgroups=grid >> halvings)
-    assert rows() * row_bytes > 64 << 20 and rows(**coarse) * row_bytes < 63 << 20
-    assert halvings == 0 or rows(pool_pct=-1, target_workgroups=grid) * row_bytes > 64 << 20
+    cuts = [{}] + [dict(pool_pct=-1, target_workgroups=grid >> i) for i in range(7)]
+    sizes = [needs(**kw) for kw in cuts]
+    print(f"[no-alloc] {n_req} requests x {width} branches: S={st.n_seqs}, MiB of the cuts {[round(n / 2**20, 1) for n in sizes]}", flush=True)
+    fits = [i for i, n in enumerate(sizes) if n <= 64 << 20]
+    assert fits
     q, kv = device_random_batch(st)
-    print(f"[no-alloc] {n_req} requests x {width} branches: S={st.n_seqs}", flush=True)
     got = torch.full_like(q, float("nan"))
     ctx.decode_step_attention_static(q, kv, st.n_pool_pages, st.block_table, st.branch_group, st.prefix_len, st.suffix_len, got)
     torch.cuda.synchronize()
-    want = run_gpu_device(ctx, st, q, kv, **coarse)
+    want = run_gpu_device(ctx, st, q, kv, **cuts[fits[0]])
     same = np.array_equal(bits_from_torch(got), bits_from_torch(want))
     assert same
     picked, sub = host_subbatch(st, q, kv, [0, width - 1, 7 * width + 3, st.n_seqs - 1])
