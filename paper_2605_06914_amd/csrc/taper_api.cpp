@@ -307,6 +307,7 @@ taper::StepArgs make_args(const taper_ctx* ctx, const taper::HostPlan& h, const 
     a.n_parts_shared = h.n_parts_shared;
     a.n_parts_private = h.n_parts_private;
     a.max_row_tiles_shared = h.max_row_tiles_shared;
+    a.long_shares = h.long_shares;
     a.scale_log2e = ctx->cfg.scale * 1.4426950408889634f;
     a.partial_format = ctx->cfg.partial_format;
 #ifdef TAPER_WG_TRACE

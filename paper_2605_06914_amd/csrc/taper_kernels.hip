@@ -421,13 +421,15 @@ struct PrivateSmem {
 // not what matters then (one set of registers refilled as it is used up, two, and two with the block after next
 // already asked for all measure within 0.5 %); two sets win where a wave has two blocks and the machine is idle
 // (mixed batch on one kv head: 27.7 us with one set, 25.3 with two).
-// SB: the block-table row is read by scalar loads (constant address space, wave-uniform pointer), which do not wait for
-// the KV loads in flight; a vector load of a page id completes in order, behind everything issued before it, and so
-// holds a wave to one block in flight.  Beside shared-prefix workgroups at head_dim 128 that restraint pays, as what a private wave asks for
-// earlier they wait for longer (vector / scalar page ids: 128 requests of 3 branches 471 / 476 us, of 17 branches 788 / 793, 16
-// branches of 32768 tokens 349 / 357, mixed batch 83.0 / 83.6; 32 branches 174 / 173).  At 64 a block holds half the bytes and the wait
-// weighs more (mixed batch 46.3 / 45.4), and without shared work there is nobody to leave bandwidth to (k = 0 of the sweep equal).
-template <int D, bool SOLO, int PF, bool SB>
+// The block-table row is read by scalar loads (constant address space, wave-uniform pointer), which do not wait for
+// the KV loads in flight; a vector load of a page id completes in order, behind everything issued before it.
+// HOLD: beside shared-prefix work (head_dim 128) a wave asks for its next block only when the one before has landed, if the
+// step's shares are long (2000 tokens and more): what it asks for earlier it only waits for longer, and the shared workgroups with
+// it.  Held back / not, us: 128 requests of 3 branches 471 / 474, of 17 branches 798 / 804; 16 branches of 32768 tokens 353.1 / 354.4; 8
+// requests of 12 branches, 2231 tokens per share, 104 / 108; no more than 0.6 % is lost anywhere above.  In shorter shares the wait
+// counts: 155 tokens per share 18.5 / 17.2, 577 31.5 / 30.4, 57 12.7 / 12.1, with 2 to 3 % the other way at others.  At
+// head_dim 64 a block holds half the bytes and the wait weighs more (mixed batch 46.3 / 45.4).
+template <int D, bool SOLO, int PF, bool HOLD>
 DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem<D>& sm) {
     constexpr int KS = D / 32, DT = D / 16, TILE = 16 * D;
     auto& sm_o = sm.o;
@@ -439,8 +441,8 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
     const float c = a.scale_log2e;
     {
         const taper_work_item item = load_item(a, it);
-        typedef typename std::conditional<SB, const __attribute__((address_space(4))) int32_t*, const int32_t*>::type table_row;
-        const table_row row = (table_row)(a.bt + (int64_t)item.seq0 * a.bt_stride + item.page0);
+        typedef const __attribute__((address_space(4))) int32_t* scalar_row;
+        const scalar_row row = (scalar_row)(a.bt + (int64_t)item.seq0 * a.bt_stride + item.page0);
         const int n_tok = item.n_tokens;
         const int n_pages = (n_tok + 15) >> 4;
         const int n_blocks = (n_tok + 31) >> 5;
@@ -469,6 +471,7 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
             pid_b = row[ib];
         };
         auto load_block = [&](KVRegs<D>& r) {
+            if (HOLD && a.long_shares) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             const char* ka = kvb + pid_a * page_bytes;
             const char* kb = kvb + pid_b * page_bytes;
             const char* va = ka + (int64_t)Hkv * TILE * 2;
@@ -611,7 +614,7 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
 // can take from its kv head's pool.  Every workgroup makes exactly one claim past the end of
 // the pool; the one that makes the last of those puts the counter back to zero for the next
 // launch.
-template <int D, int PF, bool SB>
+template <int D, int PF, bool HOLD>
 DEV void private_items(const StepArgs& a, int it0, const int it1, const int hk, PrivateSmem<D>& sm) {
     const int wgs_per_head = a.n_parts_shared + a.n_parts_private;  // = gridDim.x / n_kv_heads
 #ifdef TAPER_WG_TRACE
@@ -642,12 +645,12 @@ DEV void private_items(const StepArgs& a, int it0, const int it1, const int hk, 
             int end = it + 1;
             while (end < it1 && load_item(a, end).kind == 3) ++end;
             const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-            for (int k = it + wave; k < end; k += 4) private_item<D, true, PF, SB>(a, k, hk, sm);
+            for (int k = it + wave; k < end; k += 4) private_item<D, true, PF, false>(a, k, hk, sm);
             it0 = end;
             __syncthreads();
             continue;
         }
-        private_item<D, false, PF, SB>(a, it, hk, sm);
+        private_item<D, false, PF, HOLD>(a, it, hk, sm);
     }
 }
 
@@ -954,7 +957,7 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(StepArgs a) {
 #ifdef TAPER_WG_TRACE
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x + 1] = wall_clock64();  // shared share done (a private share: overwritten when it is done)
 #endif
-    private_items<D, PF, ALLP || D == 64>(a, it0, it1, hk, *reinterpret_cast<PrivateSmem<D>*>(smem_raw));
+    private_items<D, PF, !ALLP && D == 128>(a, it0, it1, hk, *reinterpret_cast<PrivateSmem<D>*>(smem_raw));
 #ifdef TAPER_WG_TRACE
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x + 2] = wall_clock64();
 #endif

@@ -55,6 +55,7 @@ constexpr int64_t kPieceCostTokens = 200;   // what one more piece of a cut sequ
 constexpr int64_t kOnePerUnitLossPct = 3;   // what one workgroup per compute unit instead of two costs, percent
 constexpr double kTokensPerMergedRow = 4.0;      // see least_tokens
 constexpr int64_t kSaturatingShareTokens = 350;  // shares of fewer tokens are over before the memory system is saturated
+constexpr int64_t kLongShareTokens = 2000;       // from here on private work holds back beside shared-prefix work (see private_item in the kernels)
 
 struct Segment {
     int32_t seq0, n_branch, page0, n_tokens, kind;
@@ -453,6 +454,7 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     tok_listed += tok_priv;
     const int64_t share_tokens = tok_listed / parts_total;
     const bool latency_bound = share_tokens < kSaturatingShareTokens;
+    p.long_shares = share_tokens >= kLongShareTokens;
     // An item of more than 4 row tiles gives waves two or three tiles, and a block's chain 0.85 or 1.05 us instead of 0.65: it no
     // longer keeps up with its slice of a saturated memory system.  (80 / 100 / 120 / 140 %, 8 requests of 2048 to 8192 tokens
     // beside 16 serial ones, us: 4 branches, 2 tiles, 76.0 / 76.5 / 76.3 / 77.1; 10, 5 tiles, 101.7 / 95.0 / 94.0 / 94.6; 18, 9 tiles,
