@@ -707,6 +707,14 @@ DEV void load_to_lds(const char* base, unsigned off, unsigned lds) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds) : "m0", "memory");
 }
 #pragma clang diagnostic pop
+// The same through registers, for a pool that does not start at a multiple of 16 bytes (a view into a larger buffer, say):
+// ordinary loads take any address, and that direct ones do is nothing to rely on.  Tiles are multiples of 2 KiB, so
+// that the pool's start decides for all of them.
+DEV void copy_to_lds(const char* base, unsigned off, char* lds, int lane) {
+    u32x4 v;
+    __builtin_memcpy(&v, base + off, 16);
+    *(u32x4*)(lds + lane * 16) = v;
+}
 // All but this wave's N youngest loads have landed, its LDS reads are done, and every wave of the workgroup is here.
 template <int N>
 DEV void wait_loads_and_meet() {
@@ -799,6 +807,17 @@ DEV void shared_stream(const StepArgs& a, const taper_work_item& item, const int
     };
     auto stage = [&](int b) {
         const unsigned buf = ring + (b & (Sm::RING - 1)) * Sm::BLOCK_BYTES;
+        if (__builtin_expect(a.kv_misaligned, 0)) {
+            char* dst = sm.kv + (b & (Sm::RING - 1)) * Sm::BLOCK_BYTES;
+#pragma unroll 1
+            for (int i = 0; i < 2; ++i) {  // (a page of two at head_dim 128, a half of a tile at 64)
+                const int page = D == 128 && i ? pid[D == 128] : pid[0];
+                const char* k = kvb + page * page_bytes + (D == 128 ? wave : i) * 1024;
+                copy_to_lds(k, off_k, dst + (D == 128 ? i : wave) * Sm::TILE_BYTES + (D == 128 ? wave : i) * 1024, lane);
+                copy_to_lds(k + (int64_t)Hkv * Sm::TILE_BYTES, off_v, dst + (D == 128 ? Sm::v_chunk(i, wave) : Sm::v_chunk(wave, i)), lane);
+            }
+            return;
+        }
         if constexpr (D == 128) {
 #pragma unroll
             for (int pg = 0; pg < 2; ++pg) {

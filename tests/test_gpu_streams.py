@@ -92,3 +92,41 @@ def test_a_prefix_is_not_cut_into_more_items_than_its_merge_is_worth():
         assert int(shared[:, F["n_tokens"]].sum()) == 24000
         assert 4 <= k and k * k <= 1.5 * 4.0 * 24000 / rows, (width, k)
         ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("elements", [1, 4])
+def test_a_pool_that_starts_anywhere(shape, elements):
+    """Pool, queries and results as views 2 and 8 bytes into larger buffers, over items of every number of tiles per wave: the
+    bits are those of aligned buffers."""
+    import torch
+
+    from tests.gpu_util import bits_from_torch, torch_bf16
+
+    sh = AttnShape(*shape, 16)
+    widths = sorted({max(2, 16 * t // sh.gqa) for t in (1, 4, 8, 12)})
+    reqs = [(p, [(7 * i + p) % 41 for i in range(w)]) for w in widths if (w * sh.gqa + 15) // 16 <= 12 for p in (1, 31, 64, 97, 161, 321)]
+    b = fill_values_numpy(structure_custom(sh, reqs + [(n, [0]) for n in (5, 77, 300, 1500)], seed=71))
+    ctx = context(sh)
+    _, _, want = run_gpu(ctx, b, max_branches_per_item=max(widths))
+
+    def shifted(t):
+        big = torch.zeros(t.numel() + 16, dtype=t.dtype, device=t.device)
+        view = big[elements:elements + t.numel()]
+        view.copy_(t.reshape(-1))
+        return big, view
+
+    st = b.structure
+    (_, q), (_, kv) = shifted(torch_bf16(b.q)), shifted(torch_bf16(b.kv))
+    whole, out = shifted(torch.zeros(b.q.size, dtype=torch.bfloat16, device="cuda:0"))
+    assert kv.data_ptr() % 16 == 2 * elements
+    print(f"[offset] {shape} {elements} elements: S={st.n_seqs}", flush=True)
+    plan = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, max_branches_per_item=max(widths))
+    ctx.decode_step_attention(plan, q, kv, out)
+    torch.cuda.synchronize()
+    same = np.array_equal(bits_from_torch(out).reshape(want.shape), want)
+    assert same
+    assert not whole[:elements].any() and not whole[elements + out.numel():].any()
+    plan.free()
+    ctx.close()
