@@ -278,7 +278,6 @@ taper::StepArgs make_args(const taper_ctx* ctx, const taper::HostPlan& h, const 
     std::memset(&a, 0, sizeof a);
     a.q = q;
     a.kv = kv;
-    a.kv_misaligned = ((uintptr_t)kv & 15) != 0;
     a.out = out;
     a.lse = lse;
     a.bt = img.bt;

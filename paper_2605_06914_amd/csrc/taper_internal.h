@@ -37,7 +37,6 @@ struct StepArgs {
     int32_t n_q_heads, n_kv_heads, gqa, head_dim;
     int32_t n_parts_shared, n_parts_private;
     int32_t max_row_tiles_shared;
-    int32_t kv_misaligned;     // the pool does not start at a multiple of 16 bytes (see copy_to_lds)
     int32_t long_shares;       // shares long enough for private work to hold back beside shared-prefix work (see private_item)
     float scale_log2e;         // scale * log2(e)
     int32_t partial_format;    // taper_partial_format of ws_o

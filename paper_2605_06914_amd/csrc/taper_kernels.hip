@@ -417,10 +417,10 @@ struct PrivateSmem {
 // SOLO: the item is run by the calling wave alone (short sequences that are a single item:
 // four of them proceed side by side in a workgroup, with no barrier and no LDS); otherwise the
 // four waves of the workgroup share the item's blocks.
-// Bound by HBM: 128 requests of 4096 tokens take 324 us, a bare read of the same pages 310.  The depth of the pipeline is
+// Bound by HBM: 128 requests of 4096 tokens take 321 us, a bare read of the same pages 310.  The depth of the pipeline is
 // not what matters then (one set of registers refilled as it is used up, two, and two with the block after next
 // already asked for all measure within 0.5 %); two sets win where a wave has two blocks and the machine is idle
-// (mixed batch on one kv head: 27.7 us with one set, 25.3 with two).
+// (mixed batch on one kv head: 9 % slower with one set).
 // The block-table row is read by scalar loads (constant address space, wave-uniform pointer), which do not wait for
 // the KV loads in flight; a vector load of a page id completes in order, behind everything issued before it.
 // HOLD: beside shared-prefix work (head_dim 128) a wave asks for its next block only when the one before has landed, if the
@@ -470,8 +470,8 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
             pid_a = row[ia];
             pid_b = row[ib];
         };
+        auto hold = [&] { if (HOLD && a.long_shares) asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
         auto load_block = [&](KVRegs<D>& r) {
-            if (HOLD && a.long_shares) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             const char* ka = kvb + pid_a * page_bytes;
             const char* kb = kvb + pid_b * page_bytes;
             const char* va = ka + (int64_t)Hkv * TILE * 2;
@@ -515,9 +515,11 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
             fetch_ids(b + STEP);
             while (b + 2 * STEP < n_blocks) {
                 KVRegs<D> r1;
+                hold();
                 load_block(r1);
                 fetch_ids(b + 2 * STEP);
                 compute_block(b, r0, std::false_type{});
+                hold();
                 load_block(r0);
                 fetch_ids(b + 3 * STEP);
                 compute_block(b + STEP, r1, std::false_type{});
@@ -525,6 +527,7 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
             }
             if (b + STEP < n_blocks) {
                 KVRegs<D> r1;
+                hold();
                 load_block(r1);
                 compute_block(b, r0, std::false_type{});
                 r0 = r1;
@@ -672,9 +675,9 @@ DEV void private_items(const StepArgs& a, int it0, const int it1, const int hk, 
 // loads only get longer by loads it does not know of.)
 //
 // What bounds it: on a saturated machine HBM (a launch of shared work alone, 16 requests of 32768 tokens: 2 branches
-// 339 us, 8 branches 350, 16 branches 379, of the 310 a bare read of the same pages takes; 16 branches were 454 with
-// KV staged through registers).  Alone on the machine, the chain of a block -- LDS reads, matrix instructions,
-// exponentials, the barrier: 0.65 us per block with one tile per wave and 0.2 us more for each further one (1.0 before,
+// 334 us, 8 branches 344, 16 branches 388, of the 310 a bare read of the same pages takes; 16 branches were 454 with
+// KV staged through registers; 24 branches, three tiles per wave, 502).  Alone on the machine, the chain of a block -- LDS reads, matrix
+// instructions, exponentials, the barrier: 0.67, 0.84 and 1.06 us per block with one, two and three tiles per wave (1.0 with one
 // when page ids and queries were waited for inside the loop; a ring of eight does not change it).
 // ---------------------------------------------------------------------------
 template <int D>
@@ -756,7 +759,7 @@ DEV void store_shared_partials(const StepArgs& a, const taper_work_item& item, c
 
 // Streams the item's tokens against the NA tiles wave, wave + 4, ... of its rows and stores their partial rows.
 // Every wave of the workgroup takes its part in staging and meets the others once per block, whatever its NA.
-template <int D, int NA, int PF>
+template <int D, int NA, int PF, bool ANY>
 DEV void shared_stream(const StepArgs& a, const taper_work_item& item, const int hk, SharedSmem<D>& sm, const int tid,
                        const int wave) {
     typedef SharedSmem<D> Sm;
@@ -807,18 +810,15 @@ DEV void shared_stream(const StepArgs& a, const taper_work_item& item, const int
     };
     auto stage = [&](int b) {
         const unsigned buf = ring + (b & (Sm::RING - 1)) * Sm::BLOCK_BYTES;
-        if (__builtin_expect(a.kv_misaligned, 0)) {
+        if constexpr (ANY) {
             char* dst = sm.kv + (b & (Sm::RING - 1)) * Sm::BLOCK_BYTES;
-#pragma unroll 1
+#pragma unroll
             for (int i = 0; i < 2; ++i) {  // (a page of two at head_dim 128, a half of a tile at 64)
-                const int page = D == 128 && i ? pid[D == 128] : pid[0];
-                const char* k = kvb + page * page_bytes + (D == 128 ? wave : i) * 1024;
+                const char* k = kvb + pid[D == 128 ? i : 0] * page_bytes + (D == 128 ? wave : i) * 1024;
                 copy_to_lds(k, off_k, dst + (D == 128 ? i : wave) * Sm::TILE_BYTES + (D == 128 ? wave : i) * 1024, lane);
                 copy_to_lds(k + (int64_t)Hkv * Sm::TILE_BYTES, off_v, dst + (D == 128 ? Sm::v_chunk(i, wave) : Sm::v_chunk(wave, i)), lane);
             }
-            return;
-        }
-        if constexpr (D == 128) {
+        } else if constexpr (D == 128) {
 #pragma unroll
             for (int pg = 0; pg < 2; ++pg) {
                 const char* k = kvb + pid[pg] * page_bytes + wave * 1024;
@@ -916,7 +916,7 @@ DEV void shared_stream(const StepArgs& a, const taper_work_item& item, const int
     }
 }
 
-template <int D, int NTW, int PF>
+template <int D, int NTW, int PF, bool ANY>
 DEV void shared_path(const StepArgs& a, const int part, const int hk, SharedSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int it0 = a.part_start[part], it1 = a.part_start[part + 1];
@@ -925,10 +925,10 @@ DEV void shared_path(const StepArgs& a, const int part, const int hk, SharedSmem
         const int tid = opaque(threadIdx.x);
         const int tiles = (item.n_branch * a.gqa + 15) >> 4;
         const int n_act = (tiles - wave + 3) >> 2;  // tiles wave, wave + 4, ...; 0 for a wave past the last tile (tiles >= 1)
-        if (NTW >= 3 && n_act >= 3) shared_stream<D, NTW >= 3 ? 3 : 1, PF>(a, item, hk, sm, tid, wave);
-        else if (NTW >= 2 && n_act == 2) shared_stream<D, NTW >= 2 ? 2 : 1, PF>(a, item, hk, sm, tid, wave);
-        else if (n_act == 1) shared_stream<D, 1, PF>(a, item, hk, sm, tid, wave);
-        else shared_stream<D, 0, PF>(a, item, hk, sm, tid, wave);
+        if (NTW >= 3 && n_act >= 3) shared_stream<D, NTW >= 3 ? 3 : 1, PF, ANY>(a, item, hk, sm, tid, wave);
+        else if (NTW >= 2 && n_act == 2) shared_stream<D, NTW >= 2 ? 2 : 1, PF, ANY>(a, item, hk, sm, tid, wave);
+        else if (n_act == 1) shared_stream<D, 1, PF, ANY>(a, item, hk, sm, tid, wave);
+        else shared_stream<D, 0, PF, ANY>(a, item, hk, sm, tid, wave);
         // publish the partials; merge every branch whose set is now complete
         stores_done();
         __syncthreads();
@@ -948,14 +948,14 @@ DEV void shared_path(const StepArgs& a, const int part, const int hk, SharedSmem
 // One launch per layer: workgroup (share, kv head).  Shares below n_parts_shared
 // stream shared prefixes, the others private tokens; both kinds run side by side.
 // ---------------------------------------------------------------------------
-// ALLP: a launch without shared-prefix work (no shared path in the kernel).
-template <int D, int NTW, int PF, bool ALLP>
-__global__ __launch_bounds__(256, 2) void decode_kernel(StepArgs a) {
-    union Smem {
-        SharedSmem<D> sh;
-        PrivateSmem<D> pr;
-    };
-    __shared__ __attribute__((aligned(16))) char smem_raw[sizeof(Smem)];
+template <int D>
+union StepSmem {
+    SharedSmem<D> sh;
+    PrivateSmem<D> pr;
+};
+// ALLP: a launch without shared-prefix work (no shared path in the kernel).  ANY: the pool may start at any address.
+template <int D, int NTW, int PF, bool ALLP, bool ANY>
+DEV void run_share(const StepArgs& a, char* smem_raw) {
     const int part = blockIdx.x / a.n_kv_heads;
     const int hk = (blockIdx.x + a.part_turn[part]) % a.n_kv_heads;
 #ifdef TAPER_WG_TRACE  // trace builds only (wg_trace.py): per-workgroup clocks -- start, own share done, left, time in merges
@@ -967,7 +967,7 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(StepArgs a) {
         it0 = a.part_start[part];
         it1 = a.part_start[part + 1];
     } else if (part < a.n_parts_shared) {
-        shared_path<D, NTW, PF>(a, part, hk, *reinterpret_cast<SharedSmem<D>*>(smem_raw));
+        shared_path<D, NTW, PF, ANY>(a, part, hk, *reinterpret_cast<SharedSmem<D>*>(smem_raw));
         __syncthreads();
     } else {
         it0 = a.part_start[part];
@@ -980,6 +980,19 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(StepArgs a) {
 #ifdef TAPER_WG_TRACE
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x + 2] = wall_clock64();
 #endif
+}
+
+template <int D, int NTW, int PF, bool ALLP>
+__global__ __launch_bounds__(256, 2) void decode_kernel(StepArgs a) {
+    __shared__ __attribute__((aligned(16))) char smem_raw[sizeof(StepSmem<D>)];
+    run_share<D, NTW, PF, ALLP, false>(a, smem_raw);
+}
+// Steps with shared-prefix work over a pool that does not start at a multiple of 16 bytes (a kernel of its own: a branch per block
+// in the others cost them 1 to 2 %, mixed batch on one kv head 26.4 -> 26.7 us, 64 branches 270 -> 274).
+template <int D, int PF>
+__global__ __launch_bounds__(256, 2) void any_start_kernel(StepArgs a) {
+    __shared__ __attribute__((aligned(16))) char smem_raw[sizeof(StepSmem<D>)];
+    run_share<D, 3, PF, false, true>(a, smem_raw);
 }
 
 // Physical slot of every logical position, from the device copy of the plan.
@@ -1074,10 +1087,11 @@ template <int D, int PF>
 static hipError_t launch_decode_as(const StepArgs& a, const dim3 grid, const int ntw, hipStream_t s) {
     const dim3 block(256);
     if (a.n_parts_shared == 0) hipLaunchKernelGGL((decode_kernel<D, 1, PF, true>), grid, block, 0, s, a);
+    else if (ntw > 3) return hipErrorInvalidValue;
+    else if ((uintptr_t)a.kv & 15) hipLaunchKernelGGL((any_start_kernel<D, PF>), grid, block, 0, s, a);
     else if (ntw <= 1) hipLaunchKernelGGL((decode_kernel<D, 1, PF, false>), grid, block, 0, s, a);
     else if (ntw == 2) hipLaunchKernelGGL((decode_kernel<D, 2, PF, false>), grid, block, 0, s, a);
-    else if (ntw == 3) hipLaunchKernelGGL((decode_kernel<D, 3, PF, false>), grid, block, 0, s, a);
-    else return hipErrorInvalidValue;
+    else hipLaunchKernelGGL((decode_kernel<D, 3, PF, false>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 

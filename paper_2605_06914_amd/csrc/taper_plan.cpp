@@ -136,9 +136,11 @@ int partition_fill(const std::vector<Segment>& segs, int64_t quota, int blk, con
 }
 
 // A prefix of n tokens cut into k items takes n / k tokens' time to stream and k times its R query rows to merge, and one
-// workgroup merges them all: the last to arrive, as a rule, for every branch of the request.  A token costs a
-// shared workgroup 20 ns, a row and item 7 ns (5 branches x 16 heads: 109 us for 195 items), so that k items are best at
-// k * k = kTokensPerMergedRow * n / R.
+// workgroup merges them all: the last to arrive, as a rule, for every branch of the request.  The sum is least at some
+// k * k = kTokensPerMergedRow * n / R.  A token costs a shared workgroup alone 20 ns, a row and item 7 ns (5 branches x 16 heads: 109 us
+// for 195 items), which would make the constant 2.9; the sum is flat there, and measured 4 is the better choice: 24000 tokens of 2 /
+// 5 / 12 branches on one kv head of 16 query heads 33 / 46.5 / 81 us (2.9: 32 / 49 / 85; 8: 38 / 48 / 83), 8 requests of 12 branches
+// 57 (60; 58).
 int64_t least_tokens(const Segment& s, int gqa) {
     return (int64_t)std::sqrt((double)s.n_tokens * s.n_branch * gqa / kTokensPerMergedRow);
 }
@@ -286,9 +288,10 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     const int g = cfg.n_q_heads / cfg.n_kv_heads;
     int target_wgs = opts && opts->target_workgroups > 0 ? opts->target_workgroups : 512;
     const bool share_prefix = opts ? opts->share_prefix != 0 : true;
-    // A shared item holds up to 12 row tiles.  At head_dim 128 the kernel for 9 to 12 tiles loads
-    // straight into LDS and still runs two workgroups per compute unit; at 64 it stages through
-    // registers and runs one, so requests are cut at 8 tiles unless asked otherwise.
+    // A shared item holds up to 12 row tiles.  At head_dim 64 requests are cut at 8 unless asked otherwise: a line from a kernel
+    // that ran only one workgroup of more per compute unit, which no longer holds (146 to 149 VGPRs, two workgroups).  One
+    // item of up to 12 tiles instead measures 79.6 us against 94.6 at 33 branches of 4 query heads, 93 against 99 at 40, 104 against
+    // 111 at 48; with 8 query heads 75 against 84 at 17 branches, but 80.8 against 78.4 at 20 and 83 against 81 at 24.
     // 64: per-branch flags of the shared kernel.
     const int hard_cap = std::min(64, std::max(2, kMaxRowTilesPerItem * 16 / g));
     int cap_branches = std::min(hard_cap, std::max(2, (cfg.head_dim == 128 ? kMaxRowTilesPerItem : 8) * 16 / g));
@@ -446,7 +449,7 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     //    optimum of the launch, with the pool evening out the rest: 70 to 90 % per token for items of up to 4 row tiles.
     //  * shorter ones are over before that, and what counts is a workgroup's own chain of blocks: 20 us per 1024 tokens for
     //    a shared one, 9 for a private one, whose four waves each have a block in flight.  (The mixed batch on one
-    //    kv head, 232 tokens per share: 27.4 us at 120 %, 25.0 at 200 %, and 25.7 without a pool against 31.9 with 30 % in it.)
+    //    kv head, 232 tokens per share: 26.8 us at 120 %, 26.7 at 180, 26.6 at 200; 28.6 with the constants of longer shares.)
     const int parts_total = std::max(1, target_wgs / cfg.n_kv_heads);
     int64_t tok_listed = 0, tok_priv = 0;
     for (const Segment& s : shared) tok_listed += s.n_tokens;
@@ -489,10 +492,11 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     // launch), so the shares are cut short and every workgroup that finishes its share takes items
     // from the pool until it is empty.  The longer the shares, the larger the differences and the less a pool
     // item's fixed cost weighs: a quarter of the private tokens for shares of up to 2048 tokens, rising to 60 % at
-    // 5120.  (25 / 40 / 60 %: mixed batch, 1900 tokens per share, 84.2 / 84.4 / 86.1 us; 8 requests of 64 branches, 5400 per
-    // share, 312 / 300 / 277; 640 sequences, 19000 per share, 841 / 827 / 803.)
-    // Without shared-prefix work the shares are alike and cutting a sequence costs more than the balance gains; and
-    // where latency bounds the launch a claim's round trip is too much.
+    // 5120.  (25 / 40 / 60 %: mixed batch, 1900 tokens per share, 83.1 / 83.9 / 85.8 us; 8 requests of 64 branches, 5400 per
+    // share, 335 / 330 / 267, where what changes is how often the sub-groups' prefixes are cut; 640 sequences, 19000 per share, 798 /
+    // 790 / 796.)  Without shared-prefix work the shares are alike and cutting a sequence costs more than the balance gains; and
+    // where latency bounds the launch a claim's round trip is as much as it evens out (26.7 us without, 26.0 with 30 %, 28.6 with 25 % and
+    // the constants of longer shares, mixed batch on one kv head).
     const int pool_default = shared.empty() || latency_bound
                                  ? 0
                                  : (int)(25 + 35 * std::min<int64_t>(3072, std::max<int64_t>(0, share_tokens - 2048)) / 3072);

@@ -122,3 +122,12 @@ def test_every_launch_the_host_code_makes_is_a_strong_symbol(tmp_path):
     assert len(calls) >= 5 and set(calls.values()) == {"U"}, calls
     stubs = symbols(os.path.join(ROOT, "tests", "sanitize", "kernel_stubs.cpp"))
     assert set(stubs) == set(calls) and set(stubs.values()) == {"T"}, (stubs, calls)
+
+
+def test_the_kernels_for_pools_that_start_anywhere_meet_the_same_checks(compiled):
+    asm, remarks = compiled
+    spilled = re.findall(r"Function Name: (\S*any_start_kernel\S*)(?:.|\n)*?ScratchSize \[bytes/lane\]: (\d+)", remarks)
+    assert len(spilled) == 4 and all(n == "0" for _, n in spilled), spilled
+    for check in (scan, scan_scalar_addresses):
+        findings, kernels = check(asm, name_filter="any_start_kernel")
+        assert kernels == 4 and not findings, findings[:5]
