@@ -761,7 +761,7 @@ def bench_single(args, workload):
     ctx2.close()
     partial_rows = {"format": args.partial_format,
                     "what": {"f16_scaled": "accumulator rows between workgroups in half precision, each row divided by its own sum "
-                                           "and by a power of two that brings its largest magnitude into [0.5, 1) (no range limit on V); "
+                                           "and by a power of two that brings its largest magnitude into [0.5, 1) (no range limit beyond the fp32 accumulator's); "
                                            "running max, sum and the power of two in fp32; accumulation in fp32",
                              "f32": "accumulator rows between workgroups in fp32; running max and sum in fp32; accumulation in fp32"}[args.partial_format],
                     "avg_launch_us": {args.partial_format: round(launch_us, 2), other: round(probe2.us_median / n_layers, 2)}}

@@ -83,8 +83,10 @@ typedef enum {
                                      of V rows) and by a power of two that brings its largest magnitude
                                      into [0.5, 1), in half precision; the power of two travels in fp32
                                      beside the running max and sum.  Error 2^-12 of the row's largest
-                                     element, whatever the magnitude of V (no range limit); half the
-                                     workspace traffic of fp32 rows                                        */
+                                     element, whatever the magnitude of V (the format adds no range limit to
+                                     that of the fp32 accumulator, which holds up to the sum of a row's
+                                     weights times V, the largest weight being 1); half the workspace
+                                     traffic of fp32 rows                                                  */
     TAPER_PARTIAL_F32 = 1         /* the accumulator row divided by its own sum, in fp32                   */
 } taper_partial_format;
 
@@ -317,7 +319,7 @@ TAPER_API int taper_decode_step_attention_simple(taper_ctx *ctx, int n_seqs, con
  * without a pool, then for half the workgroups, a quarter and so on.
  * TAPER_EINVAL with a message naming the sizes when the step needs more than the array holds all the
  * same (plan image above 8 MiB, or image + workspace above 64 MiB: the 64-layer admission-sweep batch at
- * 640 sequences takes 33 MiB), TAPER_EHIP on a host-only context or when the array's address
+ * 640 sequences takes 32 MiB), TAPER_EHIP on a host-only context or when the array's address
  * could not be looked up.
  * All calls on one GPU, from any context, share that GPU's array, which keeps the previous
  * call's contents: a call must not be enqueued before every earlier one on that GPU has been
