@@ -507,7 +507,8 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
         int64_t want = tok_priv * pool_pct / 100;
         while (want >= kPrivateBlockTokens && !priv.empty()) {
             Segment& s = priv.back();
-            if (s.n_tokens <= want + kPrivateBlockTokens) {  // the whole segment
+            const bool last = shared.empty() && priv.size() == 1;  // (a launch has a workgroup per share: one stays)
+            if (s.n_tokens <= want + kPrivateBlockTokens && !last) {  // the whole segment
                 want -= s.n_tokens;
                 cost_total -= cost_priv.fixed + s.n_tokens + (s.ends_seq ? cost_priv.merge : 0);
                 pool.push_back(s);

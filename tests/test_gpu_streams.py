@@ -130,3 +130,15 @@ def test_a_pool_that_starts_anywhere(shape, elements):
     assert not whole[:elements].any() and not whole[elements + out.numel():].any()
     plan.free()
     ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens,pct", [([40], 90), ([100], 70), ([100, 100], 90), ([64] * 5, 90), ([3000], 90)])
+def test_steps_whose_pool_would_take_everything(lens, pct):
+    sh = AttnShape(64, 8, 128, 16)
+    b = fill_values_numpy(structure_custom(sh, [(n, [0]) for n in lens], seed=611))
+    ctx = context(sh)
+    got, _, _ = run_gpu(ctx, b, pool_pct=pct)
+    ref, _ = run_oracle(b)
+    assert_parity(got, ref, f"{lens} {pct} %")
+    ctx.close()

@@ -110,6 +110,19 @@ def test_a_short_prefix_is_not_cut_into_more_items_than_it_has_blocks():
     ctx.close()
 
 
+@pytest.mark.parametrize("lens,pct", [([40], 90), ([60], 60), ([100], 70), ([100, 100], 90), ([64] * 5, 90), ([33], 90)])
+def test_a_pool_never_takes_everything(lens, pct):
+    """A launch has a workgroup per share: a step whose tokens all lie in the pool would have none, and no results."""
+    st = structure_custom(QWEN, [(n, [0]) for n in lens], seed=4)
+    keep = list(range(len(lens)))
+    seg = reduce_structure(st, z_len=[0] * len(lens), seed=1, keep_parallel=keep)
+    ctx = Context(64, 8, 128, device=-1)
+    e = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, pool_pct=pct).export()
+    assert e["n_parts_shared"] + e["n_parts_private"] >= 1
+    check_plan(QWEN, seg, dict(pool_pct=pct))
+    ctx.close()
+
+
 def check_plan(shape, seg, opts):
     g = shape.gqa
     ctx = Context(shape.n_q_heads, shape.n_kv_heads, shape.head_dim, device=-1)
