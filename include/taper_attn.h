@@ -161,9 +161,9 @@ typedef struct {
                                       query heads per KV head; head_dim 64: 8 row tiles); wider
                                       requests are cut into equal sub-groups of at most this
                                       size; at most 12 row tiles                               */
-    int32_t shared_cost_pct;   /* 0 = default (80 for items of up to 4 row tiles, 120 for wider ones, 110 for
-                                  wider sub-groups of one request; 180 when the step has fewer than
-                                  350 tokens per share): cost of a shared-prefix token relative to a
+    int32_t shared_cost_pct;   /* 0 = default (80 for items of up to 4 row tiles, 120 for wider ones; for
+                                  wider sub-groups of one request 160, or 110 from 2000 tokens per share
+                                  on; 180 when the step has fewer than 350 tokens per share): cost of a shared-prefix token relative to a
                                   private one when cutting the work into equal shares           */
     int32_t shared_item_cost;  /* 0 = default (450; below 350 tokens per share 60 and 32 per branch): fixed
                                   cost of a shared-prefix item, in private tokens' streaming

@@ -462,11 +462,14 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     // longer keeps up with its slice of a saturated memory system.  (80 / 100 / 120 / 140 %, 8 requests of 2048 to 8192 tokens
     // beside 16 serial ones, us: 4 branches, 2 tiles, 76.0 / 76.5 / 76.3 / 77.1; 10, 5 tiles, 101.7 / 95.0 / 94.0 / 94.6; 18, 9 tiles,
     // 130.5 / 116.9 / 114.9 / 114.8; 24, 12 tiles, 159 / 138 / 134 / 135.)  Sub-groups of one request find part of their tokens in the L2
-    // (64 branches, 11 tiles: 270 at 80 to 110 %, 275 at 120; 48, 12 tiles: 221 / 216 / 217 / 218).
+    // (64 branches, 11 tiles: 270 at 80 to 110 %, 275 at 120; 48, 12 tiles: 221 / 216 / 217 / 218), but a request has all its
+    // sub-groups' items end at once, which short shares do not even out (110 / 120 / 140 / 160 / 180 %, 5 such requests beside 48 serial
+    // ones: 40 branches, 1269 tokens per share, 82.8 / 75.2 / 75.3 / 75.7 / 76.6; 60, 837, 72.5 / 63.9 / 63.9 / 65.2 / 66.3; 60, 1340, 89.3 /
+    // 89.7 / 89.3 / 85.9 / 84.2; 60, 2011, 116 / 116 / 112 / 112 / 112; 60, 2683, 140.5 / 140.4 / 142.9 / 143.8 / 143.8).
     auto shared_pct = [&](const Segment& s, bool sub_group) -> int32_t {
         if (opts && opts->shared_cost_pct > 0) return opts->shared_cost_pct;
         if (latency_bound) return 180;
-        return s.n_branch * g <= 4 * 16 ? 80 : sub_group ? 110 : 120;
+        return s.n_branch * g <= 4 * 16 ? 80 : !sub_group ? 120 : p.long_shares ? 110 : 160;
     };
     for (size_t i = 0; i < shared.size(); ++i) {
         Segment& s = shared[i];  // (the sub-groups of a request follow each other: same pages, another first sequence)

@@ -266,6 +266,17 @@ def test_a_shared_token_weighs_more_in_items_of_more_row_tiles(head_shape, width
     ctx.close()
 
 
+@pytest.mark.parametrize("width,pct", [(8, 80), (24, 120), (25, 160), (60, 160)])
+def test_a_shared_token_of_sub_groups_weighs_more_in_short_shares(width, pct):
+    st = structure_custom(QWEN, [(700, [0])] * 48 + [(1200 + 100 * i, [100] * width) for i in range(5)], seed=6)
+    ctx = Context(64, 8, 128, device=-1)
+    assert 350 <= (st.unique_tokens + 7000 * (width > 24)) // 64 < 2000
+    a, b = (ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, **kw).export()
+            for kw in ({}, dict(shared_cost_pct=pct)))
+    assert np.array_equal(a["items"], b["items"]) and np.array_equal(a["part_start"], b["part_start"])
+    ctx.close()
+
+
 @pytest.mark.parametrize("seed", range(4))
 def test_pool_items_stay_within_their_default_size(seed):
     """A quarter of a share, between 512 and 1536 tokens, also where a quarter of a share is more."""
