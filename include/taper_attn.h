@@ -150,6 +150,8 @@ typedef struct {
     int32_t workspace_id;   /* which of the context's workspaces the plan is bound to (counts from 1 in
                                order of creation); it never changes while the plan lives          */
     int64_t workspace_rows; /* partial rows that workspace holds                                  */
+    int32_t merge_launch;   /* 1: the step's merges are a second kernel launch behind the attention's (many
+                               partials per sequence); 0: made inside the attention launch         */
 } taper_plan_view;
 
 typedef struct {
@@ -356,7 +358,7 @@ TAPER_API int taper_step_latency_probe(taper_ctx *ctx, const taper_plan *plan, i
                              void *hip_stream, taper_probe_result *result /* host */);
 
 /*
- * Duration of the decode kernel (the one launch a layer's attention consists of:
+ * Duration of a layer's attention (the decode kernel, and the merge launch behind it where the step has one:
  * shared-prefix work, private work and the merge of partials) measured with HIP
  * events on `hip_stream` (synchronises).  us[0] = mean, us[1] = minimum over
  * `iters` launches after `warmup`.

@@ -59,7 +59,7 @@ class taper_plan_view(ctypes.Structure):
                 ("merge_start", _I32P), ("merge", ctypes.POINTER(taper_merge_entry)),
                 ("n_partial_rows", ctypes.c_int64), ("tokens_unique", ctypes.c_int64),
                 ("tokens_logical", ctypes.c_int64), ("workspace_id", ctypes.c_int32),
-                ("workspace_rows", ctypes.c_int64)]
+                ("workspace_rows", ctypes.c_int64), ("merge_launch", ctypes.c_int32)]
 
 
 class taper_plan_options(ctypes.Structure):
@@ -272,7 +272,7 @@ class Plan:
                     part_start=arr(v.part_start, n_parts + 1), merge_start=arr(v.merge_start, S + 1), merge=merge,
                     n_partial_rows=int(v.n_partial_rows), tokens_unique=int(v.tokens_unique),
                     tokens_logical=int(v.tokens_logical), workspace_id=int(v.workspace_id),
-                    workspace_rows=int(v.workspace_rows))
+                    workspace_rows=int(v.workspace_rows), merge_launch=int(v.merge_launch))
 
     def resolve_slots_host(self, stride: int) -> np.ndarray:
         S = self.export()["n_seqs"]

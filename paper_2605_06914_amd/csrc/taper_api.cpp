@@ -308,6 +308,7 @@ taper::StepArgs make_args(const taper_ctx* ctx, const taper::HostPlan& h, const 
     a.n_parts_private = h.n_parts_private;
     a.max_row_tiles_shared = h.max_row_tiles_shared;
     a.long_shares = h.long_shares;
+    a.merge_after = h.merge_after;
     a.scale_log2e = ctx->cfg.scale * 1.4426950408889634f;
     a.partial_format = ctx->cfg.partial_format;
 #ifdef TAPER_WG_TRACE
@@ -619,6 +620,7 @@ int taper_plan_export(const taper_plan* plan, taper_plan_view* v) {
     v->part_start = h.part_start.data();
     v->merge_start = h.merge_start.data();
     v->merge = h.merge.data();
+    v->merge_launch = h.merge_after;
     v->n_partial_rows = h.n_partial_rows;
     v->tokens_unique = h.tokens_unique;
     v->tokens_logical = h.tokens_logical;

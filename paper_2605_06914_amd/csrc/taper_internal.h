@@ -39,6 +39,7 @@ struct StepArgs {
     int32_t max_row_tiles_shared;
     int32_t long_shares;       // shares long enough for private work to hold back beside shared-prefix work (see private_item)
     float scale_log2e;         // scale * log2(e)
+    int32_t merge_after;       // the merges are a launch of their own behind the attention launch (see merge_kernel)
     int32_t partial_format;    // taper_partial_format of ws_o
 #ifdef TAPER_WG_TRACE
     long long* trace;          // [4 * workgroups] clocks of a trace build (see wg_trace.py), or null

@@ -594,7 +594,7 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
             partial_store4<PF>(a.ws_o, slot * D + 4 * d4, row);
             if (d4 == 0) stats_store<PF>(a.ws_ml + slot, M, L, sc.x);
         }
-        if (sole) {
+        if (sole || a.merge_after) {
             __syncthreads();  // the combine buffers are free for the next item
             return;
         }
@@ -929,6 +929,10 @@ DEV void shared_path(const StepArgs& a, const int part, const int hk, SharedSmem
         else if (NTW >= 2 && n_act == 2) shared_stream<D, NTW >= 2 ? 2 : 1, PF, ANY>(a, item, hk, sm, tid, wave);
         else if (n_act == 1) shared_stream<D, 1, PF, ANY>(a, item, hk, sm, tid, wave);
         else shared_stream<D, 0, PF, ANY>(a, item, hk, sm, tid, wave);
+        if (a.merge_after) {
+            __syncthreads();  // the ring is free for the next item
+            continue;
+        }
         // publish the partials; merge every branch whose set is now complete
         stores_done();
         __syncthreads();
@@ -993,6 +997,90 @@ template <int D, int PF>
 __global__ __launch_bounds__(256, 2) void any_start_kernel(StepArgs a) {
     __shared__ __attribute__((aligned(16))) char smem_raw[sizeof(StepSmem<D>)];
     run_share<D, 3, PF, false, true>(a, smem_raw);
+}
+
+// ---------------------------------------------------------------------------
+// The merges of a step as a launch behind the attention launch: workgroup (sequence, kv head), a wave per query head.
+//
+// A sequence's partials are complete when its last item is, and where a step's items all end together the workgroup that is
+// last merges a whole request alone, a few rows at a time: 12 us after 16 us of streaming in the mixed batch on one kv
+// head (36 partials), 37 after 22 for 13 branches of 40 partials.  Here every row has a wave of its own: three dependent trips to memory (the
+// sequence's entry range, the entries, statistics and rows together) for up to 32 partials, whatever their number of rows.
+//
+// Slots of LPR lanes (16 bytes each) hold one partial row; slot i takes entries i, i + SLOTS, ...  Lane k has the statistics of the
+// k-th entry.  The order of the sum follows from the number of entries alone.
+// ---------------------------------------------------------------------------
+template <int CTRL>
+DEV float row_rotate(float v) {
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x120 + CTRL, 0xf, 0xf, true));
+}
+DEV float wave_max(float v) {
+    v = fmaxf(v, row_rotate<8>(v));
+    v = fmaxf(v, row_rotate<4>(v));
+    v = fmaxf(v, row_rotate<2>(v));
+    return max_lane_groups(fmaxf(v, row_rotate<1>(v)));
+}
+DEV float wave_sum(float v) {
+    v += row_rotate<8>(v);
+    v += row_rotate<4>(v);
+    v += row_rotate<2>(v);
+    return sum_lane_groups(v + row_rotate<1>(v));
+}
+template <int D, int PF>
+__global__ __launch_bounds__(1024) void merge_kernel(StepArgs a) {
+    typedef PartialVec<PF> Vec;
+    typedef typename Vec::type vec;
+    constexpr int LPR = D / Vec::N, SLOTS = 64 / LPR, ROW_BYTES = LPR * 16, T = 32 / SLOTS;
+    const int lane = threadIdx.x & 63, j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int s = blockIdx.x / a.n_kv_heads, hk = blockIdx.x % a.n_kv_heads;
+    typedef const __attribute__((address_space(4))) int32_t* scalar_row;
+    const int e0 = ((scalar_row)a.merge_start)[s], e1 = ((scalar_row)a.merge_start)[s + 1];
+    const int slot = lane / LPR, col = lane % LPR;
+    const auto rows = partial_buffer(a.ws_o), stats = partial_buffer(a.ws_ml);
+    float M = -INFINITY, L = 0.f;
+    vec acc = (vec)(0.f);
+    for (int c = e0; c < e1; c += 64) {
+        const bool real = c + lane < e1;
+        const taper_merge_entry me = a.merge[real ? c + lane : e0];
+        // (a single private item is its sequence's whole context and wrote the result)
+        if (e1 - e0 == 1 && __builtin_amdgcn_readfirstlane(me.rows_per_head) == a.gqa) return;
+        const int row = real ? me.first_row + hk * me.rows_per_head + j : -1;
+        const u32x4 st = coherent_load16(stats, real ? (unsigned)row * 16 : kNoLoad);
+        u32x4 o[T];
+        auto fetch = [&](const int t0) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int r = __shfl(row, (t0 + t) * SLOTS + slot);
+                o[t] = coherent_load16(rows, r >= 0 ? (unsigned)r * ROW_BYTES + 16 * col : kNoLoad);
+            }
+        };
+        fetch(0);
+        const float m = real ? __uint_as_float(st[0]) : -INFINITY;
+        const float mn = fmaxf(M, wave_max(m)), keep = fast_exp2(M - mn);  // first entries: exp2(-inf) = 0
+        const float w = fast_exp2(m - mn) * __uint_as_float(st[1]);       // (the row was stored divided by its sum)
+        const float ws = PF == PF_F16S ? w * __uint_as_float(st[2]) : w;
+        L = L * keep + wave_sum(w);
+        acc *= keep;
+        M = mn;
+        auto add = [&](const int t0) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc += __shfl(ws, (t0 + t) * SLOTS + slot) * Vec::unpack(o[t]);
+        };
+        add(0);
+        if (e1 - c > 32) {
+            fetch(T);
+            add(T);
+        }
+    }
+#pragma unroll
+    for (int o = LPR; o < 64; o *= 2)
+#pragma unroll
+        for (int i = 0; i < Vec::N; ++i) acc[i] += __shfl_xor(acc[i], o);
+    if (slot == 0) {
+        const int64_t h = (int64_t)s * a.n_q_heads + hk * a.gqa + j;
+        *(typename Vec::out_type*)((__bf16*)a.out + h * D + Vec::N * col) = __builtin_convertvector(acc * (1.0f / L), typename Vec::out_type);
+        if (a.lse && col == 0) a.lse[h] = (M + __log2f(L)) * 0.6931471805599453f;
+    }
 }
 
 // Physical slot of every logical position, from the device copy of the plan.
@@ -1092,6 +1180,7 @@ static hipError_t launch_decode_as(const StepArgs& a, const dim3 grid, const int
     else if (ntw <= 1) hipLaunchKernelGGL((decode_kernel<D, 1, PF, false>), grid, block, 0, s, a);
     else if (ntw == 2) hipLaunchKernelGGL((decode_kernel<D, 2, PF, false>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((decode_kernel<D, 3, PF, false>), grid, block, 0, s, a);
+    if (a.merge_after) hipLaunchKernelGGL((merge_kernel<D, PF>), dim3(a.n_seqs * a.n_kv_heads), dim3(64 * a.gqa), 0, s, a);
     return hipGetLastError();
 }
 

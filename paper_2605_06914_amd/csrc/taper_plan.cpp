@@ -53,7 +53,7 @@ namespace {
 
 constexpr int64_t kPieceCostTokens = 200;   // what one more piece of a cut sequence costs, in tokens' streaming time
 constexpr int64_t kOnePerUnitLossPct = 3;   // what one workgroup per compute unit instead of two costs, percent
-constexpr double kTokensPerMergedRow = 4.0;      // see least_tokens
+constexpr double kTokensPerMergedRow = 5.0;      // see least_tokens
 constexpr int64_t kSaturatingShareTokens = 350;  // shares of fewer tokens are over before the memory system is saturated
 constexpr int64_t kLongShareTokens = 2000;       // from here on private work holds back beside shared-prefix work (see private_item in the kernels)
 
@@ -135,12 +135,13 @@ int partition_fill(const std::vector<Segment>& segs, int64_t quota, int blk, con
     return fill > 0 ? part + 1 : part;
 }
 
-// A prefix of n tokens cut into k items takes n / k tokens' time to stream and k times its R query rows to merge, and one
-// workgroup merges them all: the last to arrive, as a rule, for every branch of the request.  The sum is least at some
-// k * k = kTokensPerMergedRow * n / R.  A token costs a shared workgroup alone 20 ns, a row and item 7 ns (5 branches x 16 heads: 109 us
-// for 195 items), which would make the constant 2.9; the sum is flat there, and measured 4 is the better choice: 24000 tokens of 2 /
-// 5 / 12 branches on one kv head of 16 query heads 33 / 46.5 / 81 us (2.9: 32 / 49 / 85; 8: 38 / 48 / 83), 8 requests of 12 branches
-// 57 (60; 58).
+// A prefix of n tokens cut into k items takes n / k tokens' time to stream and k times its R query rows to merge.  The sum is least at
+// some k * k = kTokensPerMergedRow * n / R.  Where one workgroup makes the merges (the last to arrive, for every branch of the
+// request), a token costs a shared workgroup alone 20 ns, a row and item 7 ns (5 branches x 16 heads: 109 us for 195 items), and 4
+// was the best constant (24000 tokens of 2 / 5 / 12 branches on one kv head of 16 query heads 33 / 46.5 / 81 us; 2.9: 32 / 49 / 85; 8: 38 /
+// 48 / 83).  A step of many items has its merges in a launch of their own, where a row is cheaper: with 5 instead of 4 the mixed
+// batch on one kv head takes 20.3 instead of 21.0, 13 branches x 8 heads of 25000 tokens 29.6 / 31.4, 13 x 16 of 4900 25.2 / 27.6; 8 would
+// give another 2 to 12 % to requests of ten branches and take 4 % from narrow ones.
 int64_t least_tokens(const Segment& s, int gqa) {
     return (int64_t)std::sqrt((double)s.n_tokens * s.n_branch * gqa / kTokensPerMergedRow);
 }
@@ -232,6 +233,27 @@ int partition_even(const std::vector<Segment>& segs, int gqa, int64_t quota, int
     }
     close();
     return part;
+}
+
+// Whether the step's merges are a launch of their own (merge_kernel) instead of being made by whoever delivers a sequence's last
+// partial.  What counts is the longest merge that one workgroup would make alone at the end: a shared item's branches side by
+// side, eight at a time, 8 rows each, in rounds of 8 entries (4 of fp32 rows); such a round is 1.3 to 1.7 us.  The launch costs 2 to 3 us, its
+// boundary and three trips to memory, and the merged rows' way through the caches, about 3 MB per us.  Measured on 180 random steps, with / without, us:
+// 5 rounds and more 21.7 / 29.1 (mixed batch on one kv head), 61 / 80, 49.6 / 73, 31.6 / 63.5, none slower by more than 1 %; 3 and 4 rounds in steps
+// that end all at once (below 350 tokens per share) 15.7 / 21.0, 16.6 / 27.8, 17.8 / 24.2; in longer ones, where most merges are hidden behind
+// other workgroups' streaming, 41 / 36, 203 / 195, 176 / 168, 292 / 278 (64 branches); 1 and 2 rounds 2 to 3 us slower as a rule.
+bool merges_after(const taper_attn_config& cfg, const HostPlan& p, bool ends_at_once) {
+    const int g = cfg.n_q_heads / cfg.n_kv_heads, per_round = cfg.partial_format == TAPER_PARTIAL_F32 ? 4 : 8;
+    int64_t rounds = 0, rows = 0;
+    for (int s = 0; s < p.n_seqs; ++s) rows += (int64_t)(p.merge_start[s + 1] - p.merge_start[s]) * cfg.n_q_heads;
+    for (const taper_work_item& it : p.items) {
+        int most = 0;
+        for (int s = it.seq0; s < it.seq0 + it.n_branch; ++s) most = std::max(most, p.merge_start[s + 1] - p.merge_start[s]);
+        const int turns = it.kind != 0 ? 1 : (it.n_branch <= 4 ? 1 : (it.n_branch + 7) / 8) * ((g + 7) / 8);
+        rounds = std::max<int64_t>(rounds, (int64_t)turns * ((most + per_round - 1) / per_round));
+    }
+    const int64_t bytes = rows * cfg.head_dim * (cfg.partial_format == TAPER_PARTIAL_F32 ? 4 : 2);
+    return rounds >= (ends_at_once ? 3 : 5) && rounds * 3 > 6 + bytes / 2500000;  // (in units of half a us)
 }
 
 // Workgroup w of share q works on kv head (w + turn[q]) mod n_kv_heads.  Workgroups are dealt to the XCDs in turn, and the
@@ -598,6 +620,7 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
         p.merge_start[s + 1] = p.merge_start[s] + (int32_t)per_seq[s].size();
         p.merge.insert(p.merge.end(), per_seq[s].begin(), per_seq[s].end());
     }
+    p.merge_after = merges_after(cfg, p, latency_bound);
     for (taper_work_item& it : p.items) {
         it.merge0 = p.merge_start[it.seq0];
         // a private item that is its sequence's whole context needs no partial rows: the kernel writes the result

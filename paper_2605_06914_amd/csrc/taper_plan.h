@@ -30,6 +30,7 @@ struct HostPlan {
     std::vector<taper_merge_entry> merge;
     int64_t n_partial_rows = 0;
     int64_t tokens_unique = 0, tokens_logical = 0;
+    int merge_after = 0;           // merges as a launch of their own
     int long_shares = 0;           // shares of at least kLongShareTokens
     int max_row_tiles_shared = 0;  // over shared items: ceil(n_branch * gqa / 16)
 };

@@ -1,0 +1,63 @@
+"""The merges as a launch behind the attention launch: partials per sequence at the edges of what a wave takes at once (32 in
+flight, 64 per pass), head counts that do not fill a workgroup, a branch whose only partial is its prefix's, sequences
+that are one item and must stay as their item wrote them."""
+import numpy as np
+import pytest
+
+from taper_inputs import AttnShape, fill_values_numpy, structure_custom
+from tests.gpu_util import assert_parity, run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+FINE = dict(target_workgroups=4096, min_share_tokens=1, private_item_cost=1, solo_item_tokens=-1, pool_pct=-1)
+
+
+@pytest.mark.parametrize("partial_format", ["f16_scaled", "f32"])
+@pytest.mark.parametrize("shape", [(6, 2, 128), (16, 1, 128), (8, 8, 64), (32, 4, 64)])
+def test_merge_launch_at_its_edges(shape, partial_format):
+    from paper_2605_06914_amd import Context
+
+    sh = AttnShape(*shape, 16)
+    # private sequences of 1 ... 70 blocks of 32 tokens (64 with some heads), shared prefixes of one item and of several
+    reqs = [(32 * k, [0]) for k in (1, 2, 31, 32, 33, 63, 64, 65, 70)] + [(16, [0, 0, 5]), (640, [0, 40, 0]), (33, [90, 0])]
+    b = fill_values_numpy(structure_custom(sh, reqs, seed=611))
+    st = b.structure
+    ctx = Context(*shape, device=0, partial_format=partial_format)
+    e = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, **FINE).export()
+    counts = np.diff(e["merge_start"])
+    print("[merge launch]", shape, "partials per sequence:", counts.tolist(), flush=True)
+    assert e["merge_launch"] == 1 and counts.max() > 64 and counts.min() == 1 and ((counts > 32) & (counts < 64)).any()
+    ref, ref_lse = run_oracle(b)
+    got, lse, bits = run_gpu(ctx, b, **FINE)
+    assert_parity(got, ref, f"merge launch {shape} {partial_format}")
+    # (fp32 sums of at most 2240 terms: some 1e-5 of a value near 8, scores rounded in fp32 alike)
+    assert np.abs(lse - ref_lse).max() <= 1e-3
+    for _ in range(3):
+        assert np.array_equal(run_gpu(ctx, b, **FINE)[2], bits)
+    ctx.close()
+
+
+def test_merge_launch_gives_what_merges_inside_the_launch_give():
+    """The same cuts merged both ways, which only the order of a few fp32 sums tells apart: results agree to one bf16 step."""
+    from paper_2605_06914_amd import Context
+
+    sh = AttnShape(16, 2, 128, 16)
+    many, few = [(4096, [0])], [(256, [0])]
+    kw = dict(FINE, min_share_tokens=128)
+    b = fill_values_numpy(structure_custom(sh, few * 3 + many, seed=5))
+    st = b.structure
+    ctx = Context(16, 2, 128, device=0)
+    plan = lambda s: ctx.plan_build(s.block_table, s.branch_group, s.prefix_len, s.suffix_len, s.n_pool_pages, **kw).export()
+    assert plan(st)["merge_launch"] == 1
+    alone = structure_custom(sh, few * 3, seed=5)
+    assert plan(alone)["merge_launch"] == 0 and np.diff(plan(alone)["merge_start"]).max() > 1
+    got, _, _ = run_gpu(ctx, b, **kw)
+    ba = fill_values_numpy(alone)
+    ba.q[:] = b.q[:3]
+    kv = b.kv.reshape(st.n_pool_pages, -1)
+    to = ba.kv.reshape(alone.n_pool_pages, -1)
+    for s in range(3):
+        to[alone.block_table[s, :16]] = kv[st.block_table[s, :16]]
+    inside, _, _ = run_gpu(ctx, ba, **kw)
+    assert np.abs(got[:3] - inside).max() <= 2.0 ** -8 * np.abs(inside).max()
+    ctx.close()
