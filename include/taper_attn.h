@@ -115,7 +115,7 @@ typedef struct {
                           = part_base + hk * n_branch * gqa + b * gqa + j           */
     int32_t kind;      /* 0 = shared prefix of a parallel request, 1 = private, 2 = private
                           and the sequence's only item (result written directly, no partial),
-                          3 = like 2 and run by a single wave (runs of short sequences)      */
+                          3 = like 2 and run by a single wave (short sequences)              */
     int32_t part;      /* workgroup share this item belongs to; n_parts for pool items */
     int32_t merge0;    /* merge_start[seq0]: where the merge entries of the item's sequences begin */
 } taper_work_item;
@@ -175,9 +175,11 @@ typedef struct {
     int32_t private_merge_cost; /* 0 = default (192 when the step has shared-prefix work, else none),
                                   -1 = none: extra cost of the private item that ends a sequence
                                   (as a rule it delivers the last partial and merges)           */
-    int32_t solo_item_tokens;  /* 0 = default (512), -1 = never: sequences that are one item of at most this
-                                  many tokens are run by single waves, four side by side, where a share
-                                  holds at least 4 of them in a row                               */
+    int32_t solo_item_tokens;  /* 0 = default (512), -1 = never: private items of at most this many tokens
+                                  are run by single waves, four side by side, where a share holds at
+                                  least 4 of them (2 or 3: of at most 256 tokens; one: of at most 32);
+                                  pieces of a sequence with other items too only in steps of at most
+                                  700 tokens per share                                            */
     int32_t min_share_tokens;  /* a small step is cut into fewer shares than target_workgroups allows
                                   rather than into shares below this size.  0 = default: 256, or 1/16
                                   of the longest private segment if that is more (keeps the partials

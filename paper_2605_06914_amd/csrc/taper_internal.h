@@ -5,6 +5,7 @@
 #include <cstdint>
 
 #include "taper_attn.h"
+#include "taper_plan.h"
 
 namespace taper {
 
@@ -17,7 +18,7 @@ struct StepArgs {
     const int32_t* bt;         // [S][bt_stride]
     const taper_work_item* items;
     const int32_t* part_start;
-    const int32_t* part_turn;  // [n_parts] kv head of a share's first workgroup
+    const int32_t* part_turn;  // [n_parts] kv head of a share's first workgroup, and the share's solo items (kPart... in taper_plan.h)
     const int32_t* merge_start;
     const taper_merge_entry* merge;
     const int32_t* prefix_len;

@@ -409,14 +409,16 @@ struct PrivateSmem {
     float o[4][16][D + 4];
     float2 ml[4][16];
     int last;
-    int pick;  // pool item a workgroup has taken
+    int pick;      // pool item a workgroup has taken
+    int todo[64];  // sequences whose last partial a run of solo items delivered
+    int n_todo;
     MergeMeta meta;
 };
 
 // One private item: a chunk of one sequence's own tokens, for kv head hk.
-// SOLO: the item is run by the calling wave alone (short sequences that are a single item:
-// four of them proceed side by side in a workgroup, with no barrier and no LDS); otherwise the
-// four waves of the workgroup share the item's blocks.
+// SOLO: the item is run by the calling wave alone (short items: four of them proceed side by side in a workgroup, with no
+// barrier and no LDS), which stores its result or its partial rows; otherwise the four waves of the workgroup share the item's
+// blocks.
 // Bound by HBM: 128 requests of 4096 tokens take 321 us, a bare read of the same pages 310.  The depth of the pipeline is
 // not what matters then (one set of registers refilled as it is used up, two, and two with the block after next
 // already asked for all measure within 0.5 %); two sets win where a wave has two blocks and the machine is idle
@@ -430,7 +432,7 @@ struct PrivateSmem {
 // counts: 155 tokens per share 18.5 / 17.2, 577 31.5 / 30.4, 57 12.7 / 12.1, with 2 to 3 % the other way at others.  At
 // head_dim 64 a block holds half the bytes and the wait weighs more (mixed batch 46.3 / 45.4).
 template <int D, bool SOLO, int PF, bool HOLD>
-DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem<D>& sm) {
+DEV void private_item(const StepArgs& a, const int it, const int hk, const int after, PrivateSmem<D>& sm) {
     constexpr int KS = D / 32, DT = D / 16, TILE = 16 * D;
     auto& sm_o = sm.o;
     auto& sm_ml = sm.ml;
@@ -446,9 +448,9 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
         const int n_tok = item.n_tokens;
         const int n_pages = (n_tok + 15) >> 4;
         const int n_blocks = (n_tok + 31) >> 5;
-        const bool sole = SOLO || item.kind >= 2;  // the sequence's whole context: no partial, no arrival, no merge
+        const bool sole = item.kind >= 2;  // the sequence's whole context: no partial, no arrival, no merge
         MetaRegs mr = {};
-        if (!sole) mr = meta_load(a, item, threadIdx.x);
+        if (!SOLO && !sole) mr = meta_load(a, item, threadIdx.x);
 
         bf16x8 qf[KS];  // (lane columns past the last query head repeat the first; not stored)
         {
@@ -536,15 +538,34 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
             compute_block(b, r0, std::true_type{});
         }
 
-        if constexpr (SOLO) {  // this wave holds the whole result: normalise and write it
+        if constexpr (SOLO) {  // this wave holds the whole state of the item's rows
             l = sum_lane_groups(l);
-            if (n < g) {
-                const int h = hk * g + n;
-                const float inv = 1.0f / l;
-                __bf16* orow = (__bf16*)a.out + ((int64_t)item.seq0 * a.n_q_heads + h) * D;
+            const float inv = 1.0f / l;
+            const int h = hk * g + n;
+            float2 sc = make_float2(1.f, 1.f);
+            if (PF == PF_F16S && !sole) {
+                float mx = 0.f;
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt) *(bf16x4*)(orow + 16 * dt + 4 * qd) = __builtin_convertvector(O[dt] * inv, bf16x4);
-                if (a.lse && qd == 0) a.lse[(int64_t)item.seq0 * a.n_q_heads + h] = (m + __log2f(l)) * 0.6931471805599453f;
+                for (int dt = 0; dt < DT; ++dt) mx = fmaxf(mx, maxabs4(O[dt]));
+                sc = row_scale(max_lane_groups(mx) * inv);
+            }
+            if (n < g) {
+                __bf16* orow = (__bf16*)a.out + ((int64_t)item.seq0 * a.n_q_heads + h) * D;
+                const int64_t slot = (int64_t)item.part_base + h;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) {
+                    f32x4 v = O[dt] * inv;
+                    if (sole) {
+                        *(bf16x4*)(orow + 16 * dt + 4 * qd) = __builtin_convertvector(v, bf16x4);
+                    } else {
+                        if constexpr (PF == PF_F16S) v *= sc.y;
+                        partial_store4<PF>(a.ws_o, slot * D + 16 * dt + 4 * qd, v);
+                    }
+                }
+                if (qd == 0) {
+                    if (!sole) stats_store<PF>(a.ws_ml + slot, m, l, sc.x);
+                    else if (a.lse) a.lse[(int64_t)item.seq0 * a.n_q_heads + h] = (m + __log2f(l)) * 0.6931471805599453f;
+                }
             }
             return;
         }
@@ -594,7 +615,7 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
             partial_store4<PF>(a.ws_o, slot * D + 4 * d4, row);
             if (d4 == 0) stats_store<PF>(a.ws_ml + slot, M, L, sc.x);
         }
-        if (sole || a.merge_after) {
+        if (sole || after) {
             __syncthreads();  // the combine buffers are free for the next item
             return;
         }
@@ -613,13 +634,55 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, PrivateSmem
     }
 }
 
-// The private items of a workgroup: those of its share [it0, it1) in order, then whatever it
+// Solo items [first, end) of a share, dealt to the waves (the plan lists them longest first; taking them as they get free cost tiny steps
+// 0.3 us, a barrier and a counter, and evened out nothing that was seen).  Their partials are announced together; the sequences that are then complete (few: what the other items of a step deliver comes later as a rule) are
+// merged by a wave each.  `announce`: there are partials among them, and merges are made in this launch.
+template <int D, int PF>
+DEV void solo_run(const StepArgs& a, const int first, const int end, const int hk, const bool announce, PrivateSmem<D>& sm) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int k = first + wave; k < end; k += 4) private_item<D, true, PF, false>(a, k, hk, 0, sm);
+    if (!announce) {
+        __syncthreads();
+        return;
+    }
+    stores_done();
+    for (int it = first; it < end; it += 64) {
+        __syncthreads();  // everyone's partial rows are stored; `todo` is free
+        if (threadIdx.x < 64) {
+            const int lane = opaque(threadIdx.x) & 63;
+            bool mine = false;
+            int seq = 0;
+            if (it + lane < end && a.items[it + lane].kind == 1) {
+                seq = a.items[it + lane].seq0;
+                mine = arrive_last(a, seq, hk, a.merge_start[seq + 1] - a.merge_start[seq]);
+            }
+            const unsigned long long mask = __ballot(mine);
+            if (mine) sm.todo[__popcll(mask & ((1ull << lane) - 1))] = seq;
+            if (lane == 0) {
+                sm.n_todo = __popcll(mask);
+                sm.meta.ms[0] = -2 * kMetaWindow;  // (their merge entries are not in the window)
+            }
+        }
+        __syncthreads();
+        for (int i = wave; i < sm.n_todo; i += 4) {
+            const int seq = __builtin_amdgcn_readfirstlane(sm.todo[i]);
+            merge_rows<D, D / PartialVec<PF>::N / 8, PF>(a, sm.meta, seq, hk, a.merge_start[seq], a.merge_start[seq + 1], opaque(threadIdx.x) & 63, 64);
+        }
+    }
+    __syncthreads();
+}
+
+// The private items of a workgroup: its share's solo items [it0, solo_end), the others [solo_end, it1) in order, then whatever it
 // can take from its kv head's pool.  Every workgroup makes exactly one claim past the end of
 // the pool; the one that makes the last of those puts the counter back to zero for the next
 // launch.
 template <int D, int PF, bool HOLD>
-DEV void private_items(const StepArgs& a, int it0, const int it1, const int hk, PrivateSmem<D>& sm) {
+DEV void private_items(const StepArgs& a, int it0, const int solo_end, const bool announce, const int it1, const int hk, const int after, PrivateSmem<D>& sm) {
     const int wgs_per_head = a.n_parts_shared + a.n_parts_private;  // = gridDim.x / n_kv_heads
+    if (it0 < solo_end) {
+        solo_run<D, PF>(a, it0, solo_end, hk, announce, sm);
+        it0 = solo_end;
+    }
 #ifdef TAPER_WG_TRACE
     bool turned = false;
 #endif
@@ -644,16 +707,7 @@ DEV void private_items(const StepArgs& a, int it0, const int it1, const int hk, 
             }
             it = a.pool_first + i;
         }
-        if (load_item(a, it).kind == 3) {  // a run of solo items of this share: dealt to the waves, no barrier inside
-            int end = it + 1;
-            while (end < it1 && load_item(a, end).kind == 3) ++end;
-            const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-            for (int k = it + wave; k < end; k += 4) private_item<D, true, PF, false>(a, k, hk, sm);
-            it0 = end;
-            __syncthreads();
-            continue;
-        }
-        private_item<D, false, PF, HOLD>(a, it, hk, sm);
+        private_item<D, false, PF, HOLD>(a, it, hk, after, sm);
     }
 }
 
@@ -917,7 +971,7 @@ DEV void shared_stream(const StepArgs& a, const taper_work_item& item, const int
 }
 
 template <int D, int NTW, int PF, bool ANY>
-DEV void shared_path(const StepArgs& a, const int part, const int hk, SharedSmem<D>& sm) {
+DEV void shared_path(const StepArgs& a, const int part, const int hk, const int after, SharedSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int it0 = a.part_start[part], it1 = a.part_start[part + 1];
     for (int it = it0; it < it1; ++it) {
@@ -929,7 +983,7 @@ DEV void shared_path(const StepArgs& a, const int part, const int hk, SharedSmem
         else if (NTW >= 2 && n_act == 2) shared_stream<D, NTW >= 2 ? 2 : 1, PF, ANY>(a, item, hk, sm, tid, wave);
         else if (n_act == 1) shared_stream<D, 1, PF, ANY>(a, item, hk, sm, tid, wave);
         else shared_stream<D, 0, PF, ANY>(a, item, hk, sm, tid, wave);
-        if (a.merge_after) {
+        if (after) {
             __syncthreads();  // the ring is free for the next item
             continue;
         }
@@ -961,26 +1015,31 @@ union StepSmem {
 template <int D, int NTW, int PF, bool ALLP, bool ANY>
 DEV void run_share(const StepArgs& a, char* smem_raw) {
     const int part = blockIdx.x / a.n_kv_heads;
-    const int hk = (blockIdx.x + a.part_turn[part]) % a.n_kv_heads;
+    const int turn = a.part_turn[part], hk = (blockIdx.x + (turn & kPartTurnMask)) % a.n_kv_heads;
+    int after = a.merge_after;  // (kept: read from the arguments where it is used it costs a trip at every item's end)
+    asm volatile("" : "+s"(after));
 #ifdef TAPER_WG_TRACE  // trace builds only (wg_trace.py): per-workgroup clocks -- start, own share done, left, time in merges
     long long* trace = a.trace;
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x] = wall_clock64();
 #endif
-    int it0 = 0, it1 = 0;  // private items of this workgroup's share
-    if constexpr (ALLP) {
+    int it0 = 0, it1 = 0, solo_end = 0;  // private items of this workgroup's share: solo ones up to solo_end, then the others
+    auto own_items = [&] {
         it0 = a.part_start[part];
         it1 = a.part_start[part + 1];
+        solo_end = it0 + (turn >> kPartSoloShift);
+    };
+    if constexpr (ALLP) {
+        own_items();
     } else if (part < a.n_parts_shared) {
-        shared_path<D, NTW, PF, ANY>(a, part, hk, *reinterpret_cast<SharedSmem<D>*>(smem_raw));
+        shared_path<D, NTW, PF, ANY>(a, part, hk, after, *reinterpret_cast<SharedSmem<D>*>(smem_raw));
         __syncthreads();
     } else {
-        it0 = a.part_start[part];
-        it1 = a.part_start[part + 1];
+        own_items();
     }
 #ifdef TAPER_WG_TRACE
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x + 1] = wall_clock64();  // shared share done (a private share: overwritten when it is done)
 #endif
-    private_items<D, PF, !ALLP && D == 128>(a, it0, it1, hk, *reinterpret_cast<PrivateSmem<D>*>(smem_raw));
+    private_items<D, PF, !ALLP && D == 128>(a, it0, solo_end, !after && (turn & kPartSoloPartials), it1, hk, after, *reinterpret_cast<PrivateSmem<D>*>(smem_raw));
 #ifdef TAPER_WG_TRACE
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x + 2] = wall_clock64();
 #endif

@@ -54,6 +54,9 @@ namespace {
 constexpr int64_t kPieceCostTokens = 200;   // what one more piece of a cut sequence costs, in tokens' streaming time
 constexpr int64_t kOnePerUnitLossPct = 3;   // what one workgroup per compute unit instead of two costs, percent
 constexpr double kTokensPerMergedRow = 5.0;      // see least_tokens
+constexpr int kBriefTokens = 128;            // private segments that are priced as a single wave's work, in steps of up to
+constexpr int64_t kBriefShareTokens = 700;   // so many tokens per share,
+constexpr int64_t kBriefItemCost = 160;      // at so much (see Cost::brief)
 constexpr int64_t kSaturatingShareTokens = 350;  // shares of fewer tokens are over before the memory system is saturated
 constexpr int64_t kLongShareTokens = 2000;       // from here on private work holds back beside shared-prefix work (see private_item in the kernels)
 
@@ -72,7 +75,18 @@ struct Cost {
     int64_t fixed;
     int64_t merge = 0;  // extra cost of the item that ends a sequence: it arrives last as a rule and merges the partials
     int64_t per_branch = 0;  // further fixed cost for each of a shared item's branches
+    // Short private segments are run by single waves, four side by side (order_solo_items), and merged by whoever comes later: they cost
+    // less than an item of the whole workgroup and no merge, and are not worth a claim from the pool.  In steps of long shares that is not
+    // so: their chain of dependent loads is several times as long on a saturated machine, and whoever finishes early takes them from the
+    // pool (411 sequences of 12 to 22 tokens beside 8 requests of 4 to 6 branches 65 -> 41 us per layer, 30 requests of 14 branches of 1 or 2 tokens 66 -> 43,
+    // 35 requests of 32 tokens and 9 branches of 11 30 -> 21; 100 us per layer where shares have 3600 tokens and 212 short
+    // branches, 110 with this price).
+    int brief_tokens = 0;
+    bool brief(const Segment& s) const { return s.n_tokens <= brief_tokens; }
     int64_t item(const Segment& s) const { return fixed + per_branch * s.n_branch; }
+    int64_t piece(const Segment& s) const { return brief(s) ? kBriefItemCost : fixed; }  // of a private segment
+    // of the item that ends a sequence: nothing where that is its only one, as a rule when it is much shorter than a share
+    int64_t end(const Segment& s, int64_t share) const { return s.ends_seq && !brief(s) && !(brief_tokens && s.whole_seq && s.n_tokens * 4 <= share) ? merge : 0; }
 };
 
 // Cuts `segs` into workgroup shares of about `quota` cost units, at multiples of `blk` tokens
@@ -86,15 +100,16 @@ int partition_fill(const std::vector<Segment>& segs, int64_t quota, int blk, con
     if (total_tokens == 0) return 0;
     quota = std::max<int64_t>(1, quota);
     const int64_t blk_cost = blk;
-    // a piece is only worth an item of its own if its streaming outweighs the item's fixed cost
-    const int64_t min_blocks = std::max<int64_t>(1, (cost.fixed + blk_cost - 1) / blk_cost);
-    const int64_t cap = std::max<int64_t>(1, (quota - cost.fixed) / blk_cost);  // blocks of an item with a share to itself
     int part = 0;
     int64_t fill = 0;
     for (const Segment& s : segs) {
+        const int64_t fixed = cost.piece(s);
+        // a piece is only worth an item of its own if its streaming outweighs the item's fixed cost
+        const int64_t min_blocks = std::max<int64_t>(1, (fixed + blk_cost - 1) / blk_cost);
+        const int64_t cap = std::max<int64_t>(1, (quota - fixed) / blk_cost);  // blocks of an item with a share to itself
         int64_t remaining = (s.n_tokens + blk - 1) / blk, off = 0;  // blocks
         while (remaining > 0) {
-            const int64_t room = (quota - fill - cost.fixed) / blk_cost;  // blocks that still fit this share
+            const int64_t room = (quota - fill - fixed) / blk_cost;  // blocks that still fit this share
             if (fill > 0 && room < remaining && room < min_blocks) {        // start the next share instead
                 ++part;
                 fill = 0;
@@ -122,10 +137,10 @@ int partition_fill(const std::vector<Segment>& segs, int64_t quota, int blk, con
             it.kind = s.kind;
             it.part = part_id0 + part;
             items->push_back(it);
-            fill += cost.fixed + take * blk_cost;
+            fill += fixed + take * blk_cost;
             off += take;
             remaining -= take;
-            if (remaining == 0 && s.ends_seq) fill += cost.merge;
+            if (remaining == 0) fill += cost.end(s, quota);
             if (fill >= quota) {
                 ++part;
                 fill = 0;
@@ -265,11 +280,53 @@ void plan_part_turns(const taper_attn_config& cfg, const int32_t* branch_group, 
     const int n_parts = p->n_parts_shared + p->n_parts_private;
     p->part_turn.resize(n_parts);
     for (int q = 0; q < n_parts; ++q) {
-        p->part_turn[q] = q % cfg.n_kv_heads;
+        p->part_turn[q] = q % std::min(cfg.n_kv_heads, kPartTurnMask + 1);
         if (q == 0 || q >= p->n_parts_shared || p->part_start[q - 1] == p->part_start[q] || p->part_start[q] == p->part_start[q + 1]) continue;
         const taper_work_item &a = p->items[p->part_start[q - 1]], &b = p->items[p->part_start[q]];
         if (a.seq0 != b.seq0 && branch_group[a.seq0] == branch_group[b.seq0] && a.page0 == b.page0 && a.n_tokens == b.n_tokens)
             p->part_turn[q] = p->part_turn[q - 1];
+    }
+}
+
+// Short private items of a share are run by single waves, four side by side, without barriers: a workgroup's four waves get one block
+// each of a 128-token item and nothing of a shorter one, all latency and no streaming, and a share of many of them was a chain of
+// item ends (30 requests of 8 to 11 branches of up to 11 tokens each, 8 items of 3 us one after the other: 30.5 us, 22.6; 9 requests of 34
+// branches of up to 32 tokens 48.6, 27.5; 289 sequences of 2 to 8 tokens 6.9 either way).  They come before the
+// share's other items, longest first, and are dealt to the waves.  An item of one block is a single wave's work in any case; fewer
+// than four longer ones leave waves idle, which costs more than the barriers from 256 tokens on.
+// Partials only in steps of short shares (`partials`): on a saturated machine an item's chain of dependent loads takes several times as long,
+// and a wave has one item at a time (57 shared shares of 3200 tokens beside 69 short branches in 7 private ones: 80 us per layer, 84 to 86).
+void order_solo_items(int n_seqs, int most_tokens, bool partials, HostPlan* p) {
+    if (most_tokens <= 0) return;
+    std::vector<int32_t> pieces;
+    if (!partials) {
+        pieces.assign(n_seqs, 0);
+        for (const taper_work_item& it : p->items)
+            for (int b = 0; b < it.n_branch; ++b) pieces[it.seq0 + b]++;
+    }
+    std::vector<taper_work_item> rest;
+    for (int q = p->n_parts_shared; q < p->n_parts_shared + p->n_parts_private; ++q) {
+        const auto first = p->items.begin() + p->part_start[q], end = p->items.begin() + p->part_start[q + 1];
+        const auto solo = [&](const taper_work_item& it, int limit) { return it.n_tokens <= limit && (partials || pieces[it.seq0] == 1); };
+        int upto[3] = {0, 0, 0};
+        const int limits[3] = {most_tokens, std::min(most_tokens, 256), std::min(most_tokens, kPrivateBlockTokens)};
+        for (auto it = first; it != end; ++it)
+            for (int k = 0; k < 3; ++k) upto[k] += solo(*it, limits[k]);
+        const int k = upto[0] >= 4 ? 0 : upto[1] >= 2 ? 1 : 2;
+        if (upto[k] == 0) continue;
+        if (end - first > 1) {
+            rest.clear();
+            auto to = first;
+            for (auto it = first; it != end; ++it) {
+                if (!solo(*it, limits[k])) rest.push_back(*it);
+                else *to++ = *it;
+            }
+            std::sort(first, to, [](const taper_work_item& x, const taper_work_item& y) {
+                return x.n_tokens != y.n_tokens ? x.n_tokens > y.n_tokens : x.seq0 != y.seq0 ? x.seq0 < y.seq0 : x.page0 < y.page0;
+            });
+            std::copy(rest.begin(), rest.end(), to);
+        }
+        p->part_turn[q] |= (int)std::min<int64_t>(upto[k], (1 << (31 - kPartSoloShift)) - 1) << kPartSoloShift;
     }
 }
 
@@ -502,14 +559,15 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
                               opts && opts->shared_item_cost > 0 ? 0 : (latency_bound ? 32 : 0)};
     const Cost cost_priv = {opts && opts->private_item_cost > 0 ? opts->private_item_cost : (shared.empty() || latency_bound ? 128 : 192),
                             opts && opts->private_merge_cost != 0 ? std::max(0, opts->private_merge_cost)
-                                                                  : (shared.empty() ? 0 : 192)};
+                                                                  : (shared.empty() ? 0 : 192),
+                            0, share_tokens <= kBriefShareTokens ? kBriefTokens : 0};
     const int64_t shared_tail_discount = 3;  // blocks: about what merging a request's branches costs
     int64_t cost_total = 0;
     for (const Segment& s : shared) {
         cost_total += cost_shared.item(s) + (int64_t)s.n_tokens * s.pct / 100;
     }
     for (const Segment& s : priv) {
-        cost_total += cost_priv.fixed + s.n_tokens + (s.ends_seq ? cost_priv.merge : 0);
+        cost_total += cost_priv.piece(s) + s.n_tokens + cost_priv.end(s, share_tokens);
     }
     // ---- the pool: private tokens no share owns.  No cost model predicts the shares' running times
     // to better than some ten percent (the XCDs are not equally fast, page placement matters, and of two workgroups
@@ -530,20 +588,21 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     std::vector<Segment> pool;
     {
         int64_t want = tok_priv * pool_pct / 100;
-        while (want >= kPrivateBlockTokens && !priv.empty()) {
-            Segment& s = priv.back();
+        for (size_t i = priv.size(); i-- > 0 && want >= kPrivateBlockTokens;) {
+            Segment& s = priv[i];
+            if (cost_priv.brief(s) && !(opts && opts->pool_pct > 0)) continue;  // (a claim would cost more than the item)
             const bool last = shared.empty() && priv.size() == 1;  // (a launch has a workgroup per share: one stays)
             if (s.n_tokens <= want + kPrivateBlockTokens && !last) {  // the whole segment
                 want -= s.n_tokens;
-                cost_total -= cost_priv.fixed + s.n_tokens + (s.ends_seq ? cost_priv.merge : 0);
+                cost_total -= cost_priv.piece(s) + s.n_tokens + cost_priv.end(s, share_tokens);
                 pool.push_back(s);
-                priv.pop_back();
+                priv.erase(priv.begin() + i);
             } else {  // its tail, from a block boundary
                 const int keep = (int)((s.n_tokens - want + kPrivateBlockTokens - 1) / kPrivateBlockTokens * kPrivateBlockTokens);
                 if (keep < s.n_tokens) {
                     pool.push_back({s.seq0, s.n_branch, s.page0 + keep / 16, s.n_tokens - keep, s.kind, s.ends_seq, 0});
+                    cost_total -= s.n_tokens - keep + cost_priv.end(s, share_tokens);
                     s.whole_seq = 0;
-                    cost_total -= s.n_tokens - keep + (s.ends_seq ? cost_priv.merge : 0);
                     s.n_tokens = keep;
                     s.ends_seq = 0;
                 }
@@ -595,6 +654,8 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     std::stable_sort(p.items.begin() + p.part_start[n_parts], p.items.end(),
                      [](const taper_work_item& x, const taper_work_item& y) { return x.n_tokens > y.n_tokens; });
 
+    order_solo_items(n_seqs, opts && opts->solo_item_tokens != 0 ? opts->solo_item_tokens : 512, share_tokens <= kBriefShareTokens, &p);
+
     // ---- partial rows and merge map
     std::vector<std::vector<taper_merge_entry>> per_seq(n_seqs);
     int64_t rows = 0;
@@ -626,21 +687,11 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
         // a private item that is its sequence's whole context needs no partial rows: the kernel writes the result
         if (it.kind == 1 && p.merge_start[it.seq0 + 1] - p.merge_start[it.seq0] == 1) it.kind = 2;
     }
-    // Runs of short such items inside one share are worked on by single waves, four items side by side
-    // (a 128-token item gives a wave one block to do when four waves share it: all latency, no streaming).
-    const int solo_tokens = opts && opts->solo_item_tokens != 0 ? opts->solo_item_tokens : 512;
-    const int n_parts_all = p.n_parts_shared + p.n_parts_private;
-    for (int part = p.n_parts_shared; part < n_parts_all && solo_tokens > 0; ++part) {
-        int i = p.part_start[part];
-        const int end = p.part_start[part + 1];
-        while (i < end) {
-            int j = i;
-            while (j < end && p.items[j].kind == 2 && p.items[j].n_tokens <= solo_tokens) ++j;
-            if (j - i >= kSoloMinRun)
-                for (int k = i; k < j; ++k) p.items[k].kind = 3;
-            i = std::max(j, i + 1);
+    for (int q = p.n_parts_shared; q < n_parts; ++q)
+        for (int i = p.part_start[q]; i < p.part_start[q] + (p.part_turn[q] >> kPartSoloShift); ++i) {
+            if (p.items[i].kind == 2) p.items[i].kind = 3;
+            else p.part_turn[q] |= kPartSoloPartials;
         }
-    }
     return TAPER_OK;
 }
 

@@ -11,7 +11,8 @@ namespace taper {
 
 constexpr int kPrivateBlockTokens = 32;  // tokens one wave of the private kernel consumes per iteration
 constexpr int kSharedBlockTokens = 64;   // shared prefixes are cut at multiples of this (the kernel stages 32 tokens per iteration at head_dim 128, 64 at 64)
-constexpr int kSoloMinRun = 4;           // shortest run of short single-item sequences handed to single waves
+// part_turn: turn | whether single waves run partial items of the share | how many of its first items they run << kPartSoloShift
+constexpr int kPartTurnMask = 0xfff, kPartSoloPartials = 0x1000, kPartSoloShift = 13;
 constexpr int kMaxRowTilesPerItem = 12;  // 16-row query tiles one shared-kernel workgroup can hold (4 waves x 3)
 
 struct HostPlan {
@@ -25,7 +26,7 @@ struct HostPlan {
     int n_parts_shared = 0, n_parts_private = 0;
     int n_pool_items = 0;  // items after the shares' items, owned by no share
     std::vector<int32_t> part_start;  // [n_parts + 1]
-    std::vector<int32_t> part_turn;   // [n_parts] which kv head a share's first workgroup takes (see plan_part_turns)
+    std::vector<int32_t> part_turn;   // [n_parts] which kv head a share's first workgroup takes (see plan_part_turns), and its solo items
     std::vector<int32_t> merge_start; // [n_seqs + 1]
     std::vector<taper_merge_entry> merge;
     int64_t n_partial_rows = 0;
