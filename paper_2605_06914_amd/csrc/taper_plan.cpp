@@ -169,7 +169,7 @@ int64_t least_tokens(const Segment& s, int gqa) {
 // `tail_discount` blocks shorter: the workgroup that finishes a shared prefix usually finds the
 // request's branches complete and has to merge them all.
 int partition_even(const std::vector<Segment>& segs, int gqa, int64_t quota, int blk, const Cost cost, int64_t tail_discount,
-                   int part_id0, std::vector<taper_work_item>* items) {
+                   bool crowded, int part_id0, std::vector<taper_work_item>* items) {
     quota = std::max<int64_t>(1, quota);
     int part = 0;
     int64_t fill = 0, blk_cost = 1;
@@ -195,11 +195,15 @@ int partition_even(const std::vector<Segment>& segs, int gqa, int64_t quota, int
         const int64_t min_blocks = std::max<int64_t>(1, (cost.item(s) + blk_cost - 1) / blk_cost);
         // blocks of an item with a share to itself
         const int64_t cap = std::max({min_blocks, (quota - cost.item(s)) / blk_cost, least_tokens(s, gqa) / blk});
-        if (s.siblings >= 2) {
+        if (s.siblings >= 2 && (!crowded || (cost.item(s) + (int64_t)s.n_tokens * s.pct / 100) * 2 >= quota)) {
             // Sub-groups of one request read the same pages.  They get the same cuts, every item a share of its
             // own and therefore the launch's start as its start, in workgroups next to each other: the sub-groups
             // then stream the prefix in step, and what the first one fetched is still in the L2 of the XCD (one
-            // per kv head) when the others ask for it.  Shares that come out short take from the pool.
+            // per kv head) when the others ask for it.  Shares that come out short take from the pool; where the sub-groups
+            // alone would have most of the grid's shares (`crowded`), only items that fill half of one are placed so (26
+            // requests of 33 branches and prefixes of 106 to 421 tokens: 52 shares of one such item each left 12 for 220000 private
+            // tokens, 297 us; 238 this way.  12 requests of 33 branches and 36 to 64 tokens, 36 of 128 shares: 194 with a share each, 204
+            // without; 64 branches 277, and 290 if a whole share were asked for).
             close();
             const int64_t blocks = (s.n_tokens + blk - 1) / blk;
             const int64_t spread = blocks + tail_discount;
@@ -618,9 +622,12 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     const int64_t min_share =
         (opts && opts->min_share_tokens > 0 ? opts->min_share_tokens : std::max<int64_t>(256, longest / 16)) + cost_priv.fixed;
     int64_t quota = std::max<int64_t>(std::max<int64_t>(kSharedBlockTokens, min_share), (cost_total + parts_total - 1) / parts_total);
+    int64_t sub_groups = 0;
+    for (const Segment& s : shared) sub_groups += s.siblings;
+    const bool crowded = sub_groups * 2 > parts_total;
     for (;;) {  // never more shares than asked for: an extra one would run after all the others
         p.items.clear();
-        p.n_parts_shared = partition_even(shared, g, quota, kSharedBlockTokens, cost_shared, shared_tail_discount, 0, &p.items);
+        p.n_parts_shared = partition_even(shared, g, quota, kSharedBlockTokens, cost_shared, shared_tail_discount, crowded, 0, &p.items);
         p.n_parts_private = partition_fill(priv, quota, kPrivateBlockTokens, cost_priv, p.n_parts_shared, &p.items);
         if (p.n_parts_shared + p.n_parts_private <= parts_total || quota >= cost_total * 2 + 4096) break;
         quota += std::max<int64_t>(16, quota / 256);
