@@ -622,16 +622,36 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     const int64_t min_share =
         (opts && opts->min_share_tokens > 0 ? opts->min_share_tokens : std::max<int64_t>(256, longest / 16)) + cost_priv.fixed;
     int64_t quota = std::max<int64_t>(std::max<int64_t>(kSharedBlockTokens, min_share), (cost_total + parts_total - 1) / parts_total);
+    // Never more shares than asked for: an extra one would run after all the others.  The quota is raised by small steps until that is
+    // so: by as many at once as the excess suggests, and halved back between the last one that was too low and the first that is not.
     int64_t sub_groups = 0;
     for (const Segment& s : shared) sub_groups += s.siblings;
     const bool crowded = sub_groups * 2 > parts_total;
-    for (;;) {  // never more shares than asked for: an extra one would run after all the others
+    auto cut = [&](int64_t q) {
         p.items.clear();
-        p.n_parts_shared = partition_even(shared, g, quota, kSharedBlockTokens, cost_shared, shared_tail_discount, crowded, 0, &p.items);
-        p.n_parts_private = partition_fill(priv, quota, kPrivateBlockTokens, cost_priv, p.n_parts_shared, &p.items);
-        if (p.n_parts_shared + p.n_parts_private <= parts_total || quota >= cost_total * 2 + 4096) break;
-        quota += std::max<int64_t>(16, quota / 256);
+        p.n_parts_shared = partition_even(shared, g, q, kSharedBlockTokens, cost_shared, shared_tail_discount, crowded, 0, &p.items);
+        p.n_parts_private = partition_fill(priv, q, kPrivateBlockTokens, cost_priv, p.n_parts_shared, &p.items);
+        return p.n_parts_shared + p.n_parts_private <= parts_total || q >= cost_total * 2 + 4096;
+    };
+    std::vector<int64_t> tried = {quota};  // the steps
+    auto step = [&](size_t i) {
+        while (tried.size() <= i) tried.push_back(tried.back() + std::max<int64_t>(16, tried.back() / 256));
+        return tried[i];
+    };
+    size_t below = 0, at = 0;
+    while (!cut(step(at))) {
+        below = at++;
+        const int64_t enough = tried[below] * (p.n_parts_shared + p.n_parts_private) / parts_total;
+        while (step(at) < enough) ++at;
     }
+    bool current = true;
+    while (at - below > 1) {
+        const size_t mid = (below + at) / 2;
+        current = cut(step(mid));
+        (current ? at : below) = mid;
+    }
+    quota = step(at);
+    if (!current) cut(quota);
     const int n_parts = p.n_parts_shared + p.n_parts_private;
     p.part_start.assign(n_parts + 1, 0);
     for (const taper_work_item& it : p.items) p.part_start[it.part + 1]++;
@@ -664,8 +684,8 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     order_solo_items(n_seqs, opts && opts->solo_item_tokens != 0 ? opts->solo_item_tokens : 512, share_tokens <= kBriefShareTokens, &p);
 
     // ---- partial rows and merge map
-    std::vector<std::vector<taper_merge_entry>> per_seq(n_seqs);
     int64_t rows = 0;
+    p.merge_start.assign(n_seqs + 1, 0);
     for (taper_work_item& it : p.items) {
         if (it.n_tokens < 1) {  // the kernels index pages by an item's last token: never launched
             *err = "internal error: a work item without tokens";
@@ -679,15 +699,15 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
         it.part_base = (int32_t)rows;
         const int rph = it.n_branch * g;
         if (it.kind == 0) p.max_row_tiles_shared = std::max(p.max_row_tiles_shared, (rph + 15) / 16);
-        for (int b = 0; b < it.n_branch; ++b) per_seq[it.seq0 + b].push_back({it.part_base + b * g, rph});
+        for (int b = 0; b < it.n_branch; ++b) p.merge_start[it.seq0 + b + 1]++;
         rows += (int64_t)rph * cfg.n_kv_heads;
     }
     p.n_partial_rows = rows;
-    p.merge_start.assign(n_seqs + 1, 0);
-    for (int s = 0; s < n_seqs; ++s) {
-        p.merge_start[s + 1] = p.merge_start[s] + (int32_t)per_seq[s].size();
-        p.merge.insert(p.merge.end(), per_seq[s].begin(), per_seq[s].end());
-    }
+    for (int s = 0; s < n_seqs; ++s) p.merge_start[s + 1] += p.merge_start[s];
+    p.merge.resize(p.merge_start[n_seqs]);
+    std::vector<int32_t> filled(p.merge_start.begin(), p.merge_start.end() - 1);
+    for (const taper_work_item& it : p.items)
+        for (int b = 0; b < it.n_branch; ++b) p.merge[filled[it.seq0 + b]++] = {it.part_base + b * g, it.n_branch * g};
     p.merge_after = merges_after(cfg, p, latency_bound);
     for (taper_work_item& it : p.items) {
         it.merge0 = p.merge_start[it.seq0];
