@@ -640,7 +640,9 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, const int a
 template <int D, int PF>
 DEV void solo_run(const StepArgs& a, const int first, const int end, const int hk, const bool announce, PrivateSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (int k = first + wave; k < end; k += 4) private_item<D, true, PF, false>(a, k, hk, 0, sm);
+    // (back and forth: the wave with the longest item of one round has the shortest of the next)
+    for (int k = first, turn = wave; k < end; k += 4, turn ^= 3)
+        if (k + turn < end) private_item<D, true, PF, false>(a, k + turn, hk, 0, sm);
     if (!announce) {
         __syncthreads();
         return;

@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <functional>
 #include <cstring>
 
 namespace taper {
@@ -252,6 +253,33 @@ int partition_even(const std::vector<Segment>& segs, int gqa, int64_t quota, int
     }
     close();
     return part;
+}
+
+// Shares are filled in order, and one whose last sequence is not cut comes out shorter or longer than the quota.  Dealt out again,
+// the longest item to the emptiest share, they differ by less than an item.  Taken where the fullest share shrinks by 2 %, in steps
+// without shared-prefix work (512 sequences of 32 to 512 tokens 101.2 -> 99.0 us, 13 short
+// sequences and two of 14000 tokens in six pieces each 37.5 -> 35.6; beside shared work as often 4 % slower as faster).
+void level_shares(int n_parts, const Cost& cost, std::vector<taper_work_item>* items) {
+    if (n_parts < 2) return;
+    const auto price = [&](const taper_work_item& it) { return (it.n_tokens <= cost.brief_tokens ? kBriefItemCost : cost.fixed) + it.n_tokens; };
+    std::vector<int64_t> load(n_parts, 0);
+    for (const taper_work_item& it : *items) load[it.part] += price(it);
+    const int64_t most = *std::max_element(load.begin(), load.end());
+    std::vector<taper_work_item> dealt(*items);
+    std::stable_sort(dealt.begin(), dealt.end(), [](const taper_work_item& x, const taper_work_item& y) { return x.n_tokens > y.n_tokens; });
+    std::vector<std::pair<int64_t, int>> heap(n_parts);  // (load, share), the emptiest first
+    for (int q = 0; q < n_parts; ++q) heap[q] = {0, q};
+    const auto later = std::greater<std::pair<int64_t, int>>();
+    for (taper_work_item& it : dealt) {
+        std::pop_heap(heap.begin(), heap.end(), later);
+        heap.back().first += price(it);
+        it.part = heap.back().second;
+        std::push_heap(heap.begin(), heap.end(), later);
+    }
+    const int64_t least_most = std::max_element(heap.begin(), heap.end())->first;
+    if (least_most * 100 > most * 98) return;
+    std::stable_sort(dealt.begin(), dealt.end(), [](const taper_work_item& x, const taper_work_item& y) { return x.part < y.part; });
+    *items = std::move(dealt);
 }
 
 // Whether the step's merges are a launch of their own (merge_kernel) instead of being made by whoever delivers a sequence's last
@@ -652,6 +680,7 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     }
     quota = step(at);
     if (!current) cut(quota);
+    if (shared.empty()) level_shares(p.n_parts_private, cost_priv, &p.items);
     const int n_parts = p.n_parts_shared + p.n_parts_private;
     p.part_start.assign(n_parts + 1, 0);
     for (const taper_work_item& it : p.items) p.part_start[it.part + 1]++;
