@@ -181,9 +181,9 @@ typedef struct {
                                   pieces of a sequence with other items too only in steps of at most
                                   700 tokens per share                                            */
     int32_t min_share_tokens;  /* a small step is cut into fewer shares than target_workgroups allows
-                                  rather than into shares below this size.  0 = default: 256, or 1/16
-                                  of the longest private segment if that is more (keeps the partials
-                                  of one sequence to about 16)                                   */
+                                  rather than into shares below this size.  0 = default: 256, or 1/64
+                                  (1/32 beside shared-prefix work) of the longest private segment if that
+                                  is more (keeps the partials of one sequence to about 64 or 32)  */
     int32_t pool_pct;          /* 0 = default (25 when the step has shared-prefix work, rising to 60 for
                                   shares of 5120 tokens; none below 350 tokens per share or
                                   without shared-prefix work): percentage of the private tokens that no share owns; workgroups
