@@ -149,9 +149,9 @@ typedef struct {
     int64_t tokens_logical; /* sum over sequences of prefix_len + suffix_len: L_context of §3.2   */
     int32_t workspace_id;   /* which of the context's workspaces the plan is bound to (counts from 1 in
                                order of creation); it never changes while the plan lives          */
-    int64_t workspace_rows; /* partial rows that workspace holds                                  */
     int32_t merge_launch;   /* 1: the step's merges are a second kernel launch behind the attention's (many
                                partials per sequence); 0: made inside the attention launch         */
+    int64_t workspace_rows; /* partial rows that workspace holds                                  */
 } taper_plan_view;
 
 typedef struct {

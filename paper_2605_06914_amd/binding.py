@@ -59,7 +59,7 @@ class taper_plan_view(ctypes.Structure):
                 ("merge_start", _I32P), ("merge", ctypes.POINTER(taper_merge_entry)),
                 ("n_partial_rows", ctypes.c_int64), ("tokens_unique", ctypes.c_int64),
                 ("tokens_logical", ctypes.c_int64), ("workspace_id", ctypes.c_int32),
-                ("workspace_rows", ctypes.c_int64), ("merge_launch", ctypes.c_int32)]
+                ("merge_launch", ctypes.c_int32), ("workspace_rows", ctypes.c_int64)]
 
 
 class taper_plan_options(ctypes.Structure):
