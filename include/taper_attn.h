@@ -286,15 +286,20 @@ TAPER_API int taper_plan_resolve_slots(taper_ctx *ctx, const taper_plan *plan, i
  * sequence s and query head h,
  *     out[s,h,:] = sum_t softmax_t(scale * q[s,h,:].K_t) V_t
  * over t in shared prefix ++ private tokens of s.  Enqueues one kernel on
- * `hip_stream` and returns; allocates nothing, does not synchronise.  q, kv_pages,
+ * `hip_stream`, or two where the plan's merges are a launch of their own
+ * (merge_launch in its view), and returns; allocates nothing, does not synchronise.  q, kv_pages,
  * out (and lse if not NULL) are device pointers owned by the caller and must stay
  * valid until the stream has run the work.  Partial results of a sequence that is
  * cut into several work items travel in the context's taper_partial_format.
- * Calls on one ctx share its workspaces and must be ordered on one stream.  The
+ * Calls on one ctx share its workspaces and must be ordered on one stream; several
+ * threads may make them (the launches of one call stay together).  The
  * call may be recorded into a HIP graph (stream capture) and replayed while the
  * plan lives (the graph holds the addresses of the plan's device arrays and of the
  * workspace the plan is bound to, both of which live as long as the plan): the
- * kernel leaves its counters at zero and nothing else is enqueued.
+ * kernels leave their counters at zero and nothing else is enqueued.  Calls made
+ * while another thread replays such a graph do not disturb it (a recorded call with
+ * a merge launch has partial rows apart from theirs), but two threads must not
+ * replay graphs that hold recorded calls of one ctx at the same time.
  */
 TAPER_API int taper_decode_step_attention(taper_ctx *ctx, const taper_plan *plan, const void *q /* device */,
                                 const void *kv_pages /* device */, void *out /* device */,
@@ -317,7 +322,8 @@ TAPER_API int taper_decode_step_attention_simple(taper_ctx *ctx, int n_seqs, con
  * of the library's device image, one copy per GPU, held until the process ends.  The call
  * allocates and frees nothing, on the device or in pinned memory (its pinned staging buffer
  * and the array's address are set up by taper_create), and unlike _simple it only enqueues
- * (an upload of the plan that also clears the counters, the decode kernel) and returns; the host
+ * (an upload of the plan that also clears the counters, the decode kernel and, where the plan has one, the merge
+ * launch) and returns; the host
  * arrays are read during the call only.  No lse output.
  * A step whose plan, cut as taper_plan_build would cut it, does not fit the array is cut coarser:
  * without a pool, then for half the workgroups, a quarter and so on.

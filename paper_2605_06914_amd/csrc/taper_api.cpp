@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -53,14 +54,16 @@ struct PlanBuffers {
     hipEvent_t uploaded = nullptr;  // recorded after the host-to-device copy
 };
 
-// Partial rows and counters of launches: [counters] int32 | [rows] float4 (m, l, row scale, -) | [rows][D] rows.
+// Partial rows and counters of launches: [counters] int32 | [rows] float4 (m, l, row scale, -) | [rows][D] rows, and statistics and rows
+// once more for calls recorded into graphs whose merges are a launch of their own: a replay enqueues the two launches without asking
+// this library, so what another thread calls may come between them, and must not find its rows where theirs are.
 // A plan is bound to one workspace for its whole life, and a workspace lives at least as long as
 // the plans bound to it: launches in flight and captured graphs keep valid addresses whatever
 // is built later.
 struct Workspace {
     void* base = nullptr;  // null on a host-only context (bookkeeping only)
     int64_t rows = 0, counters = 0;
-    size_t ml_off = 0, o_off = 0, bytes = 0;
+    size_t ml_off = 0, o_off = 0, replay_off = 0, bytes = 0;  // (replay_off: from the first rows to the second)
     int refs = 0;  // live plans bound to it
     int id = 0;
 };
@@ -87,6 +90,7 @@ struct taper_ctx {
     int next_workspace_id = 1;
     bool counters_suspect = false;  // a call reported a HIP error: clear every workspace's counters before the next launch
     std::vector<PlanBuffers> free_buffers;
+    std::mutex enqueue;  // held while a call enqueues, so that the launches of one call follow each other on the stream
     int default_workgroups = 0;  // two resident workgroups per compute unit of the device (0: the builder's own default)
     // for taper_decode_step_attention_static: the device's copy of the library's scratch array, and a pinned
     // image of the plan that is uploaded into it (made at taper_create: the call itself allocates nothing)
@@ -244,7 +248,9 @@ int current_workspace(taper_ctx* ctx, int64_t rows, int64_t counters, bool headr
     if (!w) return fail(TAPER_ENOMEM, "host allocation failed");
     w->rows = headroom ? rows + rows / 4 + 1024 : rows;  // head-room so that slowly growing steps do not reallocate
     w->counters = headroom ? counters + counters / 4 + 1024 : counters;
-    w->bytes = layout_workspace(ctx->cfg, w->rows, w->counters, &w->ml_off, &w->o_off);
+    const size_t once = layout_workspace(ctx->cfg, w->rows, w->counters, &w->ml_off, &w->o_off);
+    w->replay_off = once - w->ml_off;
+    w->bytes = once + w->replay_off;
     w->id = ctx->next_workspace_id++;
     if (!ctx->host_only) {
         hipError_t e = hipSetDevice(ctx->cfg.device);
@@ -317,8 +323,16 @@ taper::StepArgs make_args(const taper_ctx* ctx, const taper::HostPlan& h, const 
     return a;
 }
 taper::StepArgs make_args(const taper_ctx* ctx, const taper_plan* plan, const void* q, const void* kv, void* out,
-                          float* lse) {
-    return make_args(ctx, plan->host, plan->img, plan->ws->base, plan->ws->ml_off, plan->ws->o_off, q, kv, out, lse);
+                          float* lse, bool recorded = false) {
+    const size_t by = recorded && plan->host.merge_after ? plan->ws->replay_off : 0;
+    return make_args(ctx, plan->host, plan->img, plan->ws->base, plan->ws->ml_off + by, plan->ws->o_off + by, q, kv, out, lse);
+}
+
+// Whether what is enqueued on `s` is recorded into a graph.
+bool recording(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();  // (the launch itself will say what is wrong)
+    return status == hipStreamCaptureStatusActive;
 }
 
 // Where the parts of a step lie in the static scratch array: plan image | counters | statistics | partial rows.
@@ -376,6 +390,7 @@ int hip_failed(taper_ctx* ctx, hipError_t e, const char* what) {
 }
 
 int enqueue_step(taper_ctx* ctx, const taper::StepArgs& a, hipStream_t s) {
+    std::lock_guard<std::mutex> alone(ctx->enqueue);
     int st = recover_counters(ctx, s);
     if (st != TAPER_OK) return st;
     hipError_t e = taper::launch_decode(a, s);
@@ -650,7 +665,8 @@ int taper_decode_step_attention(taper_ctx* ctx, const taper_plan* plan, const vo
     int st = check_step(ctx, plan);
     if (st != TAPER_OK) return st;
     if (!q || !kv_pages || !out) return fail(TAPER_EINVAL, "null tensor pointer");
-    return enqueue_step(ctx, make_args(ctx, plan, q, kv_pages, out, lse), (hipStream_t)hip_stream);
+    hipStream_t s = (hipStream_t)hip_stream;
+    return enqueue_step(ctx, make_args(ctx, plan, q, kv_pages, out, lse, plan->host.merge_after && recording(s)), s);
 }
 
 int taper_decode_step_attention_simple(taper_ctx* ctx, int n_seqs, const void* q, const void* kv_pages,
@@ -775,7 +791,10 @@ int taper_kernel_times_layers(taper_ctx* ctx, const taper_plan* plan, int n_laye
         const taper::StepArgs a = make_args(ctx, plan, q_per_layer[l], kv_per_layer[l], out_per_layer[l], nullptr);
         hipError_t e = hipSuccess;
         if (k >= 0) e = hipEventRecord(ev[2 * k], s);
-        if (e == hipSuccess) e = taper::launch_decode(a, s);
+        if (e == hipSuccess) {
+            std::lock_guard<std::mutex> alone(ctx->enqueue);
+            e = taper::launch_decode(a, s);
+        }
         if (k >= 0 && e == hipSuccess) e = hipEventRecord(ev[2 * k + 1], s);
         if (e != hipSuccess) rc = hip_failed(ctx, e, "kernel timing enqueue");
     }

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from taper_inputs import AttnShape, fill_values_numpy, structure_custom
-from tests.gpu_util import assert_parity, run_gpu, run_oracle
+from tests.gpu_util import assert_parity, run_gpu, run_oracle, torch_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -60,4 +60,43 @@ def test_merge_launch_gives_what_merges_inside_the_launch_give():
         to[alone.block_table[s, :16]] = kv[st.block_table[s, :16]]
     inside, _, _ = run_gpu(ctx, ba, **kw)
     assert np.abs(got[:3] - inside).max() <= 2.0 ** -8 * np.abs(inside).max()
+    ctx.close()
+
+
+def test_two_threads_on_one_stream():
+    """Two threads call on one context and one stream, each a plan with a merge launch: every result is the one the plan gives alone."""
+    import threading
+
+    import torch
+
+    from paper_2605_06914_amd import Context
+
+    sh = AttnShape(8, 1, 128, 16)
+    ctx = Context(8, 1, 128, device=0)
+    work = []
+    for seed, reqs in ((1, [(15000, [0])]), (2, [(9000, [0, 30, 700]), (5000, [0])])):
+        b = fill_values_numpy(structure_custom(sh, reqs, seed=seed))
+        st = b.structure
+        plan = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages)
+        assert plan.export()["merge_launch"] == 1
+        q, kv = torch_bf16(b.q), torch_bf16(b.kv)
+        alone = torch.empty_like(q)
+        ctx.decode_step_attention(plan, q, kv, alone)
+        work.append((plan, q, kv, alone, [torch.full_like(q, float("nan")) for _ in range(200)]))
+    torch.cuda.synchronize()
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def calls(plan, q, kv, _, outs):
+        for out in outs:
+            ctx.decode_step_attention(plan, q, kv, out, stream=stream)
+
+    threads = [threading.Thread(target=calls, args=w) for w in work]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for plan, _, _, alone, outs in work:
+        assert all(torch.equal(out.view(torch.int16), alone.view(torch.int16)) for out in outs)
+        plan.free()
     ctx.close()
