@@ -270,6 +270,13 @@ TAPER_API int taper_plan_build_segments(taper_ctx *ctx, int n_seqs, const int32_
                                         taper_plan **out_plan);
 TAPER_API void taper_plan_free(taper_plan *plan);
 TAPER_API int taper_plan_export(const taper_plan *plan, taper_plan_view *out_view /* host */);
+/*
+ * Where the merges of the plan's later calls are made, instead of where the plan's rule puts them: 1 = in a
+ * launch of their own behind the attention launch, 0 = inside it.  Items, partial rows and merge map stay as
+ * they are; results agree up to the order of fp32 sums.  Calls already enqueued or recorded are not affected.
+ * TAPER_EINVAL for another value or a null plan.  Not safe beside a call that uses the plan.
+ */
+TAPER_API int taper_plan_set_merge_launch(taper_plan *plan, int merge_launch);
 
 /*
  * Physical slot id (page * page_size + token-in-page) of every logical position:

@@ -27,7 +27,7 @@ EXPORTED = [
     "taper_predictor_fit", "taper_predictor_eval", "taper_predictor_mape", "taper_window_create",
     "taper_window_destroy", "taper_window_push", "taper_window_size", "taper_window_fit", "taper_admit_step",
     "taper_predictor_fit_monotone", "taper_window_fit_monotone",
-    "taper_stream_read_probe", "taper_reserve", "taper_decode_step_attention_static",
+    "taper_stream_read_probe", "taper_reserve", "taper_decode_step_attention_static", "taper_plan_set_merge_launch",
 ]
 
 
@@ -135,6 +135,7 @@ def load_library() -> ctypes.CDLL:
     lib.taper_plan_free.argtypes = [vp]
     lib.taper_plan_free.restype = None
     lib.taper_plan_export.argtypes = [vp, ctypes.POINTER(taper_plan_view)]
+    lib.taper_plan_set_merge_launch.argtypes = [vp, ci]
     lib.taper_plan_resolve_slots_host.argtypes = [vp, vp, i64]
     lib.taper_plan_resolve_slots.argtypes = [vp, vp, vp, i64, vp]
     lib.taper_decode_step_attention.argtypes = [vp, vp, vp, vp, vp, vp, vp]
@@ -274,6 +275,10 @@ class Plan:
                     tokens_logical=int(v.tokens_logical), workspace_id=int(v.workspace_id),
                     workspace_rows=int(v.workspace_rows), merge_launch=int(v.merge_launch))
 
+    def set_merge_launch(self, on: bool):
+        """Merges of later calls in a launch of their own (True) or inside the attention launch (False), whatever the plan's rule says."""
+        _check(load_library().taper_plan_set_merge_launch(self._h, int(on)))
+
     def resolve_slots_host(self, stride: int) -> np.ndarray:
         S = self.export()["n_seqs"]
         out = np.zeros((S, stride), np.int64)
@@ -321,7 +326,9 @@ class Context:
                    target_workgroups: int = 0, share_prefix: bool = True, max_branches_per_item: int = 0,
                    shared_cost_pct: int = 0, shared_item_cost: int = 0, private_item_cost: int = 0,
                    pool_pct: int = 0, pool_item_tokens: int = 0, private_merge_cost: int = 0, solo_item_tokens: int = 0,
-                   min_share_tokens: int = 0, scatter_sub_groups: bool = False, small_step_grid: int = 0, stream=None) -> Plan:
+                   min_share_tokens: int = 0, scatter_sub_groups: bool = False, small_step_grid: int = 0, stream=None,
+                   merge_launch: Optional[bool] = None) -> Plan:
+        """merge_launch: None leaves it to the plan's rule where merges are made (see Plan.set_merge_launch)."""
         bt = _i32(block_table)
         grp, pl, sl = _i32(branch_group), _i32(prefix_len), _i32(suffix_len)
         if bt.ndim != 2 or not (len(grp) == len(pl) == len(sl) == bt.shape[0]):
@@ -334,10 +341,16 @@ class Context:
         _check(load_library().taper_plan_build(self._h, bt.shape[0], bt.ctypes.data, bt.shape[1], grp.ctypes.data,
                                                pl.ctypes.data, sl.ctypes.data, int(n_pool_pages), ctypes.byref(opts),
                                                st, ctypes.byref(h)))
-        return Plan(self, h.value, bt.shape[0], n_pool_pages)
+        return self._built(h, bt.shape[0], n_pool_pages, merge_launch)
+
+    def _built(self, h, n_seqs, n_pool_pages, merge_launch) -> Plan:
+        plan = Plan(self, h.value, n_seqs, n_pool_pages)
+        if merge_launch is not None:
+            plan.set_merge_launch(merge_launch)
+        return plan
 
     def plan_build_segments(self, block_table, branch_group, prefix_len, seg_start, seg_len, n_pool_pages: int,
-                            stream=None, **options) -> Plan:
+                            stream=None, merge_launch: Optional[bool] = None, **options) -> Plan:
         """Plan for sequences that see their prefix and then a list of private segments (reduce phase)."""
         bt = _i32(block_table)
         grp, pl, ss, sl = _i32(branch_group), _i32(prefix_len), _i32(seg_start), _i32(seg_len)
@@ -358,7 +371,7 @@ class Context:
         _check(load_library().taper_plan_build_segments(self._h, bt.shape[0], bt.ctypes.data, bt.shape[1], grp.ctypes.data,
                                                         pl.ctypes.data, ss.ctypes.data, sl.ctypes.data if len(sl) else None,
                                                         int(n_pool_pages), ctypes.byref(opts), st, ctypes.byref(h)))
-        return Plan(self, h.value, bt.shape[0], n_pool_pages)
+        return self._built(h, bt.shape[0], n_pool_pages, merge_launch)
 
     def _step_ptrs(self, n_seqs, n_pool_pages, q, kv_pages, out, lse=None):
         d, qo = self.cfg.device, int(n_seqs) * self._qo_row

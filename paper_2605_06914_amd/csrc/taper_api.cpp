@@ -644,6 +644,13 @@ int taper_plan_export(const taper_plan* plan, taper_plan_view* v) {
     return TAPER_OK;
 }
 
+int taper_plan_set_merge_launch(taper_plan* plan, int merge_launch) {
+    if (!plan) return fail(TAPER_EINVAL, "null argument");
+    if (merge_launch != 0 && merge_launch != 1) return fail(TAPER_EINVAL, "merge_launch must be 0 or 1");
+    plan->host.merge_after = merge_launch;
+    return TAPER_OK;
+}
+
 int taper_plan_resolve_slots_host(const taper_plan* plan, int64_t* slots, int64_t stride) {
     if (!plan || !slots || stride < 0) return fail(TAPER_EINVAL, "bad argument");
     taper::resolve_slots_host(plan->host, plan->ctx->cfg.page_size, slots, stride);

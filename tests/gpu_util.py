@@ -1,10 +1,13 @@
 """Helpers for the GPU parity tests: move a seeded batch to the device, run the
 library through its C ABI, bring the result back as float64."""
 import numpy as np
+import pytest
 
 import oracle
 from taper_inputs import Batch, f32_from_bf16_bits
 
+# both places where merges are made: by whoever delivers a sequence's last partial, inside the attention launch, and in a launch of their own
+both_merges = pytest.mark.parametrize("merge_launch", [False, True], ids=["merges_inside", "merge_launch"])
 MAX_ABS, MEAN_ABS = 2e-2, 2e-3  # parity bar for bf16 inputs / fp32 accumulation
 
 

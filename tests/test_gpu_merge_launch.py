@@ -37,29 +37,38 @@ def test_merge_launch_at_its_edges(shape, partial_format):
     ctx.close()
 
 
-def test_merge_launch_gives_what_merges_inside_the_launch_give():
-    """The same cuts merged both ways, which only the order of a few fp32 sums tells apart: results agree to one bf16 step."""
+@pytest.mark.parametrize("partial_format", ["f16_scaled", "f32"])
+@pytest.mark.parametrize("shape", [(16, 2, 128), (8, 8, 64)])
+def test_merge_launch_gives_what_merges_inside_the_launch_give(shape, partial_format):
+    """One plan merged both ways, which only the order of fp32 sums tells apart: up to 70 rows of values below 6, each sum off by at
+    most 70 x 6 x 2^-23 = 5e-5 before both round to bf16, to the same value or to neighbours."""
+    import torch
+
     from paper_2605_06914_amd import Context
 
-    sh = AttnShape(16, 2, 128, 16)
-    many, few = [(4096, [0])], [(256, [0])]
-    kw = dict(FINE, min_share_tokens=128)
-    b = fill_values_numpy(structure_custom(sh, few * 3 + many, seed=5))
+    sh = AttnShape(*shape, 16)
+    reqs = [(32 * k, [0]) for k in (1, 2, 7, 8, 9, 16, 17, 33, 70)] + [(640, [0, 40, 0]), (200, [90, 3, 5, 7, 1, 64])]
+    b = fill_values_numpy(structure_custom(sh, reqs, seed=5))
     st = b.structure
-    ctx = Context(16, 2, 128, device=0)
-    plan = lambda s: ctx.plan_build(s.block_table, s.branch_group, s.prefix_len, s.suffix_len, s.n_pool_pages, **kw).export()
-    assert plan(st)["merge_launch"] == 1
-    alone = structure_custom(sh, few * 3, seed=5)
-    assert plan(alone)["merge_launch"] == 0 and np.diff(plan(alone)["merge_start"]).max() > 1
-    got, _, _ = run_gpu(ctx, b, **kw)
-    ba = fill_values_numpy(alone)
-    ba.q[:] = b.q[:3]
-    kv = b.kv.reshape(st.n_pool_pages, -1)
-    to = ba.kv.reshape(alone.n_pool_pages, -1)
-    for s in range(3):
-        to[alone.block_table[s, :16]] = kv[st.block_table[s, :16]]
-    inside, _, _ = run_gpu(ctx, ba, **kw)
-    assert np.abs(got[:3] - inside).max() <= 2.0 ** -8 * np.abs(inside).max()
+    ctx = Context(*shape, device=0, partial_format=partial_format)
+    plan = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, **FINE)
+    counts = np.diff(plan.export()["merge_start"])
+    assert counts.max() == 70 and len(set(counts.tolist())) >= 8
+    q, kv = torch_bf16(b.q), torch_bf16(b.kv)
+    got = []
+    for on in (False, True):
+        plan.set_merge_launch(on)
+        out = torch.full_like(q, float("nan"))
+        lse = torch.full(q.shape[:2], float("nan"), device=q.device)
+        ctx.decode_step_attention(plan, q, kv, out, lse)
+        torch.cuda.synchronize()
+        got.append((out.double().cpu().numpy(), lse.cpu().numpy()))
+    (x, lx), (y, ly) = got
+    step = 2.0 ** -7 * np.maximum(np.abs(x), np.abs(y))  # (a bf16 step is at most this much of the value)
+    assert np.abs(kv.float().abs().max().item()) < 6
+    assert (np.abs(x - y) <= step + 5e-5).all(), np.abs(x - y).max()
+    assert np.abs(lx - ly).max() <= 1e-5 * np.abs(lx).max()  # (fp32 sums of positive numbers, their logarithm)
+    plan.free()
     ctx.close()
 
 

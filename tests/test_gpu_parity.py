@@ -7,7 +7,7 @@ import pytest
 import oracle
 from taper_inputs import (AttnShape, Batch, bf16_bits_from_f32, compact_rows, f32_from_bf16_bits, fill_values_numpy,
                           structure_config1, structure_config2, structure_config3, structure_custom)
-from tests.gpu_util import assert_parity, bits_from_torch, run_gpu, run_oracle, torch_bf16
+from tests.gpu_util import assert_parity, bits_from_torch, both_merges, run_gpu, run_oracle, torch_bf16
 from tests.layout_ref import PoolView
 
 pytestmark = pytest.mark.gpu
@@ -191,7 +191,8 @@ def test_wide_requests_in_one_pass(ctx_qwen, width):
     assert_parity(got2, ref, f"wide {width}, 8 workgroups")
 
 
-def test_same_plan_replayed(ctx_qwen):
+@both_merges
+def test_same_plan_replayed(ctx_qwen, merge_launch):
     """The arrival counters and the pool's claim counter reset themselves inside the
     kernel: replaying one plan must give the same bits every time."""
     import torch
@@ -200,7 +201,7 @@ def test_same_plan_replayed(ctx_qwen):
     st = b.structure
     q, kv = torch_bf16(b.q), torch_bf16(b.kv)
     plan = ctx_qwen.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages,
-                               pool_pct=60, pool_item_tokens=128)
+                               pool_pct=60, pool_item_tokens=128, merge_launch=merge_launch)
     assert plan.export()["n_pool_items"] > 0
     bits = []
     for _ in range(6):
@@ -215,20 +216,22 @@ def test_same_plan_replayed(ctx_qwen):
         assert np.array_equal(bits[0], x)
 
 
-def test_many_partials_per_sequence(ctx_qwen):
+@both_merges
+def test_many_partials_per_sequence(ctx_qwen, merge_launch):
     """Very fine shares: a sequence's partials number in the hundreds, far more than one merge round holds
     and more than the item-start prefetch of merge entries covers (the rest is fetched during the merge)."""
     reqs = [(9000, [0]), (6000, [3, 0, 70, 1, 200, 16, 5, 9, 130, 2, 31, 64, 8, 4, 77, 12]), (40, [0])]
     b = fill_values_numpy(structure_custom(QWEN, reqs, seed=109))
     st = b.structure
     plan = ctx_qwen.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages,
-                               target_workgroups=8192, pool_pct=-1, min_share_tokens=1)
+                               target_workgroups=8192, pool_pct=-1, min_share_tokens=1, merge_launch=merge_launch)
     e = plan.export()
     per_seq = np.diff(e["merge_start"])
     plan.free()
     assert per_seq[0] > 128 and per_seq[1:17].sum() > 128 and per_seq[1] > 8
     ref, ref_lse = run_oracle(b)
-    got, lse, _ = run_gpu(ctx_qwen, b, target_workgroups=8192, pool_pct=-1, min_share_tokens=1)
+    assert e["merge_launch"] == merge_launch
+    got, lse, _ = run_gpu(ctx_qwen, b, target_workgroups=8192, pool_pct=-1, min_share_tokens=1, merge_launch=merge_launch)
     assert_parity(got, ref, f"{int(per_seq.max())} partials per sequence")
     assert np.max(np.abs(lse - ref_lse)) <= 2e-3
 
@@ -533,8 +536,9 @@ def test_config5_k16_every_output_two_ways(ctx_qwen):
     assert float((a - b).abs().max()) <= 2e-2 and float((a - b).abs().mean()) <= 2e-3
 
 
-def test_layer_launches_replay_from_a_captured_graph(ctx_qwen):
-    """The attention call is one kernel launch on the caller's stream (no memset, no allocation, no host wait), so a
+@both_merges
+def test_layer_launches_replay_from_a_captured_graph(ctx_qwen, merge_launch):
+    """The attention call is one or two kernel launches on the caller's stream (no memset, no allocation, no host wait), so a
     stack of layers can be captured once per plan and replayed.  Several replays, with eager work and
     synchronisations between them, must each reproduce the eager bits (the arrival and pool counters put
     themselves back to zero inside the kernel)."""
@@ -547,7 +551,7 @@ def test_layer_launches_replay_from_a_captured_graph(ctx_qwen):
     gen.manual_seed(5)
     kvs = [torch_bf16(b.kv)] + [torch.randn(b.kv.size, generator=gen, device="cuda:0").to(torch.bfloat16) for _ in range(n_layers - 1)]
     qs = [torch_bf16(b.q)] + [torch.randn(b.q.shape, generator=gen, device="cuda:0").to(torch.bfloat16) for _ in range(n_layers - 1)]
-    plan = ctx_qwen.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages)
+    plan = ctx_qwen.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, merge_launch=merge_launch)
     eager = [torch.full_like(qs[0], float("nan")) for _ in range(n_layers)]
     for l in range(n_layers):
         ctx_qwen.decode_step_attention(plan, qs[l], kvs[l], eager[l])
@@ -577,20 +581,21 @@ def test_layer_launches_replay_from_a_captured_graph(ctx_qwen):
     plan.free()
 
 
+@both_merges
 @pytest.mark.parametrize("log2_scale", [9, 13])
-def test_large_values_of_v_pass_through_the_partials(ctx_qwen, log2_scale):
+def test_large_values_of_v_pass_through_the_partials(ctx_qwen, log2_scale, merge_launch):
     """V scaled by 2^9 and 2^13 (|V| up to about 3e4) must give the unscaled result times the same power of two
     (partial rows between workgroups travel normalised and scaled row by row; larger factors and the fp32
     format are covered in test_gpu_robustness.py)."""
     b = fill_values_numpy(structure_custom(QWEN, POOL_REQS, seed=141))
-    base, _, _ = run_gpu(ctx_qwen, b, target_workgroups=2048, min_share_tokens=1)
+    base, _, _ = run_gpu(ctx_qwen, b, target_workgroups=2048, min_share_tokens=1, merge_launch=merge_launch)
     st, sh = b.structure, b.structure.shape
     pv = PoolView(sh.n_kv_heads, sh.head_dim, sh.page_size)
     kv = b.kv.reshape(st.n_pool_pages, 2, sh.n_kv_heads, sh.page_size * sh.head_dim)
     v = f32_from_bf16_bits(kv[:, 1]) * np.float32(2.0 ** log2_scale)  # exact: a power of two
     kv[:, 1] = bf16_bits_from_f32(v)
     assert np.abs(v).max() < 65504
-    got, _, _ = run_gpu(ctx_qwen, b, target_workgroups=2048, min_share_tokens=1)
+    got, _, _ = run_gpu(ctx_qwen, b, target_workgroups=2048, min_share_tokens=1, merge_launch=merge_launch)
     assert np.isfinite(got).all()
     assert np.max(np.abs(got / 2.0 ** log2_scale - base)) <= 1e-3
 

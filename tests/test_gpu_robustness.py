@@ -6,7 +6,7 @@ import pytest
 
 from taper_inputs import (AttnShape, bf16_bits_from_f32, f32_from_bf16_bits, fill_values_numpy, structure_config3,
                           structure_custom)
-from tests.gpu_util import assert_parity, bits_from_torch, run_gpu, run_oracle, torch_bf16
+from tests.gpu_util import assert_parity, bits_from_torch, both_merges, run_gpu, run_oracle, torch_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -24,15 +24,17 @@ def new_ctx(**kw):
     return Context(64, 8, 128, device=0, **kw)
 
 
+@both_merges
 @pytest.mark.parametrize("reqs,kw", [(RAGGED, {}), (POOL_REQS, {}), (POOL_REQS, FINE),
                                      (POOL_REQS, dict(max_branches_per_item=24)),
                                      ([(333, [int(x) for x in range(40)]), (300, [0])], {})],
                          ids=["ragged", "pool", "pool_fine", "pool_wide_items", "width40"])
-def test_fp32_partial_rows_meet_the_same_bar(reqs, kw):
+def test_fp32_partial_rows_meet_the_same_bar(reqs, kw, merge_launch):
     """partial_format = fp32: the other route between workgroups, same parity bar, same lse."""
     ctx = new_ctx(partial_format="f32")
     b = fill_values_numpy(structure_custom(QWEN, reqs, seed=501))
     ref, ref_lse = run_oracle(b)
+    kw = dict(kw, merge_launch=merge_launch)
     got, lse, bits = run_gpu(ctx, b, **kw)
     assert_parity(got, ref, f"fp32 partial rows {kw}")
     assert np.max(np.abs(lse - ref_lse)) <= 2e-3
@@ -41,16 +43,17 @@ def test_fp32_partial_rows_meet_the_same_bar(reqs, kw):
     ctx.close()
 
 
+@both_merges
 @pytest.mark.parametrize("partial_format", ["f16_scaled", "f32"])
 @pytest.mark.parametrize("log2_scale", [-60, 13, 20, 100])
-def test_values_of_v_far_beyond_the_half_precision_range(partial_format, log2_scale):
+def test_values_of_v_far_beyond_the_half_precision_range(partial_format, log2_scale, merge_launch):
     """V times 2^s (|V| up to 1e31 at s = 100, down to 1e-18 at s = -60; bf16 holds both): the result must be the
     unscaled result times 2^s whatever format the partial rows travel in -- no overflow to Inf, no flush to
     zero -- with the sequences cut so finely that nearly every output goes through partials."""
     ctx = new_ctx(partial_format=partial_format)
     b = fill_values_numpy(structure_custom(QWEN, POOL_REQS, seed=141))
     ref, _ = run_oracle(b)
-    base, _, _ = run_gpu(ctx, b, **FINE)
+    base, _, _ = run_gpu(ctx, b, **FINE, merge_launch=merge_launch)
     assert_parity(base, ref, "unscaled")
     st, sh = b.structure, b.structure.shape
     kv = b.kv.reshape(st.n_pool_pages, 2, sh.n_kv_heads, sh.page_size * sh.head_dim)
@@ -58,7 +61,7 @@ def test_values_of_v_far_beyond_the_half_precision_range(partial_format, log2_sc
     kv[:, 1] = bf16_bits_from_f32(v)
     if log2_scale >= 13:
         assert np.abs(v).max() > (65504 if log2_scale > 13 else 1e4)
-    got, _, _ = run_gpu(ctx, b, **FINE)
+    got, _, _ = run_gpu(ctx, b, **FINE, merge_launch=merge_launch)
     assert np.isfinite(got).all()
     back = got / 2.0 ** log2_scale
     assert_parity(back, ref, f"V x 2^{log2_scale}, {partial_format}")
@@ -66,7 +69,8 @@ def test_values_of_v_far_beyond_the_half_precision_range(partial_format, log2_sc
     ctx.close()
 
 
-def test_a_graph_captured_from_a_plan_survives_a_larger_plan():
+@both_merges
+def test_a_graph_captured_from_a_plan_survives_a_larger_plan(merge_launch):
     """Capture the launches of plan A, then build a plan B that needs a larger workspace (it gets one of its
     own) and run it, then replay A's graph: the bits of the eager run of A, every time."""
     import torch
@@ -75,7 +79,7 @@ def test_a_graph_captured_from_a_plan_survives_a_larger_plan():
     a = fill_values_numpy(structure_custom(QWEN, POOL_REQS, seed=131))
     sa = a.structure
     qa, kva = torch_bf16(a.q), torch_bf16(a.kv)
-    plan_a = ctx.plan_build(sa.block_table, sa.branch_group, sa.prefix_len, sa.suffix_len, sa.n_pool_pages)
+    plan_a = ctx.plan_build(sa.block_table, sa.branch_group, sa.prefix_len, sa.suffix_len, sa.n_pool_pages, merge_launch=merge_launch)
     ea = plan_a.export()
     eager = torch.full_like(qa, float("nan"))
     ctx.decode_step_attention(plan_a, qa, kva, eager)
@@ -95,7 +99,7 @@ def test_a_graph_captured_from_a_plan_survives_a_larger_plan():
     b = fill_values_numpy(structure_config3())  # 22k partial rows against A's few thousand
     sb = b.structure
     qb, kvb = torch_bf16(b.q), torch_bf16(b.kv)
-    plan_b = ctx.plan_build(sb.block_table, sb.branch_group, sb.prefix_len, sb.suffix_len, sb.n_pool_pages)
+    plan_b = ctx.plan_build(sb.block_table, sb.branch_group, sb.prefix_len, sb.suffix_len, sb.n_pool_pages, merge_launch=merge_launch)
     eb = plan_b.export()
     assert eb["n_partial_rows"] > ea["workspace_rows"] and eb["workspace_id"] != ea["workspace_id"]
     assert plan_a.export()["workspace_id"] == ea["workspace_id"]
@@ -114,7 +118,8 @@ def test_a_graph_captured_from_a_plan_survives_a_larger_plan():
     ctx.close()
 
 
-def test_partial_rows_of_an_earlier_batch_do_not_leak():
+@both_merges
+def test_partial_rows_of_an_earlier_batch_do_not_leak(merge_launch):
     """Two different batches back to back on one context (the second finds the first one's partial rows and
     statistics in the workspace), against the second batch alone on a fresh context: same bits.  A merge
     that read a row before its writer had delivered it would pick up the other batch's numbers."""
@@ -122,7 +127,7 @@ def test_partial_rows_of_an_earlier_batch_do_not_leak():
     second = fill_values_numpy(structure_custom(QWEN, [(1800, [9, 0, 40, 77, 5]), (2500, [0]), (640, [3, 700]), (90, [0]),
                                                        (1300, [1] * 11)], seed=602))
     used = new_ctx()
-    for kw in ({}, FINE):
+    for kw in (dict(merge_launch=merge_launch), dict(FINE, merge_launch=merge_launch)):
         _, _, _ = run_gpu(used, first, **kw)
         _, _, bits_after = run_gpu(used, second, **kw)
         fresh = new_ctx()
@@ -152,7 +157,8 @@ def test_reserve_then_no_growth():
     ctx.close()
 
 
-def test_two_batches_taking_turns_repeat_their_bits():
+@both_merges
+def test_two_batches_taking_turns_repeat_their_bits(merge_launch):
     """Two different batches, finely cut (thousands of partial rows each, the same workspace), launched in
     turns without a host synchronisation between the launches, 150 times each: every result must be the bits
     of the first.  The partial rows, statistics and counters of one launch are what the next one finds in the
@@ -167,7 +173,9 @@ def test_two_batches_taking_turns_repeat_their_bits():
     dev = []
     for b in batches:
         st = b.structure
-        plan = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, **FINE)
+        plan = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, **FINE,
+                              merge_launch=merge_launch)
+        assert plan.export()["merge_launch"] == merge_launch
         q, kv = torch_bf16(b.q), torch_bf16(b.kv)
         first = torch.full_like(q, float("nan"))
         ctx.decode_step_attention(plan, q, kv, first)

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from taper_inputs import AttnShape, fill_values_numpy, structure_custom
-from tests.gpu_util import assert_parity, run_gpu, run_oracle
+from tests.gpu_util import assert_parity, both_merges, run_gpu, run_oracle
 
 # tokens per block are 32 at head_dim 128 and 64 at 64; the ring holds four blocks
 PREFIXES = [1, 16, 17, 31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 160, 193, 255, 256, 257, 321]
@@ -55,19 +55,20 @@ def test_private_items_of_few_blocks(shape, partial_format):
 
 
 @pytest.mark.gpu
+@both_merges
 @pytest.mark.parametrize("partial_format", ["f16_scaled", "f32"])
-def test_merges_of_few_and_of_very_many_partials(partial_format):
+def test_merges_of_few_and_of_very_many_partials(partial_format, merge_launch):
     """1 to 9 partials per sequence (rounds of 2, 4, 8), and more than the 128 entries a workgroup keeps on chip."""
     sh = AttnShape(16, 1, 128, 16)
     reqs = [(32 * k, [0]) for k in range(1, 11)] + [(6000, [0]), (96, [5] * 5), (64, [40, 0, 33])]
     b = fill_values_numpy(structure_custom(sh, reqs, seed=511))
     ctx = context(sh, partial_format=partial_format)
     st = b.structure
-    kw = dict(target_workgroups=4096, min_share_tokens=1, private_item_cost=1, solo_item_tokens=-1)
+    kw = dict(target_workgroups=4096, min_share_tokens=1, private_item_cost=1, solo_item_tokens=-1, merge_launch=merge_launch)
     e = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, **kw).export()
     counts = np.diff(e["merge_start"])
     print("[merge] partials per sequence:", counts.tolist(), flush=True)
-    assert counts.max() > 64 and len(set(counts.tolist()) & {1, 2, 3, 4, 5, 6}) >= 4
+    assert e["merge_launch"] == merge_launch and counts.max() > 128 and len(set(counts.tolist()) & {1, 2, 3, 4, 5, 6}) >= 4
     ref, _ = run_oracle(b)
     got, _, bits = run_gpu(ctx, b, **kw)
     assert_parity(got, ref, "many partials")

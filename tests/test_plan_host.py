@@ -288,3 +288,26 @@ def test_pool_items_stay_within_their_default_size(seed):
     pool = e["items"][e["part_start"][-1]:, F["n_tokens"]]
     assert e["n_pool_items"] > 0 and 1024 < pool.max() <= 1536, pool.max()
     ctx.close()
+
+
+def test_where_merges_are_made_can_be_set():
+    """The rule's choice, the other one, and back; nothing else of the plan changes."""
+    st = structure_config3()
+    ctx = Context(64, 8, 128, device=-1)
+    args = (st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages)
+    rule = ctx.plan_build(*args).export()
+    for on in (False, True):
+        for plan in (ctx.plan_build(*args, merge_launch=on),
+                     ctx.plan_build_segments(*args[:3], np.arange(st.n_seqs + 1), st.suffix_len, st.n_pool_pages, merge_launch=on)):
+            e = plan.export()
+            assert e["merge_launch"] == on
+            assert all(np.array_equal(e[k], rule[k]) for k in ("items", "part_start", "merge_start", "merge"))
+            plan.set_merge_launch(not on)
+            assert plan.export()["merge_launch"] == (not on)
+            plan.free()
+    plan = ctx.plan_build(*args)
+    with pytest.raises(TaperError) as err:
+        plan.set_merge_launch(2)
+    assert err.value.status == TAPER_EINVAL and plan.export()["merge_launch"] == rule["merge_launch"]
+    plan.free()
+    ctx.close()
