@@ -277,6 +277,9 @@ TAPER_API int taper_plan_export(const taper_plan *plan, taper_plan_view *out_vie
  * TAPER_EINVAL for another value or a null plan.  Not safe beside a call that uses the plan.
  */
 TAPER_API int taper_plan_set_merge_launch(taper_plan *plan, int merge_launch);
+/* How many of each share's items, its first ones, are run by single waves side by side (see solo_item_tokens):
+ * n_items[q] for the n_parts_shared + n_parts_private shares of the view, 0 for shared ones. */
+TAPER_API int taper_plan_solo_items(const taper_plan *plan, int32_t *n_items /* host, out */);
 
 /*
  * Physical slot id (page * page_size + token-in-page) of every logical position:

@@ -28,6 +28,7 @@ EXPORTED = [
     "taper_window_destroy", "taper_window_push", "taper_window_size", "taper_window_fit", "taper_admit_step",
     "taper_predictor_fit_monotone", "taper_window_fit_monotone",
     "taper_stream_read_probe", "taper_reserve", "taper_decode_step_attention_static", "taper_plan_set_merge_launch",
+    "taper_plan_solo_items",
 ]
 
 
@@ -136,6 +137,7 @@ def load_library() -> ctypes.CDLL:
     lib.taper_plan_free.restype = None
     lib.taper_plan_export.argtypes = [vp, ctypes.POINTER(taper_plan_view)]
     lib.taper_plan_set_merge_launch.argtypes = [vp, ci]
+    lib.taper_plan_solo_items.argtypes = [vp, vp]
     lib.taper_plan_resolve_slots_host.argtypes = [vp, vp, i64]
     lib.taper_plan_resolve_slots.argtypes = [vp, vp, vp, i64, vp]
     lib.taper_decode_step_attention.argtypes = [vp, vp, vp, vp, vp, vp, vp]
@@ -259,6 +261,8 @@ class Plan:
         _check(load_library().taper_plan_export(self._h, ctypes.byref(v)))
         S, G = v.n_seqs, v.n_groups
         n_parts = v.n_parts_shared + v.n_parts_private
+        solo = np.zeros(n_parts, np.int32)
+        _check(load_library().taper_plan_solo_items(self._h, solo.ctypes.data))
         arr = lambda p, n: np.ctypeslib.as_array(p, shape=(n,)).copy() if n else np.zeros(0, np.int32)
         items = np.ctypeslib.as_array(ctypes.cast(v.items, _I32P), shape=(v.n_items, 8)).copy()
         n_merge = int(arr(v.merge_start, S + 1)[-1])
@@ -273,7 +277,7 @@ class Plan:
                     part_start=arr(v.part_start, n_parts + 1), merge_start=arr(v.merge_start, S + 1), merge=merge,
                     n_partial_rows=int(v.n_partial_rows), tokens_unique=int(v.tokens_unique),
                     tokens_logical=int(v.tokens_logical), workspace_id=int(v.workspace_id),
-                    workspace_rows=int(v.workspace_rows), merge_launch=int(v.merge_launch))
+                    workspace_rows=int(v.workspace_rows), merge_launch=int(v.merge_launch), solo_items=solo)
 
     def set_merge_launch(self, on: bool):
         """Merges of later calls in a launch of their own (True) or inside the attention launch (False), whatever the plan's rule says."""

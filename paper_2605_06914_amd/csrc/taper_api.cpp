@@ -651,6 +651,12 @@ int taper_plan_set_merge_launch(taper_plan* plan, int merge_launch) {
     return TAPER_OK;
 }
 
+int taper_plan_solo_items(const taper_plan* plan, int32_t* n_items) {
+    if (!plan || !n_items) return fail(TAPER_EINVAL, "null argument");
+    for (size_t q = 0; q < plan->host.part_turn.size(); ++q) n_items[q] = plan->host.part_turn[q] >> taper::kPartSoloShift;
+    return TAPER_OK;
+}
+
 int taper_plan_resolve_slots_host(const taper_plan* plan, int64_t* slots, int64_t stride) {
     if (!plan || !slots || stride < 0) return fail(TAPER_EINVAL, "bad argument");
     taper::resolve_slots_host(plan->host, plan->ctx->cfg.page_size, slots, stride);
