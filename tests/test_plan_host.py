@@ -311,3 +311,16 @@ def test_where_merges_are_made_can_be_set():
     assert err.value.status == TAPER_EINVAL and plan.export()["merge_launch"] == rule["merge_launch"]
     plan.free()
     ctx.close()
+
+
+def test_short_steps_keep_their_merges_inside_the_attention_launch():
+    """A second launch per layer costs the host more than it saves the GPU there; the mixed batch on one kv head has it."""
+    small = structure_custom(AttnShape(32, 8, 64, 16), [(1246, [0]), (1135, [0]), (912, [104, 251, 451, 370, 119]), (376, [145, 272, 316, 135]),
+                                                        (607, [97, 191, 195, 413])], seed=4)
+    ctx = Context(32, 8, 64, device=-1, partial_format="f32")
+    e = build(small, ctx).export()
+    assert np.diff(e["merge_start"]).max() > 8 and e["merge_launch"] == 0  # (three rounds of 4 entries, 10.6 us either way)
+    ctx.close()
+    ctx = Context(8, 1, 128, device=-1)
+    assert build(structure_config3(), ctx).export()["merge_launch"] == 1
+    ctx.close()
