@@ -171,7 +171,10 @@ typedef struct {
                                   cost of a shared-prefix item, in private tokens' streaming
                                   time                                                          */
     int32_t private_item_cost; /* 0 = default (192; 128 below 350 tokens per share and in steps without
-                                  shared-prefix work): fixed cost of a private item, same unit  */
+                                  shared-prefix work): fixed cost of a private item, same unit.
+                                  With this and private_merge_cost at their defaults, items of up to 128
+                                  tokens that single waves may run cost 160 and no merge in steps of up
+                                  to 700 tokens per share, and stay out of a pool whose size is the default */
     int32_t private_merge_cost; /* 0 = default (192 when the step has shared-prefix work, else none),
                                   -1 = none: extra cost of the private item that ends a sequence
                                   (as a rule it delivers the last partial and merges)           */

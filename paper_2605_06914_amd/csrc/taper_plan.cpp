@@ -78,7 +78,9 @@ struct Cost {
     int64_t merge = 0;  // extra cost of the item that ends a sequence: it arrives last as a rule and merges the partials
     int64_t per_branch = 0;  // further fixed cost for each of a shared item's branches
     // Short private segments are run by single waves, four side by side (order_solo_items), and merged by whoever comes later: they cost
-    // less than an item of the whole workgroup and no merge, and are not worth a claim from the pool.  In steps of long shares that is not
+    // no merge, and are not worth a claim from the pool; with it an item of the whole workgroup is 320 to 384.  (Where steps have no such
+    // merge cost, or short shares, `fixed` is 128: 160 is more than that, and still the better price there: with 128 35 random steps take 0.8 % more
+    // on average, from 5 % less to 9 % more.)  In steps of long shares that is not
     // so: their chain of dependent loads is several times as long on a saturated machine, and whoever finishes early takes them from the
     // pool (411 sequences of 12 to 22 tokens beside 8 requests of 4 to 6 branches 65 -> 41 us per layer, 30 requests of 14 branches of 1 or 2 tokens 66 -> 43,
     // 35 requests of 32 tokens and 9 branches of 11 30 -> 21; 100 us per layer where shares have 3600 tokens and 212 short
@@ -619,10 +621,14 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     }
     const Cost cost_shared = {opts && opts->shared_item_cost > 0 ? opts->shared_item_cost : (latency_bound ? 60 : 450), 0,
                               opts && opts->shared_item_cost > 0 ? 0 : (latency_bound ? 32 : 0)};
+    // (a caller's own costs are taken as they are, and what no single wave will run is priced as the workgroup's)
+    const bool own_costs = opts && (opts->private_item_cost > 0 || opts->private_merge_cost != 0);
+    const int solo_tokens = opts && opts->solo_item_tokens != 0 ? std::max(0, opts->solo_item_tokens) : 512;
+    const int brief_tokens = share_tokens <= kBriefShareTokens && !own_costs ? std::min(kBriefTokens, solo_tokens) : 0;
     const Cost cost_priv = {opts && opts->private_item_cost > 0 ? opts->private_item_cost : (shared.empty() || latency_bound ? 128 : 192),
                             opts && opts->private_merge_cost != 0 ? std::max(0, opts->private_merge_cost)
                                                                   : (shared.empty() ? 0 : 192),
-                            0, share_tokens <= kBriefShareTokens ? kBriefTokens : 0};
+                            0, brief_tokens};
     const int64_t shared_tail_discount = 3;  // blocks: about what merging a request's branches costs
     int64_t cost_total = 0;
     for (const Segment& s : shared) {
@@ -742,7 +748,7 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     std::stable_sort(p.items.begin() + p.part_start[n_parts], p.items.end(),
                      [](const taper_work_item& x, const taper_work_item& y) { return x.n_tokens > y.n_tokens; });
 
-    order_solo_items(n_seqs, opts && opts->solo_item_tokens != 0 ? opts->solo_item_tokens : 512, share_tokens <= kBriefShareTokens, &p);
+    order_solo_items(n_seqs, solo_tokens, share_tokens <= kBriefShareTokens, &p);
 
     // ---- partial rows and merge map
     int64_t rows = 0;

@@ -324,3 +324,14 @@ def test_short_steps_keep_their_merges_inside_the_attention_launch():
     ctx = Context(8, 1, 128, device=-1)
     assert build(structure_config3(), ctx).export()["merge_launch"] == 1
     ctx.close()
+
+
+def test_a_callers_costs_hold_for_short_items_too():
+    """100 sequences of 20 tokens (a block of 32 each): as many to a share as its size and the caller's item cost say."""
+    st = structure_custom(QWEN, [(20, [0])] * 100, seed=6)
+    full = lambda cost, share_cost: (1000 + share_cost) // (cost + 32)  # whole items in a share of 1000 tokens and an item's cost
+    for kw, per_share in ((dict(private_item_cost=1), full(1, 1)), (dict(private_item_cost=64), full(64, 64)),
+                          (dict(private_merge_cost=-1), full(128, 128)), (dict(solo_item_tokens=-1), full(128, 128)),
+                          (dict(solo_item_tokens=19), full(128, 128)), (dict(), full(160, 128))):
+        e = check_plan_against_oracle(st, min_share_tokens=1000, **kw)
+        assert len(e["part_start"]) - 1 == -(-100 // per_share), (kw, np.diff(e["part_start"]))
