@@ -23,7 +23,7 @@ def test_short_branches_beside_their_prefix(shape, partial_format):
     ctx = Context(*shape, device=0, partial_format=partial_format)
     hkv = shape[1]
     st, runs = b.structure, set()
-    for kw in (dict(), dict(target_workgroups=hkv), dict(target_workgroups=3 * hkv), dict(target_workgroups=6 * hkv, solo_item_tokens=100),
+    for kw in (dict(), dict(target_workgroups=hkv), dict(target_workgroups=3 * hkv), dict(target_workgroups=7 * hkv), dict(target_workgroups=6 * hkv, solo_item_tokens=100),
                dict(min_share_tokens=1, private_item_cost=1), dict(solo_item_tokens=-1)):
         got, lse, bits = run_gpu(ctx, b, **kw)
         assert_parity(got, ref, f"solo {shape} {partial_format} {kw}")
@@ -32,7 +32,7 @@ def test_short_branches_beside_their_prefix(shape, partial_format):
         runs |= {int(n) for q, n in enumerate(e["solo_items"]) if (kind[e["part_start"][q]:e["part_start"][q] + n] == 1).any()}
         assert np.abs(lse - ref_lse).max() <= 1e-3  # (fp32 sums of at most 768 terms)
         assert np.array_equal(run_gpu(ctx, b, **kw)[2], bits)
-    assert {1, 2, 3, 5} <= runs  # (runs with partials among them, of fewer items than waves and of more)
+    assert {1, 2, 3, 4, 5} <= runs  # (runs with partials among them, of fewer items than waves and of more)
     ctx.close()
 
 
