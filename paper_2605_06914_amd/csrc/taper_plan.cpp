@@ -656,15 +656,17 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     std::vector<Segment> pool;
     {
         int64_t want = tok_priv * pool_pct / 100;
+        size_t left = priv.size();
         for (size_t i = priv.size(); i-- > 0 && want >= kPrivateBlockTokens;) {
             Segment& s = priv[i];
             if (cost_priv.brief(s) && !(opts && opts->pool_pct > 0)) continue;  // (a claim would cost more than the item)
-            const bool last = shared.empty() && priv.size() == 1;  // (a launch has a workgroup per share: one stays)
+            const bool last = shared.empty() && left == 1;  // (a launch has a workgroup per share: one stays)
             if (s.n_tokens <= want + kPrivateBlockTokens && !last) {  // the whole segment
                 want -= s.n_tokens;
                 cost_total -= cost_priv.piece(s) + s.n_tokens + cost_priv.end(s, share_tokens);
                 pool.push_back(s);
-                priv.erase(priv.begin() + i);
+                s.n_tokens = 0;
+                --left;
             } else {  // its tail, from a block boundary
                 const int keep = (int)((s.n_tokens - want + kPrivateBlockTokens - 1) / kPrivateBlockTokens * kPrivateBlockTokens);
                 if (keep < s.n_tokens) {
@@ -678,6 +680,7 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
             }
         }
         std::reverse(pool.begin(), pool.end());
+        priv.erase(std::remove_if(priv.begin(), priv.end(), [](const Segment& s) { return s.n_tokens == 0; }), priv.end());
     }
     // A small step is not cut as finely as the grid allows: below a few hundred tokens per share the
     // time goes into the item ends.  Nor is a sequence cut into very many partials: up to some 64 are one trip of the merge launch, 32

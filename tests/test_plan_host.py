@@ -4,6 +4,7 @@ integer side.  No device call is made (host-only contexts)."""
 import ctypes
 import os
 import re
+import time
 
 import numpy as np
 import pytest
@@ -335,3 +336,28 @@ def test_a_callers_costs_hold_for_short_items_too():
                           (dict(solo_item_tokens=19), full(128, 128)), (dict(), full(160, 128))):
         e = check_plan_against_oracle(st, min_share_tokens=1000, **kw)
         assert len(e["part_start"]) - 1 == -(-100 // per_share), (kw, np.diff(e["part_start"]))
+
+
+def test_a_pool_taken_from_before_many_short_segments_costs_no_more_time():
+    """1500 sequences of 129 tokens, a quarter of which go to the pool, before 150000 branches of one token, which stay: the plan takes
+    about as long as with the sequences behind the branches, not a move of all branches for each."""
+    n_long, n_req, width = 1500, 12500, 12
+    ctx = Context(1, 1, 64, device=-1)
+
+    def best(long_first):
+        long_ = (np.full(n_long, 129), np.zeros(n_long), np.ones(n_long))
+        short = (np.ones(n_req * width), np.ones(n_req * width), np.tile([1] + [0] * (width - 1), n_req))
+        parts = [long_, short] if long_first else [short, long_]
+        prefix, suffix, opens = (np.concatenate([p[i] for p in parts]).astype(np.int32) for i in range(3))
+        table, times = np.zeros((len(prefix), 9), np.int32), []
+        for _ in range(3):
+            t0 = time.perf_counter()
+            plan = ctx.plan_build(table, np.cumsum(opens) - 1, prefix, suffix, 1)
+            times.append(time.perf_counter() - t0)
+            assert plan.export()["n_pool_items"] > 300
+            plan.free()
+        return min(times)
+
+    ahead, behind = best(True), best(False)
+    assert ahead < 2 * behind, (ahead, behind)
+    ctx.close()
