@@ -975,7 +975,10 @@ DEV void shared_stream(const StepArgs& a, const taper_work_item& item, const int
 template <int D, int NTW, int PF, bool ANY>
 DEV void shared_path(const StepArgs& a, const int part, const int hk, const int after, SharedSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int it0 = a.part_start[part], it1 = a.part_start[part + 1];
+    // (by scalar loads: behind run_share's asm statement the compiler takes memory for written and would use a vector load, 0.1 us more
+    // before the first block: tiny steps 7.2 -> 7.1 us.  Private shares, whose first page ids wait for other loads, are no faster for it)
+    typedef const __attribute__((address_space(4))) int32_t* scalar_row;
+    const int it0 = ((scalar_row)a.part_start)[part], it1 = ((scalar_row)a.part_start)[part + 1];
     for (int it = it0; it < it1; ++it) {
         const taper_work_item item = load_item(a, it);
         const int tid = opaque(threadIdx.x);

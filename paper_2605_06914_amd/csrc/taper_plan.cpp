@@ -315,7 +315,7 @@ double expected_us(const taper_attn_config& cfg, const HostPlan& p, int64_t roun
 // worst the other way 82.8 / 79.8; 3 and 4 rounds in steps that end all at once (below 350 tokens per share) 20.4 / 27.4, 17 / 21.7, worst 15.0 /
 // 13.6; in longer ones, where most merges are hidden behind other workgroups' streaming, 18
 // of 37 slower (119.5 / 105.1 at worst) and 19 faster (46.4 / 51.4 at best).
-// A launch is also 4 us of the host's time, which a step of several layers with their appends waits for where the layers are short (15.5 us
+// A launch is also 3 us of the host's time (a call 8.5 instead of 5.9), which a step of several layers with their appends waits for where the layers are short (15.5 us
 // per layer with one launch, 20 with two): steps expected to take less than kMergeLaunchFromUs would gain 0.7 us per call (11 of 113, from -2
 // to 2) and lose 2 to 4.5 per layer of such a loop (2 requests of 1100 to 1600 tokens and 3 of 3 to 5 branches, four layers: 68 us, 84
 // with the launch).  Just above that line loops of two or three layers still lose (27 -> 29.6, 23.6 -> 26.3 us per layer), calls alone gain (10.6 / 13.2, 12.3 /
