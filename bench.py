@@ -3,7 +3,8 @@
 
 A *step* is one decode step of a layer stack over one synthetic batch: the index
 resolution / plan build (once per step, inside the timed region) followed by the
-attention of every layer (one launch: shared-prefix work, private work, merge), each
+attention of every layer (one launch: shared-prefix work, private work, merge; the merges of
+steps of many partials are a second one), each
 layer reading its own KV pool.  Inputs are resident in HBM before the timed
 region starts.  Prints ONE JSON line.
 

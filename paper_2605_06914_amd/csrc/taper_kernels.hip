@@ -18,7 +18,8 @@
 // (scale*log2(e) folded in), running sum l, unnormalised O.  Partials of the KV
 // chunks of a sequence (m, l in fp32; O / l in fp32 or, by default, in half precision with a
 // per-row power-of-two scale) are combined through their (m, l) by the workgroup that delivers
-// the sequence's last partial (merge_rows).
+// the sequence's last partial (merge_rows) or, in steps of many partials, by a launch of their own
+// behind the attention launch (merge_kernel).
 #include <type_traits>
 
 #include "taper_internal.h"
@@ -107,7 +108,7 @@ DEV void settle() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Partials travel between workgroups inside one launch.  Workgroups may sit on
+// Partials travel between workgroups inside one launch (to the merge launch, where a step has one, in the same way).  Workgroups may sit on
 // different XCDs, whose L2s are not kept coherent for ordinary cached accesses,
 // and a device-scope fence per workgroup (L2 write-back + invalidate) is far too
 // slow.  So every partial word is written and read with device-scope atomic
@@ -1008,7 +1009,7 @@ DEV void shared_path(const StepArgs& a, const int part, const int hk, const int 
 }
 
 // ---------------------------------------------------------------------------
-// One launch per layer: workgroup (share, kv head).  Shares below n_parts_shared
+// The attention launch of a layer: workgroup (share, kv head).  Shares below n_parts_shared
 // stream shared prefixes, the others private tokens; both kinds run side by side.
 // ---------------------------------------------------------------------------
 template <int D>

@@ -158,8 +158,8 @@ int partition_fill(const std::vector<Segment>& segs, int64_t quota, int blk, con
 // some k * k = kTokensPerMergedRow * n / R.  Where one workgroup makes the merges (the last to arrive, for every branch of the
 // request), a token costs a shared workgroup alone 20 ns, a row and item 7 ns (5 branches x 16 heads: 109 us for 195 items), and 4
 // was the best constant (24000 tokens of 2 / 5 / 12 branches on one kv head of 16 query heads 33 / 46.5 / 81 us; 2.9: 32 / 49 / 85; 8: 38 /
-// 48 / 83).  A step of many items has its merges in a launch of their own, where a row is cheaper: with 5 instead of 4 the mixed
-// batch on one kv head takes 20.3 instead of 21.0, 13 branches x 8 heads of 25000 tokens 29.6 / 31.4, 13 x 16 of 4900 25.2 / 27.6; 8 would
+// 48 / 83).  A step of so many items that this decides its cut has its merges in a launch of their own (all of 76 among 1250 random steps),
+// where a row is cheaper: with 5 instead of 4 the mixed batch on one kv head takes 20.3 instead of 21.0, 13 branches x 8 heads of 25000 tokens 29.6 / 31.4, 13 x 16 of 4900 25.2 / 27.6; 8 would
 // give another 2 to 12 % to requests of ten branches and take 4 % from narrow ones.
 int64_t least_tokens(const Segment& s, int gqa) {
     return (int64_t)std::sqrt((double)s.n_tokens * s.n_branch * gqa / kTokensPerMergedRow);
@@ -683,9 +683,11 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
         priv.erase(std::remove_if(priv.begin(), priv.end(), [](const Segment& s) { return s.n_tokens == 0; }), priv.end());
     }
     // A small step is not cut as finely as the grid allows: below a few hundred tokens per share the
-    // time goes into the item ends.  Nor is a sequence cut into very many partials: up to some 64 are one trip of the merge launch, 32
-    // beside shared prefixes, whose own cuts come on top (one sequence of 15000 tokens on 2 kv heads 12.4 -> 10.2 us, 12 requests of 14 branches or
-    // reduced and 27000 tokens on one 32.5 -> 23.8 against 16 partials at most; two small steps the other way, 28.6 -> 30.1 and 15.6 -> 16.4).
+    // time goes into the item ends.  Nor is a sequence cut into very many partials: up to 32 are one trip of the merge launch and 64 two; half
+    // as many beside shared prefixes, whose own cuts come on top (one sequence of 15000 tokens on 2 kv heads 12.4 -> 10.2 us, 12 requests of
+    // 14 branches or reduced and 27000 tokens on one 32.5 -> 23.8 against 16 partials at most; two small steps the other way, 28.6 -> 30.1 and
+    // 15.6 -> 16.4).  Where the merges stay inside the launch as well: 26.4 -> 24.4, 34.0 -> 30.3, 34.4 -> 31.5; two even, and two of ten or
+    // eleven sequences of some 3000 tokens on one kv head 9.4 -> 9.8 and 9.5 -> 9.9 (a third round of merges).
     int64_t longest = 0;
     for (const Segment& s : priv) longest = std::max<int64_t>(longest, s.n_tokens);
     const int64_t min_share =

@@ -7,7 +7,8 @@
  * zeroed by the caller before each launch): the 100 MHz wall clock when the workgroup
  * started, when its own share was done (when it first turned to the pool; without a pool: when a
  * shared-prefix share was done, or a private one started), when it
- * left the kernel, and the clock ticks it spent merging.  NULL switches tracing off.
+ * left the kernel, and the clock ticks it spent merging behind shared items and private ones of
+ * the whole workgroup (nothing where merges are a launch of their own).  NULL switches tracing off.
  */
 #ifndef TAPER_TRACE_H
 #define TAPER_TRACE_H

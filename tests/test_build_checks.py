@@ -124,6 +124,13 @@ def test_every_launch_the_host_code_makes_is_a_strong_symbol(tmp_path):
     assert set(stubs) == set(calls) and set(stubs.values()) == {"T"}, (stubs, calls)
 
 
+def test_the_merge_kernels_use_no_scratch_memory_and_fit_sixteen_waves(compiled):
+    """A workgroup is a wave per query head, up to 16: 128 vector registers each."""
+    _, remarks = compiled
+    found = re.findall(r"Function Name: (\S*merge_kernel\S*)(?:.|\n)*?VGPRs: (\d+)(?:.|\n)*?ScratchSize \[bytes/lane\]: (\d+)", remarks)
+    assert len(found) == 4 and all(int(v) <= 128 and s == "0" for _, v, s in found), found
+
+
 def test_the_kernels_for_pools_that_start_anywhere_meet_the_same_checks(compiled):
     asm, remarks = compiled
     spilled = re.findall(r"Function Name: (\S*any_start_kernel\S*)(?:.|\n)*?ScratchSize \[bytes/lane\]: (\d+)", remarks)
