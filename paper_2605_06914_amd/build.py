@@ -14,6 +14,8 @@ HIP_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-x", "hip",
     # never let the compiler form packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # leading kernel arguments arrive in registers (up to 14 words)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-fvisibility=hidden", "-Wall", "-Wno-unused-command-line-argument", "-Wno-unknown-attributes",
 ]
 

@@ -72,8 +72,7 @@ struct Workspace {
 struct DeviceImage {
     const int32_t* bt = nullptr;
     const taper_work_item* items = nullptr;
-    const int32_t* part_start = nullptr;
-    const int32_t* part_turn = nullptr;
+    const taper::ShareStart* starts = nullptr;
     const int32_t* merge_start = nullptr;
     const taper_merge_entry* merge = nullptr;
     const int32_t* prefix_len = nullptr;
@@ -151,19 +150,18 @@ int acquire_buffers(taper_ctx* ctx, size_t bytes, PlanBuffers* out) {
     return TAPER_OK;
 }
 
-// The arrays of a host plan as one image: bt | items | part_start, part_turn | merge_start | merge | prefix_len |
-// seg_start | ctx_len | seg_len | seg_page0, each piece 256-byte aligned but for part_turn, which follows part_start directly.
+// The arrays of a host plan as one image: starts | bt | items | merge_start | merge | prefix_len |
+// seg_start | ctx_len | seg_len | seg_page0, each piece 256-byte aligned.
 struct ImagePiece {
     const void* src;
     size_t bytes, off;
 };
-constexpr int kImagePieces = 11, kPartStartPiece = 2;
+constexpr int kImagePieces = 10;
 size_t layout_image(const taper::HostPlan& h, ImagePiece (&pieces)[kImagePieces]) {
     const ImagePiece init[kImagePieces] = {
+        {h.starts.data(), h.starts.size() * sizeof(taper::ShareStart), 0},
         {h.block_table.data(), h.block_table.size() * sizeof(int32_t), 0},
         {h.items.data(), h.items.size() * sizeof(taper_work_item), 0},
-        {h.part_start.data(), h.part_start.size() * sizeof(int32_t), 0},
-        {h.part_turn.data(), h.part_turn.size() * sizeof(int32_t), 0},
         {h.merge_start.data(), h.merge_start.size() * sizeof(int32_t), 0},
         {h.merge.data(), h.merge.size() * sizeof(taper_merge_entry), 0},
         {h.prefix_len.data(), h.prefix_len.size() * sizeof(int32_t), 0},
@@ -176,10 +174,11 @@ size_t layout_image(const taper::HostPlan& h, ImagePiece (&pieces)[kImagePieces]
     for (int i = 0; i < kImagePieces; ++i) {
         pieces[i] = init[i];
         pieces[i].off = total;
-        total = i == kPartStartPiece ? total + pieces[i].bytes : align_up(total + std::max<size_t>(pieces[i].bytes, 16), 256);
+        total = align_up(total + std::max<size_t>(pieces[i].bytes, 16), 256);
     }
     return total;
 }
+size_t starts_bytes(const ImagePiece (&pieces)[kImagePieces]) { return pieces[1].off; }  // (they come first)
 void write_image(const ImagePiece (&pieces)[kImagePieces], void* host_dst) {
     for (const ImagePiece& p : pieces)
         if (p.bytes) std::memcpy((char*)host_dst + p.off, p.src, p.bytes);
@@ -187,17 +186,16 @@ void write_image(const ImagePiece (&pieces)[kImagePieces], void* host_dst) {
 DeviceImage bind_image(const ImagePiece (&pieces)[kImagePieces], void* dev_base) {
     char* d = (char*)dev_base;
     DeviceImage m;
-    m.bt = (const int32_t*)(d + pieces[0].off);
-    m.items = (const taper_work_item*)(d + pieces[1].off);
-    m.part_start = (const int32_t*)(d + pieces[2].off);
-    m.part_turn = (const int32_t*)(d + pieces[3].off);
-    m.merge_start = (const int32_t*)(d + pieces[4].off);
-    m.merge = (const taper_merge_entry*)(d + pieces[5].off);
-    m.prefix_len = (const int32_t*)(d + pieces[6].off);
-    m.seg_start = (const int32_t*)(d + pieces[7].off);
-    m.ctx_len = (const int32_t*)(d + pieces[8].off);
-    m.seg_len = (const int32_t*)(d + pieces[9].off);
-    m.seg_page0 = (const int32_t*)(d + pieces[10].off);
+    m.starts = (const taper::ShareStart*)(d + pieces[0].off);
+    m.bt = (const int32_t*)(d + pieces[1].off);
+    m.items = (const taper_work_item*)(d + pieces[2].off);
+    m.merge_start = (const int32_t*)(d + pieces[3].off);
+    m.merge = (const taper_merge_entry*)(d + pieces[4].off);
+    m.prefix_len = (const int32_t*)(d + pieces[5].off);
+    m.seg_start = (const int32_t*)(d + pieces[6].off);
+    m.ctx_len = (const int32_t*)(d + pieces[7].off);
+    m.seg_len = (const int32_t*)(d + pieces[8].off);
+    m.seg_page0 = (const int32_t*)(d + pieces[9].off);
     return m;
 }
 
@@ -288,8 +286,7 @@ taper::StepArgs make_args(const taper_ctx* ctx, const taper::HostPlan& h, const 
     a.lse = lse;
     a.bt = img.bt;
     a.items = img.items;
-    a.part_start = img.part_start;
-    a.part_turn = img.part_turn;
+    a.starts = img.starts;
     a.merge_start = img.merge_start;
     a.merge = img.merge;
     a.prefix_len = img.prefix_len;
@@ -360,13 +357,13 @@ int static_plan(const taper_ctx* ctx, int n_seqs, int64_t n_pool_pages, const in
         if (st != TAPER_OK) return fail(st, err);
         lay->image = layout_image(*h, pieces);
         lay->workspace = layout_workspace(ctx->cfg, h->n_partial_rows, lay->counters, &lay->ml_off, &lay->o_off);
-        if (lay->image <= kStaticImageBytes && lay->image + lay->workspace <= taper::kStaticScratchBytes) return TAPER_OK;
-        const size_t cut_bytes = h->items.size() * sizeof(taper_work_item) + h->merge.size() * sizeof(taper_merge_entry) +
-                                 (h->part_start.size() + h->part_turn.size()) * sizeof(int32_t);
-        if (lay->image > kStaticImageBytes + cut_bytes || o.target_workgroups <= ctx->cfg.n_kv_heads)
-            return fail(TAPER_EINVAL, "step too large for the static scratch array: plan image " + std::to_string(lay->image) +
+        const size_t starts = starts_bytes(pieces), image = lay->image - starts;  // (the start records have room of their own in the array)
+        if (starts <= taper::kStaticStartsBytes && image <= kStaticImageBytes && image + lay->workspace <= taper::kStaticScratchBytes) return TAPER_OK;
+        const size_t cut_bytes = h->items.size() * sizeof(taper_work_item) + h->merge.size() * sizeof(taper_merge_entry);
+        if (image > kStaticImageBytes + cut_bytes || o.target_workgroups <= ctx->cfg.n_kv_heads)
+            return fail(TAPER_EINVAL, "step too large for the static scratch array: plan image " + std::to_string(image) +
                                           " bytes (limit " + std::to_string(kStaticImageBytes) + "), image + workspace " +
-                                          std::to_string(lay->image + lay->workspace) + " bytes (limit " +
+                                          std::to_string(image + lay->workspace) + " bytes (limit " +
                                           std::to_string(taper::kStaticScratchBytes) + ")");
         if (o.pool_pct == 0 && h->n_pool_items > 0) o.pool_pct = -1;
         else o.target_workgroups /= 2;
@@ -494,7 +491,7 @@ int taper_create(const taper_attn_config* cfg, taper_ctx** out_ctx) {
             ctx->default_workgroups = 2 * cus;  // the decode kernel keeps two workgroups resident per compute unit
         // set-up of the entry point that allocates nothing (cfg->device is current)
         e = taper::static_scratch(cfg->device, &ctx->static_scratch);
-        if (e == hipSuccess) e = hipHostMalloc(&ctx->static_staging, kStaticImageBytes, hipHostMallocDefault);
+        if (e == hipSuccess) e = hipHostMalloc(&ctx->static_staging, taper::kStaticStartsBytes + kStaticImageBytes, hipHostMallocDefault);
         if (e == hipSuccess) e = hipHostGetDevicePointer(&ctx->static_staging_dev, ctx->static_staging, 0);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->static_uploaded, hipEventDisableTiming);
         if (e != hipSuccess) {  // the other entry points do not need it: the static one reports this

@@ -232,8 +232,64 @@ DEV void zero_tail(bf16x4 (&va)[DT], bf16x4 (&vb)[DT], int qd, int n_valid) {
 
 // A work item by one scalar load (the compiler is not told that nothing here writes to the plan, and would use vector loads).
 typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(4))) int32_t* scalar_row;
 DEV taper_work_item load_item(const StepArgs& a, const int it) {
     return __builtin_bit_cast(taper_work_item, ((const __attribute__((address_space(4))) i32x8*)a.items)[it]);
+}
+// What a launch's first loads need, beside a wave's start record: leading kernel arguments, which arrive in registers.
+struct Inputs {
+    const ShareStart* starts;
+    const void *kv, *q;
+    int n_kv_heads, n_q_heads, gqa, n_parts_shared;
+};
+// A wave's start record, by scalar loads side by side.  A launch's first KV loads used to wait for five trips to memory one after the other
+// (arguments, the share's range, its item, the block table, the pool), 0.2 us each while the plan is in the L2; with the record's address in
+// registers at the start there are two.  tiny step 7.08 -> 6.70 us, one request of 2048 tokens 8.01 -> 7.73, 11.7 -> 11.3, 20.7 -> 20.2, 57.9 -> 56.2;
+// shared items of all sizes take their first four blocks' page ids by one trip instead of one per block.
+struct Start {
+    int first, end, turn, n_solo;
+    taper_work_item item;
+    i32x4 page, more;
+};
+#define CONSTANT const __attribute__((address_space(4)))
+DEV Start load_start(const Inputs& in, const int part, const int wave) {
+    const auto share = (CONSTANT ShareStart*)in.starts + part;
+    const auto r = (CONSTANT char*)&share->wave[0] + wave * sizeof(WaveStart);
+    const i32x4 head = *(CONSTANT i32x4*)r;
+    Start s;
+    s.first = head[0];
+    s.end = head[1];
+    s.turn = head[2];
+    s.n_solo = head[3];
+    s.item = __builtin_bit_cast(taper_work_item, *(CONSTANT i32x8*)(r + 16));
+    s.page = *(CONSTANT i32x4*)(r + 48);
+    s.more = *(CONSTANT i32x4*)&share->more;
+    // (all of it is asked for here, and the other arguments' cache lines with it, which later loads then find)
+    const auto args = (CONSTANT int*)__builtin_amdgcn_kernarg_segment_ptr();
+    const int line1 = args[16], line2 = args[32];
+    asm volatile("" : "+s"(s.item.seq0), "+s"(s.page), "+s"(s.more) : "s"(line1), "s"(line2));
+    return s;
+}
+// The other arguments, read from where they lie as they are needed.  (As a parameter that is used they are all loaded at the kernel's start,
+// and waited for, 60 registers of them, before the start record is asked for.)
+DEV const StepArgs& step_args() {
+    constexpr int at = (sizeof(Inputs) + alignof(StepArgs) - 1) / alignof(StepArgs) * alignof(StepArgs);
+    return *(const StepArgs*)((CONSTANT char*)__builtin_amdgcn_kernarg_segment_ptr() + at);
+}
+DEV scalar_row table_row(const StepArgs& a, const taper_work_item& item) {
+    return (scalar_row)(a.bt + (int64_t)item.seq0 * a.bt_stride + item.page0);
+}
+// Pages of blocks b and b + step of a private item (past the last page: the last page).
+DEV i32x4 private_pages(const StepArgs& a, const taper_work_item& item, const int b, const int step) {
+    const scalar_row row = table_row(a, item);
+    const int last = ((item.n_tokens + 15) >> 4) - 1;
+    i32x4 p;
+    p[0] = row[min(2 * b, last)];
+    p[1] = row[min(2 * b + 1, last)];
+    p[2] = row[min(2 * (b + step), last)];
+    p[3] = row[min(2 * (b + step) + 1, last)];
+    return p;
 }
 
 // (No branches: a lane without a value asks for one past the descriptor's end and gets zeros, so nothing is waited
@@ -433,19 +489,17 @@ struct PrivateSmem {
 // counts: 155 tokens per share 18.5 / 17.2, 577 31.5 / 30.4, 57 12.7 / 12.1, with 2 to 3 % the other way at others.  At
 // head_dim 64 a block holds half the bytes and the wait weighs more (mixed batch 46.3 / 45.4).
 template <int D, bool SOLO, int PF, bool HOLD>
-DEV void private_item(const StepArgs& a, const int it, const int hk, const int after, PrivateSmem<D>& sm) {
+DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item& item, const i32x4 page, const int hk, const int after, PrivateSmem<D>& sm) {
     constexpr int KS = D / 32, DT = D / 16, TILE = 16 * D;
     auto& sm_o = sm.o;
     auto& sm_ml = sm.ml;
     const int lane = opaque(threadIdx.x) & 63;  // (opaque: per-lane constants are recomputed per item, not kept for the whole kernel)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, qd = lane >> 4;
-    const int Hkv = a.n_kv_heads, g = a.gqa;
+    const int Hkv = in.n_kv_heads, g = in.gqa;
     const float c = a.scale_log2e;
     {
-        const taper_work_item item = load_item(a, it);
-        typedef const __attribute__((address_space(4))) int32_t* scalar_row;
-        const scalar_row row = (scalar_row)(a.bt + (int64_t)item.seq0 * a.bt_stride + item.page0);
+        const scalar_row row = table_row(a, item);
         const int n_tok = item.n_tokens;
         const int n_pages = (n_tok + 15) >> 4;
         const int n_blocks = (n_tok + 31) >> 5;
@@ -455,7 +509,7 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, const int a
 
         bf16x8 qf[KS];  // (lane columns past the last query head repeat the first; not stored)
         {
-            const __bf16* qrow = (const __bf16*)a.q + ((int64_t)item.seq0 * a.n_q_heads + hk * g + (n < g ? n : 0)) * D;
+            const __bf16* qrow = (const __bf16*)in.q + ((int64_t)item.seq0 * in.n_q_heads + hk * g + (n < g ? n : 0)) * D;
 #pragma unroll
             for (int j = 0; j < KS; ++j) qf[j] = *(const bf16x8*)(qrow + 8 * (4 * j + qd));
         }
@@ -465,9 +519,9 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, const int a
         for (int dt = 0; dt < DT; ++dt) O[dt] = (f32x4)(0.f);
 
         const int64_t page_bytes = (int64_t)Hkv * TILE * 4;
-        const char* kvb = (const char*)a.kv + (int64_t)hk * TILE * 2;
+        const char* kvb = (const char*)in.kv + (int64_t)hk * TILE * 2;
         const unsigned koff = lane * 16, voff = (qd * (4 * D) + n * 4) * 2;
-        int pid_a = 0, pid_b = 0;  // the pages of the block loaded next
+        int pid_a = page[0], pid_b = page[1];  // the pages of the block loaded next
         auto fetch_ids = [&](int b) {
             const int ia = 2 * b < n_pages ? 2 * b : n_pages - 1, ib = 2 * b + 1 < n_pages ? 2 * b + 1 : n_pages - 1;
             pid_a = row[ia];
@@ -513,9 +567,9 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, const int a
         int b = SOLO ? 0 : wave;
         if (b < n_blocks) {
             KVRegs<D> r0;
-            fetch_ids(b);
             load_block(r0);
-            fetch_ids(b + STEP);
+            pid_a = page[2];
+            pid_b = page[3];
             while (b + 2 * STEP < n_blocks) {
                 KVRegs<D> r1;
                 hold();
@@ -551,7 +605,7 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, const int a
                 sc = row_scale(max_lane_groups(mx) * inv);
             }
             if (n < g) {
-                __bf16* orow = (__bf16*)a.out + ((int64_t)item.seq0 * a.n_q_heads + h) * D;
+                __bf16* orow = (__bf16*)a.out + ((int64_t)item.seq0 * in.n_q_heads + h) * D;
                 const int64_t slot = (int64_t)item.part_base + h;
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
@@ -565,7 +619,7 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, const int a
                 }
                 if (qd == 0) {
                     if (!sole) stats_store<PF>(a.ws_ml + slot, m, l, sc.x);
-                    else if (a.lse) a.lse[(int64_t)item.seq0 * a.n_q_heads + h] = (m + __log2f(l)) * 0.6931471805599453f;
+                    else if (a.lse) a.lse[(int64_t)item.seq0 * in.n_q_heads + h] = (m + __log2f(l)) * 0.6931471805599453f;
                 }
             }
             return;
@@ -599,8 +653,8 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, const int a
             if (sole) {
                 const int h = hk * g + r;
                 const f32x4 res = acc * (1.0f / L);
-                *(bf16x4*)((__bf16*)a.out + ((int64_t)item.seq0 * a.n_q_heads + h) * D + 4 * d4) = __builtin_convertvector(res, bf16x4);
-                if (a.lse && d4 == 0) a.lse[(int64_t)item.seq0 * a.n_q_heads + h] = (M + __log2f(L)) * 0.6931471805599453f;
+                *(bf16x4*)((__bf16*)a.out + ((int64_t)item.seq0 * in.n_q_heads + h) * D + 4 * d4) = __builtin_convertvector(res, bf16x4);
+                if (a.lse && d4 == 0) a.lse[(int64_t)item.seq0 * in.n_q_heads + h] = (M + __log2f(L)) * 0.6931471805599453f;
                 continue;
             }
             const int64_t slot = (int64_t)item.part_base + hk * g + r;
@@ -639,11 +693,19 @@ DEV void private_item(const StepArgs& a, const int it, const int hk, const int a
 // 0.3 us, a barrier and a counter, and evened out nothing that was seen).  Their partials are announced together; the sequences that are then complete (few: what the other items of a step deliver comes later as a rule) are
 // merged by a wave each.  `announce`: there are partials among them, and merges are made in this launch.
 template <int D, int PF>
-DEV void solo_run(const StepArgs& a, const int first, const int end, const int hk, const bool announce, PrivateSmem<D>& sm) {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+DEV void solo_run(const StepArgs& a, const Inputs& in, const Start& start, const int end, const int hk, const bool announce, PrivateSmem<D>& sm) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), first = start.first;
+    taper_work_item item = start.item;
+    i32x4 page = start.page;
     // (back and forth: the wave with the longest item of one round has the shortest of the next)
-    for (int k = first, turn = wave; k < end; k += 4, turn ^= 3)
-        if (k + turn < end) private_item<D, true, PF, false>(a, k + turn, hk, 0, sm);
+    for (int k = first, turn = wave; k < end; k += 4, turn ^= 3) {
+        if (k + turn >= end) continue;
+        if (k != first) {
+            item = load_item(a, k + turn);
+            page = private_pages(a, item, 0, 1);
+        }
+        private_item<D, true, PF, false>(a, in, item, page, hk, 0, sm);
+    }
     if (!announce) {
         __syncthreads();
         return;
@@ -680,10 +742,16 @@ DEV void solo_run(const StepArgs& a, const int first, const int end, const int h
 // the pool; the one that makes the last of those puts the counter back to zero for the next
 // launch.
 template <int D, int PF, bool HOLD>
-DEV void private_items(const StepArgs& a, int it0, const int solo_end, const bool announce, const int it1, const int hk, const int after, PrivateSmem<D>& sm) {
-    const int wgs_per_head = a.n_parts_shared + a.n_parts_private;  // = gridDim.x / n_kv_heads
+DEV void private_items(const StepArgs& a, const Inputs& in, const Start& start, const bool announce, const int hk, const int after, PrivateSmem<D>& sm) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int it0 = start.first;
+    const int solo_end = it0 + start.n_solo, it1 = start.end;
+    taper_work_item item = start.item;
+    i32x4 page = start.page;
+    bool given = it0 < it1 && it0 == solo_end;  // the first item is the start record's
+    const int wgs_per_head = in.n_parts_shared + a.n_parts_private;  // = gridDim.x / n_kv_heads
     if (it0 < solo_end) {
-        solo_run<D, PF>(a, it0, solo_end, hk, announce, sm);
+        solo_run<D, PF>(a, in, start, solo_end, hk, announce, sm);
         it0 = solo_end;
     }
 #ifdef TAPER_WG_TRACE
@@ -710,7 +778,12 @@ DEV void private_items(const StepArgs& a, int it0, const int solo_end, const boo
             }
             it = a.pool_first + i;
         }
-        private_item<D, false, PF, HOLD>(a, it, hk, after, sm);
+        if (!given) {
+            item = load_item(a, it);
+            page = private_pages(a, item, wave, 4);
+        }
+        given = false;
+        private_item<D, false, PF, HOLD>(a, in, item, page, hk, after, sm);
     }
 }
 
@@ -817,18 +890,17 @@ DEV void store_shared_partials(const StepArgs& a, const taper_work_item& item, c
 // Streams the item's tokens against the NA tiles wave, wave + 4, ... of its rows and stores their partial rows.
 // Every wave of the workgroup takes its part in staging and meets the others once per block, whatever its NA.
 template <int D, int NA, int PF, bool ANY>
-DEV void shared_stream(const StepArgs& a, const taper_work_item& item, const int hk, SharedSmem<D>& sm, const int tid,
-                       const int wave) {
+DEV void shared_stream(const StepArgs& a, const Inputs& in, const taper_work_item& item, const i32x4 page, const i32x4 page2, const int hk,
+                       SharedSmem<D>& sm, const int tid, const int wave) {
     typedef SharedSmem<D> Sm;
     constexpr int KS = D / 32, DT = D / 16, NT = NA ? NA : 1, QB = 8 * D;  // QB: bytes of a 4-token quarter of a V tile
     constexpr int LOADS = 4;  // wave-level loads per wave and block
     const int lane = tid & 63, n = lane & 15, qd = lane >> 4;
-    const int Hkv = a.n_kv_heads, g = a.gqa;
+    const int Hkv = in.n_kv_heads, g = in.gqa;
     const int64_t page_bytes = (int64_t)Hkv * Sm::PAGE_BYTES;
-    const char* kvb = (const char*)a.kv + (int64_t)hk * Sm::TILE_BYTES;
+    const char* kvb = (const char*)in.kv + (int64_t)hk * Sm::TILE_BYTES;
     const float c = a.scale_log2e;
-    typedef const __attribute__((address_space(4))) int32_t* scalar_row;  // (wave-uniform: page ids come by scalar loads)
-    const scalar_row row = (scalar_row)(a.bt + (int64_t)item.seq0 * a.bt_stride + item.page0);
+    const scalar_row row = table_row(a, item);  // (wave-uniform: page ids come by scalar loads)
     const int n_tok = item.n_tokens, n_pages = (n_tok + 15) >> 4, n_blocks = (n_tok + Sm::TOKENS - 1) / Sm::TOKENS;
     const int R = item.n_branch * g;
 
@@ -840,7 +912,7 @@ DEV void shared_stream(const StepArgs& a, const taper_work_item& item, const int
 #pragma unroll
         for (int k = 0; k < NA; ++k) {
             const int r = 16 * (wave + 4 * k) + n, rr = r < R ? r : 0;  // (lane columns past the last row repeat the first; not stored)
-            const __bf16* qrow = (const __bf16*)a.q + ((int64_t)(item.seq0 + rr / g) * a.n_q_heads + hk * g + rr % g) * D;
+            const __bf16* qrow = (const __bf16*)in.q + ((int64_t)(item.seq0 + rr / g) * in.n_q_heads + hk * g + rr % g) * D;
 #pragma unroll
             for (int j = 0; j < KS; ++j) qf[k][j] = *(const bf16x8*)(qrow + 8 * (4 * j + qd));
             m[k] = -INFINITY;
@@ -944,11 +1016,15 @@ DEV void shared_stream(const StepArgs& a, const taper_work_item& item, const int
 
     // (the previous item's LDS reads of these buffers ended before its closing barriers)
 #pragma unroll
-    for (int b = 0; b < Sm::RING - 1; ++b) {
-        fetch_ids(b);
-        if (b < n_blocks) stage(b);
+    for (int b = 0; b < Sm::RING; ++b) {
+        if constexpr (D == 128) {
+            pid[0] = b < 2 ? page[2 * (b & 1)] : page2[2 * (b & 1)];
+            pid[1] = b < 2 ? page[2 * (b & 1) + 1] : page2[2 * (b & 1) + 1];
+        } else {
+            pid[0] = page[b];
+        }
+        if (b < Sm::RING - 1 && b < n_blocks) stage(b);
     }
-    fetch_ids(Sm::RING - 1);
     meta_store(sm.meta, mr, item.n_branch, tid);
     // (the queries' loads are waited for here: inside the loop that wait would also drain the blocks in flight, every time)
     if constexpr (NA > 0) {
@@ -974,21 +1050,29 @@ DEV void shared_stream(const StepArgs& a, const taper_work_item& item, const int
 }
 
 template <int D, int NTW, int PF, bool ANY>
-DEV void shared_path(const StepArgs& a, const int part, const int hk, const int after, SharedSmem<D>& sm) {
+DEV void shared_path(const StepArgs& a, const Inputs& in, const Start& start, const int hk, const int after, SharedSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // (by scalar loads: behind run_share's asm statement the compiler takes memory for written and would use a vector load, 0.1 us more
-    // before the first block: tiny steps 7.2 -> 7.1 us.  Private shares, whose first page ids wait for other loads, are no faster for it)
-    typedef const __attribute__((address_space(4))) int32_t* scalar_row;
-    const int it0 = ((scalar_row)a.part_start)[part], it1 = ((scalar_row)a.part_start)[part + 1];
+    const int it0 = start.first, it1 = start.end;
+    taper_work_item item = start.item;
+    i32x4 page = start.page, page2 = start.more;
     for (int it = it0; it < it1; ++it) {
-        const taper_work_item item = load_item(a, it);
+        if (it != it0) {
+            item = load_item(a, it);
+            const scalar_row row = table_row(a, item);
+            const int last = ((item.n_tokens + 15) >> 4) - 1;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                page[i] = row[min(D == 128 ? i : 4 * i + wave, last)];
+                if (D == 128) page2[i] = row[min(4 + i, last)];
+            }
+        }
         const int tid = opaque(threadIdx.x);
-        const int tiles = (item.n_branch * a.gqa + 15) >> 4;
+        const int tiles = (item.n_branch * in.gqa + 15) >> 4;
         const int n_act = (tiles - wave + 3) >> 2;  // tiles wave, wave + 4, ...; 0 for a wave past the last tile (tiles >= 1)
-        if (NTW >= 3 && n_act >= 3) shared_stream<D, NTW >= 3 ? 3 : 1, PF, ANY>(a, item, hk, sm, tid, wave);
-        else if (NTW >= 2 && n_act == 2) shared_stream<D, NTW >= 2 ? 2 : 1, PF, ANY>(a, item, hk, sm, tid, wave);
-        else if (n_act == 1) shared_stream<D, 1, PF, ANY>(a, item, hk, sm, tid, wave);
-        else shared_stream<D, 0, PF, ANY>(a, item, hk, sm, tid, wave);
+        if (NTW >= 3 && n_act >= 3) shared_stream<D, NTW >= 3 ? 3 : 1, PF, ANY>(a, in, item, page, page2, hk, sm, tid, wave);
+        else if (NTW >= 2 && n_act == 2) shared_stream<D, NTW >= 2 ? 2 : 1, PF, ANY>(a, in, item, page, page2, hk, sm, tid, wave);
+        else if (n_act == 1) shared_stream<D, 1, PF, ANY>(a, in, item, page, page2, hk, sm, tid, wave);
+        else shared_stream<D, 0, PF, ANY>(a, in, item, page, page2, hk, sm, tid, wave);
         if (after) {
             __syncthreads();  // the ring is free for the next item
             continue;
@@ -1019,49 +1103,43 @@ union StepSmem {
 };
 // ALLP: a launch without shared-prefix work (no shared path in the kernel).  ANY: the pool may start at any address.
 template <int D, int NTW, int PF, bool ALLP, bool ANY>
-DEV void run_share(const StepArgs& a, char* smem_raw) {
-    const int part = blockIdx.x / a.n_kv_heads;
-    const int turn = a.part_turn[part], hk = (blockIdx.x + (turn & kPartTurnMask)) % a.n_kv_heads;
+DEV void run_share(const StepArgs& a, const Inputs& in, char* smem_raw) {
+    const int part = blockIdx.x / in.n_kv_heads;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Start start = load_start(in, part, wave);
+    int hk = blockIdx.x - part * in.n_kv_heads + (start.turn & kPartTurnMask);
+    if (hk >= in.n_kv_heads) hk -= in.n_kv_heads;
     int after = a.merge_after;  // (kept: read from the arguments where it is used it costs a trip at every item's end)
     asm volatile("" : "+s"(after));
 #ifdef TAPER_WG_TRACE  // trace builds only (wg_trace.py): per-workgroup clocks -- start, own share done, left, time in merges
     long long* trace = a.trace;
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x] = wall_clock64();
 #endif
-    int it0 = 0, it1 = 0, solo_end = 0;  // private items of this workgroup's share: solo ones up to solo_end, then the others
-    auto own_items = [&] {
-        it0 = a.part_start[part];
-        it1 = a.part_start[part + 1];
-        solo_end = it0 + (turn >> kPartSoloShift);
-    };
-    if constexpr (ALLP) {
-        own_items();
-    } else if (part < a.n_parts_shared) {
-        shared_path<D, NTW, PF, ANY>(a, part, hk, after, *reinterpret_cast<SharedSmem<D>*>(smem_raw));
+    if (!ALLP && part < in.n_parts_shared) {
+        shared_path<D, NTW, PF, ANY>(a, in, start, hk, after, *reinterpret_cast<SharedSmem<D>*>(smem_raw));
         __syncthreads();
-    } else {
-        own_items();
+        start.first = start.end = start.n_solo = 0;  // (what is left for it is the pool)
     }
 #ifdef TAPER_WG_TRACE
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x + 1] = wall_clock64();  // shared share done (a private share: overwritten when it is done)
 #endif
-    private_items<D, PF, !ALLP && D == 128>(a, it0, solo_end, !after && (turn & kPartSoloPartials), it1, hk, after, *reinterpret_cast<PrivateSmem<D>*>(smem_raw));
+    private_items<D, PF, !ALLP && D == 128>(a, in, start, !after && (start.turn & kPartSoloPartials), hk, after, *reinterpret_cast<PrivateSmem<D>*>(smem_raw));
 #ifdef TAPER_WG_TRACE
     if (threadIdx.x == 0 && trace) trace[4 * blockIdx.x + 2] = wall_clock64();
 #endif
 }
 
 template <int D, int NTW, int PF, bool ALLP>
-__global__ __launch_bounds__(256, 2) void decode_kernel(StepArgs a) {
+__global__ __launch_bounds__(256, 2) void decode_kernel(const ShareStart* starts, const void* kv, const void* q, int n_kv_heads, int n_q_heads, int gqa, int n_parts_shared, StepArgs) {
     __shared__ __attribute__((aligned(16))) char smem_raw[sizeof(StepSmem<D>)];
-    run_share<D, NTW, PF, ALLP, false>(a, smem_raw);
+    run_share<D, NTW, PF, ALLP, false>(step_args(), {starts, kv, q, n_kv_heads, n_q_heads, gqa, n_parts_shared}, smem_raw);
 }
 // Steps with shared-prefix work over a pool that does not start at a multiple of 16 bytes (a kernel of its own: a branch per block
 // in the others cost them 1 to 2 %, mixed batch on one kv head 26.4 -> 26.7 us, 64 branches 270 -> 274).
 template <int D, int PF>
-__global__ __launch_bounds__(256, 2) void any_start_kernel(StepArgs a) {
+__global__ __launch_bounds__(256, 2) void any_start_kernel(const ShareStart* starts, const void* kv, const void* q, int n_kv_heads, int n_q_heads, int gqa, int n_parts_shared, StepArgs) {
     __shared__ __attribute__((aligned(16))) char smem_raw[sizeof(StepSmem<D>)];
-    run_share<D, 3, PF, false, true>(a, smem_raw);
+    run_share<D, 3, PF, false, true>(step_args(), {starts, kv, q, n_kv_heads, n_q_heads, gqa, n_parts_shared}, smem_raw);
 }
 
 // ---------------------------------------------------------------------------
@@ -1239,12 +1317,12 @@ hipError_t launch_stream_read(const void* base, int64_t pieces_per_wg, int n_wor
 template <int D, int PF>
 static hipError_t launch_decode_as(const StepArgs& a, const dim3 grid, const int ntw, hipStream_t s) {
     const dim3 block(256);
-    if (a.n_parts_shared == 0) hipLaunchKernelGGL((decode_kernel<D, 1, PF, true>), grid, block, 0, s, a);
+    if (a.n_parts_shared == 0) hipLaunchKernelGGL((decode_kernel<D, 1, PF, true>), grid, block, 0, s, a.starts, a.kv, a.q, a.n_kv_heads, a.n_q_heads, a.gqa, a.n_parts_shared, a);
     else if (ntw > 3) return hipErrorInvalidValue;
-    else if ((uintptr_t)a.kv & 15) hipLaunchKernelGGL((any_start_kernel<D, PF>), grid, block, 0, s, a);
-    else if (ntw <= 1) hipLaunchKernelGGL((decode_kernel<D, 1, PF, false>), grid, block, 0, s, a);
-    else if (ntw == 2) hipLaunchKernelGGL((decode_kernel<D, 2, PF, false>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((decode_kernel<D, 3, PF, false>), grid, block, 0, s, a);
+    else if ((uintptr_t)a.kv & 15) hipLaunchKernelGGL((any_start_kernel<D, PF>), grid, block, 0, s, a.starts, a.kv, a.q, a.n_kv_heads, a.n_q_heads, a.gqa, a.n_parts_shared, a);
+    else if (ntw <= 1) hipLaunchKernelGGL((decode_kernel<D, 1, PF, false>), grid, block, 0, s, a.starts, a.kv, a.q, a.n_kv_heads, a.n_q_heads, a.gqa, a.n_parts_shared, a);
+    else if (ntw == 2) hipLaunchKernelGGL((decode_kernel<D, 2, PF, false>), grid, block, 0, s, a.starts, a.kv, a.q, a.n_kv_heads, a.n_q_heads, a.gqa, a.n_parts_shared, a);
+    else hipLaunchKernelGGL((decode_kernel<D, 3, PF, false>), grid, block, 0, s, a.starts, a.kv, a.q, a.n_kv_heads, a.n_q_heads, a.gqa, a.n_parts_shared, a);
     if (a.merge_after) hipLaunchKernelGGL((merge_kernel<D, PF>), dim3(a.n_seqs * a.n_kv_heads), dim3(64 * a.gqa), 0, s, a);
     return hipGetLastError();
 }

@@ -394,6 +394,34 @@ void order_solo_items(int n_seqs, int most_tokens, bool partials, HostPlan* p) {
     }
 }
 
+// The start records: the first item of a share and the pages its waves ask for first (past the item's last page: that one).  A private
+// item's block is two pages, and wave w takes blocks w and w + 4; of a solo item it takes blocks 0 and 1.  Of a shared item every wave
+// stages its part of pages 0 to 7 at head_dim 128, and pages w, w + 4, ... at 64.
+void make_starts(const taper_attn_config& cfg, HostPlan* p) {
+    const int n_parts = p->n_parts_shared + p->n_parts_private;
+    p->starts.assign(n_parts, ShareStart());
+    for (int q = 0; q < n_parts; ++q) {
+        const int first = p->part_start[q], end = p->part_start[q + 1], n_solo = p->part_turn[q] >> kPartSoloShift;
+        for (int w = 0; w < 4; ++w) {
+            WaveStart& r = p->starts[q].wave[w];
+            r.first = first;
+            r.end = end;
+            r.turn = p->part_turn[q] & ((1 << kPartSoloShift) - 1);
+            r.n_solo = n_solo;
+            if (first == end) continue;
+            const bool solo = w < n_solo;
+            r.item = p->items[solo ? first + w : first];
+            const int32_t* row = p->block_table.data() + (size_t)r.item.seq0 * p->bt_stride + r.item.page0;
+            const int last = (r.item.n_tokens + 15) / 16 - 1;
+            for (int i = 0; i < 4; ++i) {
+                const int page = r.item.kind == 0 ? (cfg.head_dim == 128 ? i : 4 * i + w) : solo ? i : 2 * (w + 4 * (i / 2)) + i % 2;
+                r.page[i] = row[std::min(page, last)];
+                p->starts[q].more[i] = row[std::min(4 + i, last)];
+            }
+        }
+    }
+}
+
 }  // namespace
 
 int build_host_plan(const taper_attn_config& cfg, int n_seqs, const int32_t* block_table, int bt_row_stride,
@@ -800,32 +828,40 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
 // compute unit instead of two, which alone reads 1 to 4 % slower -- and that plan is taken when it saves enough
 // pieces to pay for it.  (32 requests of 1024-4096 tokens: 86 pieces become 54 and the launch 2.5 % faster;
 // 32 equal requests: no piece at all, 5-10 % faster; a large step has few pieces per share either way.)
-int build_host_plan_segments(const taper_attn_config& cfg, int n_seqs, const int32_t* block_table, int bt_row_stride,
-                             const int32_t* branch_group, const int32_t* prefix_len, const int32_t* seg_start,
-                             const int32_t* seg_len, int64_t n_pool_pages, const taper_plan_options* opts,
-                             HostPlan* out, std::string* err) {
-    int st = build_for_grid(cfg, n_seqs, block_table, bt_row_stride, branch_group, prefix_len, seg_start, seg_len,
-                            n_pool_pages, opts, out, err);
-    if (st != TAPER_OK || !opts || opts->small_step_grid <= 0) return st;
+static void take_fewer_pieces(const taper_attn_config& cfg, int n_seqs, const int32_t* block_table, int bt_row_stride,
+                              const int32_t* branch_group, const int32_t* prefix_len, const int32_t* seg_start,
+                              const int32_t* seg_len, int64_t n_pool_pages, const taper_plan_options* opts, HostPlan* out) {
+    if (!opts || opts->small_step_grid <= 0) return;
     const int grid = opts->target_workgroups > 0 ? opts->target_workgroups : 512;
     const int parts_full = std::max(1, grid / cfg.n_kv_heads);
-    if (out->n_parts_shared != 0 || out->n_pool_items != 0 || out->n_parts_private < parts_full || parts_full < 2) return st;
+    if (out->n_parts_shared != 0 || out->n_pool_items != 0 || out->n_parts_private < parts_full || parts_full < 2) return;
     auto pieces = [](const HostPlan& h) {
         int64_t n = 0;
         for (const taper_work_item& it : h.items) n += it.kind == 1;
         return n;
     };
     const int64_t pieces_full = pieces(*out);
-    if (pieces_full * kPieceCostTokens * 100 <= out->tokens_unique * kOnePerUnitLossPct) return st;  // cannot pay even if all went
+    if (pieces_full * kPieceCostTokens * 100 <= out->tokens_unique * kOnePerUnitLossPct) return;  // cannot pay even if all went
     taper_plan_options half = *opts;
     half.target_workgroups = grid / 2;
     HostPlan alt;
     std::string err2;
     if (build_for_grid(cfg, n_seqs, block_table, bt_row_stride, branch_group, prefix_len, seg_start, seg_len, n_pool_pages,
                        &half, &alt, &err2) != TAPER_OK)
-        return st;
+        return;
     if ((pieces_full - pieces(alt)) * kPieceCostTokens * 100 > out->tokens_unique * kOnePerUnitLossPct) *out = std::move(alt);
-    return st;
+}
+
+int build_host_plan_segments(const taper_attn_config& cfg, int n_seqs, const int32_t* block_table, int bt_row_stride,
+                             const int32_t* branch_group, const int32_t* prefix_len, const int32_t* seg_start,
+                             const int32_t* seg_len, int64_t n_pool_pages, const taper_plan_options* opts,
+                             HostPlan* out, std::string* err) {
+    int st = build_for_grid(cfg, n_seqs, block_table, bt_row_stride, branch_group, prefix_len, seg_start, seg_len,
+                            n_pool_pages, opts, out, err);
+    if (st != TAPER_OK) return st;
+    take_fewer_pieces(cfg, n_seqs, block_table, bt_row_stride, branch_group, prefix_len, seg_start, seg_len, n_pool_pages, opts, out);
+    make_starts(cfg, out);
+    return TAPER_OK;
 }
 
 void resolve_slots_host(const HostPlan& p, int P, int64_t* slots, int64_t stride) {

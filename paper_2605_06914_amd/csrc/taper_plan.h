@@ -15,6 +15,19 @@ constexpr int kSharedBlockTokens = 64;   // shared prefixes are cut at multiples
 constexpr int kPartTurnMask = 0xfff, kPartSoloPartials = 0x1000, kPartSoloShift = 13;
 constexpr int kMaxRowTilesPerItem = 12;  // 16-row query tiles one shared-kernel workgroup can hold (4 waves x 3)
 
+// What a wave of a share begins with, so that its first KV loads wait for one trip to memory and not for one to the share's range, one
+// to its item and one to the block table.
+struct alignas(64) WaveStart {
+    int32_t first, end;    // the share's items
+    int32_t turn, n_solo;  // part_turn's flags; how many of the items single waves run
+    taper_work_item item;  // the share's first item; of a solo run, this wave's first
+    int32_t page[4];       // its first pages, in the order the wave loads them (see make_starts)
+};
+struct alignas(64) ShareStart {
+    WaveStart wave[4];
+    int32_t more[4];  // pages 4 to 7 of a shared item at head_dim 128
+};
+
 struct HostPlan {
     int n_seqs = 0, n_groups = 0, bt_stride = 0;
     int64_t n_pool_pages = 0;
@@ -27,6 +40,7 @@ struct HostPlan {
     int n_pool_items = 0;  // items after the shares' items, owned by no share
     std::vector<int32_t> part_start;  // [n_parts + 1]
     std::vector<int32_t> part_turn;   // [n_parts] which kv head a share's first workgroup takes (see plan_part_turns), and its solo items
+    std::vector<ShareStart> starts;   // [n_parts]
     std::vector<int32_t> merge_start; // [n_seqs + 1]
     std::vector<taper_merge_entry> merge;
     int64_t n_partial_rows = 0;

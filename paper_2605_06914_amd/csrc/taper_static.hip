@@ -5,7 +5,7 @@
 
 namespace taper {
 
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticStartsBytes + kStaticScratchBytes];
 
 // In host code the array's name is only a handle for the symbol, not a device address: what kernels,
 // copies and fills are given is the address looked up here, once per device.
