@@ -40,7 +40,11 @@ DEV bf16x8 cat(bf16x4 a, bf16x4 b) { return __builtin_shufflevector(a, b, 0, 1, 
 // KV is read exactly once per launch: stream it past the caches (measurably faster than cached loads)
 template <typename T>
 DEV T stream_load(const T* p) { return __builtin_nontemporal_load(p); }
-DEV float max4(f32x4 v) { return fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])); }
+// (maximum, not maxnum: v_maximum3 takes three values as they are, where maxnum first quiets each of them.  A NaN makes its row NaN either way.)
+DEV float max3(float a, float b, float c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); }
+DEV float max8(f32x4 v, f32x4 w) {
+    return max3(max3(v[0], v[1], v[2]), max3(v[3], w[0], w[1]), __builtin_elementwise_maximum(w[2], w[3]));
+}
 
 // Scores of invalid tokens of a chunk's last 32-token block -> -inf.
 // sx: tokens 4*qd+i of the block's first page, sy: of its second page.
@@ -75,25 +79,39 @@ DEV float sum_lane_groups(float v) {
 // weight is 1, which bf16 holds exactly (with a reference up to 2^8 lower, for fewer rescales, the error against 64 bits
 // was 4 to 10 % larger on N(0,1) inputs and up to 20 % on wider scores, and accumulators overflowed 2^8 earlier).
 // The lane groups' maxima are brought together, and the accumulators rescaled, only when some lane's is above m.
-template <int DT>
-DEV bf16x8 softmax_block(f32x4 sx, f32x4 sy, float c, float& m, float& l, f32x4 (&O)[DT]) {
-    const float mx = fmaxf(max4(sx), max4(sy));
-    if (__any(mx * c > m)) {  // wave-uniform
-        const float mn = fmaxf(m, max_lane_groups(mx) * c);
-        const float alpha = fast_exp2(m - mn);
-        l *= alpha;
+// NA tiles at a time: one branch for all of them, so that the instructions of one can fill the waits of another.
+template <int DT, int NA>
+DEV void softmax_block(const f32x4 (&sx)[NA], const f32x4 (&sy)[NA], float c, float (&m)[NA], float (&l)[NA], f32x4 (&O)[NA][DT], bf16x8 (&pf)[NA]) {
+    float mx[NA];
+    bool higher = false;
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) O[dt] *= alpha;
-        m = mn;
+    for (int k = 0; k < NA; ++k) {
+        mx[k] = max8(sx[k], sy[k]);
+        higher |= mx[k] * c > m[k];
     }
-    f32x8 p;
+    if (__any(higher)) {  // wave-uniform
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        p[i] = fast_exp2(fmaf(sx[i], c, -m));
-        p[4 + i] = fast_exp2(fmaf(sy[i], c, -m));
+        for (int k = 0; k < NA; ++k) {
+            if (NA > 1 && !__any(mx[k] * c > m[k])) continue;
+            const float mn = fmaxf(m[k], max_lane_groups(mx[k]) * c);
+            const float alpha = fast_exp2(m[k] - mn);
+            l[k] *= alpha;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) O[k][dt] *= alpha;
+            m[k] = mn;
+        }
     }
-    l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-    return __builtin_convertvector(p, bf16x8);
+#pragma unroll
+    for (int k = 0; k < NA; ++k) {
+        f32x8 p;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = fast_exp2(fmaf(sx[k][i], c, -m[k]));
+            p[4 + i] = fast_exp2(fmaf(sy[k][i], c, -m[k]));
+        }
+        l[k] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+        pf[k] = __builtin_convertvector(p, bf16x8);
+    }
 }
 
 // The accumulator a block's last matrix instruction wrote must not be read by a vector instruction
@@ -243,10 +261,7 @@ struct Inputs {
     const void *kv, *q;
     int n_kv_heads, n_q_heads, gqa, n_parts_shared;
 };
-// A wave's start record, by scalar loads side by side.  A launch's first KV loads used to wait for five trips to memory one after the other
-// (arguments, the share's range, its item, the block table, the pool), 0.2 us each while the plan is in the L2; with the record's address in
-// registers at the start there are two.  tiny step 7.08 -> 6.70 us, one request of 2048 tokens 8.01 -> 7.73, 11.7 -> 11.3, 20.7 -> 20.2, 57.9 -> 56.2;
-// shared items of all sizes take their first four blocks' page ids by one trip instead of one per block.
+// A wave's start record, by scalar loads side by side.
 struct Start {
     int first, end, turn, n_solo;
     taper_work_item item;
@@ -513,12 +528,14 @@ DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item
 #pragma unroll
             for (int j = 0; j < KS; ++j) qf[j] = *(const bf16x8*)(qrow + 8 * (4 * j + qd));
         }
-        float m = -INFINITY, l = 0.f;
-        f32x4 O[DT];
+        float m1[1] = {-INFINITY}, l1[1] = {0.f};
+        f32x4 O1[1][DT];
+        float &m = m1[0], &l = l1[0];
+        f32x4(&O)[DT] = O1[0];
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) O[dt] = (f32x4)(0.f);
 
-        const int64_t page_bytes = (int64_t)Hkv * TILE * 4;
+        const unsigned page_bytes = Hkv * TILE * 4;
         const char* kvb = (const char*)in.kv + (int64_t)hk * TILE * 2;
         const unsigned koff = lane * 16, voff = (qd * (4 * D) + n * 4) * 2;
         int pid_a = page[0], pid_b = page[1];  // the pages of the block loaded next
@@ -529,8 +546,8 @@ DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item
         };
         auto hold = [&] { if (HOLD && a.long_shares) asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
         auto load_block = [&](KVRegs<D>& r) {
-            const char* ka = kvb + pid_a * page_bytes;
-            const char* kb = kvb + pid_b * page_bytes;
+            const char* ka = kvb + (uint64_t)(unsigned)pid_a * page_bytes;  // (32 x 32 bits)
+            const char* kb = kvb + (uint64_t)(unsigned)pid_b * page_bytes;
             const char* va = ka + (int64_t)Hkv * TILE * 2;
             const char* vb = kb + (int64_t)Hkv * TILE * 2;
 #pragma unroll
@@ -545,18 +562,19 @@ DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item
             }
         };
         auto compute_block = [&](int b, KVRegs<D>& r, auto last) {
-            f32x4 sx = (f32x4)(0.f), sy = (f32x4)(0.f);
+            f32x4 sx[1] = {(f32x4)(0.f)}, sy[1] = {(f32x4)(0.f)};
 #pragma unroll
             for (int j = 0; j < KS; ++j) {
-                sx = mfma16(r.kx[j], qf[j], sx);
-                sy = mfma16(r.ky[j], qf[j], sy);
+                sx[0] = mfma16(r.kx[j], qf[j], sx[0]);
+                sy[0] = mfma16(r.ky[j], qf[j], sy[0]);
             }
             const int nv = n_tok - 32 * b;
-            if (last && nv < 32) mask_tail(sx, sy, qd, nv);
-            const bf16x8 pf = softmax_block<DT>(sx, sy, c, m, l, O);
+            if (last && nv < 32) mask_tail(sx[0], sy[0], qd, nv);
+            bf16x8 pf[1];
+            softmax_block<DT, 1>(sx, sy, c, m1, l1, O1, pf);
             if (last && nv < 32) zero_tail(r.va, r.vb, qd, nv);
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) O[dt] = mfma16(cat(r.va[dt], r.vb[dt]), pf, O[dt]);
+            for (int dt = 0; dt < DT; ++dt) O[dt] = mfma16(cat(r.va[dt], r.vb[dt]), pf[0], O[dt]);
             settle();
         };
 
@@ -792,10 +810,10 @@ DEV void private_items(const StepArgs& a, const Inputs& in, const Start& start, 
 // once and multiplied against the query rows of all n_branch admitted branches x g
 // heads.  16-row tiles are dealt round-robin to the four waves, up to 3 tiles per wave.
 //
-// KV goes from global memory straight into LDS, 16 KiB blocks (32 tokens at head_dim 128, 64 at 64) in a ring
-// of four: one is computed from while three are in flight, whatever the number of tiles.  Every wave-level
-// 16-byte load lands as 1 KiB at a wave-uniform LDS address, lane after lane.  Which 16 bytes of memory
-// a lane fetches is free, and that is where V's bank swizzle is made: inside an odd 4-token quarter the two
+// KV goes from global memory straight into LDS, 16 KiB blocks (32 tokens at head_dim 128, 64 at 64), K in a ring of four
+// halves, V in one of five: scores are made from K of one block while V of the block before is used, and three more are in flight,
+// whatever the number of tiles.  Every wave-level 16-byte load lands as 1 KiB at a wave-uniform LDS address, lane after lane.  Which 16
+// bytes of memory a lane fetches is free, and that is where V's bank swizzle is made: inside an odd 4-token quarter the two
 // 128-byte halves of each 256 bytes change places, so that the 8-byte fragment reads of lane groups 0/1
 // (2/3) hit different bank halves.
 //
@@ -804,11 +822,14 @@ DEV void private_items(const StepArgs& a, const Inputs& in, const Start& start, 
 // their memory clobbers.  (The loads have no register results, and the waits the compiler makes for its own
 // loads only get longer by loads it does not know of.)
 //
-// What bounds it: on a saturated machine HBM (a launch of shared work alone, 16 requests of 32768 tokens: 2 branches
-// 334 us, 8 branches 344, 16 branches 388, of the 310 a bare read of the same pages takes; 16 branches were 454 with
-// KV staged through registers; 24 branches, three tiles per wave, 502).  Alone on the machine, the chain of a block -- LDS reads, matrix
-// instructions, exponentials, the barrier: 0.67, 0.84 and 1.06 us per block with one, two and three tiles per wave (1.0 with one
-// when page ids and queries were waited for inside the loop; a ring of eight does not change it).
+// What bounds it: on a saturated machine HBM, and above some ten branches the block's own instructions (a launch of shared work alone, 16
+// requests of 32768 tokens, of the 310 us a bare read of the same pages takes, the loads without the computation 314 to 325: 2 branches
+// 322 us, 8 339, 16 361 to 373, 24 484; before / with the loop described below 332 / 338 / 400 to 410 / 514).  Alone on the machine, the chain of a
+// block: 0.39, 0.47, 0.70 to 0.74 and 0.89 us with 1 to 4, 4, 8 and 12 tiles (2, 8, 16, 24 branches), 0.25 of it the loads' issue and the barrier; 0.58, 0.64,
+// 0.88 and 1.02 before.  What made the difference, in this order: page ids by one load in the middle of a block's work, not behind it
+// (0.05); the maximum of eight scores in four instructions and page offsets by 32-bit products; V's two fragments of an operand by one
+// read into its four registers (32 moves a block less); the scores a block ahead.  What is left is 16 matrix instructions a tile, 17 cycles each, and some
+// 60 vector instructions.
 // ---------------------------------------------------------------------------
 template <int D>
 struct SharedSmem {
@@ -817,13 +838,13 @@ struct SharedSmem {
     static constexpr int BLOCK_BYTES = 16384;
     static constexpr int PAGES = BLOCK_BYTES / PAGE_BYTES;     // pages per block: 2 at head_dim 128, 4 at 64
     static constexpr int TOKENS = 16 * PAGES;
-    static constexpr int RING = 4;
-    // A block: the K tiles of its pages one after the other, then V in 1 KiB chunks (token quarters at head_dim 128, pairs
+    // K of a block: the tiles of its pages one after the other.  V in 1 KiB chunks (token quarters at head_dim 128, pairs
     // of quarters at 64): pair of pages, chunk, page of the pair.  The two pages' fragments that make up one operand
     // are then 1 KiB apart, which one two-address read fetches into neighbouring registers.
-    static constexpr int V_OFF = PAGES * TILE_BYTES;
-    static constexpr int v_chunk(int page, int chunk) { return V_OFF + (page >> 1) * 2 * TILE_BYTES + chunk * 2048 + (page & 1) * 1024; }
-    char kv[RING * BLOCK_BYTES];
+    static constexpr int v_chunk(int page, int chunk) { return (page >> 1) * 2 * TILE_BYTES + chunk * 2048 + (page & 1) * 1024; }
+    static constexpr int HALF = BLOCK_BYTES / 2;               // K or V of a block
+    static constexpr int K_RING = 4, V_RING = 5;               // (a block's scores are made one iteration before its V is used)
+    char k[K_RING * HALF], v[V_RING * HALF];
     int todo[64];  // branches of the current item whose partials are complete
     int n_todo;
     MergeMeta meta;
@@ -897,17 +918,149 @@ DEV void shared_stream(const StepArgs& a, const Inputs& in, const taper_work_ite
     constexpr int LOADS = 4;  // wave-level loads per wave and block
     const int lane = tid & 63, n = lane & 15, qd = lane >> 4;
     const int Hkv = in.n_kv_heads, g = in.gqa;
-    const int64_t page_bytes = (int64_t)Hkv * Sm::PAGE_BYTES;
+    const unsigned page_bytes = Hkv * Sm::PAGE_BYTES;
     const char* kvb = (const char*)in.kv + (int64_t)hk * Sm::TILE_BYTES;
     const float c = a.scale_log2e;
     const scalar_row row = table_row(a, item);  // (wave-uniform: page ids come by scalar loads)
     const int n_tok = item.n_tokens, n_pages = (n_tok + 15) >> 4, n_blocks = (n_tok + Sm::TOKENS - 1) / Sm::TOKENS;
     const int R = item.n_branch * g;
 
-    const MetaRegs mr = meta_load(a, item, tid);
     bf16x8 qf[NT][KS];
     float m[NT], l[NT];
     f32x4 O[NT][DT];
+
+    // staging: at head_dim 128 a wave loads quarter `wave` of K and V of both pages, at 64 all of page `wave`
+    const unsigned k_ring = lds_address(sm.k), v_ring = lds_address(sm.v);
+    const unsigned off_k = lane * 16;
+    const unsigned off_v = (lane ^ ((D == 128 ? wave & 1 : lane >> 5) << 3)) * 16;
+    int pid[D == 128 ? 2 : 1];  // the pool pages this wave stages next
+    auto fetch_ids = [&](int b) {  // past the last page (a block that ends early or does not exist): the last page
+        if constexpr (D == 128) {
+            typedef int i32x2 __attribute__((ext_vector_type(2), aligned(4)));
+            const int bb = b < n_blocks ? b : n_blocks - 1;
+            const i32x2 two = *(CONSTANT i32x2*)(row + 2 * bb);  // (a row of an odd number of pages: the entry behind it is read, not used)
+            pid[0] = two[0];
+            pid[1] = 2 * bb + 1 < n_pages ? two[1] : two[0];
+        } else {
+            const int i = 4 * b + wave;
+            pid[0] = row[i < n_pages ? i : n_pages - 1];
+        }
+    };
+    const unsigned v_bytes = Hkv * Sm::TILE_BYTES;  // from a page's K tiles to its V tiles
+    auto stage = [&](int k_slot, int v_slot) {      // (byte offsets in the rings)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {  // (a page of two at head_dim 128, a half of a tile at 64)
+            const char* from = kvb + (uint64_t)(unsigned)pid[D == 128 ? i : 0] * page_bytes + (D == 128 ? wave : i) * 1024;
+            const int k_to = k_slot + (D == 128 ? i * Sm::TILE_BYTES + wave * 1024 : wave * Sm::TILE_BYTES + i * 1024);
+            const int v_to = v_slot + (D == 128 ? Sm::v_chunk(i, wave) : Sm::v_chunk(wave, i));
+            if constexpr (ANY) {
+                copy_to_lds(from, off_k, sm.k + k_to, lane);
+                copy_to_lds(from + v_bytes, off_v, sm.v + v_to, lane);
+            } else {
+                load_to_lds(from, off_k, k_ring + k_to);
+                load_to_lds(from + v_bytes, off_v, v_ring + v_to);
+            }
+        }
+    };
+    // this lane's V fragment of 16-dim group dt (the swizzle: odd quarters have their 128-byte halves exchanged)
+    const int v_lane = v_ring + (D == 128 ? qd * 2048 : (qd >> 1) * 2048 + (qd & 1) * QB) + n * 8;
+    const int v_even = v_lane + (qd & 1) * 128, v_odd = v_lane - (qd & 1) * 128;
+    // The scores of a block are made one iteration ahead of its exponentials, so that the matrix instructions of the one fill the time of
+    // the vector instructions of the other.
+    constexpr int H = Sm::PAGES / 2;  // halves of 32 tokens
+    f32x4 sx[H][NT], sy[H][NT];
+    bf16x8 kx[H][KS], ky[H][KS];
+    auto read_k = [&](int k_slot, int hf) {
+        const char* kp = sm.k + k_slot + hf * 2 * Sm::TILE_BYTES + lane * 16;
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+            kx[hf][j] = *(const bf16x8*)(kp + j * 1024);
+            ky[hf][j] = *(const bf16x8*)(kp + Sm::TILE_BYTES + j * 1024);
+        }
+    };
+    auto scores = [&](int hf) {
+#pragma unroll
+        for (int k = 0; k < NA; ++k) {
+            sx[hf][k] = sy[hf][k] = (f32x4)(0.f);
+#pragma unroll
+            for (int j = 0; j < KS; ++j) {
+                sx[hf][k] = mfma16(kx[hf][j], qf[k][j], sx[hf][k]);
+                sy[hf][k] = mfma16(ky[hf][j], qf[k][j], sy[hf][k]);
+            }
+        }
+    };
+    auto read_v = [&](int v_slot, int hf, int h, bf16x4 (&va)[4], bf16x4 (&vb)[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // (an address of its own for each pair, so that the pair is one two-address read into the operand's four registers;
+            // else the compiler joins reads of different pairs and moves half of the registers)
+            const auto v = (__attribute__((address_space(3))) const bf16x4*)(uintptr_t)(unsigned)opaque(v_slot + hf * 2 * Sm::TILE_BYTES + (i & 1 ? v_odd : v_even) + (4 * h + i) * 128);
+            va[i] = v[0];
+            vb[i] = v[128];
+        }
+    };
+    auto compute = [&](int b, int k_next, int v_slot, auto tail) {
+        if constexpr (NA > 0) {
+#pragma unroll
+            for (int hf = 0; hf < H; ++hf) {
+                const int nv = n_tok - Sm::TOKENS * b - 32 * hf;
+                if (tail && nv <= 0) break;
+                if (!tail) read_k(k_next, hf);
+                bf16x4 vas[DT], vbs[DT];
+                if constexpr (NA == 2) {
+#pragma unroll
+                    for (int h = 0; h < DT / 4; ++h) {
+                        bf16x4 va[4], vb[4];
+                        read_v(v_slot, hf, h, va, vb);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) vas[4 * h + i] = va[i], vbs[4 * h + i] = vb[i];
+                    }
+                }
+                if (!tail && hf == 0) fetch_ids(b + 5);
+                if (tail && nv < 32) {
+#pragma unroll
+                    for (int k = 0; k < NA; ++k) mask_tail(sx[hf][k], sy[hf][k], qd, nv);
+                }
+                bf16x8 pf[NA];
+                softmax_block<DT, NA>(sx[hf], sy[hf], c, m, l, O, pf);
+                if (!tail) scores(hf);
+#pragma unroll
+                for (int h = 0; h < DT / 4; ++h) {
+                    bf16x4 va[4], vb[4];
+                    if constexpr (NA == 2) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) va[i] = vas[4 * h + i], vb[i] = vbs[4 * h + i];
+                    } else {
+                        read_v(v_slot, hf, h, va, vb);
+                    }
+                    if (tail && nv < 32) zero_tail(va, vb, qd, nv);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const bf16x8 vf = cat(va[i], vb[i]);
+#pragma unroll
+                        for (int k = 0; k < NA; ++k) O[k][4 * h + i] = mfma16(vf, pf[k], O[k][4 * h + i]);
+                    }
+                }
+                settle();
+            }
+        } else if (!tail) {
+            fetch_ids(b + 5);
+        }
+    };
+
+    // (the previous item's LDS reads of these buffers ended before its closing barriers)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        if constexpr (D == 128) {
+            pid[0] = b < 2 ? page[2 * (b & 1)] : page2[2 * (b & 1)];
+            pid[1] = b < 2 ? page[2 * (b & 1) + 1] : page2[2 * (b & 1) + 1];
+        } else {
+            pid[0] = page[b];
+        }
+        if (b < n_blocks) stage(b * Sm::HALF, b * Sm::HALF);
+    }
+    fetch_ids(4);
+    const MetaRegs mr = meta_load(a, item, tid);
     if constexpr (NA > 0) {
 #pragma unroll
         for (int k = 0; k < NA; ++k) {
@@ -921,110 +1074,6 @@ DEV void shared_stream(const StepArgs& a, const Inputs& in, const taper_work_ite
             for (int dt = 0; dt < DT; ++dt) O[k][dt] = (f32x4)(0.f);
         }
     }
-
-    // staging: at head_dim 128 a wave loads quarter `wave` of K and V of both pages, at 64 all of page `wave`
-    const unsigned ring = lds_address(sm.kv);
-    const unsigned off_k = lane * 16;
-    const unsigned off_v = (lane ^ ((D == 128 ? wave & 1 : lane >> 5) << 3)) * 16;
-    int pid[D == 128 ? 2 : 1];  // the pool pages this wave stages next
-    auto fetch_ids = [&](int b) {  // past the last page (a block that ends early or does not exist): the last page
-        if constexpr (D == 128) {
-            const int i0 = 2 * b, i1 = 2 * b + 1;
-            pid[0] = row[i0 < n_pages ? i0 : n_pages - 1];
-            pid[1] = row[i1 < n_pages ? i1 : n_pages - 1];
-        } else {
-            const int i = 4 * b + wave;
-            pid[0] = row[i < n_pages ? i : n_pages - 1];
-        }
-    };
-    auto stage = [&](int b) {
-        const unsigned buf = ring + (b & (Sm::RING - 1)) * Sm::BLOCK_BYTES;
-        if constexpr (ANY) {
-            char* dst = sm.kv + (b & (Sm::RING - 1)) * Sm::BLOCK_BYTES;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {  // (a page of two at head_dim 128, a half of a tile at 64)
-                const char* k = kvb + pid[D == 128 ? i : 0] * page_bytes + (D == 128 ? wave : i) * 1024;
-                copy_to_lds(k, off_k, dst + (D == 128 ? i : wave) * Sm::TILE_BYTES + (D == 128 ? wave : i) * 1024, lane);
-                copy_to_lds(k + (int64_t)Hkv * Sm::TILE_BYTES, off_v, dst + (D == 128 ? Sm::v_chunk(i, wave) : Sm::v_chunk(wave, i)), lane);
-            }
-        } else if constexpr (D == 128) {
-#pragma unroll
-            for (int pg = 0; pg < 2; ++pg) {
-                const char* k = kvb + pid[pg] * page_bytes + wave * 1024;
-                load_to_lds(k, off_k, buf + pg * Sm::TILE_BYTES + wave * 1024);
-                load_to_lds(k + (int64_t)Hkv * Sm::TILE_BYTES, off_v, buf + Sm::v_chunk(pg, wave));
-            }
-        } else {
-            const char* k = kvb + pid[0] * page_bytes;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                load_to_lds(k + h * 1024, off_k, buf + wave * Sm::TILE_BYTES + h * 1024);
-                load_to_lds(k + (int64_t)Hkv * Sm::TILE_BYTES + h * 1024, off_v, buf + Sm::v_chunk(wave, h));
-            }
-        }
-    };
-    // this lane's V fragment of 16-dim group dt (the swizzle: odd quarters have their 128-byte halves exchanged)
-    const int v_lane = Sm::V_OFF + (D == 128 ? qd * 2048 : (qd >> 1) * 2048 + (qd & 1) * QB) + n * 8;
-    const int v_even = v_lane + (qd & 1) * 128, v_odd = v_lane - (qd & 1) * 128;
-    auto compute = [&](int b, auto tail) {
-        if constexpr (NA > 0) {
-            const char* blk = sm.kv + (b & (Sm::RING - 1)) * Sm::BLOCK_BYTES;
-#pragma unroll
-            for (int hf = 0; hf < Sm::PAGES / 2; ++hf) {
-                const int nv = n_tok - Sm::TOKENS * b - 32 * hf;
-                if (tail && nv <= 0) break;
-                const char *kp = blk + hf * 2 * Sm::TILE_BYTES + lane * 16, *vp = blk + hf * 2 * Sm::TILE_BYTES;
-                bf16x8 kx[KS], ky[KS], pf[NA];
-#pragma unroll
-                for (int j = 0; j < KS; ++j) {
-                    kx[j] = *(const bf16x8*)(kp + j * 1024);
-                    ky[j] = *(const bf16x8*)(kp + Sm::TILE_BYTES + j * 1024);
-                }
-#pragma unroll
-                for (int k = 0; k < NA; ++k) {
-                    f32x4 sx = (f32x4)(0.f), sy = (f32x4)(0.f);
-#pragma unroll
-                    for (int j = 0; j < KS; ++j) {
-                        sx = mfma16(kx[j], qf[k][j], sx);
-                        sy = mfma16(ky[j], qf[k][j], sy);
-                    }
-                    if (tail && nv < 32) mask_tail(sx, sy, qd, nv);
-                    pf[k] = softmax_block<DT>(sx, sy, c, m[k], l[k], O[k]);
-                }
-                // (four V fragment pairs at a time: all eight do not fit the registers of three tiles per wave)
-#pragma unroll
-                for (int h = 0; h < DT / 4; ++h) {
-                    bf16x4 va[4], vb[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const char* v = vp + (i & 1 ? v_odd : v_even) + (4 * h + i) * 128;
-                        va[i] = *(const bf16x4*)v;
-                        vb[i] = *(const bf16x4*)(v + 1024);
-                    }
-                    if (tail && nv < 32) zero_tail(va, vb, qd, nv);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const bf16x8 vf = cat(va[i], vb[i]);
-#pragma unroll
-                        for (int k = 0; k < NA; ++k) O[k][4 * h + i] = mfma16(vf, pf[k], O[k][4 * h + i]);
-                    }
-                }
-                settle();
-            }
-        }
-    };
-
-    // (the previous item's LDS reads of these buffers ended before its closing barriers)
-#pragma unroll
-    for (int b = 0; b < Sm::RING; ++b) {
-        if constexpr (D == 128) {
-            pid[0] = b < 2 ? page[2 * (b & 1)] : page2[2 * (b & 1)];
-            pid[1] = b < 2 ? page[2 * (b & 1) + 1] : page2[2 * (b & 1) + 1];
-        } else {
-            pid[0] = page[b];
-        }
-        if (b < Sm::RING - 1 && b < n_blocks) stage(b);
-    }
     meta_store(sm.meta, mr, item.n_branch, tid);
     // (the queries' loads are waited for here: inside the loop that wait would also drain the blocks in flight, every time)
     if constexpr (NA > 0) {
@@ -1033,15 +1082,26 @@ DEV void shared_stream(const StepArgs& a, const Inputs& in, const taper_work_ite
 #pragma unroll
             for (int j = 0; j < KS; ++j) asm volatile("" : "+v"(qf[k][j]));
     }
-    for (int b = 0; b < n_blocks - 1; ++b) {
-        if (b + 2 < n_blocks) wait_loads_and_meet<2 * LOADS>();  // block b is in LDS for every wave; everyone is done with block b - 1
-        else wait_loads_and_meet<LOADS>();
-        if (b + Sm::RING - 1 < n_blocks) stage(b + Sm::RING - 1);  // into the buffer block b - 1 was computed from
-        compute(b, std::false_type{});
-        fetch_ids(b + Sm::RING);  // for the next iteration's stage: waited for together with block b + 1
-    }
     wait_loads_and_meet<0>();
-    compute(n_blocks - 1, std::true_type{});
+    if constexpr (NA > 0) {
+#pragma unroll
+        for (int hf = 0; hf < H; ++hf) {
+            read_k(0, hf);
+            scores(hf);
+        }
+    }
+    int v_slot = 0, k_slot = 0;  // of block b
+    for (int b = 0; b < n_blocks - 1; ++b) {
+        // block b + 1 is in LDS for every wave; everyone is done with K of block b and V of block b - 1
+        if (b + 3 < n_blocks) wait_loads_and_meet<2 * LOADS>();
+        else if (b + 3 == n_blocks) wait_loads_and_meet<LOADS>();
+        else wait_loads_and_meet<0>();
+        if (b + 4 < n_blocks) stage(k_slot, v_slot == 0 ? 4 * Sm::HALF : v_slot - Sm::HALF);  // block b + 4, where K of b and V of b - 1 were
+        k_slot = (k_slot + Sm::HALF) & (Sm::K_RING * Sm::HALF - 1);
+        compute(b, k_slot, v_slot, std::false_type{});
+        v_slot = v_slot == 4 * Sm::HALF ? 0 : v_slot + Sm::HALF;
+    }
+    compute(n_blocks - 1, 0, v_slot, std::true_type{});
     if constexpr (NA > 0) {
         // (lane coordinates are derived afresh: shared with the ones above, they would stay live through the streaming loop)
         const int tid_e = opaque(threadIdx.x);

@@ -60,6 +60,7 @@ constexpr int64_t kBriefShareTokens = 700;   // so many tokens per share,
 constexpr int64_t kBriefItemCost = 160;      // at so much (see Cost::brief)
 constexpr double kMergeLaunchFromUs = 12;    // see merges_after
 constexpr int64_t kSaturatingShareTokens = 350;  // shares of fewer tokens are over before the memory system is saturated
+constexpr int64_t kRoomyShareTokens = 128;       // with so few there are shares to spare (one holds 256 as a rule): prefixes may be cut finer
 constexpr int64_t kLongShareTokens = 2000;       // from here on private work holds back beside shared-prefix work (see private_item in the kernels)
 
 struct Segment {
@@ -173,7 +174,7 @@ int64_t least_tokens(const Segment& s, int gqa) {
 // `tail_discount` blocks shorter: the workgroup that finishes a shared prefix usually finds the
 // request's branches complete and has to merge them all.
 int partition_even(const std::vector<Segment>& segs, int gqa, int64_t quota, int blk, const Cost cost, int64_t tail_discount,
-                   bool crowded, int part_id0, std::vector<taper_work_item>* items) {
+                   bool crowded, bool apart, int part_id0, std::vector<taper_work_item>* items) {
     quota = std::max<int64_t>(1, quota);
     int part = 0;
     int64_t fill = 0, blk_cost = 1;
@@ -195,6 +196,7 @@ int partition_even(const std::vector<Segment>& segs, int gqa, int64_t quota, int
     };
     for (size_t si = 0; si < segs.size(); ++si) {
         const Segment& s = segs[si];
+        if (apart) close();
         blk_cost = std::max<int64_t>(1, (int64_t)blk * s.pct / 100);
         const int64_t min_blocks = std::max<int64_t>(1, (cost.item(s) + blk_cost - 1) / blk_cost);
         // blocks of an item with a share to itself
@@ -618,16 +620,19 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     //    shared workgroup then takes 0.6 to 0.65 of the time of a private one per token (20.6 against 31.8 us per 1024
     //    tokens in the mixed batch, least squares over its shares) and 13.8 us per item, a private one 6.1 us.  Measured
     //    optimum of the launch, with the pool evening out the rest: 70 to 90 % per token for items of up to 4 row tiles.
-    //  * shorter ones are over before that, and what counts is a workgroup's own chain of blocks: 20 us per 1024 tokens for
-    //    a shared one, 9 for a private one, whose four waves each have a block in flight.  (The mixed batch on one
-    //    kv head, 232 tokens per share: 26.8 us at 120 %, 26.7 at 180, 26.6 at 200; 28.6 with the constants of longer shares.)
+    //  * shorter ones are over before that, and what counts is a workgroup's own chain of blocks: 15, 23 and 29 us per 1024 tokens for
+    //    a shared one of up to 4, 8 and 12 row tiles, 9 for a private one, whose four waves each have a block in flight.  180 % for
+    //    all and 32 per branch where the grid is full (140 / 220 / 300 and 20 there: the mixed batch on one kv head, 232 tokens per share, 19.5
+    //    us either way, two steps of 233 and 236 4 and 7 % slower); 140 / 220 / 300 and 20 below kRoomyShareTokens, where finer cuts cost no other
+    //    work its share (34 random steps of 20 to 128 tokens per share: ten 9 to 58 % faster, three 2 to 3 % slower; 19 branches of some 500 tokens
+    //    31.9 -> 20.1 us, 13 of 800 22.1 -> 15.7, 43 of 1100 26.4 -> 18.1).
     const int parts_total = std::max(1, target_wgs / cfg.n_kv_heads);
     int64_t tok_listed = 0, tok_priv = 0;
     for (const Segment& s : shared) tok_listed += s.n_tokens;
     for (const Segment& s : priv) tok_priv += s.n_tokens;
     tok_listed += tok_priv;
     const int64_t share_tokens = tok_listed / parts_total;
-    const bool latency_bound = share_tokens < kSaturatingShareTokens;
+    const bool latency_bound = share_tokens < kSaturatingShareTokens, roomy = share_tokens < kRoomyShareTokens;
     p.long_shares = share_tokens >= kLongShareTokens;
     // An item of more than 4 row tiles gives waves two or three tiles, and a block's chain 0.85 or 1.05 us instead of 0.65: it no
     // longer keeps up with its slice of a saturated memory system.  (80 / 100 / 120 / 140 %, 8 requests of 2048 to 8192 tokens
@@ -639,7 +644,8 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     // 89.7 / 89.3 / 85.9 / 84.2; 60, 2011, 116 / 116 / 112 / 112 / 112; 60, 2683, 140.5 / 140.4 / 142.9 / 143.8 / 143.8).
     auto shared_pct = [&](const Segment& s, bool sub_group) -> int32_t {
         if (opts && opts->shared_cost_pct > 0) return opts->shared_cost_pct;
-        if (latency_bound) return 180;
+        if (latency_bound && !roomy) return 180;
+        if (latency_bound) return s.n_branch * g <= 4 * 16 ? 140 : s.n_branch * g <= 8 * 16 ? 220 : 300;
         return s.n_branch * g <= 4 * 16 ? 80 : !sub_group ? 120 : p.long_shares ? 110 : 160;
     };
     for (size_t i = 0; i < shared.size(); ++i) {
@@ -648,7 +654,7 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
         s.pct = shared_pct(s, same_request(i + 1) || (i > 0 && same_request(i - 1)));
     }
     const Cost cost_shared = {opts && opts->shared_item_cost > 0 ? opts->shared_item_cost : (latency_bound ? 60 : 450), 0,
-                              opts && opts->shared_item_cost > 0 ? 0 : (latency_bound ? 32 : 0)};
+                              opts && opts->shared_item_cost > 0 ? 0 : (roomy ? 20 : latency_bound ? 32 : 0)};
     // (a caller's own costs are taken as they are, and what no single wave will run is priced as the workgroup's)
     const bool own_costs = opts && (opts->private_item_cost > 0 || opts->private_merge_cost != 0);
     const int solo_tokens = opts && opts->solo_item_tokens != 0 ? std::max(0, opts->solo_item_tokens) : 512;
@@ -670,15 +676,17 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     // on a compute unit the one dispatched first is served first: with equal long shares it leaves at half the
     // launch), so the shares are cut short and every workgroup that finishes its share takes items
     // from the pool until it is empty.  The longer the shares, the larger the differences and the less a pool
-    // item's fixed cost weighs: a quarter of the private tokens for shares of up to 2048 tokens, rising to 60 % at
-    // 5120.  (25 / 40 / 60 %: mixed batch, 1900 tokens per share, 83.1 / 83.9 / 85.8 us; 8 requests of 64 branches, 5400 per
+    // item's fixed cost weighs: a quarter of the private tokens for shares of up to 2048 tokens, rising to 40 % at
+    // 5120; to 60 % where requests have sub-groups, which a larger pool leaves uncut.  (40 against 60 %, 27 steps of more than 2100 tokens per share: 0.9 % less on
+    // average, 8 requests of 16 branches x 32768 tokens 360.5 / 354, 4 reduced and 4 of 17 branches 182.4 / 180.3.  Shared workgroups are faster than when these were measured:)  (25 / 40 / 60 %: mixed batch, 1900 tokens per share, 83.1 / 83.9 / 85.8 us; 8 requests of 64 branches, 5400 per
     // share, 335 / 330 / 267, where what changes is how often the sub-groups' prefixes are cut; 640 sequences, 19000 per share, 798 /
     // 790 / 796.)  Without shared-prefix work the shares are alike and cutting a sequence costs more than the balance gains; and
     // where latency bounds the launch a claim's round trip is as much as it evens out (26.7 us without, 26.0 with 30 %, 28.6 with 25 % and
     // the constants of longer shares, mixed batch on one kv head).
+    const bool any_sub = std::any_of(shared.begin(), shared.end(), [](const Segment& s) { return s.siblings >= 2; });
     const int pool_default = shared.empty() || latency_bound
                                  ? 0
-                                 : (int)(25 + 35 * std::min<int64_t>(3072, std::max<int64_t>(0, share_tokens - 2048)) / 3072);
+                                 : (int)(25 + (any_sub ? 35 : 15) * std::min<int64_t>(3072, std::max<int64_t>(0, share_tokens - 2048)) / 3072);
     const int pool_pct = opts && opts->pool_pct != 0 ? std::max(0, std::min(90, opts->pool_pct)) : pool_default;
     const int pool_item_opt = opts && opts->pool_item_tokens > 0 ? opts->pool_item_tokens : 0;
     std::vector<Segment> pool;
@@ -726,9 +734,11 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     int64_t sub_groups = 0;
     for (const Segment& s : shared) sub_groups += s.siblings;
     const bool crowded = sub_groups * 2 > parts_total;
+    // Where shares are over early and there are enough of them a prefix gets one of its own (two of 60 tokens one after the other: 11.6 us, 8.4).
+    const bool apart = roomy && (int64_t)shared.size() * 2 <= parts_total;
     auto cut = [&](int64_t q) {
         p.items.clear();
-        p.n_parts_shared = partition_even(shared, g, q, kSharedBlockTokens, cost_shared, shared_tail_discount, crowded, 0, &p.items);
+        p.n_parts_shared = partition_even(shared, g, q, kSharedBlockTokens, cost_shared, shared_tail_discount, crowded, apart, 0, &p.items);
         p.n_parts_private = partition_fill(priv, q, kPrivateBlockTokens, cost_priv, p.n_parts_shared, &p.items);
         return p.n_parts_shared + p.n_parts_private <= parts_total || q >= cost_total * 2 + 4096;
     };

@@ -1,0 +1,30 @@
+"""Streaming loops at their edges: shared items of one block, of as many as the ring holds and a few more, with remainders of every kind, one after
+the other in one workgroup's ring."""
+import pytest
+
+from taper_inputs import AttnShape, fill_values_numpy, structure_custom
+from tests.gpu_util import assert_parity, run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("partial_format", ["f16_scaled", "f32"])
+@pytest.mark.parametrize("branches", [2, 9, 24])
+@pytest.mark.parametrize("shape", [(8, 1, 128), (16, 2, 128), (8, 2, 64), (16, 1, 64)])
+def test_shared_items_of_few_blocks(shape, branches, partial_format):
+    """Prefixes of 1 to 9 blocks (32 tokens at head_dim 128, 64 at 64), a token less and a token more, half blocks and whole pages; rows of 1 to 12
+    tiles, so that waves of one workgroup hold different numbers of them.  Bits repeat, and the whole workgroup's ring is used by item after item."""
+    from paper_2605_06914_amd import Context
+
+    sh, block = AttnShape(*shape, 16), 32 if shape[2] == 128 else 64
+    lengths = [1, 15, 16, 17] + [n * block + d for n in (1, 2, 3, 4, 5, 6, 9) for d in (-1, 0, 1)] + [3 * block + block // 2, 7 * block + 16]
+    reqs = [(n, [(i + k) % 3 for k in range(branches)]) for i, n in enumerate(lengths)]
+    b = fill_values_numpy(structure_custom(sh, reqs, seed=81))
+    ref, ref_lse = run_oracle(b)
+    ctx = Context(*shape, device=0, partial_format=partial_format)
+    for kw in (dict(), dict(target_workgroups=shape[1]), dict(target_workgroups=5 * shape[1])):
+        got, lse, bits = run_gpu(ctx, b, **kw)
+        assert_parity(got, ref, f"few blocks {shape} {branches} {partial_format} {kw}")
+        assert abs(lse - ref_lse).max() <= 1e-3  # (fp32 sums of at most 580 terms)
+        assert (run_gpu(ctx, b, **kw)[2] == bits).all()
+    ctx.close()
