@@ -484,6 +484,7 @@ struct PrivateSmem {
     int pick;      // pool item a workgroup has taken
     int todo[64];  // sequences whose last partial a run of solo items delivered
     int n_todo;
+    int sink[4][64];  // see touch_block
     MergeMeta meta;
 };
 
@@ -503,15 +504,90 @@ struct PrivateSmem {
 // requests of 12 branches, 2231 tokens per share, 104 / 108; no more than 0.6 % is lost anywhere above.  In shorter shares the wait
 // counts: 155 tokens per share 18.5 / 17.2, 577 31.5 / 30.4, 57 12.7 / 12.1, with 2 to 3 % the other way at others.  At
 // head_dim 64 a block holds half the bytes and the wait weighs more (mixed batch 46.3 / 45.4).
-template <int D, bool SOLO, int PF, bool HOLD>
-DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item& item, const i32x4 page, const int hk, const int after, PrivateSmem<D>& sm) {
+DEV unsigned lds_address(const void* p) { return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)p; }
+// 64 lanes x 16 bytes: lane l's from base + off (per lane) to LDS address `lds` + 16 l; streamed past the caches.
+// The compiler's hazard pass does not look inside: the statement itself keeps the one wait state from m0's write and the five that
+// lie between a vector instruction's write of the base (a v_readlane of a spilled register) and the load that reads it.
+// (That m0 is reserved is what the compiler would warn of at each use; nothing else in these kernels reads m0.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+DEV void load_to_lds(const char* base, unsigned off, unsigned lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds) : "m0", "memory");
+}
+// 64 lanes x 4 bytes, to be found in the L2 later.
+DEV void word_to_lds(const char* base, unsigned off, unsigned lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds) : "m0", "memory");
+}
+#pragma clang diagnostic pop
+// Brings a block's lines into the L2 for loads that follow when there are registers for them: a word of each 64 (32) bytes of its four tiles goes
+// to a place in LDS that nobody reads.  (Loads into registers would have to be waited for, or be moved while in flight.)  The wave's later loads
+// come in behind these, and it waits for some before it ends: a block is touched by the wave that goes on to compute it.
+template <int D>
+DEV void touch_block(const Inputs& in, const int hk, const int pid_a, const int pid_b, const void* sink) {
+    constexpr int TILE_BYTES = 32 * D;
+    const unsigned off = (opaque(threadIdx.x) & 63) * (TILE_BYTES / 64), lds = lds_address(sink);
+    const unsigned page_bytes = in.n_kv_heads * TILE_BYTES * 2;
+    // (words: a pool may start anywhere)
+    const char* kvb = (const char*)((uintptr_t)in.kv & ~(uintptr_t)3) + (int64_t)hk * TILE_BYTES;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const char* k = kvb + (uint64_t)(unsigned)(i ? pid_b : pid_a) * page_bytes;
+        word_to_lds(k, off, lds);
+        word_to_lds(k + (int64_t)in.n_kv_heads * TILE_BYTES, off, lds);
+    }
+}
+// What a wave has asked for of the item it does next: its queries and its first block.
+template <int D>
+struct Ahead {
+    bf16x8 qf[D / 32];
+    KVRegs<D> kv;
+};
+template <int D>
+DEV void load_block(const Inputs& in, const int hk, const int lane, const int pid_a, const int pid_b, KVRegs<D>& r) {
     constexpr int KS = D / 32, DT = D / 16, TILE = 16 * D;
+    const int n = lane & 15, qd = lane >> 4;
+    const unsigned page_bytes = in.n_kv_heads * TILE * 4;
+    const char* kvb = (const char*)in.kv + (int64_t)hk * TILE * 2;
+    const unsigned koff = lane * 16, voff = (qd * (4 * D) + n * 4) * 2;
+    const char* ka = kvb + (uint64_t)(unsigned)pid_a * page_bytes;  // (32 x 32 bits)
+    const char* kb = kvb + (uint64_t)(unsigned)pid_b * page_bytes;
+    const char* va = ka + (int64_t)in.n_kv_heads * TILE * 2;
+    const char* vb = kb + (int64_t)in.n_kv_heads * TILE * 2;
+#pragma unroll
+    for (int j = 0; j < KS; ++j) {
+        r.kx[j] = stream_load((const bf16x8*)(ka + koff + j * 1024));
+        r.ky[j] = stream_load((const bf16x8*)(kb + koff + j * 1024));
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+        r.va[dt] = stream_load((const bf16x4*)(va + voff + dt * 128));
+        r.vb[dt] = stream_load((const bf16x4*)(vb + voff + dt * 128));
+    }
+}
+// Asks for the queries and the first block (if it has one, of pages page[0] and page[1]) of an item of which the wave takes block b first.
+template <int D>
+DEV void begin_item(const Inputs& in, const taper_work_item& item, const i32x4 page, const int hk, const int lane, const int b, Ahead<D>& w) {
+    const int n = lane & 15, qd = lane >> 4, g = in.gqa;
+    // (lane columns past the last query head repeat the first; not stored)
+    const __bf16* qrow = (const __bf16*)in.q + ((int64_t)item.seq0 * in.n_q_heads + hk * g + (n < g ? n : 0)) * D;
+#pragma unroll
+    for (int j = 0; j < D / 32; ++j) w.qf[j] = *(const bf16x8*)(qrow + 8 * (4 * j + qd));
+    if (b < (item.n_tokens + 31) >> 5) load_block<D>(in, hk, lane, page[0], page[1], w.kv);
+}
+
+// `page`: the pages of the wave's first two blocks.  `tail` is called by every wave before its last block (or where that would be).  SOLO: the item's
+// queries and first block have been asked for (`w`), and `next`, called once its blocks are done with, may ask for the next item's.
+// (For items of the whole workgroup that gains nothing: 512 of 600 tokens 205.9 us with it and 206.9 without.)
+template <int D, bool SOLO, int PF, bool HOLD, typename Tail, typename Next>
+DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item item, const i32x4 page, const int hk, const int after, PrivateSmem<D>& sm,
+                      Ahead<D>& w, Tail&& tail, Next&& next) {
+    constexpr int KS = D / 32, DT = D / 16;
     auto& sm_o = sm.o;
     auto& sm_ml = sm.ml;
     const int lane = opaque(threadIdx.x) & 63;  // (opaque: per-lane constants are recomputed per item, not kept for the whole kernel)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, qd = lane >> 4;
-    const int Hkv = in.n_kv_heads, g = in.gqa;
+    const int g = in.gqa;
     const float c = a.scale_log2e;
     {
         const scalar_row row = table_row(a, item);
@@ -521,13 +597,9 @@ DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item
         const bool sole = item.kind >= 2;  // the sequence's whole context: no partial, no arrival, no merge
         MetaRegs mr = {};
         if (!SOLO && !sole) mr = meta_load(a, item, threadIdx.x);
+        if (!SOLO) begin_item<D>(in, item, page, hk, lane, wave, w);
 
-        bf16x8 qf[KS];  // (lane columns past the last query head repeat the first; not stored)
-        {
-            const __bf16* qrow = (const __bf16*)in.q + ((int64_t)item.seq0 * in.n_q_heads + hk * g + (n < g ? n : 0)) * D;
-#pragma unroll
-            for (int j = 0; j < KS; ++j) qf[j] = *(const bf16x8*)(qrow + 8 * (4 * j + qd));
-        }
+        bf16x8(&qf)[KS] = w.qf;
         float m1[1] = {-INFINITY}, l1[1] = {0.f};
         f32x4 O1[1][DT];
         float &m = m1[0], &l = l1[0];
@@ -535,32 +607,13 @@ DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) O[dt] = (f32x4)(0.f);
 
-        const unsigned page_bytes = Hkv * TILE * 4;
-        const char* kvb = (const char*)in.kv + (int64_t)hk * TILE * 2;
-        const unsigned koff = lane * 16, voff = (qd * (4 * D) + n * 4) * 2;
-        int pid_a = page[0], pid_b = page[1];  // the pages of the block loaded next
+        int pid_a = page[2], pid_b = page[3];  // the pages of the block loaded next
         auto fetch_ids = [&](int b) {
             const int ia = 2 * b < n_pages ? 2 * b : n_pages - 1, ib = 2 * b + 1 < n_pages ? 2 * b + 1 : n_pages - 1;
             pid_a = row[ia];
             pid_b = row[ib];
         };
         auto hold = [&] { if (HOLD && a.long_shares) asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
-        auto load_block = [&](KVRegs<D>& r) {
-            const char* ka = kvb + (uint64_t)(unsigned)pid_a * page_bytes;  // (32 x 32 bits)
-            const char* kb = kvb + (uint64_t)(unsigned)pid_b * page_bytes;
-            const char* va = ka + (int64_t)Hkv * TILE * 2;
-            const char* vb = kb + (int64_t)Hkv * TILE * 2;
-#pragma unroll
-            for (int j = 0; j < KS; ++j) {
-                r.kx[j] = stream_load((const bf16x8*)(ka + koff + j * 1024));
-                r.ky[j] = stream_load((const bf16x8*)(kb + koff + j * 1024));
-            }
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                r.va[dt] = stream_load((const bf16x4*)(va + voff + dt * 128));
-                r.vb[dt] = stream_load((const bf16x4*)(vb + voff + dt * 128));
-            }
-        };
         auto compute_block = [&](int b, KVRegs<D>& r, auto last) {
             f32x4 sx[1] = {(f32x4)(0.f)}, sy[1] = {(f32x4)(0.f)};
 #pragma unroll
@@ -584,34 +637,37 @@ DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item
         constexpr int STEP = SOLO ? 1 : 4;
         int b = SOLO ? 0 : wave;
         if (b < n_blocks) {
-            KVRegs<D> r0;
-            load_block(r0);
-            pid_a = page[2];
-            pid_b = page[3];
+            KVRegs<D>& r0 = w.kv;
             while (b + 2 * STEP < n_blocks) {
                 KVRegs<D> r1;
                 hold();
-                load_block(r1);
+                load_block<D>(in, hk, lane, pid_a, pid_b, r1);
                 fetch_ids(b + 2 * STEP);
                 compute_block(b, r0, std::false_type{});
                 hold();
-                load_block(r0);
+                load_block<D>(in, hk, lane, pid_a, pid_b, r0);
                 fetch_ids(b + 3 * STEP);
                 compute_block(b + STEP, r1, std::false_type{});
                 b += 2 * STEP;
             }
+            // (the last block is computed from where it lies: moved to r0 it would have to be there as a whole first)
             if (b + STEP < n_blocks) {
                 KVRegs<D> r1;
                 hold();
-                load_block(r1);
+                load_block<D>(in, hk, lane, pid_a, pid_b, r1);
                 compute_block(b, r0, std::false_type{});
-                r0 = r1;
-                b += STEP;
+                tail();
+                compute_block(b + STEP, r1, std::true_type{});
+            } else {
+                tail();
+                compute_block(b, r0, std::true_type{});
             }
-            compute_block(b, r0, std::true_type{});
+        } else {
+            tail();
         }
 
         if constexpr (SOLO) {  // this wave holds the whole state of the item's rows
+            next();
             l = sum_lane_groups(l);
             const float inv = 1.0f / l;
             const int h = hk * g + n;
@@ -710,19 +766,32 @@ DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item
 // Solo items [first, end) of a share, dealt to the waves (the plan lists them longest first; taking them as they get free cost tiny steps
 // 0.3 us, a barrier and a counter, and evened out nothing that was seen).  Their partials are announced together; the sequences that are then complete (few: what the other items of a step deliver comes later as a rule) are
 // merged by a wave each.  `announce`: there are partials among them, and merges are made in this launch.
+// While an item's last block is computed the next one's first is brought into the L2, and it is asked for before this one's rows are
+// stored (1024 items of 128 tokens 96 -> 89.5 us, of 300 tokens 216 -> 206; 512 of 32 to 512 98.2 -> 95.6).
 template <int D, int PF>
 DEV void solo_run(const StepArgs& a, const Inputs& in, const Start& start, const int end, const int hk, const bool announce, PrivateSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), first = start.first;
-    taper_work_item item = start.item;
-    i32x4 page = start.page;
     // (back and forth: the wave with the longest item of one round has the shortest of the next)
-    for (int k = first, turn = wave; k < end; k += 4, turn ^= 3) {
-        if (k + turn >= end) continue;
-        if (k != first) {
-            item = load_item(a, k + turn);
-            page = private_pages(a, item, 0, 1);
+    int k = first, turn = wave;
+    if (k + turn < end) {
+        taper_work_item item = start.item, after_it = {};
+        i32x4 page = start.page, after_page = {};
+        Ahead<D> w;
+        begin_item<D>(in, item, page, hk, opaque(threadIdx.x) & 63, 0, w);
+        for (bool more = true; more;) {
+            k += 4;
+            turn ^= 3;
+            more = k + turn < end;
+            if (more) {
+                after_it = load_item(a, k + turn);
+                after_page = private_pages(a, after_it, 0, 1);
+            }
+            private_item<D, true, PF, false>(
+                a, in, item, page, hk, 0, sm, w, [&] { if (more) touch_block<D>(in, hk, after_page[0], after_page[1], sm.sink[wave]); },
+                [&] { if (more) begin_item<D>(in, after_it, after_page, hk, opaque(threadIdx.x) & 63, 0, w); });
+            item = after_it;
+            page = after_page;
         }
-        private_item<D, true, PF, false>(a, in, item, page, hk, 0, sm);
     }
     if (!announce) {
         __syncthreads();
@@ -759,15 +828,21 @@ DEV void solo_run(const StepArgs& a, const Inputs& in, const Start& start, const
 // can take from its kv head's pool.  Every workgroup makes exactly one claim past the end of
 // the pool; the one that makes the last of those puts the counter back to zero for the next
 // launch.
+//
+// At an item's end nothing of the next one is in flight: its page ids and then its first blocks are asked for one after the other, 4 to 5 us each on a
+// saturated machine.  Where the item is long (kTouchFrom tokens and more) the share's next item and its page ids are read at its start, and its first blocks
+// are brought into the L2 while the last of this one is computed.  Launches of nothing but items of 600 tokens 208 -> 203 us, 99.8 -> 97 (partials 107 -> 102),
+// of 1200 193 -> 187.5; of 300 tokens 227 and of 128 105, but 235 and 122 with it: there the reading of item and ids holds up the item itself.
+constexpr int kTouchFrom = 512;
 template <int D, int PF, bool HOLD>
 DEV void private_items(const StepArgs& a, const Inputs& in, const Start& start, const bool announce, const int hk, const int after, PrivateSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int it0 = start.first;
     const int solo_end = it0 + start.n_solo, it1 = start.end;
+    const int wgs_per_head = in.n_parts_shared + a.n_parts_private;  // = gridDim.x / n_kv_heads
     taper_work_item item = start.item;
     i32x4 page = start.page;
-    bool given = it0 < it1 && it0 == solo_end;  // the first item is the start record's
-    const int wgs_per_head = in.n_parts_shared + a.n_parts_private;  // = gridDim.x / n_kv_heads
+    bool given = it0 < it1 && it0 == solo_end;  // item and page are the next item's (at first the start record's)
     if (it0 < solo_end) {
         solo_run<D, PF>(a, in, start, solo_end, hk, announce, sm);
         it0 = solo_end;
@@ -775,6 +850,7 @@ DEV void private_items(const StepArgs& a, const Inputs& in, const Start& start, 
 #ifdef TAPER_WG_TRACE
     bool turned = false;
 #endif
+    Ahead<D> w;
     for (;;) {
         int it = it0;
         if (it0 < it1) {
@@ -800,8 +876,18 @@ DEV void private_items(const StepArgs& a, const Inputs& in, const Start& start, 
             item = load_item(a, it);
             page = private_pages(a, item, wave, 4);
         }
-        given = false;
-        private_item<D, false, PF, HOLD>(a, in, item, page, hk, after, sm);
+        given = it0 < it1 && item.n_tokens > kTouchFrom;
+        taper_work_item own = {};
+        i32x4 own_page = {};
+        if (given) {
+            own = load_item(a, it0);
+            own_page = private_pages(a, own, wave, 4);
+        }
+        private_item<D, false, PF, HOLD>(
+            a, in, item, page, hk, after, sm, w,
+            [&] { if (given && wave < (own.n_tokens + 31) >> 5) touch_block<D>(in, hk, own_page[0], own_page[1], sm.sink[wave]); }, [] {});
+        item = own;
+        page = own_page;
     }
 }
 
@@ -850,17 +936,6 @@ struct SharedSmem {
     MergeMeta meta;
 };
 
-DEV unsigned lds_address(const void* p) { return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)p; }
-// 64 lanes x 16 bytes: lane l's from base + off (per lane) to LDS address `lds` + 16 l; streamed past the caches.
-// The compiler's hazard pass does not look inside: the statement itself keeps the one wait state from m0's write and the five that
-// lie between a vector instruction's write of the base (a v_readlane of a spilled register) and the load that reads it.
-// (That m0 is reserved is what the compiler would warn of at each use; nothing else in these kernels reads m0.)
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-DEV void load_to_lds(const char* base, unsigned off, unsigned lds) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds) : "m0", "memory");
-}
-#pragma clang diagnostic pop
 // The same through registers, for a pool that does not start at a multiple of 16 bytes (a view into a larger buffer, say):
 // ordinary loads take any address, and that direct ones do is nothing to rely on.  Tiles are multiples of 2 KiB, so
 // that the pool's start decides for all of them.

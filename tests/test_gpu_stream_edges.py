@@ -1,9 +1,9 @@
 """Streaming loops at their edges: shared items of one block, of as many as the ring holds and a few more, with remainders of every kind, one after
-the other in one workgroup's ring."""
+the other in one workgroup's ring; private items that follow each other."""
 import pytest
 
 from taper_inputs import AttnShape, fill_values_numpy, structure_custom
-from tests.gpu_util import assert_parity, run_gpu, run_oracle
+from tests.gpu_util import assert_parity, both_merges, run_gpu, run_oracle, torch_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -27,4 +27,32 @@ def test_shared_items_of_few_blocks(shape, branches, partial_format):
         assert_parity(got, ref, f"few blocks {shape} {branches} {partial_format} {kw}")
         assert abs(lse - ref_lse).max() <= 1e-3  # (fp32 sums of at most 580 terms)
         assert (run_gpu(ctx, b, **kw)[2] == bits).all()
+    ctx.close()
+
+
+@both_merges
+@pytest.mark.parametrize("offset", [0, 1, 2])
+@pytest.mark.parametrize("shape", [(8, 1, 128), (6, 2, 128), (8, 2, 64)])
+def test_items_that_follow_each_other(shape, offset, merge_launch):
+    """Long private items, behind which a share's next item is brought closer, followed by items of one block, of fewer blocks than waves, of as many, of
+    long ones; whole sequences and pieces, alone in a workgroup and dealt to single waves; pools that start at multiples of 2 and 4 bytes."""
+    import torch
+
+    from paper_2605_06914_amd import Context
+
+    sh = AttnShape(*shape, 16)
+    reqs = [(n, [0]) for n in (600, 1, 513, 33, 700, 64, 545, 97, 512, 520, 640, 128, 1100, 2, 513, 513, 129, 1030, 31)] + [(40, [600, 20, 530, 0, 900, 3])]
+    b = fill_values_numpy(structure_custom(sh, reqs, seed=82))
+    ref, ref_lse = run_oracle(b)
+    st = b.structure
+    room = torch.empty(st.n_pool_pages * sh.page_elems + 8, dtype=torch.bfloat16, device="cuda:0")
+    kv = room[offset:offset + st.n_pool_pages * sh.page_elems]
+    kv.copy_(torch_bf16(b.kv).view(-1))
+    ctx = Context(*shape, device=0)
+    one = dict(target_workgroups=shape[1])
+    for kw in (dict(), one, dict(one, solo_item_tokens=-1), dict(one, solo_item_tokens=4096), dict(target_workgroups=3 * shape[1], solo_item_tokens=-1, pool_pct=30)):
+        got, lse, bits = run_gpu(ctx, b, kv_dev=kv, merge_launch=merge_launch, **kw)
+        assert_parity(got, ref, f"items in a row {shape} {offset} {kw}")
+        assert abs(lse - ref_lse).max() <= 1e-3  # (fp32 sums of at most 1100 terms)
+        assert (run_gpu(ctx, b, kv_dev=kv, merge_launch=merge_launch, **kw)[2] == bits).all()
     ctx.close()
