@@ -9,9 +9,8 @@
 
 namespace taper {
 
-// Device-resident integer metadata of one step plus the tensors of one layer.
-struct StepArgs {
-    // (what the attention kernels read comes first, in as few cache lines as it takes)
+// What the attention and merge kernels read of a step, in as few cache lines as it takes, but for what comes to them in registers.
+struct DecodeArgs {
     void* out;                 // bf16 [S][Hq][D]
     float* lse;                // f32 [S][Hq] or null
     const int32_t* bt;         // [S][bt_stride]
@@ -27,13 +26,21 @@ struct StepArgs {
     int32_t bt_stride;
     int32_t n_merge;           // entries in `merge`
     int32_t n_q_heads, n_kv_heads, gqa;
-    int32_t n_parts_shared, n_parts_private;
+    int32_t n_parts_private;
     int32_t long_shares;       // shares long enough for private work to hold back beside shared-prefix work (see private_item)
     int32_t merge_after;       // the merges are a launch of their own behind the attention launch (see merge_kernel)
     float scale_log2e;         // scale * log2(e)
+#ifdef TAPER_WG_TRACE
+    long long* trace;          // [4 * workgroups] clocks of a trace build (see wg_trace.py), or null
+#endif
+};
+
+// Device-resident integer metadata of one step plus the tensors of one layer.
+struct StepArgs : DecodeArgs {
     const ShareStart* starts;  // [n_parts]
     const void* q;             // bf16 [S][Hq][D]
     const void* kv;            // bf16 pool
+    int32_t n_parts_shared;
     int32_t n_seqs, head_dim;
     int32_t max_row_tiles_shared;
     int32_t partial_format;    // taper_partial_format of ws_o
@@ -42,11 +49,7 @@ struct StepArgs {
     const int32_t* seg_len;        // tokens of each private segment
     const int32_t* seg_page0;      // block-table entry each private segment starts at
     const int32_t* ctx_len;
-#ifdef TAPER_WG_TRACE
-    long long* trace;          // [4 * workgroups] clocks of a trace build (see wg_trace.py), or null
-#endif
 };
-
 
 // Device memory that belongs to no context: the scratch array of taper_decode_step_attention_static.
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;

@@ -252,15 +252,30 @@ DEV void zero_tail(bf16x4 (&va)[DT], bf16x4 (&vb)[DT], int qd, int n_valid) {
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(4))) int32_t* scalar_row;
-DEV taper_work_item load_item(const StepArgs& a, const int it) {
+DEV taper_work_item load_item(const DecodeArgs& a, const int it) {
     return __builtin_bit_cast(taper_work_item, ((const __attribute__((address_space(4))) i32x8*)a.items)[it]);
 }
-// What a launch's first loads need, beside a wave's start record: leading kernel arguments, which arrive in registers.
+// What a launch's first loads need, beside a wave's start record.  It comes as two leading kernel arguments of four words, which arrive in
+// registers.  (Each argument more is host time of every launch: with seven of them, calls that wait for the host took 5.4 us, with these 4.9 us.)
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 struct Inputs {
     const ShareStart* starts;
     const void *kv, *q;
     int n_kv_heads, n_q_heads, gqa, n_parts_shared;
 };
+static u32x4 pack_pointers(const StepArgs& a) {
+    const uint64_t starts = (uint64_t)a.starts, kv = (uint64_t)a.kv;
+    return {(unsigned)starts, (unsigned)(starts >> 32), (unsigned)kv, (unsigned)(kv >> 32)};
+}
+static u32x4 pack_queries(const StepArgs& a) {  // (gqa is at most 16)
+    return {(unsigned)(uint64_t)a.q, (unsigned)((uint64_t)a.q >> 32), (unsigned)a.n_kv_heads, (unsigned)a.n_parts_shared << 5 | (unsigned)a.gqa};
+}
+DEV Inputs unpack_inputs(const u32x4 p, const u32x4 q) {
+    typedef const __attribute__((address_space(1))) char* global_bytes;
+    const auto pointer = [](unsigned lo, unsigned hi) { return (const void*)(global_bytes)((uint64_t)hi << 32 | lo); };
+    const int gqa = q[3] & 31;
+    return {(const ShareStart*)pointer(p[0], p[1]), pointer(p[2], p[3]), pointer(q[0], q[1]), (int)q[2], (int)q[2] * gqa, gqa, (int)(q[3] >> 5)};
+}
 // A wave's start record, by scalar loads side by side.
 struct Start {
     int first, end, turn, n_solo;
@@ -288,15 +303,13 @@ DEV Start load_start(const Inputs& in, const int part, const int wave) {
 }
 // The other arguments, read from where they lie as they are needed.  (As a parameter that is used they are all loaded at the kernel's start,
 // and waited for, 60 registers of them, before the start record is asked for.)
-DEV const StepArgs& step_args() {
-    constexpr int at = (sizeof(Inputs) + alignof(StepArgs) - 1) / alignof(StepArgs) * alignof(StepArgs);
-    return *(const StepArgs*)((CONSTANT char*)__builtin_amdgcn_kernarg_segment_ptr() + at);
-}
-DEV scalar_row table_row(const StepArgs& a, const taper_work_item& item) {
+DEV const DecodeArgs& decode_args() { return *(const DecodeArgs*)((CONSTANT char*)__builtin_amdgcn_kernarg_segment_ptr() + 2 * sizeof(u32x4)); }
+static_assert(alignof(DecodeArgs) <= sizeof(u32x4), "the arguments follow the leading two directly");
+DEV scalar_row table_row(const DecodeArgs& a, const taper_work_item& item) {
     return (scalar_row)(a.bt + (int64_t)item.seq0 * a.bt_stride + item.page0);
 }
 // Pages of blocks b and b + step of a private item (past the last page: the last page).
-DEV i32x4 private_pages(const StepArgs& a, const taper_work_item& item, const int b, const int step) {
+DEV i32x4 private_pages(const DecodeArgs& a, const taper_work_item& item, const int b, const int step) {
     const scalar_row row = table_row(a, item);
     const int last = ((item.n_tokens + 15) >> 4) - 1;
     i32x4 p;
@@ -309,7 +322,7 @@ DEV i32x4 private_pages(const StepArgs& a, const taper_work_item& item, const in
 
 // (No branches: a lane without a value asks for one past the descriptor's end and gets zeros, so nothing is waited
 // for before meta_store.)
-DEV MetaRegs meta_load(const StepArgs& a, const taper_work_item& item, const int tid_) {
+DEV MetaRegs meta_load(const DecodeArgs& a, const taper_work_item& item, const int tid_) {
     const int tid = opaque(tid_);
     const auto starts = partial_buffer(a.merge_start), entries = partial_buffer(a.merge);
     MetaRegs r;
@@ -341,7 +354,7 @@ DEV void meta_store(MergeMeta& mm, const MetaRegs& r, const int n_branch, const 
 // groups of one wave may work on different sequences side by side.  Lane idx of the group owns
 // 16-byte columns c, c + LPR, ... (U of them) of one row; n_thr / LPR rows are merged per pass.
 template <int D, int U, int PF>
-DEV void merge_rows(const StepArgs& a, const MergeMeta& mm, const int s, const int hk, const int e0, const int e1,
+DEV void merge_rows(const DecodeArgs& a, const MergeMeta& mm, const int s, const int hk, const int e0, const int e1,
                     const int idx_, const int n_thr) {
     typedef PartialVec<PF> Vec;
     typedef typename Vec::type vec;
@@ -426,7 +439,7 @@ DEV void merge_rows(const StepArgs& a, const MergeMeta& mm, const int s, const i
 // that (s, hk) has then been written through (each writer waited for its stores before
 // its increment) and the caller must merge.  The counter is left at zero for the next launch
 // (by a device-scope store, like every other access to it).
-DEV bool arrive_last(const StepArgs& a, const int s, const int hk, const int n_entries) {
+DEV bool arrive_last(const DecodeArgs& a, const int s, const int hk, const int n_entries) {
     int* c = a.counters + (int64_t)s * a.n_kv_heads + hk;
     const bool last = atomicAdd(c, 1) == n_entries - 1;
     if (last) __hip_atomic_store(c, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -439,7 +452,7 @@ DEV bool arrive_last(const StepArgs& a, const int s, const int hk, const int n_e
 // launch's longest workgroups.)  Called by all threads after the partial rows have been stored
 // and waited for; `todo` and `n_todo` are workgroup-shared.
 template <int D, int PF>
-DEV void arrive_and_merge(const StepArgs& a, const MergeMeta& mm, int* todo, int* n_todo, const taper_work_item& item,
+DEV void arrive_and_merge(const DecodeArgs& a, const MergeMeta& mm, int* todo, int* n_todo, const taper_work_item& item,
                           const int hk, const int tid) {
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (wave == 0) {  // (an item has at most 64 branches)
@@ -579,7 +592,7 @@ DEV void begin_item(const Inputs& in, const taper_work_item& item, const i32x4 p
 // queries and first block have been asked for (`w`), and `next`, called once its blocks are done with, may ask for the next item's.
 // (For items of the whole workgroup that gains nothing: 512 of 600 tokens 205.9 us with it and 206.9 without.)
 template <int D, bool SOLO, int PF, bool HOLD, typename Tail, typename Next>
-DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item item, const i32x4 page, const int hk, const int after, PrivateSmem<D>& sm,
+DEV void private_item(const DecodeArgs& a, const Inputs& in, const taper_work_item item, const i32x4 page, const int hk, const int after, PrivateSmem<D>& sm,
                       Ahead<D>& w, Tail&& tail, Next&& next) {
     constexpr int KS = D / 32, DT = D / 16;
     auto& sm_o = sm.o;
@@ -769,7 +782,7 @@ DEV void private_item(const StepArgs& a, const Inputs& in, const taper_work_item
 // While an item's last block is computed the next one's first is brought into the L2, and it is asked for before this one's rows are
 // stored (1024 items of 128 tokens 96 -> 89.5 us, of 300 tokens 216 -> 206; 512 of 32 to 512 98.2 -> 95.6).
 template <int D, int PF>
-DEV void solo_run(const StepArgs& a, const Inputs& in, const Start& start, const int end, const int hk, const bool announce, PrivateSmem<D>& sm) {
+DEV void solo_run(const DecodeArgs& a, const Inputs& in, const Start& start, const int end, const int hk, const bool announce, PrivateSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), first = start.first;
     // (back and forth: the wave with the longest item of one round has the shortest of the next)
     int k = first, turn = wave;
@@ -835,7 +848,7 @@ DEV void solo_run(const StepArgs& a, const Inputs& in, const Start& start, const
 // of 1200 193 -> 187.5; of 300 tokens 227 and of 128 105, but 235 and 122 with it: there the reading of item and ids holds up the item itself.
 constexpr int kTouchFrom = 512;
 template <int D, int PF, bool HOLD>
-DEV void private_items(const StepArgs& a, const Inputs& in, const Start& start, const bool announce, const int hk, const int after, PrivateSmem<D>& sm) {
+DEV void private_items(const DecodeArgs& a, const Inputs& in, const Start& start, const bool announce, const int hk, const int after, PrivateSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int it0 = start.first;
     const int solo_end = it0 + start.n_solo, it1 = start.end;
@@ -953,7 +966,7 @@ DEV void wait_loads_and_meet() {
 // The partial rows of a shared-prefix item: tile k of this wave holds row 16 * (wave + 4k) + n of the
 // item's R rows in lane column n, 4 values per 16-dim group and lane group.
 template <int D, int NTW, int PF>
-DEV void store_shared_partials(const StepArgs& a, const taper_work_item& item, const int hk, const int R, const int wave, const int n, const int qd, const float (&m)[NTW], const float (&l)[NTW],
+DEV void store_shared_partials(const DecodeArgs& a, const taper_work_item& item, const int hk, const int R, const int wave, const int n, const int qd, const float (&m)[NTW], const float (&l)[NTW],
                                const f32x4 (&O)[NTW][D / 16]) {
     constexpr int DT = D / 16;
 #pragma unroll
@@ -986,7 +999,7 @@ DEV void store_shared_partials(const StepArgs& a, const taper_work_item& item, c
 // Streams the item's tokens against the NA tiles wave, wave + 4, ... of its rows and stores their partial rows.
 // Every wave of the workgroup takes its part in staging and meets the others once per block, whatever its NA.
 template <int D, int NA, int PF, bool ANY>
-DEV void shared_stream(const StepArgs& a, const Inputs& in, const taper_work_item& item, const i32x4 page, const i32x4 page2, const int hk,
+DEV void shared_stream(const DecodeArgs& a, const Inputs& in, const taper_work_item& item, const i32x4 page, const i32x4 page2, const int hk,
                        SharedSmem<D>& sm, const int tid, const int wave) {
     typedef SharedSmem<D> Sm;
     constexpr int KS = D / 32, DT = D / 16, NT = NA ? NA : 1, QB = 8 * D;  // QB: bytes of a 4-token quarter of a V tile
@@ -1185,7 +1198,7 @@ DEV void shared_stream(const StepArgs& a, const Inputs& in, const taper_work_ite
 }
 
 template <int D, int NTW, int PF, bool ANY>
-DEV void shared_path(const StepArgs& a, const Inputs& in, const Start& start, const int hk, const int after, SharedSmem<D>& sm) {
+DEV void shared_path(const DecodeArgs& a, const Inputs& in, const Start& start, const int hk, const int after, SharedSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int it0 = start.first, it1 = start.end;
     taper_work_item item = start.item;
@@ -1238,7 +1251,7 @@ union StepSmem {
 };
 // ALLP: a launch without shared-prefix work (no shared path in the kernel).  ANY: the pool may start at any address.
 template <int D, int NTW, int PF, bool ALLP, bool ANY>
-DEV void run_share(const StepArgs& a, const Inputs& in, char* smem_raw) {
+DEV void run_share(const DecodeArgs& a, const Inputs& in, char* smem_raw) {
     const int part = blockIdx.x / in.n_kv_heads;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     Start start = load_start(in, part, wave);
@@ -1265,16 +1278,16 @@ DEV void run_share(const StepArgs& a, const Inputs& in, char* smem_raw) {
 }
 
 template <int D, int NTW, int PF, bool ALLP>
-__global__ __launch_bounds__(256, 2) void decode_kernel(const ShareStart* starts, const void* kv, const void* q, int n_kv_heads, int n_q_heads, int gqa, int n_parts_shared, StepArgs) {
+__global__ __launch_bounds__(256, 2) void decode_kernel(u32x4 pointers, u32x4 queries, DecodeArgs) {
     __shared__ __attribute__((aligned(16))) char smem_raw[sizeof(StepSmem<D>)];
-    run_share<D, NTW, PF, ALLP, false>(step_args(), {starts, kv, q, n_kv_heads, n_q_heads, gqa, n_parts_shared}, smem_raw);
+    run_share<D, NTW, PF, ALLP, false>(decode_args(), unpack_inputs(pointers, queries), smem_raw);
 }
 // Steps with shared-prefix work over a pool that does not start at a multiple of 16 bytes (a kernel of its own: a branch per block
 // in the others cost them 1 to 2 %, mixed batch on one kv head 26.4 -> 26.7 us, 64 branches 270 -> 274).
 template <int D, int PF>
-__global__ __launch_bounds__(256, 2) void any_start_kernel(const ShareStart* starts, const void* kv, const void* q, int n_kv_heads, int n_q_heads, int gqa, int n_parts_shared, StepArgs) {
+__global__ __launch_bounds__(256, 2) void any_start_kernel(u32x4 pointers, u32x4 queries, DecodeArgs) {
     __shared__ __attribute__((aligned(16))) char smem_raw[sizeof(StepSmem<D>)];
-    run_share<D, 3, PF, false, true>(step_args(), {starts, kv, q, n_kv_heads, n_q_heads, gqa, n_parts_shared}, smem_raw);
+    run_share<D, 3, PF, false, true>(decode_args(), unpack_inputs(pointers, queries), smem_raw);
 }
 
 // ---------------------------------------------------------------------------
@@ -1305,7 +1318,7 @@ DEV float wave_sum(float v) {
     return sum_lane_groups(v + row_rotate<1>(v));
 }
 template <int D, int PF>
-__global__ __launch_bounds__(1024) void merge_kernel(StepArgs a) {
+__global__ __launch_bounds__(1024) void merge_kernel(DecodeArgs a) {
     typedef PartialVec<PF> Vec;
     typedef typename Vec::type vec;
     constexpr int LPR = D / Vec::N, SLOTS = 64 / LPR, ROW_BYTES = LPR * 16, T = 32 / SLOTS;
@@ -1452,13 +1465,13 @@ hipError_t launch_stream_read(const void* base, int64_t pieces_per_wg, int n_wor
 template <int D, int PF>
 static hipError_t launch_decode_as(const StepArgs& a, const dim3 grid, const int ntw, hipStream_t s) {
     const dim3 block(256);
-    if (a.n_parts_shared == 0) hipLaunchKernelGGL((decode_kernel<D, 1, PF, true>), grid, block, 0, s, a.starts, a.kv, a.q, a.n_kv_heads, a.n_q_heads, a.gqa, a.n_parts_shared, a);
+    if (a.n_parts_shared == 0) hipLaunchKernelGGL((decode_kernel<D, 1, PF, true>), grid, block, 0, s, pack_pointers(a), pack_queries(a), static_cast<const DecodeArgs&>(a));
     else if (ntw > 3) return hipErrorInvalidValue;
-    else if ((uintptr_t)a.kv & 15) hipLaunchKernelGGL((any_start_kernel<D, PF>), grid, block, 0, s, a.starts, a.kv, a.q, a.n_kv_heads, a.n_q_heads, a.gqa, a.n_parts_shared, a);
-    else if (ntw <= 1) hipLaunchKernelGGL((decode_kernel<D, 1, PF, false>), grid, block, 0, s, a.starts, a.kv, a.q, a.n_kv_heads, a.n_q_heads, a.gqa, a.n_parts_shared, a);
-    else if (ntw == 2) hipLaunchKernelGGL((decode_kernel<D, 2, PF, false>), grid, block, 0, s, a.starts, a.kv, a.q, a.n_kv_heads, a.n_q_heads, a.gqa, a.n_parts_shared, a);
-    else hipLaunchKernelGGL((decode_kernel<D, 3, PF, false>), grid, block, 0, s, a.starts, a.kv, a.q, a.n_kv_heads, a.n_q_heads, a.gqa, a.n_parts_shared, a);
-    if (a.merge_after) hipLaunchKernelGGL((merge_kernel<D, PF>), dim3(a.n_seqs * a.n_kv_heads), dim3(64 * a.gqa), 0, s, a);
+    else if ((uintptr_t)a.kv & 15) hipLaunchKernelGGL((any_start_kernel<D, PF>), grid, block, 0, s, pack_pointers(a), pack_queries(a), static_cast<const DecodeArgs&>(a));
+    else if (ntw <= 1) hipLaunchKernelGGL((decode_kernel<D, 1, PF, false>), grid, block, 0, s, pack_pointers(a), pack_queries(a), static_cast<const DecodeArgs&>(a));
+    else if (ntw == 2) hipLaunchKernelGGL((decode_kernel<D, 2, PF, false>), grid, block, 0, s, pack_pointers(a), pack_queries(a), static_cast<const DecodeArgs&>(a));
+    else hipLaunchKernelGGL((decode_kernel<D, 3, PF, false>), grid, block, 0, s, pack_pointers(a), pack_queries(a), static_cast<const DecodeArgs&>(a));
+    if (a.merge_after) hipLaunchKernelGGL((merge_kernel<D, PF>), dim3(a.n_seqs * a.n_kv_heads), dim3(64 * a.gqa), 0, s, static_cast<const DecodeArgs&>(a));
     return hipGetLastError();
 }
 
