@@ -780,7 +780,10 @@ DEV void private_item(const DecodeArgs& a, const Inputs& in, const taper_work_it
 // 0.3 us, a barrier and a counter, and evened out nothing that was seen).  Their partials are announced together; the sequences that are then complete (few: what the other items of a step deliver comes later as a rule) are
 // merged by a wave each.  `announce`: there are partials among them, and merges are made in this launch.
 // While an item's last block is computed the next one's first is brought into the L2, and it is asked for before this one's rows are
-// stored (1024 items of 128 tokens 96 -> 89.5 us, of 300 tokens 216 -> 206; 512 of 32 to 512 98.2 -> 95.6).
+// stored (1024 items of 128 tokens 97 -> 89 us, of 300 tokens 216 -> 206; 512 of 32 to 512 98.2 -> 95.7).  Not behind short items, where more requests are in the
+// way of the item's own.  Touched ahead / not: 4096 items of 6 tokens 109 / 88 us, 4096 of 40 199 / 174, 2048 of 96 164 / 158.  Asked for before the rows
+// are stored / behind it: 4096 of 6 88 / 80, 10 requests of 48 branches of 4 to 8 tokens 37.5 / 36.0; 2048 of 40 92.7 / 93.4, and of 96 as fast either way.
+constexpr int kSoloTouchFrom = 96, kSoloAheadFrom = 32;
 template <int D, int PF>
 DEV void solo_run(const DecodeArgs& a, const Inputs& in, const Start& start, const int end, const int hk, const bool announce, PrivateSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), first = start.first;
@@ -799,9 +802,11 @@ DEV void solo_run(const DecodeArgs& a, const Inputs& in, const Start& start, con
                 after_it = load_item(a, k + turn);
                 after_page = private_pages(a, after_it, 0, 1);
             }
+            const bool touch = more && item.n_tokens > kSoloTouchFrom, ahead = more && item.n_tokens > kSoloAheadFrom;
+            const auto begin = [&] { begin_item<D>(in, after_it, after_page, hk, opaque(threadIdx.x) & 63, 0, w); };
             private_item<D, true, PF, false>(
-                a, in, item, page, hk, 0, sm, w, [&] { if (more) touch_block<D>(in, hk, after_page[0], after_page[1], sm.sink[wave]); },
-                [&] { if (more) begin_item<D>(in, after_it, after_page, hk, opaque(threadIdx.x) & 63, 0, w); });
+                a, in, item, page, hk, 0, sm, w, [&] { if (touch) touch_block<D>(in, hk, after_page[0], after_page[1], sm.sink[wave]); }, [&] { if (ahead) begin(); });
+            if (more && !ahead) begin();
             item = after_it;
             page = after_page;
         }

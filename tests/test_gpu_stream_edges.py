@@ -41,7 +41,7 @@ def test_items_that_follow_each_other(shape, offset, merge_launch):
     from paper_2605_06914_amd import Context
 
     sh = AttnShape(*shape, 16)
-    reqs = [(n, [0]) for n in (600, 1, 513, 33, 700, 64, 545, 97, 512, 520, 640, 128, 1100, 2, 513, 513, 129, 1030, 31)] + [(40, [600, 20, 530, 0, 900, 3])]
+    reqs = [(n, [0]) for n in (600, 1, 513, 33, 700, 64, 545, 97, 512, 520, 640, 128, 1100, 2, 513, 513, 129, 1030, 31, 96, 97, 95, 32, 5, 65, 98)] + [(40, [600, 20, 530, 0, 900, 3])]
     b = fill_values_numpy(structure_custom(sh, reqs, seed=82))
     ref, ref_lse = run_oracle(b)
     st = b.structure
