@@ -634,7 +634,7 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     const int64_t share_tokens = tok_listed / parts_total;
     const bool latency_bound = share_tokens < kSaturatingShareTokens, roomy = share_tokens < kRoomyShareTokens;
     p.long_shares = share_tokens >= kLongShareTokens;
-    // An item of more than 4 row tiles gives waves two or three tiles, and a block's chain 0.85 or 1.05 us instead of 0.65: it no
+    // An item of more than 4 row tiles gives waves two or three tiles, and a block's chain 0.74 or 0.89 us instead of 0.47: it no
     // longer keeps up with its slice of a saturated memory system.  (80 / 100 / 120 / 140 %, 8 requests of 2048 to 8192 tokens
     // beside 16 serial ones, us: 4 branches, 2 tiles, 76.0 / 76.5 / 76.3 / 77.1; 10, 5 tiles, 101.7 / 95.0 / 94.0 / 94.6; 18, 9 tiles,
     // 130.5 / 116.9 / 114.9 / 114.8; 24, 12 tiles, 159 / 138 / 134 / 135.)  Sub-groups of one request find part of their tokens in the L2
