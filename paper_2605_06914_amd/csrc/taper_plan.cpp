@@ -676,17 +676,15 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     // on a compute unit the one dispatched first is served first: with equal long shares it leaves at half the
     // launch), so the shares are cut short and every workgroup that finishes its share takes items
     // from the pool until it is empty.  The longer the shares, the larger the differences and the less a pool
-    // item's fixed cost weighs: a quarter of the private tokens for shares of up to 2048 tokens, rising to 40 % at
-    // 5120; to 60 % where requests have sub-groups, which a larger pool leaves uncut.  (40 against 60 %, 27 steps of more than 2100 tokens per share: 0.9 % less on
-    // average, 8 requests of 16 branches x 32768 tokens 360.5 / 354, 4 reduced and 4 of 17 branches 182.4 / 180.3.  Shared workgroups are faster than when these were measured:)  (25 / 40 / 60 %: mixed batch, 1900 tokens per share, 83.1 / 83.9 / 85.8 us; 8 requests of 64 branches, 5400 per
+    // item's fixed cost weighs: a quarter of the private tokens for shares of up to 2048 tokens, rising to 60 % at
+    // 5120.  (25 / 40 / 60 %: mixed batch, 1900 tokens per share, 83.1 / 83.9 / 85.8 us; 8 requests of 64 branches, 5400 per
     // share, 335 / 330 / 267, where what changes is how often the sub-groups' prefixes are cut; 640 sequences, 19000 per share, 798 /
     // 790 / 796.)  Without shared-prefix work the shares are alike and cutting a sequence costs more than the balance gains; and
     // where latency bounds the launch a claim's round trip is as much as it evens out (26.7 us without, 26.0 with 30 %, 28.6 with 25 % and
     // the constants of longer shares, mixed batch on one kv head).
-    const bool any_sub = std::any_of(shared.begin(), shared.end(), [](const Segment& s) { return s.siblings >= 2; });
     const int pool_default = shared.empty() || latency_bound
                                  ? 0
-                                 : (int)(25 + (any_sub ? 35 : 15) * std::min<int64_t>(3072, std::max<int64_t>(0, share_tokens - 2048)) / 3072);
+                                 : (int)(25 + 35 * std::min<int64_t>(3072, std::max<int64_t>(0, share_tokens - 2048)) / 3072);
     const int pool_pct = opts && opts->pool_pct != 0 ? std::max(0, std::min(90, opts->pool_pct)) : pool_default;
     const int pool_item_opt = opts && opts->pool_item_tokens > 0 ? opts->pool_item_tokens : 0;
     std::vector<Segment> pool;

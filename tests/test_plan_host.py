@@ -291,6 +291,23 @@ def test_pool_items_stay_within_their_default_size(seed):
     ctx.close()
 
 
+@pytest.mark.parametrize("shape,share_tokens,pct", [("serial", 2040, 25), ("serial", 2600, 31), ("serial", 3584, 42), ("serial", 5120, 60),
+                                                    ("serial", 12000, 60), ("sub_groups", 5120, 60)])
+def test_the_pools_part_of_the_private_tokens_follows_the_length_of_the_shares(shape, share_tokens, pct):
+    """A quarter for shares of up to 2048 tokens, 60 % from 5120 on, in proportion between; whether requests have sub-groups makes no
+    difference.  One prefix of 4 (or 64) branches beside 200 equal serial requests that fill the rest."""
+    total, prefix, n, width = share_tokens * 64, 4096, 200, 64 if shape == "sub_groups" else 4
+    listed = prefix * (1 if width == 4 else 3)  # (three sub-groups of at most 24 branches each stream the prefix)
+    each = (total - listed - 64 * width) // n
+    reqs = [(prefix, [64] * width)] + [(0, [each + (1 if i < total - listed - 64 * width - each * n else 0)]) for i in range(n)]
+    e = build(structure_custom(QWEN, reqs, seed=3)).export()
+    F = {k: i for i, k in enumerate(e["item_fields"])}
+    it = e["items"]
+    private = it[it[:, F["kind"]] != 0][:, F["n_tokens"]].sum()
+    pooled = it[e["part_start"][-1]:, F["n_tokens"]].sum()
+    assert abs(pooled - private * pct / 100) <= private / 100 + 64, (pooled / private, pct)  # (whole percents, cut at 32 tokens)
+
+
 def test_where_merges_are_made_can_be_set():
     """The rule's choice, the other one, and back; nothing else of the plan changes."""
     st = structure_config3()
