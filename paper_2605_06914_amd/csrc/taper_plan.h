@@ -18,12 +18,14 @@ constexpr int kMaxRowTilesPerItem = 12;  // 16-row query tiles one shared-kernel
 // What a wave of a share begins with, so that its first KV loads wait for one trip to memory and not for one to the share's range, one
 // to its item and one to the block table.
 struct alignas(64) WaveStart {
+    WaveStart() {}         // (left as it is: make_starts writes every field, and an array of them need not be cleared first)
     int32_t first, end;    // the share's items
     int32_t turn, n_solo;  // part_turn's flags; how many of the items single waves run
     taper_work_item item;  // the share's first item; of a solo run, this wave's first
     int32_t page[4];       // its first pages, in the order the wave loads them (see make_starts)
 };
 struct alignas(64) ShareStart {
+    ShareStart() {}
     WaveStart wave[4];
     int32_t more[4];  // pages 4 to 7 of a shared item at head_dim 128
 };
