@@ -115,8 +115,8 @@ DEV void softmax_block(const f32x4 (&sx)[NA], const f32x4 (&sy)[NA], float c, fl
 }
 
 // The accumulator a block's last matrix instruction wrote must not be read by a vector instruction
-// before the matrix pipeline has delivered it (eight passes; the hardware does not interlock, the
-// compiler inserts the wait states).  On a path that leaves the block's code through two branches
+// before the matrix pipeline has delivered it (four passes, 8 wait states; the hardware does not interlock, the
+// compiler inserts them).  On a path that leaves the block's code through two branches
 // and starts with register copies of the accumulators, the compiler was seen to leave too few: the
 // last 16 dims of long private items came out wrong, in one build and not in another.  So a block
 // ends with the wait states written out, fenced so that the scheduler leaves them where they are.

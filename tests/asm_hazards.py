@@ -4,14 +4,14 @@ instruction wrote it.
 The matrix pipeline delivers its result some cycles after issue and the hardware does not
 interlock a following vector-ALU read; the compiler pads with wait states.  It was seen to
 leave a path uncovered (matrix instruction, two branches, a register copy of the accumulator:
-3 to 4 wait states instead of 7), which gave wrong numbers in one build and not in the next.
+3 to 4 wait states instead of 8), which gave wrong numbers in one build and not in the next.
 This walks every control-flow path from each matrix instruction for NEED wait states and
 reports vector-ALU reads of its destination inside that window.  `s_nop k` counts k + 1, any
 other instruction 1; a register that is overwritten drops out of the dependence.
 """
 import re
 
-NEED = 7  # wait states between a 4-pass matrix instruction and a vector-ALU read of its result
+NEED = 8  # wait states between a 4-pass matrix instruction and a vector-ALU read of its result: what the compiler keeps on gfx950, nowhere fewer
 _REG = re.compile(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b")
 
 

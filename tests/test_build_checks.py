@@ -65,6 +65,8 @@ def test_the_scanner_sees_a_planted_hazard():
     assert n == 1 and len(bad) == 1 and bad[0][4] == 3 and "v_mov_b64" in bad[0][3]
     good, _ = scan(kernel(["\ts_nop 5"]))
     assert good == []
+    one_short, _ = scan(kernel(["\ts_nop 4"]))
+    assert len(one_short) == 1 and one_short[0][4] == 7
     overwritten, _ = scan(kernel(["\tv_mov_b64_e32 v[108:109], v[4:5]", "\tv_mov_b64_e32 v[110:111], v[6:7]"]))
     assert [f for f in overwritten if f[1] == ".LBB0_2" and "v[2:3]" in f[3]] == []
 
