@@ -332,7 +332,8 @@ bool recording(hipStream_t s) {
     return status == hipStreamCaptureStatusActive;
 }
 
-// Where the parts of a step lie in the static scratch array: plan image | counters | statistics | partial rows.
+// Where the parts of a step lie in the static scratch array: plan image (the start records first) | counters | statistics | partial rows.
+// The start records have kStaticStartsBytes of their own; the limits of the rest count without them.
 struct StaticLayout {
     size_t image = 0, workspace = 0, ml_off = 0, o_off = 0;
     int64_t counters = 0;
@@ -364,7 +365,8 @@ int static_plan(const taper_ctx* ctx, int n_seqs, int64_t n_pool_pages, const in
             return fail(TAPER_EINVAL, "step too large for the static scratch array: plan image " + std::to_string(image) +
                                           " bytes (limit " + std::to_string(kStaticImageBytes) + "), image + workspace " +
                                           std::to_string(image + lay->workspace) + " bytes (limit " +
-                                          std::to_string(taper::kStaticScratchBytes) + ")");
+                                          std::to_string(taper::kStaticScratchBytes) + "), start records " + std::to_string(starts) +
+                                          " bytes (limit " + std::to_string(taper::kStaticStartsBytes) + ")");
         if (o.pool_pct == 0 && h->n_pool_items > 0) o.pool_pct = -1;
         else o.target_workgroups /= 2;
     }

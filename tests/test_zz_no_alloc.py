@@ -85,6 +85,8 @@ def test_static_entry_rejects_a_step_beyond_the_array():
         ctx.decode_step_attention_static(q, kv, 16, bt, np.arange(S, dtype=np.int32), np.full(S, 5, np.int32),
                                          np.zeros(S, np.int32), out)
     assert e.value.status == TAPER_EINVAL and "static scratch" in str(e.value)
+    for limit in (8 << 20, 64 << 20, 160 << 10):  # every limit that the call checks, with the step's size beside it
+        assert f"bytes (limit {limit})" in str(e.value)
     ctx.close()
 
 
@@ -104,12 +106,13 @@ def test_static_entry_cuts_a_step_coarser_that_does_not_fit_as_it_would_best_be_
     ctx = Context(64, 8, 128, device=0, partial_format="f32")
     grid = 2 * torch.cuda.get_device_properties(0).multi_processor_count
 
-    def needs(**kw):  # image (every piece aligned to 256 bytes) and workspace of the plan
+    def needs(**kw):  # image without the start records (every piece aligned to 256 bytes) and workspace of the plan
         p = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, **kw)
         e = p.export()
         p.free()
-        S, rows, shares = st.n_seqs, e["n_partial_rows"], len(e["part_start"]) - 1
-        pieces = [st.block_table.size * 4, len(e["items"]) * 32, (2 * shares + 1) * 4, len(e["merge"]) * 8, (S + 1) * 8 * 4, rows * 16,
+        S, rows = st.n_seqs, e["n_partial_rows"]
+        assert (len(e["part_start"]) - 1) * 320 <= 160 << 10  # (the start records' own room)
+        pieces = [st.block_table.size * 4, len(e["items"]) * 32, len(e["merge"]) * 8, (S + 1) * 8 * 4, rows * 16,
                   rows * 128 * 4] + [(S + 1) * 4] * 2 + [S * 4] * 4
         return sum(-(-n // 256) * 256 for n in pieces)
 
