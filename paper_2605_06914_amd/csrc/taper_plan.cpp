@@ -58,7 +58,7 @@ constexpr double kTokensPerMergedRow = 5.0;      // see least_tokens
 constexpr int kBriefTokens = 128;            // private segments that are priced as a single wave's work, in steps of up to
 constexpr int64_t kBriefShareTokens = 700;   // so many tokens per share,
 constexpr int64_t kBriefItemCost = 160;      // at so much (see Cost::brief)
-constexpr double kMergeLaunchFromUs = 12;    // see merges_after
+constexpr double kMergeLaunchFromUs = 10.5;   // see merges_after
 constexpr int64_t kSaturatingShareTokens = 350;  // shares of fewer tokens are over before the memory system is saturated
 constexpr int64_t kRoomyShareTokens = 128;       // with so few there are shares to spare (one holds 256 as a rule): prefixes may be cut finer
 constexpr int64_t kLongShareTokens = 2000;       // from here on private work holds back beside shared-prefix work (see private_item in the kernels)
@@ -288,11 +288,13 @@ void level_shares(int n_parts, const Cost& cost, std::vector<taper_work_item>* i
 }
 
 // What a step that ends all at once takes, in us, if its merges are made in the attention launch: 4 to the first block, the longest
-// share's chain of blocks and query rows, and `rounds` of its longest merge.  Within 7 % of the measured time for half of 185 such steps,
-// within 15 % rms.
+// share's chain of blocks (a shared one's by the row tiles of its waves) and query rows, and `rounds` of its longest merge.  Least squares over
+// 318 random steps of 3 rounds and more below 350 tokens per share: within 11 % of the measured time for half of them, 18 % rms (15 below 25 us; those
+// below 13 us read 10 % long).  With 1.4 us for every shared block, as before its scores were made a block ahead, half were within 13 %, 23 % rms.
 double expected_us(const taper_attn_config& cfg, const HostPlan& p, int64_t rounds) {
     const int g = cfg.n_q_heads / cfg.n_kv_heads, shared_block = cfg.head_dim == 128 ? 32 : 64;
     const auto blocks = [](int n, int per) { return (double)((n + per - 1) / per); };
+    const double block_us = cfg.head_dim == 128 ? 1 : 0.8;
     double longest = 0;
     for (int q = 0; q < p.n_parts_shared + p.n_parts_private; ++q) {
         double us = 0, wave[4] = {0, 0, 0, 0};
@@ -300,28 +302,28 @@ double expected_us(const taper_attn_config& cfg, const HostPlan& p, int64_t roun
         for (int i = p.part_start[q]; i < p.part_start[q + 1]; ++i) {
             const taper_work_item& it = p.items[i];
             const int k = i - p.part_start[q];
-            if (it.kind == 0) us += 1.4 * blocks(it.n_tokens, shared_block) + 0.024 * it.n_branch * g;
-            else if (i < solo_end) wave[k / 4 % 2 ? 3 - k % 4 : k % 4] += 0.4 * blocks(it.n_tokens, kPrivateBlockTokens);
-            else us += 0.9 * blocks(it.n_tokens, 4 * kPrivateBlockTokens);
+            if (it.kind == 0) us += (it.n_branch * g <= 4 * 16 ? 0.85 : it.n_branch * g <= 8 * 16 ? 1.3 : 1.55) * block_us * blocks(it.n_tokens, shared_block) + 0.04 * it.n_branch * g;
+            else if (i < solo_end) wave[k / 4 % 2 ? 3 - k % 4 : k % 4] += 1.2 * blocks(it.n_tokens, kPrivateBlockTokens);
+            else us += 0.6 * blocks(it.n_tokens, 4 * kPrivateBlockTokens);
         }
         longest = std::max(longest, us + *std::max_element(wave, wave + 4));
     }
-    return 4 + longest + (cfg.head_dim == 128 ? 1.6 : 1.1) * rounds;
+    return 4 + longest + (cfg.head_dim == 128 ? 1.25 : 1.05) * rounds;
 }
 
 // Whether the step's merges are a launch of their own (merge_kernel) instead of being made by whoever delivers a sequence's last
 // partial.  What counts is the longest merge that one workgroup would make alone at the end: a shared item's branches side by
-// side, eight at a time, 8 rows each, in rounds of 8 entries (4 of fp32 rows); such a round is 1.3 to 1.7 us.  The launch costs 2 to 3 us, its
-// boundary and three trips to memory, and the merged rows' way through the caches, about 3 MB per us.  Attention calls of 312 random steps on
-// the same cuts, merged behind / inside, us: 5 rounds and more 20.3 / 28.5 (mixed batch on one kv head), 19.5 / 29.5, 42 / 83, 73.6 / 111, the
-// worst the other way 82.8 / 79.8; 3 and 4 rounds in steps that end all at once (below 350 tokens per share) 20.4 / 27.4, 17 / 21.7, worst 15.0 /
-// 13.6; in longer ones, where most merges are hidden behind other workgroups' streaming, 18
-// of 37 slower (119.5 / 105.1 at worst) and 19 faster (46.4 / 51.4 at best).
-// A launch is also 3 us of the host's time (a call 8.5 instead of 5.9), which a step of several layers with their appends waits for where the layers are short (15.5 us
-// per layer with one launch, 20 with two): steps expected to take less than kMergeLaunchFromUs would gain 0.7 us per call (11 of 113, from -2
-// to 2) and lose 2 to 4.5 per layer of such a loop (2 requests of 1100 to 1600 tokens and 3 of 3 to 5 branches, four layers: 68 us, 84
-// with the launch).  Just above that line loops of two or three layers still lose (27 -> 29.6, 23.6 -> 26.3 us per layer), calls alone gain (10.6 / 13.2, 12.3 /
-// 16.6); from some 25 us per layer on both gain (28.6 / 33.6, 31 / 50).
+// side, eight at a time, 8 rows each, in rounds of 8 entries (4 of fp32 rows); such a round is 1 to 1.7 us.  The launch costs 2 to 3 us, its
+// boundary and three trips to memory, and the merged rows' way through the caches, about 3 MB per us.  Attention calls on the same cuts,
+// merged behind / inside, us.  Steps that end all at once (below 350 tokens per share): 5 rounds and more 0.60 of the time on average over 169 random
+// ones (11.5 / 39.5 at best, 12.2 / 11.7 the only one slower); 3 and 4 rounds 0.85 over 149, 26 of them slower (12.0 / 19.4 at best, 46.6 / 35.8 at worst).
+// Longer ones, where most merges are hidden behind other workgroups' streaming: 18 of 37 of 3 and 4 rounds slower (119.5 / 105.1 at worst) and 19 faster
+// (46.4 / 51.4 at best).
+// A launch is also 3 us of the host's time (a call 8.5 instead of 5.9), which a step of several layers with a small launch between them waits for where the
+// layers are short.  With merges inside, the same 318 steps by what a call takes: below 10, 10 to 12, 12 to 15, 15 to 18 and 18 to 22 us a call alone gains 0.9,
+// 1.4, 2.6, 3.5 and 5.2 us by the launch; a loop of four layers loses 3.9, 3.1 and 0.9 us per layer, then gains 1.1 and 3.7.  kMergeLaunchFromUs lies
+// where the one side's gain grows past the other's loss: of the 8 steps expected to take less, calls would gain 0 to 3.5 us and loops lose
+// 3.2 to 4.7; of the 5 from there to 12, calls gain 0.7 to 4.8 and loops lose 0 to 3.6.
 bool merges_after(const taper_attn_config& cfg, const HostPlan& p, bool ends_at_once) {
     const int g = cfg.n_q_heads / cfg.n_kv_heads, per_round = cfg.partial_format == TAPER_PARTIAL_F32 ? 4 : 8;
     int64_t rounds = 0, rows = 0;

@@ -344,6 +344,19 @@ def test_short_steps_keep_their_merges_inside_the_attention_launch():
     ctx.close()
 
 
+@pytest.mark.parametrize("shape,partial,reqs,launch", [
+    # a chain of 14 to 18 blocks of one row tile and three rounds: 9.4 us a call (8.5 with the launch), 19.3 a layer in a loop (22.7)
+    ((4, 1, 64), "f32", [(868, [1, 3, 3, 0, 3]), (823, [0, 2, 1, 2, 2]), (877, [1, 4, 1, 1, 4, 3, 4]), (851, [1, 3, 1, 3, 1, 1, 4]),
+                         (861, [0, 1, 0, 4, 5, 3, 4]), (875, [0, 4, 1, 2, 0, 4])], 0),
+    # four rounds: 14.0 us a call (9.2), 21.1 a layer (21.4)
+    ((32, 8, 64), "f32", [(2685, [16, 6, 10, 3, 19, 29, 11]), (2449, [13, 14, 7, 27, 3, 6, 15, 21])], 1)])
+def test_the_line_between_merges_inside_and_a_launch_of_their_own(shape, partial, reqs, launch):
+    """Steps of three and four rounds on either side of it, by what the present kernels take for them."""
+    ctx = Context(*shape, device=-1, partial_format=partial)
+    assert build(structure_custom(AttnShape(*shape, 16), reqs, seed=5), ctx).export()["merge_launch"] == launch
+    ctx.close()
+
+
 def test_a_callers_costs_hold_for_short_items_too():
     """100 sequences of 20 tokens (a block of 32 each): as many to a share as its size and the caller's item cost say."""
     st = structure_custom(QWEN, [(20, [0])] * 100, seed=6)
