@@ -391,3 +391,33 @@ def test_a_pool_taken_from_before_many_short_segments_costs_no_more_time():
     ahead, behind = best(True), best(False)
     assert ahead < 2 * behind, (ahead, behind)
     ctx.close()
+
+
+def shared_shares(st, **kw):
+    """Requests whose prefix each shared share has items of, and the number of shares in all."""
+    e = build(st, **kw).export()
+    F = {k: i for i, k in enumerate(e["item_fields"])}
+    it, ps = e["items"], e["part_start"]
+    return [{int(st.branch_group[s]) for s in it[ps[q]:ps[q + 1], F["seq0"]]} for q in range(e["n_parts_shared"])], len(ps) - 1
+
+
+@pytest.mark.parametrize("serial,requests,apart", [(6600, 20, True), (6700, 20, False), (10, 32, True), (10, 33, False)])
+def test_short_prefixes_get_shares_of_their_own_where_there_are_enough(serial, requests, apart):
+    """Below 128 tokens per share (64 shares: 8192 tokens; 20 prefixes of 60 tokens and 3 branches of 5 make 1500) and up to half the shares."""
+    st = structure_custom(QWEN, [(60, [5, 5, 5])] * requests + [(0, [serial])], seed=6)
+    held, n = shared_shares(st)
+    assert n <= 64 and set().union(*held) == set(range(requests))
+    assert all(len(h) == 1 for h in held) == apart, held
+
+
+@pytest.mark.parametrize("heads,branches,pct", [(2, 32, 140), (1, 64, 140), (8, 9, 220), (8, 16, 220), (8, 17, 300), (8, 24, 300)])
+def test_prices_of_shared_items_in_short_shares(heads, branches, pct):
+    """A shared token's price by the item's row tiles and 20 per branch below 128 tokens per share, 180 % and 32 per branch up to 350: the default cuts
+    are those of these prices given by hand, and not those of the other range.  (4, 4, 5, 8, 9 and 12 row tiles; 512 shares.)"""
+    sh = AttnShape(heads, 1, 128, 16)
+    cuts = lambda n, **kw: build(structure_custom(sh, [(n * (1 + i) // 12, [3 + i] * branches) for i in range(24)], seed=7), Context(heads, 1, 128, device=-1), **kw).export()["items"][:, :8].tolist()
+    below, above = dict(shared_cost_pct=pct, shared_item_cost=60 + 20 * branches), dict(shared_cost_pct=180, shared_item_cost=60 + 32 * branches)
+    for lengths, right, wrong in (((800, 1100, 1500), below, above), ((3000, 3500, 4500), above, below)):
+        default = [cuts(n) for n in lengths]
+        assert default == [cuts(n, **right) for n in lengths]
+        assert default != [cuts(n, **wrong) for n in lengths]
