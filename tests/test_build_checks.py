@@ -140,3 +140,11 @@ def test_the_kernels_for_pools_that_start_anywhere_meet_the_same_checks(compiled
     for check in (scan, scan_scalar_addresses):
         findings, kernels = check(asm, name_filter="any_start_kernel")
         assert kernels == 4 and not findings, findings[:5]
+
+
+def test_the_leading_arguments_arrive_in_registers(compiled):
+    """Eight words of arguments are preloaded (a compiler option that is not part of any interface): without it every launch waits for
+    a trip to the argument segment before its start record is asked for."""
+    asm, _ = compiled
+    words = re.findall(r"\.amdhsa_kernel (\S*(?:decode_kernel|any_start_kernel)\S*)(?:.|\n)*?\.amdhsa_user_sgpr_kernarg_preload_length (\d+)", asm)
+    assert len(words) == 20 and all(int(n) == 8 for _, n in words), words

@@ -195,3 +195,33 @@ def test_two_batches_taking_turns_repeat_their_bits(merge_launch):
     for plan, *_ in dev:
         plan.free()
     ctx.close()
+
+
+@both_merges
+@pytest.mark.parametrize("partial_format", ["f16_scaled", "f32"])
+@pytest.mark.parametrize("shape", [(16, 2, 128), (8, 2, 64)])
+def test_a_nan_in_a_visible_key_makes_its_own_rows_nan_and_no_others(shape, partial_format, merge_launch):
+    """One not-a-number in K of a prefix's last token, of a branch's own first token and in the middle of a long sequence, on one kv head each: every row that
+    sees it is NaN in all its elements and its lse, every other row has the bits that it has without."""
+    from paper_2605_06914_amd import Context
+
+    sh = AttnShape(*shape, 16)
+    b = fill_values_numpy(structure_custom(sh, [(700, [0, 33, 300]), (2100, [0]), (0, [45]), (129, [1] * 20), (64, [5, 600, 2])], seed=503))
+    st, g = b.structure, shape[0] // shape[1]
+    ctx = Context(*shape, device=0, partial_format=partial_format)
+    clean, poisoned = torch_bf16(b.kv), b.kv.reshape(st.n_pool_pages, 2, shape[1], sh.page_size * sh.head_dim).copy()
+    expect = np.zeros((st.n_seqs, shape[0]), bool)
+    # (first sequence, its sequences, kv head, the token's place in its context)
+    for seq, n, head, token in ((0, 3, 0, 699), (3, 1, 1, 1000), (9, 1, 1, 129), (26, 1, 0, 64 + 599)):
+        n_prefix = int(st.prefix_len[seq])
+        entry, slot = (token // 16, token % 16) if token < n_prefix else (-(-n_prefix // 16) + (token - n_prefix) // 16, (token - n_prefix) % 16)
+        poisoned[st.block_table[seq, entry], 0, head, slot * 8] = 0x7FC0  # (dim 0: a K tile is [D / 8][token][8])
+        expect[seq:seq + n, head * g:(head + 1) * g] = True
+    bad = torch_bf16(poisoned.reshape(b.kv.shape))
+    for kw in (dict(), dict(target_workgroups=shape[1]), FINE):
+        _, _, want = run_gpu(ctx, b, kv_dev=clean, merge_launch=merge_launch, **kw)
+        got, lse, bits = run_gpu(ctx, b, kv_dev=bad, merge_launch=merge_launch, **kw)
+        assert np.array_equal(np.isnan(got), np.broadcast_to(expect[:, :, None], got.shape)), kw
+        assert np.array_equal(np.isnan(lse), expect), kw
+        assert np.array_equal(bits[~expect], want[~expect]), kw
+    ctx.close()
