@@ -20,6 +20,7 @@
 // per-row power-of-two scale) are combined through their (m, l) by the workgroup that delivers
 // the sequence's last partial (merge_rows) or, in steps of many partials, by a launch of their own
 // behind the attention launch (merge_kernel).
+#include <climits>
 #include <type_traits>
 
 #include "taper_internal.h"
@@ -257,7 +258,6 @@ DEV taper_work_item load_item(const DecodeArgs& a, const int it) {
 }
 // What a launch's first loads need, beside a wave's start record.  It comes as two leading kernel arguments of four words, which arrive in
 // registers.  (Each argument more is host time of every launch: with seven of them, calls that wait for the host took 5.4 us, with these 4.9 us.)
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 struct Inputs {
     const ShareStart* starts;
     const void *kv, *q;
@@ -501,22 +501,6 @@ struct PrivateSmem {
     MergeMeta meta;
 };
 
-// One private item: a chunk of one sequence's own tokens, for kv head hk.
-// SOLO: the item is run by the calling wave alone (short items: four of them proceed side by side in a workgroup, with no
-// barrier and no LDS), which stores its result or its partial rows; otherwise the four waves of the workgroup share the item's
-// blocks.
-// Bound by HBM: 128 requests of 4096 tokens take 321 us, a bare read of the same pages 310.  The depth of the pipeline is
-// not what matters then (one set of registers refilled as it is used up, two, and two with the block after next
-// already asked for all measure within 0.5 %); two sets win where a wave has two blocks and the machine is idle
-// (mixed batch on one kv head: 9 % slower with one set).
-// The block-table row is read by scalar loads (constant address space, wave-uniform pointer), which do not wait for
-// the KV loads in flight; a vector load of a page id completes in order, behind everything issued before it.
-// HOLD: beside shared-prefix work (head_dim 128) a wave asks for its next block only when the one before has landed, if the
-// step's shares are long (2000 tokens and more): what it asks for earlier it only waits for longer, and the shared workgroups with
-// it.  Held back / not, us: 128 requests of 3 branches 471 / 474, of 17 branches 798 / 804; 16 branches of 32768 tokens 353.1 / 354.4; 8
-// requests of 12 branches, 2231 tokens per share, 104 / 108; no more than 0.6 % is lost anywhere above.  In shorter shares the wait
-// counts: 155 tokens per share 18.5 / 17.2, 577 31.5 / 30.4, 57 12.7 / 12.1, with 2 to 3 % the other way at others.  At
-// head_dim 64 a block holds half the bytes and the wait weighs more (mixed batch 46.3 / 45.4).
 DEV unsigned lds_address(const void* p) { return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)p; }
 // 64 lanes x 16 bytes: lane l's from base + off (per lane) to LDS address `lds` + 16 l; streamed past the caches.
 // The compiler's hazard pass does not look inside: the statement itself keeps the one wait state from m0's write and the five that
@@ -588,6 +572,22 @@ DEV void begin_item(const Inputs& in, const taper_work_item& item, const i32x4 p
     if (b < (item.n_tokens + 31) >> 5) load_block<D>(in, hk, lane, page[0], page[1], w.kv);
 }
 
+// One private item: a chunk of one sequence's own tokens, for kv head hk.
+// SOLO: the item is run by the calling wave alone (short items: four of them proceed side by side in a workgroup, with no
+// barrier and no LDS), which stores its result or its partial rows; otherwise the four waves of the workgroup share the item's
+// blocks.
+// Bound by HBM: 128 requests of 4096 tokens take 321 us, a bare read of the same pages 310.  The depth of the pipeline is
+// not what matters then (one set of registers refilled as it is used up, two, and two with the block after next
+// already asked for all measure within 0.5 %); two sets win where a wave has two blocks and the machine is idle
+// (mixed batch on one kv head: 9 % slower with one set).
+// The block-table row is read by scalar loads (constant address space, wave-uniform pointer), which do not wait for
+// the KV loads in flight; a vector load of a page id completes in order, behind everything issued before it.
+// HOLD: beside shared-prefix work (head_dim 128) a wave asks for its next block only when the one before has landed, if the
+// step's shares are long (2000 tokens and more): what it asks for earlier it only waits for longer, and the shared workgroups with
+// it.  Held back / not, us: 128 requests of 3 branches 471 / 474, of 17 branches 798 / 804; 16 branches of 32768 tokens 353.1 / 354.4; 8
+// requests of 12 branches, 2231 tokens per share, 104 / 108; no more than 0.6 % is lost anywhere above.  In shorter shares the wait
+// counts: 155 tokens per share 18.5 / 17.2, 577 31.5 / 30.4, 57 12.7 / 12.1, with 2 to 3 % the other way at others.  At
+// head_dim 64 a block holds half the bytes and the wait weighs more (mixed batch 46.3 / 45.4).
 // `page`: the pages of the wave's first two blocks.  `tail` is called by every wave before its last block (or where that would be).  SOLO: the item's
 // queries and first block have been asked for (`w`), and `next`, called once its blocks are done with, may ask for the next item's.
 // (For items of the whole workgroup that gains nothing: 512 of 600 tokens 205.9 us with it and 206.9 without.)
@@ -779,11 +779,15 @@ DEV void private_item(const DecodeArgs& a, const Inputs& in, const taper_work_it
 // Solo items [first, end) of a share, dealt to the waves (the plan lists them longest first; taking them as they get free cost tiny steps
 // 0.3 us, a barrier and a counter, and evened out nothing that was seen).  Their partials are announced together; the sequences that are then complete (few: what the other items of a step deliver comes later as a rule) are
 // merged by a wave each.  `announce`: there are partials among them, and merges are made in this launch.
-// While an item's last block is computed the next one's first is brought into the L2, and it is asked for before this one's rows are
-// stored (1024 items of 128 tokens 97 -> 89 us, of 300 tokens 216 -> 206; 512 of 32 to 512 98.2 -> 95.7).  Not behind short items, where more requests are in the
-// way of the item's own.  Touched ahead / not: 4096 items of 6 tokens 109 / 88 us, 4096 of 40 199 / 174, 2048 of 96 164 / 158.  Asked for before the rows
-// are stored / behind it: 4096 of 6 88 / 80, 10 requests of 48 branches of 4 to 8 tokens 37.5 / 36.0; 2048 of 40 92.7 / 93.4, and of 96 as fast either way.
-constexpr int kSoloTouchFrom = 96, kSoloAheadFrom = 32;
+// The next item's first block is asked for before this one's rows are stored, behind items of more than 32 tokens (before / behind, us, inputs taking turns: 2048 items of
+// 40 tokens 92.6 / 94.9, 41.5 / 42.5 at head_dim 64; 1024 of 128 97.0 / 98.0; 2048 of 96 157.0 / 155.4; 4096 of 6 88 / 80; 8 kv heads here and below).
+// It is also brought into the L2 while this one's last block is computed, behind items of more than 96 tokens: beside shared-prefix work (455 of 84 to 133 beside 4
+// prefixes of 30000 tokens 172.5 touched, 175.2 not; 150 of 91 to 169 beside 2 of 150 to 300 at head_dim 64 16.4 / 16.6), and in launches of private work alone at head_dim 128 in runs
+// of at most kSoloTouchRun.  Touched / not: 512 of 256 tokens (8 items a run) 91.0 / 94.2, 512 of 32 to 512 95.6 / 97.7, 600 of 130 (9 or 10) 59.0 / 60.3, 655 of 200 (10) 97.1 / 98.0.  In longer runs the waves
+// drift apart and the machine is busy throughout, so that what is touched only waits in front of what is needed: 1500 of 130 on 4 kv heads (12) 88.3 / 81.9, 1008
+// of 130 (16) 109.3 / 103.1, 1310 of 100 (20) 120.6 / 111.0, 1024 of 300 224.7 / 219.3.  Behind short items as well: 4096 of 6 107 / 91.  At head_dim 64 a block is half the bytes:
+// 655 of 200 47.3 / 46.5, 400 of 100 to 400 35.0 / 34.6, 1310 of 100 52.8 / 52.3, the other way 1024 of 128 44.4 / 46.2.
+constexpr int kSoloTouchFrom = 96, kSoloTouchRun = 10, kSoloAheadFrom = 32;
 template <int D, int PF>
 DEV void solo_run(const DecodeArgs& a, const Inputs& in, const Start& start, const int end, const int hk, const bool announce, PrivateSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), first = start.first;
@@ -802,7 +806,7 @@ DEV void solo_run(const DecodeArgs& a, const Inputs& in, const Start& start, con
                 after_it = load_item(a, k + turn);
                 after_page = private_pages(a, after_it, 0, 1);
             }
-            const bool touch = more && item.n_tokens > kSoloTouchFrom, ahead = more && item.n_tokens > kSoloAheadFrom;
+            const bool touch = more && item.n_tokens > kSoloTouchFrom && (in.n_parts_shared || (D == 128 && end - first <= kSoloTouchRun)), ahead = more && item.n_tokens > kSoloAheadFrom;
             const auto begin = [&] { begin_item<D>(in, after_it, after_page, hk, opaque(threadIdx.x) & 63, 0, w); };
             private_item<D, true, PF, false>(
                 a, in, item, page, hk, 0, sm, w, [&] { if (touch) touch_block<D>(in, hk, after_page[0], after_page[1], sm.sink[wave]); }, [&] { if (ahead) begin(); });
@@ -848,10 +852,13 @@ DEV void solo_run(const DecodeArgs& a, const Inputs& in, const Start& start, con
 // launch.
 //
 // At an item's end nothing of the next one is in flight: its page ids and then its first blocks are asked for one after the other, 4 to 5 us each on a
-// saturated machine.  Where the item is long (kTouchFrom tokens and more) the share's next item and its page ids are read at its start, and its first blocks
-// are brought into the L2 while the last of this one is computed.  Launches of nothing but items of 600 tokens 208 -> 203 us, 99.8 -> 97 (partials 107 -> 102),
-// of 1200 193 -> 187.5; of 300 tokens 227 and of 128 105, but 235 and 122 with it: there the reading of item and ids holds up the item itself.
-constexpr int kTouchFrom = 512;
+// saturated machine.  Where the item is long the share's next item and its page ids are read at its start, and its first blocks are brought into the L2 while
+// the last of this one is computed.  Touched / not, us, inputs taking turns, 8 kv heads.  Beside shared-prefix work behind items of more than 512 tokens: mixed batch 83.4 / 83.9,
+// 44.9 / 45.1 at head_dim 64, 178.0 / 178.6 with half of its requests in the reduce phase.  In launches of private work alone at head_dim 128 behind more than 768: 163 items of 800 tokens
+// 88.8 / 91.4, 256 of 1200 197.3 / 199.4, 100 of 1300 83.9 / 86.9, 50 of 2600 84.2 / 86.0; shorter ones end all at once, and what is touched waits in front of what is
+// needed: 500 of 600 211.6 / 205.3, 400 of 700 199.5 / 195.0, 600 of 600 on 4 kv heads 138.5 / 131.4.  At head_dim 64 not in those: 512 of 600 107.5 / 103.5, 131 of 1000
+// 51.1 / 50.0, 50 of 2600 43.9 / 43.4, the other way 256 of 1200 96.7 / 98.2.
+DEV int touch_from(const Inputs& in, int d) { return in.n_parts_shared ? 512 : d == 128 ? 768 : INT_MAX; }
 template <int D, int PF, bool HOLD>
 DEV void private_items(const DecodeArgs& a, const Inputs& in, const Start& start, const bool announce, const int hk, const int after, PrivateSmem<D>& sm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -894,7 +901,7 @@ DEV void private_items(const DecodeArgs& a, const Inputs& in, const Start& start
             item = load_item(a, it);
             page = private_pages(a, item, wave, 4);
         }
-        given = it0 < it1 && item.n_tokens > kTouchFrom;
+        given = it0 < it1 && item.n_tokens > touch_from(in, D);
         taper_work_item own = {};
         i32x4 own_page = {};
         if (given) {

@@ -56,3 +56,28 @@ def test_items_that_follow_each_other(shape, offset, merge_launch):
         assert abs(lse - ref_lse).max() <= 1e-3  # (fp32 sums of at most 1100 terms)
         assert (run_gpu(ctx, b, kv_dev=kv, merge_launch=merge_launch, **kw)[2] == bits).all()
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [5, 10, 11])
+@pytest.mark.parametrize("shape", [(8, 1, 128), (6, 2, 128), (8, 2, 64)])
+def test_runs_of_solo_items_and_rows_of_long_ones(shape, n):
+    """Runs of as many single-wave items as the next one's first block is brought closer for, and one more, behind items of 96 and 97 tokens; whole
+    workgroup's items of 768 and 769 tokens behind each other in a launch of private work alone.  One share per kv head, bits repeat."""
+    from paper_2605_06914_amd import Context
+
+    sh = AttnShape(*shape, 16)
+    ctx = Context(*shape, device=0)
+    one = dict(target_workgroups=shape[1], pool_pct=-1)
+    for lengths, solo in (([97] * n, 512), ([96] * (n - 1) + [130], 512), ([97 + 31 * i for i in range(n)], 512), ([769, 768, 769, 1, 1000, 33, 769], -1)):
+        b = fill_values_numpy(structure_custom(sh, [(k, [0]) for k in lengths], seed=83))
+        ref, ref_lse = run_oracle(b)
+        st = b.structure
+        plan = ctx.plan_build(st.block_table, st.branch_group, st.prefix_len, st.suffix_len, st.n_pool_pages, solo_item_tokens=solo, **one)
+        e = plan.export()
+        plan.free()
+        assert e["n_parts_private"] == 1 and e["solo_items"][0] == (0 if solo < 0 else n), lengths
+        got, lse, bits = run_gpu(ctx, b, solo_item_tokens=solo, **one)
+        assert_parity(got, ref, f"rows of items {shape} {lengths}")
+        assert abs(lse - ref_lse).max() <= 1e-3  # (fp32 sums of at most 1000 terms)
+        assert (run_gpu(ctx, b, solo_item_tokens=solo, **one)[2] == bits).all()
+    ctx.close()
