@@ -640,15 +640,16 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     //    a shared one of up to 4, 8 and 12 row tiles, 9 for a private one, whose four waves each have a block in flight.  180 % for
     //    all and 32 per branch where the grid is full (140 / 220 / 300 and 20 there: the mixed batch on one kv head, 232 tokens per share, 19.5
     //    us either way, two steps of 233 and 236 4 and 7 % slower); 140 / 220 / 300 and 20 below kRoomyShareTokens, where finer cuts cost no other
-    //    work its share (34 random steps of 20 to 128 tokens per share: ten 9 to 58 % faster, three 2 to 3 % slower; 19 branches of some 500 tokens
-    //    31.9 -> 20.1 us, 13 of 800 22.1 -> 15.7, 43 of 1100 26.4 -> 18.1).
+    //    work its share.  (Against 180 and 32, with the loops as they are: 2 prefixes of 500 tokens and 19 branches 28.6 -> 17.8 us, 2 of 736 and 41
+    //    31.7 -> 24.5, 10 of 402 and 10 24.2 -> 18.7; 11 of 300 to 600 and 8 24.8 -> 27.5, whose rows are then too many for a merge launch of their own.)
     const int parts_total = std::max(1, target_wgs / cfg.n_kv_heads);
     int64_t tok_listed = 0, tok_priv = 0;
     for (const Segment& s : shared) tok_listed += s.n_tokens;
     for (const Segment& s : priv) tok_priv += s.n_tokens;
     tok_listed += tok_priv;
     const int64_t share_tokens = tok_listed / parts_total;
-    const bool latency_bound = share_tokens < kSaturatingShareTokens, roomy = share_tokens < kRoomyShareTokens;
+    const bool latency_bound = share_tokens < kSaturatingShareTokens;
+    bool roomy = share_tokens < kRoomyShareTokens;  // (until the cut says otherwise)
     p.long_shares = share_tokens >= kLongShareTokens;
     // An item of more than 4 row tiles gives waves two or three tiles, and a block's chain 0.74 or 0.89 us instead of 0.47: it no
     // longer keeps up with its slice of a saturated memory system.  (80 / 100 / 120 / 140 %, 8 requests of 2048 to 8192 tokens
@@ -664,13 +665,19 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
         if (latency_bound) return s.n_branch * g <= 4 * 16 ? 140 : s.n_branch * g <= 8 * 16 ? 220 : 300;
         return s.n_branch * g <= 4 * 16 ? 80 : !sub_group ? 120 : p.long_shares ? 110 : 160;
     };
-    for (size_t i = 0; i < shared.size(); ++i) {
-        Segment& s = shared[i];  // (the sub-groups of a request follow each other: same pages, another first sequence)
-        auto same_request = [&](size_t j) { return j < shared.size() && branch_group[shared[j].seq0] == branch_group[s.seq0]; };
-        s.pct = shared_pct(s, same_request(i + 1) || (i > 0 && same_request(i - 1)));
-    }
-    const Cost cost_shared = {opts && opts->shared_item_cost > 0 ? opts->shared_item_cost : (latency_bound ? 60 : 450), 0,
-                              opts && opts->shared_item_cost > 0 ? 0 : (roomy ? 20 : latency_bound ? 32 : 0)};
+    Cost cost_shared = {};
+    const auto price_shared = [&] {  // the sum of all
+        cost_shared = {opts && opts->shared_item_cost > 0 ? opts->shared_item_cost : (latency_bound ? 60 : 450), 0,
+                       opts && opts->shared_item_cost > 0 ? 0 : (roomy ? 20 : latency_bound ? 32 : 0)};
+        int64_t sum = 0;
+        for (size_t i = 0; i < shared.size(); ++i) {
+            Segment& s = shared[i];  // (the sub-groups of a request follow each other: same pages, another first sequence)
+            auto same_request = [&](size_t j) { return j < shared.size() && branch_group[shared[j].seq0] == branch_group[s.seq0]; };
+            s.pct = shared_pct(s, same_request(i + 1) || (i > 0 && same_request(i - 1)));
+            sum += cost_shared.item(s) + (int64_t)s.n_tokens * s.pct / 100;
+        }
+        return sum;
+    };
     // (a caller's own costs are taken as they are, and what no single wave will run is priced as the workgroup's)
     const bool own_costs = opts && (opts->private_item_cost > 0 || opts->private_merge_cost != 0);
     const int solo_tokens = opts && opts->solo_item_tokens != 0 ? std::max(0, opts->solo_item_tokens) : 512;
@@ -680,10 +687,7 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
                                                                   : (shared.empty() ? 0 : 192),
                             0, brief_tokens};
     const int64_t shared_tail_discount = 3;  // blocks: about what merging a request's branches costs
-    int64_t cost_total = 0;
-    for (const Segment& s : shared) {
-        cost_total += cost_shared.item(s) + (int64_t)s.n_tokens * s.pct / 100;
-    }
+    int64_t cost_of_shared = price_shared(), cost_total = cost_of_shared;
     for (const Segment& s : priv) {
         cost_total += cost_priv.piece(s) + s.n_tokens + cost_priv.end(s, share_tokens);
     }
@@ -742,39 +746,54 @@ static int build_for_grid(const taper_attn_config& cfg, int n_seqs, const int32_
     for (const Segment& s : priv) longest = std::max<int64_t>(longest, s.n_tokens);
     const int64_t min_share =
         (opts && opts->min_share_tokens > 0 ? opts->min_share_tokens : std::max<int64_t>(256, longest / (shared.empty() ? 64 : 32))) + cost_priv.fixed;
-    int64_t quota = std::max<int64_t>(std::max<int64_t>(kSharedBlockTokens, min_share), (cost_total + parts_total - 1) / parts_total);
+    int64_t quota = 0;
     // Never more shares than asked for: an extra one would run after all the others.  The quota is raised by small steps until that is
     // so: by as many at once as the excess suggests, and halved back between the last one that was too low and the first that is not.
     int64_t sub_groups = 0;
     for (const Segment& s : shared) sub_groups += s.siblings;
     const bool crowded = sub_groups * 2 > parts_total;
     // Where shares are over early and there are enough of them a prefix gets one of its own (two of 60 tokens one after the other: 11.6 us, 8.4).
-    const bool apart = roomy && (int64_t)shared.size() * 2 <= parts_total;
-    auto cut = [&](int64_t q) {
+    const auto cut = [&](int64_t q) {
+        const bool apart = roomy && (int64_t)shared.size() * 2 <= parts_total;
         p.items.clear();
         p.n_parts_shared = partition_even(shared, g, q, kSharedBlockTokens, cost_shared, shared_tail_discount, crowded, apart, 0, &p.items);
         p.n_parts_private = partition_fill(priv, q, kPrivateBlockTokens, cost_priv, p.n_parts_shared, &p.items);
         return p.n_parts_shared + p.n_parts_private <= parts_total || q >= cost_total * 2 + 4096;
     };
-    std::vector<int64_t> tried = {quota};  // the steps
-    auto step = [&](size_t i) {
-        while (tried.size() <= i) tried.push_back(tried.back() + std::max<int64_t>(16, tried.back() / 256));
-        return tried[i];
+    const auto search = [&] {
+        quota = std::max<int64_t>(std::max<int64_t>(kSharedBlockTokens, min_share), (cost_total + parts_total - 1) / parts_total);
+        std::vector<int64_t> tried = {quota};  // the steps
+        auto step = [&](size_t i) {
+            while (tried.size() <= i) tried.push_back(tried.back() + std::max<int64_t>(16, tried.back() / 256));
+            return tried[i];
+        };
+        size_t below = 0, at = 0;
+        while (!cut(step(at))) {
+            below = at++;
+            const int64_t enough = tried[below] * (p.n_parts_shared + p.n_parts_private) / parts_total;
+            while (step(at) < enough) ++at;
+        }
+        bool current = true;
+        while (at - below > 1) {
+            const size_t mid = (below + at) / 2;
+            current = cut(step(mid));
+            (current ? at : below) = mid;
+        }
+        quota = step(at);
+        if (!current) cut(quota);
     };
-    size_t below = 0, at = 0;
-    while (!cut(step(at))) {
-        below = at++;
-        const int64_t enough = tried[below] * (p.n_parts_shared + p.n_parts_private) / parts_total;
-        while (step(at) < enough) ++at;
+    search();
+    // Finer cuts pay while shared workgroups have a compute unit each.  Two side by side share its matrix cores and issue slots, and at head_dim 128
+    // their chains of blocks become longer than the coarser ones: beyond half of the shares the prices are those of fuller grids.  us, with
+    // the one and the other: 8 requests of 33 branches 32.2 / 26.7 (51 % of the shares), 7 of 49 33.8 / 29.0 (52 %), 10 of 40 36.2 / 29.3 (54 %), 8 of 17 36.8 / 30.8 (59 %), 10
+    // of 20 39.9 / 30.2 (69 %), 12 of 49 47.1 / 47.2 (80 %); below it 8 of 33 22.8 / 24.3 (38 %), 11 of 49 24.2 / 29.1 (41 %), 3 of 17 17.3 / 20.4 (48 %), 7 of 49 25.8 / 28.9
+    // (50 %), one the other way (7 of 40, 49 %, 25.9 / 24.0).  At head_dim 64 a block is half the work: 9 of 17 15.0 / 19.6 (52 %).
+    if (roomy && cfg.head_dim == 128 && p.n_parts_shared * 2 > parts_total) {
+        roomy = false;
+        cost_total -= cost_of_shared;
+        cost_total += price_shared();
+        search();
     }
-    bool current = true;
-    while (at - below > 1) {
-        const size_t mid = (below + at) / 2;
-        current = cut(step(mid));
-        (current ? at : below) = mid;
-    }
-    quota = step(at);
-    if (!current) cut(quota);
     if (shared.empty()) level_shares(p.n_parts_private, cost_priv, &p.items);
     const int n_parts = p.n_parts_shared + p.n_parts_private;
     p.part_start.assign(n_parts + 1, 0);

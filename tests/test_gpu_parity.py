@@ -173,7 +173,7 @@ def test_plan_options_do_not_change_the_result(ctx_qwen, kw):
 @pytest.mark.parametrize("width", [17, 20, 24])
 def test_wide_requests_in_one_pass(ctx_qwen, width):
     """Requests of 9 to 12 row tiles served by one item per prefix chunk (the kernel variant that loads
-    straight into LDS, four 32-token buffers): prefix lengths around every block and page boundary,
+    straight into LDS, K in a ring of four 32-token blocks and V in one of five): prefix lengths around every block and page boundary,
     so one to many blocks, odd page counts and ragged tails; narrower requests ride in the same launch."""
     rng = np.random.default_rng(400 + width)
     reqs = [(pl, [int(x) for x in rng.integers(0, 40, size=width)]) for pl in (1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 95, 96, 97, 129, 1000)]

@@ -417,7 +417,23 @@ def test_prices_of_shared_items_in_short_shares(heads, branches, pct):
     sh = AttnShape(heads, 1, 128, 16)
     cuts = lambda n, **kw: build(structure_custom(sh, [(n * (1 + i) // 12, [3 + i] * branches) for i in range(24)], seed=7), Context(heads, 1, 128, device=-1), **kw).export()["items"][:, :8].tolist()
     below, above = dict(shared_cost_pct=pct, shared_item_cost=60 + 20 * branches), dict(shared_cost_pct=180, shared_item_cost=60 + 32 * branches)
-    for lengths, right, wrong in (((800, 1100, 1500), below, above), ((3000, 3500, 4500), above, below)):
+    for lengths, right, wrong in (((400, 800, 1000), below, above), ((3000, 3500, 4500), above, below)):
         default = [cuts(n) for n in lengths]
         assert default == [cuts(n, **right) for n in lengths]
         assert default != [cuts(n, **wrong) for n in lengths]
+
+
+@pytest.mark.parametrize("shape,n,shares", [((8, 1, 128), 3500, 240), ((8, 1, 128), 4500, 228), ((8, 1, 64), 4500, 300)])
+def test_short_shares_are_cut_finer_only_while_shared_ones_are_half_of_them(shape, n, shares):
+    """12 requests of 9 branches (5 row tiles) below 128 tokens per share, of 512: by the finer prices they take 240 and 300 shares; beyond half, at head_dim 128,
+    the prices are those of 128 tokens per share and more (180 %, 60 and 32 per branch)."""
+    st = structure_custom(AttnShape(*shape, 16), [(n, [3] * 9)] * 12, seed=8)
+    ctx = Context(*shape, device=-1)
+    prefix_cuts = lambda e: sorted(int(t) for t in e["items"][:, 3] if t > 3)
+    default = build(st, ctx).export()
+    fine = build(st, ctx, shared_cost_pct=220, shared_item_cost=60 + 20 * 9).export()
+    coarse = build(st, ctx, shared_cost_pct=180, shared_item_cost=60 + 32 * 9).export()
+    right, wrong = (coarse, fine) if shares == 228 else (fine, coarse)
+    assert default["n_parts_shared"] == shares and fine["n_parts_shared"] == (240 if n == 3500 else 300)
+    assert prefix_cuts(default) == prefix_cuts(right) != prefix_cuts(wrong)
+    ctx.close()
