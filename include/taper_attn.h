@@ -165,9 +165,14 @@ typedef struct {
                                       size; at most 12 row tiles                               */
     int32_t shared_cost_pct;   /* 0 = default (80 for items of up to 4 row tiles, 120 for wider ones; for
                                   wider sub-groups of one request 160, or 110 from 2000 tokens per share
-                                  on; 180 when the step has fewer than 350 tokens per share): cost of a shared-prefix token relative to a
-                                  private one when cutting the work into equal shares           */
-    int32_t shared_item_cost;  /* 0 = default (450; below 350 tokens per share 60 and 32 per branch): fixed
+                                  on; 180 when the step has fewer than 350 tokens per share; below 128, 140, 220 and
+                                  300 for items of up to 4, 8 and 12 row tiles): cost of a shared-prefix token
+                                  relative to a private one when cutting the work into equal shares.  Below
+                                  128 tokens per share each prefix also has shares of its own, unless that
+                                  would take more than half of them; at head_dim 128 these prices hold only
+                                  while shared-prefix work takes no more than half of the shares */
+    int32_t shared_item_cost;  /* 0 = default (450; 60 and 32 per branch below 350 tokens per share, 60 and 20
+                                  per branch below 128): fixed
                                   cost of a shared-prefix item, in private tokens' streaming
                                   time                                                          */
     int32_t private_item_cost; /* 0 = default (192; 128 below 350 tokens per share and in steps without
