@@ -336,7 +336,7 @@ TAPER_API int taper_decode_step_attention_simple(taper_ctx *ctx, int n_seqs, con
  * For callers that cannot allocate device memory -- code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc: the operation and arguments of
  * taper_decode_step_attention_simple, but the plan's device arrays and the partials
- * workspace (counters, statistics, partial rows) live in a fixed array (64 MiB and 160 KiB) that is part
+ * workspace (counters, statistics, partial rows) live in a fixed array (64 MiB and 112 KiB) that is part
  * of the library's device image, one copy per GPU, held until the process ends.  The call
  * allocates and frees nothing, on the device or in pinned memory (its pinned staging buffer
  * and the array's address are set up by taper_create), and unlike _simple it only enqueues
@@ -347,8 +347,8 @@ TAPER_API int taper_decode_step_attention_simple(taper_ctx *ctx, int n_seqs, con
  * without a pool, then for half the workgroups, a quarter and so on.
  * TAPER_EINVAL with a message naming the sizes when the step needs more than the array holds all the
  * same (plan image above 8 MiB, image + workspace above 64 MiB -- the 64-layer admission-sweep batch at
- * 640 sequences takes 32 MiB -- or the start records, 320 bytes for each share of the work and not
- * counted in the other two, above 160 KiB), TAPER_EHIP on a host-only context or when the array's address
+ * 640 sequences takes 32 MiB -- or the start records, up to 224 bytes for each share of the work and not
+ * counted in the other two, above 112 KiB), TAPER_EHIP on a host-only context or when the array's address
  * could not be looked up.
  * All calls on one GPU, from any context, share that GPU's array, which keeps the previous
  * call's contents: a call must not be enqueued before every earlier one on that GPU has been

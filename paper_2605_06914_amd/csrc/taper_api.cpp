@@ -72,7 +72,7 @@ struct Workspace {
 struct DeviceImage {
     const int32_t* bt = nullptr;
     const taper_work_item* items = nullptr;
-    const taper::ShareStart* starts = nullptr;
+    const void* starts = nullptr;
     const int32_t* merge_start = nullptr;
     const taper_merge_entry* merge = nullptr;
     const int32_t* prefix_len = nullptr;
@@ -159,7 +159,7 @@ struct ImagePiece {
 constexpr int kImagePieces = 10;
 size_t layout_image(const taper::HostPlan& h, ImagePiece (&pieces)[kImagePieces]) {
     const ImagePiece init[kImagePieces] = {
-        {h.starts.data(), h.starts.size() * sizeof(taper::ShareStart), 0},
+        {h.starts.data(), h.starts.size() * sizeof(taper::StartWords), 0},
         {h.block_table.data(), h.block_table.size() * sizeof(int32_t), 0},
         {h.items.data(), h.items.size() * sizeof(taper_work_item), 0},
         {h.merge_start.data(), h.merge_start.size() * sizeof(int32_t), 0},
@@ -186,7 +186,7 @@ void write_image(const ImagePiece (&pieces)[kImagePieces], void* host_dst) {
 DeviceImage bind_image(const ImagePiece (&pieces)[kImagePieces], void* dev_base) {
     char* d = (char*)dev_base;
     DeviceImage m;
-    m.starts = (const taper::ShareStart*)(d + pieces[0].off);
+    m.starts = d + pieces[0].off;
     m.bt = (const int32_t*)(d + pieces[1].off);
     m.items = (const taper_work_item*)(d + pieces[2].off);
     m.merge_start = (const int32_t*)(d + pieces[3].off);
@@ -287,6 +287,7 @@ taper::StepArgs make_args(const taper_ctx* ctx, const taper::HostPlan& h, const 
     a.bt = img.bt;
     a.items = img.items;
     a.starts = img.starts;
+    a.start_bytes = h.start_bytes;
     a.merge_start = img.merge_start;
     a.merge = img.merge;
     a.prefix_len = img.prefix_len;

@@ -37,7 +37,8 @@ struct DecodeArgs {
 
 // Device-resident integer metadata of one step plus the tensors of one layer.
 struct StepArgs : DecodeArgs {
-    const ShareStart* starts;  // [n_parts]
+    const void* starts;        // [n_parts] start records (ShareStart) of
+    int32_t start_bytes;       // this size
     const void* q;             // bf16 [S][Hq][D]
     const void* kv;            // bf16 pool
     int32_t n_parts_shared;
@@ -53,7 +54,7 @@ struct StepArgs : DecodeArgs {
 
 // Device memory that belongs to no context: the scratch array of taper_decode_step_attention_static.
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
-constexpr size_t kStaticStartsBytes = (size_t)160 << 10;  // in front of it: the start records of up to 512 shares
+constexpr size_t kStaticStartsBytes = (size_t)512 * kStartBytesFour;  // in front of it: the start records of up to 512 shares
 // Address of the calling device's copy of the array (looked up once per device; `device` must be current).
 hipError_t static_scratch(int device, void** ptr);
 // `bytes` (a multiple of 16, both ends 16-byte aligned) from pinned host memory as the device addresses it, and n_zero words cleared.

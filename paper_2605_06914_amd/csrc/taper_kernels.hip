@@ -21,6 +21,7 @@
 // the sequence's last partial (merge_rows) or, in steps of many partials, by a launch of their own
 // behind the attention launch (merge_kernel).
 #include <climits>
+#include <cstddef>
 #include <type_traits>
 
 #include "taper_internal.h"
@@ -259,22 +260,22 @@ DEV taper_work_item load_item(const DecodeArgs& a, const int it) {
 // What a launch's first loads need, beside a wave's start record.  It comes as two leading kernel arguments of four words, which arrive in
 // registers.  (Each argument more is host time of every launch: with seven of them, calls that wait for the host took 5.4 us, with these 4.9 us.)
 struct Inputs {
-    const ShareStart* starts;
-    const void *kv, *q;
+    const void *starts, *kv, *q;
     int n_kv_heads, n_q_heads, gqa, n_parts_shared;
+    bool four_items;  // in each start record
 };
 static u32x4 pack_pointers(const StepArgs& a) {
     const uint64_t starts = (uint64_t)a.starts, kv = (uint64_t)a.kv;
     return {(unsigned)starts, (unsigned)(starts >> 32), (unsigned)kv, (unsigned)(kv >> 32)};
 }
-static u32x4 pack_queries(const StepArgs& a) {  // (gqa is at most 16)
-    return {(unsigned)(uint64_t)a.q, (unsigned)((uint64_t)a.q >> 32), (unsigned)a.n_kv_heads, (unsigned)a.n_parts_shared << 5 | (unsigned)a.gqa};
+static u32x4 pack_queries(const StepArgs& a) {  // (gqa is at most 16: five bits, then one, then the number of shares)
+    return {(unsigned)(uint64_t)a.q, (unsigned)((uint64_t)a.q >> 32), (unsigned)a.n_kv_heads, (unsigned)a.n_parts_shared << 6 | (a.start_bytes == kStartBytesFour ? 32u : 0u) | (unsigned)a.gqa};
 }
 DEV Inputs unpack_inputs(const u32x4 p, const u32x4 q) {
     typedef const __attribute__((address_space(1))) char* global_bytes;
     const auto pointer = [](unsigned lo, unsigned hi) { return (const void*)(global_bytes)((uint64_t)hi << 32 | lo); };
     const int gqa = q[3] & 31;
-    return {(const ShareStart*)pointer(p[0], p[1]), pointer(p[2], p[3]), pointer(q[0], q[1]), (int)q[2], (int)q[2] * gqa, gqa, (int)(q[3] >> 5)};
+    return {pointer(p[0], p[1]), pointer(p[2], p[3]), pointer(q[0], q[1]), (int)q[2], (int)q[2] * gqa, gqa, (int)(q[3] >> 6), (q[3] & 32) != 0};
 }
 // A wave's start record, by scalar loads side by side.
 struct Start {
@@ -284,17 +285,16 @@ struct Start {
 };
 #define CONSTANT const __attribute__((address_space(4)))
 DEV Start load_start(const Inputs& in, const int part, const int wave) {
-    const auto share = (CONSTANT ShareStart*)in.starts + part;
-    const auto r = (CONSTANT char*)&share->wave[0] + wave * sizeof(WaveStart);
+    const auto r = (CONSTANT char*)in.starts + (uint64_t)(unsigned)part * (unsigned)(in.four_items ? kStartBytesFour : kStartBytesOne);
     const i32x4 head = *(CONSTANT i32x4*)r;
     Start s;
     s.first = head[0];
     s.end = head[1];
     s.turn = head[2];
     s.n_solo = head[3];
-    s.item = __builtin_bit_cast(taper_work_item, *(CONSTANT i32x8*)(r + 16));
-    s.page = *(CONSTANT i32x4*)(r + 48);
-    s.more = *(CONSTANT i32x4*)&share->more;
+    s.item = __builtin_bit_cast(taper_work_item, *(CONSTANT i32x8*)(r + offsetof(ShareStart, item) + (in.four_items ? wave : 0) * sizeof(taper_work_item)));
+    s.page = *(CONSTANT i32x4*)(r + offsetof(ShareStart, page) + wave * sizeof(i32x4));
+    s.more = *(CONSTANT i32x4*)(r + offsetof(ShareStart, more));
     // (all of it is asked for here, and the other arguments' cache lines with it, which later loads then find)
     const auto args = (CONSTANT int*)__builtin_amdgcn_kernarg_segment_ptr();
     const int line1 = args[16], line2 = args[32];

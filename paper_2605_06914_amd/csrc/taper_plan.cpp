@@ -401,42 +401,50 @@ void order_solo_items(int n_seqs, int most_tokens, bool partials, HostPlan* p) {
 // The start records: the first item of a share and the pages its waves ask for first (past the item's last page: that one).  A private
 // item's block is two pages, and wave w takes blocks w and w + 4; of a solo item it takes blocks 0 and 1.  Of a shared item every wave
 // stages its part of pages 0 to 7 at head_dim 128, and pages w, w + 4, ... at 64.
-// A step on one kv head has some 490 shares and 157 KB of them: every word is written once.  (Cleared first, with pages 4 to 7 read once for
-// each wave, they took 24.5 us of such a plan's 84 on a host whose plans without them take 59; so 9.9 of 74.5.)
+// A step on one kv head has some 490 shares, so every word is written once and an item not once for each wave unless some share needs it.
+// (From the call to the image on the device such a plan takes 56.7 us; 62.5 with a record of 80 bytes for each wave, 157 KB, and 47 without records.)
 void make_starts(const taper_attn_config& cfg, HostPlan* p) {
     const int n_parts = p->n_parts_shared + p->n_parts_private;
-    p->starts.resize(n_parts);
+    bool four = false;
+    for (int q = 0; q < n_parts; ++q) four |= p->part_turn[q] >> kPartSoloShift > 1;
+    p->start_bytes = four ? kStartBytesFour : kStartBytesOne;
+    p->starts.resize((size_t)n_parts * p->start_bytes / sizeof(StartWords));
     for (int q = 0; q < n_parts; ++q) {
-        const int first = p->part_start[q], end = p->part_start[q + 1], n_solo = p->part_turn[q] >> kPartSoloShift;
-        ShareStart& s = p->starts[q];
-        std::fill(s.more, s.more + 4, 0);
-        for (int w = 0; w < 4; ++w) {
-            WaveStart& r = s.wave[w];
-            r.first = first;
-            r.end = end;
-            r.turn = p->part_turn[q] & ((1 << kPartSoloShift) - 1);
-            r.n_solo = n_solo;
-            r.item = first == end ? taper_work_item() : p->items[w < n_solo ? first + w : first];
-            std::fill(r.page, r.page + 4, 0);
-        }
-        if (first == end) continue;
-        const auto row_of = [&](const taper_work_item& it) { return p->block_table.data() + (size_t)it.seq0 * p->bt_stride + it.page0; };
-        const auto last_of = [](const taper_work_item& it) { return (it.n_tokens + 15) / 16 - 1; };
-        const taper_work_item& it = p->items[first];
-        const int32_t* row = row_of(it);
-        const int last = last_of(it);
-        if (it.kind == 0) {
-            for (int w = 0; w < 4; ++w)
-                for (int i = 0; i < 4; ++i) s.wave[w].page[i] = row[std::min(cfg.head_dim == 128 ? i : 4 * i + w, last)];
-            for (int i = 0; i < 4; ++i) s.more[i] = row[std::min(4 + i, last)];
+        char* to = (char*)p->starts.data() + (size_t)q * p->start_bytes;
+        ShareStart s;
+        s.first = p->part_start[q];
+        s.end = p->part_start[q + 1];
+        s.turn = p->part_turn[q] & ((1 << kPartSoloShift) - 1);
+        s.n_solo = p->part_turn[q] >> kPartSoloShift;
+        std::memset(s.more, 0, sizeof s.more);
+        std::memset(s.page, 0, sizeof s.page);
+        if (s.first == s.end) {
+            std::memset(s.item, 0, sizeof s.item);
+            std::memcpy(to, &s, p->start_bytes);
             continue;
         }
-        for (int w = 0; w < 4; ++w)
-            for (int i = 0; i < 4; ++i) {
-                const bool solo = w < n_solo;
-                const taper_work_item& own = p->items[solo ? first + w : first];
-                s.wave[w].page[i] = row_of(own)[std::min(solo ? i : 2 * (w + 4 * (i / 2)) + i % 2, last_of(own))];
-            }
+        const auto row_of = [&](const taper_work_item& it) { return p->block_table.data() + (size_t)it.seq0 * p->bt_stride + it.page0; };
+        const auto last_of = [](const taper_work_item& it) { return (it.n_tokens + 15) / 16 - 1; };
+        const taper_work_item& it = p->items[s.first];
+        const int32_t* row = row_of(it);
+        const int last = last_of(it);
+        for (int w = 0; w < (four ? 4 : 1); ++w) s.item[w] = p->items[s.first + (w < s.n_solo ? w : 0)];
+        if (it.kind == 0) {
+            for (int w = 0; w < 4; ++w)
+                for (int i = 0; i < 4; ++i) s.page[w][i] = row[std::min(cfg.head_dim == 128 ? i : 4 * i + w, last)];
+            for (int i = 0; i < 4; ++i) s.more[i] = row[std::min(4 + i, last)];
+        } else if (s.n_solo == 0) {
+            for (int w = 0; w < 4; ++w)
+                for (int i = 0; i < 4; ++i) s.page[w][i] = row[std::min(2 * (w + 4 * (i / 2)) + i % 2, last)];
+        } else {
+            for (int w = 0; w < 4; ++w)
+                for (int i = 0; i < 4; ++i) {
+                    const bool solo = w < s.n_solo;
+                    const taper_work_item& own = p->items[s.first + (solo ? w : 0)];
+                    s.page[w][i] = row_of(own)[std::min(solo ? i : 2 * (w + 4 * (i / 2)) + i % 2, last_of(own))];
+                }
+        }
+        std::memcpy(to, &s, p->start_bytes);
     }
 }
 

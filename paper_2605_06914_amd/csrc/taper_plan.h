@@ -15,19 +15,21 @@ constexpr int kSharedBlockTokens = 64;   // shared prefixes are cut at multiples
 constexpr int kPartTurnMask = 0xfff, kPartSoloPartials = 0x1000, kPartSoloShift = 13;
 constexpr int kMaxRowTilesPerItem = 12;  // 16-row query tiles one shared-kernel workgroup can hold (4 waves x 3)
 
-// What a wave of a share begins with, so that its first KV loads wait for one trip to memory and not for one to the share's range, one
-// to its item and one to the block table.
-struct alignas(64) WaveStart {
-    WaveStart() {}         // (left as it is: make_starts writes every field, and an array of them need not be cleared first)
+// What the waves of a share begin with, so that their first KV loads wait for one trip to memory and not for one to the share's range, one
+// to its item and one to the block table.  A record's items are one, which all its waves begin with, or four where the plan has a share whose first
+// waves run items of their own: all records of a plan have the same size.
+struct ShareStart {
     int32_t first, end;    // the share's items
     int32_t turn, n_solo;  // part_turn's flags; how many of the items single waves run
-    taper_work_item item;  // the share's first item; of a solo run, this wave's first
-    int32_t page[4];       // its first pages, in the order the wave loads them (see make_starts)
+    int32_t more[4];       // pages 4 to 7 of a shared item at head_dim 128
+    int32_t page[4][4];    // per wave: its item's first pages, in the order the wave loads them (see make_starts)
+    taper_work_item item[4];  // the share's first item, or per wave; the last three only where the plan has them
 };
-struct alignas(64) ShareStart {
-    ShareStart() {}
-    WaveStart wave[4];
-    int32_t more[4];  // pages 4 to 7 of a shared item at head_dim 128
+constexpr int kStartBytesOne = sizeof(ShareStart) - 3 * sizeof(taper_work_item), kStartBytesFour = sizeof(ShareStart);
+static_assert(kStartBytesOne == 128 && kStartBytesFour % sizeof(taper_work_item) == 0, "items are read by aligned loads");
+struct StartWords {  // (32 bytes of records, not cleared before they are written)
+    StartWords() {}
+    int32_t w[8];
 };
 
 struct HostPlan {
@@ -42,7 +44,8 @@ struct HostPlan {
     int n_pool_items = 0;  // items after the shares' items, owned by no share
     std::vector<int32_t> part_start;  // [n_parts + 1]
     std::vector<int32_t> part_turn;   // [n_parts] which kv head a share's first workgroup takes (see plan_part_turns), and its solo items
-    std::vector<ShareStart> starts;   // [n_parts]
+    std::vector<StartWords> starts;   // [n_parts] records of start_bytes each
+    int start_bytes = kStartBytesOne;
     std::vector<int32_t> merge_start; // [n_seqs + 1]
     std::vector<taper_merge_entry> merge;
     int64_t n_partial_rows = 0;

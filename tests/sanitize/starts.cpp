@@ -49,23 +49,25 @@ int main() {
             return 1;
         }
         const int n_parts = p.n_parts_shared + p.n_parts_private;
-        if ((int)p.starts.size() != n_parts) return 2;
+        if (p.starts.size() * sizeof(StartWords) != (size_t)n_parts * p.start_bytes) return 2;
         for (int q = 0; q < n_parts; ++q) {
             const int first = p.part_start[q], end = p.part_start[q + 1], n_solo = p.part_turn[q] >> kPartSoloShift;
             if (first == end) return 3;
             checked[3] += end - first > 1;
             for (int w = 0; w < 4; ++w) {
-                const WaveStart& r = p.starts[q].wave[w];
+                const ShareStart& r = *(const ShareStart*)((const char*)p.starts.data() + (size_t)q * p.start_bytes);
                 const bool solo = w < n_solo;
                 const taper_work_item& it = p.items[solo ? first + w : first];
+                const taper_work_item& has = r.item[p.start_bytes == kStartBytesFour ? w : 0];
+                if (p.start_bytes == kStartBytesOne && n_solo > 1) return 6;
                 bool ok = r.first == first && r.end == end && r.n_solo == n_solo && r.turn == (p.part_turn[q] & ((1 << kPartSoloShift) - 1)) &&
-                          (r.turn & kPartTurnMask) < s[1] && r.item.seq0 == it.seq0 && r.item.n_tokens == it.n_tokens && r.item.page0 == it.page0 &&
-                          r.item.kind == it.kind && r.item.part_base == it.part_base && r.item.merge0 == it.merge0 && r.item.n_branch == it.n_branch;
+                          (r.turn & kPartTurnMask) < s[1] && has.seq0 == it.seq0 && has.n_tokens == it.n_tokens && has.page0 == it.page0 &&
+                          has.kind == it.kind && has.part_base == it.part_base && has.merge0 == it.merge0 && has.n_branch == it.n_branch;
                 for (int block = 0; block < 2 && it.kind != 0; ++block)  // a wave's first two blocks, two pages each
-                    for (int half = 0; half < 2; ++half) ok &= r.page[2 * block + half] == page_of(p, it, 2 * (solo ? block : w + 4 * block) + half);
+                    for (int half = 0; half < 2; ++half) ok &= r.page[w][2 * block + half] == page_of(p, it, 2 * (solo ? block : w + 4 * block) + half);
                 for (int i = 0; i < 4 && it.kind == 0; ++i) {  // the first four blocks: of two pages, which every wave stages a part of, or of four, a page a wave
-                    if (s[2] == 128) ok &= r.page[i] == page_of(p, it, i) && p.starts[q].more[i] == page_of(p, it, 4 + i);
-                    else ok &= r.page[i] == page_of(p, it, 4 * i + w);
+                    if (s[2] == 128) ok &= r.page[w][i] == page_of(p, it, i) && r.more[i] == page_of(p, it, 4 + i);
+                    else ok &= r.page[w][i] == page_of(p, it, 4 * i + w);
                 }
                 if (!ok) {
                     std::printf("round %d share %d wave %d\n", round, q, w);

@@ -85,7 +85,7 @@ def test_static_entry_rejects_a_step_beyond_the_array():
         ctx.decode_step_attention_static(q, kv, 16, bt, np.arange(S, dtype=np.int32), np.full(S, 5, np.int32),
                                          np.zeros(S, np.int32), out)
     assert e.value.status == TAPER_EINVAL and "static scratch" in str(e.value)
-    for limit in (8 << 20, 64 << 20, 160 << 10):  # every limit that the call checks, with the step's size beside it
+    for limit in (8 << 20, 64 << 20, 112 << 10):  # every limit that the call checks, with the step's size beside it
         assert f"bytes (limit {limit})" in str(e.value)
     ctx.close()
 
@@ -111,7 +111,7 @@ def test_static_entry_cuts_a_step_coarser_that_does_not_fit_as_it_would_best_be_
         e = p.export()
         p.free()
         S, rows = st.n_seqs, e["n_partial_rows"]
-        assert (len(e["part_start"]) - 1) * 320 <= 160 << 10  # (the start records' own room)
+        assert (len(e["part_start"]) - 1) * 224 <= 112 << 10  # (the start records' own room)
         pieces = [st.block_table.size * 4, len(e["items"]) * 32, len(e["merge"]) * 8, (S + 1) * 8 * 4, rows * 16,
                   rows * 128 * 4] + [(S + 1) * 4] * 2 + [S * 4] * 4
         return sum(-(-n // 256) * 256 for n in pieces)
